@@ -24,7 +24,8 @@
  *     sp_index outside [0,dim) are contract violations).
  *   - Calls on one maxk_graph must not overlap in time (they share its workspace).
  *   - Tuning knobs, read from the environment once per handle by maxk_graph_create (results never depend on
- *     them): MAXK_CHUNK (entries per work item, default 2048), MAXK_SLAB_KB (KiB of dY per slab of the slab-pull
+ *     them): MAXK_CHUNK (entries per work item; default nnz / 4096,
+ *     at least 128 and at most 2048), MAXK_SLAB_KB (KiB of dY per slab of the slab-pull
  *     backward kernel, default 3584), MAXK_FWD_PACK_MAX (largest CBSR row in bytes that the forward pass
  *     repacks into one record per node, default 96).
  */

@@ -77,6 +77,20 @@ int env_int(const char* name, int dflt, int lo, int hi)
     return (int)x;
 }
 
+// Entries per work item when the caller sets none.  One wavefront walks an item serially, so a launch takes at least
+// as long as its longest item: on a graph of a few million entries an item of 2048 outlasted all the other work.  A
+// 4096th of the entries per item keeps that tail below the rest (MI355X, us at 2048 -> at this rule: 2.5 M entries,
+// 169 k nodes, k=32: forward 150 -> 97, pull 387 -> 228, expand/reduce 336 -> 281; 1.2 M entries, 40 k nodes, k=13:
+// forward 74 -> 50, pull 114 -> 49; 2.1 M entries, 4 k nodes, k=16: forward 49 -> 34).  From 8 M entries up the tail
+// is hidden and shorter items only add partial rows (43 M entries: forward 1405 us at 2048, 1491 at 512).  Below
+// 128 an item costs more to start than to walk.  A row of more than `chunk` entries makes at most 2 * len / chunk
+// items, so there are never more than 8192 partial rows from this rule while it is below 2048: 32 MiB at the widest
+// row, which the fixed scratch array of maxk_spgemm_fwd_noalloc holds.
+int default_chunk(int64_t nnz)
+{
+    return (int)std::min<int64_t>(2048, std::max<int64_t>(128, (nnz + 4095) / 4096));
+}
+
 // Host side of the partition: ptr[n+1] -> items (longest first) + split rows.
 void build_items(const std::vector<int32_t>& ptr, int64_t n, int chunk, std::vector<WorkItem>& items,
                  std::vector<SplitRow>& split, int64_t& n_slots, int64_t& max_len)
@@ -588,7 +602,7 @@ MAXK_API maxk_status maxk_graph_create(maxk_graph** out, int64_t N, int64_t nnz,
     g->d_rowptr = d_rowptr;
     g->d_col = d_colidx;
     g->d_val = d_val;
-    g->chunk = env_int("MAXK_CHUNK", 2048, 64, 1 << 20);  // measured plateau: 2048 and up
+    g->chunk = env_int("MAXK_CHUNK", default_chunk(nnz), 64, 1 << 20);
     g->slab_kb = env_int("MAXK_SLAB_KB", 3584, 64, 1 << 20);
     g->fwd_pack_max = env_int("MAXK_FWD_PACK_MAX", 96, 0, 1 << 20);
     (void)hipGetDevice(&g->device);

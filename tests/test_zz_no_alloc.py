@@ -82,3 +82,26 @@ def test_no_alloc_forward_rejects_what_does_not_fit():
     torch.cuda.synchronize()
     assert bool(torch.isfinite(Y).all())
     gr.destroy()
+
+
+@pytest.mark.parametrize("dim,k", [(1024, 16), (64, 7)])
+def test_no_alloc_forward_takes_the_most_partial_rows_the_default_item_length_makes(monkeypatch, dim, k):
+    # every row one entry longer than an item of the default length: two partial rows each, as many as that rule ever
+    # makes (below 8192), at the widest row 32 MB of the array
+    monkeypatch.delenv("MAXK_CHUNK", raising=False)
+    N, per_row = 4000, 129
+    rowptr = (np.arange(N + 1) * per_row).astype(np.int32)
+    col = ((np.arange(N)[:, None] * 7 + np.arange(per_row)[None, :] * 31) % N).astype(np.int32).ravel()
+    val = np.random.default_rng(5).standard_normal(N * per_row).astype(np.float32)
+    H = synth.normal_matrix(N, dim, 6)
+    gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val))
+    assert gr.info()["n_split_rows"] == N
+    sp_data = torch.empty((N, k), device="cuda")
+    sp_index = torch.empty((N, k), dtype=maxk.index_dtype(2), device="cuda")
+    maxk.maxk_topk_cbsr(to_dev(H), k, sp_data, sp_index)
+    Y = torch.full((N, dim), float("nan"), device="cuda")
+    maxk.maxk_spgemm_fwd_noalloc(gr, sp_data, sp_index, dim, Y)
+    torch.cuda.synchronize()
+    ref, refabs = oracle.spgemm_fwd(rowptr, col, val, *oracle.topk_cbsr(H, k), dim)
+    assert (np.abs(Y.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all()
+    gr.destroy()
