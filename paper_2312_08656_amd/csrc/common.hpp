@@ -169,7 +169,7 @@ maxk_status launch_bwd_slab_pull(const SlabSet& S, const void* dY, int value_typ
                                  int index_bytes, int64_t N, int dim, int k, float* dXs, hipStream_t s);
 
 // LDS-tiled backward kernel (fp32 dY, k % 4 == 0, dim % 4 == 0, dim <= 512)
-struct TiledShape { int D = 0, TR = 0, n_dsets = 0; };
+struct TiledShape { int D = 0, TR = 0, n_dsets = 0, R = 0; };  // R: source ranges
 bool tiled_shape(int64_t N, int dim, int k, TiledShape& sh);  // false: (N, dim, k) not supported
 int tiled_positions_per_lane(int k);
 bool tiled_supports(const void* dY, int value_type, const void* sp_index, int index_bytes, int dim, int k);

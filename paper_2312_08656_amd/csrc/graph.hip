@@ -40,7 +40,9 @@ struct maxk_graph {
     std::vector<maxk::TiledSet*> tiled_cache;  // visit lists of the LDS-tiled kernel, one per (set size, k / 4)
     char* d_packed = nullptr;   // forward kernel's per-call repack of a small-k CBSR (one record per node)
     int64_t packed_bytes = 0;
-    int64_t max_degree = 0;
+    int64_t max_degree = 0;      // longest row of A (entries with one source)
+    int64_t max_in_degree = 0;   // longest column (entries with one destination)
+    float hot_share[33] = {};    // share of the entries whose source is among the 2^i sources with most entries
     int32_t bwd_mode = MAXK_BWD_AUTO;
     int32_t chunk = 0;         // tuning knobs, read from the environment once, by maxk_graph_create
     int32_t slab_kb = 0;
@@ -534,41 +536,93 @@ maxk_status ensure_expand(maxk_graph* g, int k)
     return MAXK_OK;
 }
 
-// Backward kernel choice when the caller leaves it to the library (rates measured on MI355X).
-// Slab pull gathers dY from L2 but re-reads and re-writes a destination's dXs row once per
-// (slab, destination) visit, so it needs several in-entries per visit: dense neighbourhoods.
-// Otherwise: expand/reduce moves 8k bytes per stored entry through HBM, plain pull touches about
-// min(k, dim/32) cache lines of a dY row per entry whatever k is, so pull wins once k is large.
+// hot_share[i] = share of the entries in the 2^i longest rows (1 once every row is counted).  Linear in N: rows are
+// counted per length, lengths above the table's end one by one.
+void hot_source_shares(const std::vector<int32_t>& rowptr, int64_t n, int64_t nnz, float (&share)[33])
+{
+    constexpr int kTable = 1 << 16;
+    std::vector<int64_t> count(kTable, 0);
+    std::vector<int32_t> longer;
+    for (int64_t i = 0; i < n; ++i) {
+        const int32_t len = rowptr[(size_t)i + 1] - rowptr[(size_t)i];
+        if (len < kTable) ++count[(size_t)len]; else longer.push_back(len);
+    }
+    std::sort(longer.begin(), longer.end(), [](int32_t a, int32_t b) { return a > b; });
+    int64_t rows = 0, entries = 0;
+    int step = 0;  // share[0..step) are known
+    const auto take = [&](int64_t len, int64_t times) {
+        while (times > 0 && step < 33) {
+            const int64_t now = std::min(times, ((int64_t)1 << step) - rows);
+            rows += now;
+            entries += now * len;
+            times -= now;
+            if (rows == (int64_t)1 << step) share[step++] = (float)((double)entries / (double)std::max<int64_t>(nnz, 1));
+        }
+    };
+    for (int32_t len : longer) take(len, 1);
+    for (int len = kTable - 1; len > 0; --len)
+        if (count[(size_t)len]) take(len, count[(size_t)len]);
+    while (step < 33) share[step++] = 1.f;
+}
+
+// Share of the entries whose source is one of the `rows` most frequent ones: what a cache of that many rows can hit.
+double hot_share(const maxk_graph* g, double rows)
+{
+    if (rows <= 1.0) return g->hot_share[0];
+    const double at = std::min(31.999, std::log2(rows));
+    const int i = (int)at;
+    return g->hot_share[i] + (std::exp2(at - i) - 1.0) * (g->hot_share[i + 1] - g->hot_share[i]);
+}
+
+// Backward kernel choice when the caller leaves it to the library: the lowest of five cost models, fitted on MI355X to
+// 160 shapes (R-MAT and uniform graphs of 4 thousand to 1 million nodes, average degree 12 to 400; widths 64 to 512;
+// k 8 to 128; fp32 and 16-bit dY) and the benchmark graphs.  Over those shapes the chosen kernel takes 5 % longer than
+// the best one on average (43 % with the rule before, which looked at entries per slab visit only).
+// Times in seconds; vb = bytes of a dY element, `lines` = 128-byte lines of a dY row that k sorted columns touch.
 int auto_bwd_mode(const maxk_graph* g, int dim, int k, int val_bytes = 4, bool tiled_ok = true)
 {
-    const double n_slabs = std::ceil((double)g->N / slab_rows_for(g, dim, val_bytes));
-    const double entries_per_visit = (double)g->nnz / std::max(1.0, (double)g->N * n_slabs);
+    const double N = (double)g->N, nnz = (double)g->nnz, row_bytes = (double)dim * val_bytes;
     const double per_line = 128.0 / val_bytes;  // dY elements per cache line
     const double lines = dim <= per_line ? 1.0 : (dim / per_line) * (1.0 - std::pow(1.0 - per_line / dim, (double)k));
-    if (entries_per_visit >= 2.0 && n_slabs * (double)g->N < 1.8e19) {
-        // Dense neighbourhoods: slab pull or the LDS-tiled kernel, by cost models fitted on the dense and the
-        // ogbn-proteins-like workload (256 CUs): slab pull moves the cache lines that an entry's k columns touch (plus
-        // ~0.35 lines of streamed arrays) at ~5.2 ps per line, and pays ~10 us per slab launch; the tiled kernel pays
-        // ~150 ns per (destination set, tile) step on each CU and ~(3.0 + 0.73 k) ps per entry.  Both models are
-        // within 10 % of the measurements from k = 16 up (they run high at k = 8, where the choice is clear).
-        TiledShape sh;
-        if (tiled_ok && val_bytes == 4 && tiled_shape(g->N, dim, k, sh)) {
-            const double n_tiles = std::ceil((double)g->N / sh.TR);
-            const double t_slab = (double)g->nnz * (lines + 0.35) * 5.2e-12 + n_slabs * 10e-6;
-            const double t_tiled = 150e-9 * sh.n_dsets * n_tiles / 256.0 + (double)g->nnz * (3.0e-12 + 0.73e-12 * k);
-            // (graphs of a few thousand nodes: both models miss the fixed costs, and the tiled kernel, one launch,
-            // measured faster at every k)
-            const double margin = (double)sh.n_dsets * n_tiles < 256.0 * 256.0 ? 0.9 : 1.05;
-            if (margin * t_tiled < t_slab && (double)sh.n_dsets * n_tiles < 2.6e8) return MAXK_BWD_TILED;
-        }
-        return MAXK_BWD_SLAB_PULL;
+
+    // pull: a line costs 5 ps when the row sits in L2 (4 MB of the most frequent rows), 17 ps when it does not; below
+    // that the gather's own instructions (12 + 0.55 k ps an entry).  One wavefront walks an item of at most `chunk`
+    // entries, 4 loads at a time and 0.6 us a round: the tail of small graphs.
+    const double miss = 1.0 - hot_share(g, 4e6 / row_bytes);
+    int kp = 64;
+    while (kp > 1 && kp / 2 >= k) kp /= 2;
+    const double rounds = (double)std::min<int64_t>(g->chunk, g->max_in_degree) / (4.0 * (64 / kp));
+    const double pull = 6e-6 + nnz * std::max(lines * (5.0 + 12.0 * miss), 12.0 + 0.55 * k) * (k > 64 ? 1.15e-12 : 1e-12) +
+                        N * 200e-12 + 0.5 * rounds * 0.6e-6;
+
+    // expand/reduce: 8k bytes an entry through HBM, whatever the graph looks like (scalar stores when
+    // k % 4 != 0, two-byte columns above dim 256)
+    const double expand = nnz * k * 4.0 > 96e9 ? HUGE_VAL
+                          : 8e-6 + nnz * (18e-12 + (dim > 256 ? 1.75e-12 : 1.5e-12) * k) * (k % 4 ? 1.7 : 1.0) +
+                                N * (400e-12 + 0.22e-12 * row_bytes);
+
+    // slab pull: lines from L2 at 5.2 ps (plus ~0.35 lines an entry of streamed arrays) and one launch a slab, ~22 us
+    // with its ramp and tail
+    const double n_slabs = std::ceil(N / slab_rows_for(g, dim, val_bytes));
+    const double slab = n_slabs * N >= 1.8e19 ? HUGE_VAL : 5e-6 + nnz * (lines + 0.35) * 5.2e-12 + n_slabs * 22e-6;
+
+    // LDS-tiled: a (destination set, tile) step on each CU (the dim = 256 specialization is 3-5 times cheaper than the
+    // general one), the entries, and fp32 atomics when the source rows are cut into ranges
+    double tiled = HUGE_VAL;
+    TiledShape sh;
+    if (tiled_ok && val_bytes == 4 && tiled_shape(g->N, dim, k, sh)) {
+        const double n_tiles = std::ceil(N / sh.TR);
+        if (sh.n_dsets * n_tiles < 2.6e8)
+            tiled = 15e-6 + (dim == 256 ? 0.2e-6 : 0.5e-6 + 1.2e-9 * dim) * sh.n_dsets * n_tiles / 256.0 +
+                    nnz * (3e-12 + 0.6e-12 * k) + (sh.R > 1 ? sh.R * N * k / 330e9 : 0.0);
     }
-    // `lines`: expected cache lines of a dY row touched by k sorted columns; measured crossover on four graphs:
-    // expand/reduce (8k bytes per entry) beats pull (lines * 128 bytes per entry) while 8k < 44 * lines
-    const double pull_cost = lines * 128.0 / 2.9;
-    const double expand_cost = 8.0 * k;
-    const bool fits = (double)g->nnz * k * 4.0 <= 96e9;
-    return (fits && expand_cost < pull_cost) ? MAXK_BWD_EXPAND_REDUCE : MAXK_BWD_PULL_CSC;
+
+    int mode = MAXK_BWD_PULL_CSC;
+    double best = pull;
+    if (expand < best) { best = expand; mode = MAXK_BWD_EXPAND_REDUCE; }
+    if (slab < best) { best = slab; mode = MAXK_BWD_SLAB_PULL; }
+    if (tiled < best) mode = MAXK_BWD_TILED;
+    return mode;
 }
 
 bool bad_index_bytes(int index_bytes, int dim)
@@ -626,6 +680,7 @@ MAXK_API maxk_status maxk_graph_create(maxk_graph** out, int64_t N, int64_t nnz,
         int64_t n_slots = 0, max_len = 0;
         build_items(h_rowptr, N, g->chunk, items, split, n_slots, max_len);
         g->max_degree = max_len;
+        hot_source_shares(h_rowptr, N, nnz, g->hot_share);
         st = upload_items(items, split, n_slots, g->csr_items, s);
         if (st != MAXK_OK) goto fail;
 
@@ -633,6 +688,7 @@ MAXK_API maxk_status maxk_graph_create(maxk_graph** out, int64_t N, int64_t nnz,
         st = build_csc(g, h_csc_ptr, s);
         if (st != MAXK_OK) goto fail;
         build_items(h_csc_ptr, N, g->chunk, items, split, n_slots, max_len);
+        g->max_in_degree = max_len;
         st = upload_items(items, split, n_slots, g->csc_items, s);
         if (st != MAXK_OK) goto fail;
     } catch (const std::bad_alloc&) {

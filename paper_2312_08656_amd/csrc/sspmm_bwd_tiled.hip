@@ -739,25 +739,6 @@ void free_tiled(TiledSet& T)
 // Destination-set size for (N, dim, k): as many nodes as LDS holds accumulators for beside two row buffers, rounded
 // so that the number of sets is a power of two (the 32 CUs of an XCD then hold whole groups of sets).  Tiles of 16
 // rows: taller ones (32, 48 rows, with correspondingly smaller sets) were measured slower at every k.
-bool tiled_shape(int64_t N, int dim, int k, TiledShape& sh)
-{
-    if (N < 1 || k % 4 != 0 || k < 4 || k > 256 || dim % 4 != 0 || dim > 512) return false;
-    const int tr = 16;
-    const int64_t row_bytes = 2ll * tr * dim * 4;
-    const int64_t dmax = std::min<int64_t>((kLdsBytes - row_bytes - 256) / (4ll * k), 4096);
-    if (dmax < 64) return false;
-    int64_t S = 8;
-    while ((N + S - 1) / S > dmax) S *= 2;
-    const int64_t D = (N + S - 1) / S;
-    const int64_t n_dsets = (N + D - 1) / D;
-    if (n_dsets > 65536) return false;
-    sh.D = (int)D;
-    sh.TR = tr;
-    sh.n_dsets = (int)n_dsets;
-    return true;
-}
-
-// Builds the visit lists for destination sets of D nodes and k/4 lanes per visit.  Synchronises the device.
 // An XCD holds G destination sets and runs 32 workgroups at a time; the source rows are cut into R ranges so that
 // its G * R workgroups fill whole rounds of 32 (as nearly as a small R allows).
 void tiled_ranges(int n_dsets, int n_tiles, int& G, int& R, int& tiles_per_range)
@@ -775,6 +756,27 @@ void tiled_ranges(int n_dsets, int n_tiles, int& G, int& R, int& tiles_per_range
     R = (n_tiles + tiles_per_range - 1) / tiles_per_range;
 }
 
+bool tiled_shape(int64_t N, int dim, int k, TiledShape& sh)
+{
+    if (N < 1 || k % 4 != 0 || k < 4 || k > 256 || dim % 4 != 0 || dim > 512) return false;
+    const int tr = 16;
+    const int64_t row_bytes = 2ll * tr * dim * 4;
+    const int64_t dmax = std::min<int64_t>((kLdsBytes - row_bytes - 256) / (4ll * k), 4096);
+    if (dmax < 64) return false;
+    int64_t S = 8;
+    while ((N + S - 1) / S > dmax) S *= 2;
+    const int64_t D = (N + S - 1) / S;
+    const int64_t n_dsets = (N + D - 1) / D;
+    if (n_dsets > 65536) return false;
+    sh.D = (int)D;
+    sh.TR = tr;
+    sh.n_dsets = (int)n_dsets;
+    int G, tiles_per_range;
+    tiled_ranges(sh.n_dsets, (int)((N + tr - 1) / tr), G, sh.R, tiles_per_range);
+    return true;
+}
+
+// Builds the visit lists for destination sets of D nodes and k/4 lanes per visit.  Synchronises the device.
 maxk_status build_tiled(TiledSet& T, int64_t N, int64_t nnz, const int32_t* d_csc_ptr, const int32_t* d_csc_src,
                         const float* d_csc_val, int D, int TR, int k)
 {

@@ -552,3 +552,23 @@ def test_random_shapes_sweep(seed):
             synth.add_tie_rows(H, seed=case, percent=30, pool=8, const_every=4)
         full_pass(dg, H, dY, k, ib, sampled=False, spmm=bool(rng.random() < 0.3))
         dg.close()
+
+
+@pytest.mark.parametrize("shape", ["one node", "no entries", "one row", "one column", "diagonal"])
+@pytest.mark.parametrize("dim,k", [(33, 5), (256, 32), (512, 128)])
+def test_auto_choice_at_the_ends_of_the_degree_distribution(shape, dim, k):
+    # the cost models behind MAXK_BWD_AUTO read how the entries spread over the rows: the extreme spreads
+    N = 1 if shape == "one node" else 257
+    pairs = {"one node": [(0, 0)], "no entries": [], "one row": [(3, j) for j in range(N)],
+             "one column": [(i, N - 1) for i in range(N)], "diagonal": [(i, i) for i in range(N)]}[shape]
+    rowptr, col, val = csr_from_coo(N, [(i, j, 0.5 + 0.001 * i) for i, j in pairs])
+    H, dY = synth.normal_matrix(N, dim, 51), synth.normal_matrix(N, dim, 52)
+    gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val))
+    assert gr.bwd_choice(dim, k) in ("pull", "expand_reduce", "slab_pull", "tiled")
+    sp_data, sp_index = gpu_topk(to_dev(H), k, 2)
+    dXs = torch.full((N, k), float("nan"), device="cuda")
+    maxk.maxk_sspmm_bwd(gr, to_dev(dY), sp_index, dXs)
+    torch.cuda.synchronize()
+    ref, refabs = oracle.sspmm_bwd(rowptr, col, val, dY, oracle.topk_cbsr(H, k)[1])
+    assert (np.abs(dXs.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all()
+    gr.destroy()
