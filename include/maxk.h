@@ -27,7 +27,8 @@
  *     them): MAXK_CHUNK (entries per work item; default nnz / 4096,
  *     at least 128 and at most 2048), MAXK_SLAB_KB (KiB of dY per slab of the slab-pull
  *     backward kernel, default 3584), MAXK_FWD_PACK_MAX (largest CBSR row in bytes that the forward pass
- *     repacks into one record per node, default 96).
+ *     repacks into one record per node, default 96), MAXK_PULL_FORM (form of the CSC pull: 0 = by cost, 1 = whole
+ *     rows, 2 = column slices wherever the shape allows them; default 0).
  */
 #ifndef MAXK_H
 #define MAXK_H
@@ -101,7 +102,8 @@ MAXK_API maxk_status maxk_graph_destroy(maxk_graph* g);
  * Builds everything the handle's compute calls need for hidden width `dim`, MaxK `k` and (for the backward pass)
  * dY stored as `dy_value_type`: the partial-sum workspace of split rows, the forward pass's repack buffer, and
  * what the backward kernel that would run needs (the nnz*k float buffer of expand/reduce, the slab regrouping
- * of A^T for the slab height of (dim, dy_value_type), the visit lists of the LDS-tiled kernel for (dim, k)).
+ * of A^T for the slab height of (dim, dy_value_type), the visit lists of the LDS-tiled kernel for (dim, k), the
+ * slice-major copy of dY that the pull kernel's column-sliced form keeps for rows that are not whole cache lines).
  * After it, compute calls with the same dim and k (forward, SpMM: any dim' <= dim, k' <= k) allocate nothing,
  * do not synchronise and read no environment variable.  Tables are cached per shape for the life of the handle,
  * so alternating several (dim, k) or dY formats never rebuilds one.  Without a reserve, the first compute call that

@@ -34,7 +34,12 @@ struct ItemList {
     int64_t n_items = 0;
     int64_t n_split = 0;
     int64_t n_slots = 0;
+    int64_t n_long = 0;  // items longer than kSlicedLongItem entries (they come first: longest first)
 };
+
+// The column-sliced pull walks items longer than this with a whole wavefront (8 entries at a time) and shorter ones with
+// 8 lanes each (16 / 32 / 64 measured within 3 % of each other, 64 best on graphs of 40 k nodes and more)
+constexpr int kSlicedLongItem = 64;
 
 // A^T regrouped for the L2-tiled pull kernel: source rows are cut into slabs of `slab_rows`
 // rows (a slab of dY fits one XCD's L2); in-entries are ordered by (slab of source, destination,
@@ -155,6 +160,23 @@ maxk_status launch_spmm(const ItemList& items, const int32_t* col, const float* 
 maxk_status launch_bwd_pull(const ItemList& csc_items, const int32_t* csc_src, const float* csc_val, const void* dY,
                             int value_type, const void* sp_index, int index_bytes, int dim, int k, float* dXs,
                             float* partials, hipStream_t s);
+
+// Column-sliced pull: slices of one 128-byte line of a dY row.  It gathers from dY itself when rows are whole lines and
+// 16-byte aligned, else from a slice-major copy made by the call (`copy`, sliced_copy_bytes; odd rows would straddle one
+// line more per slice).  Offsets are 32 bits: each slice must end within kSlicedMaxBytes.  MAXK_UNSUPPORTED: too many
+// work items for one launch (nothing was launched but the copy).
+constexpr int64_t kSlicedMaxBytes = 0xFFFF0000ll;
+inline int sliced_slices(int dim, int val_bytes) { return (dim * val_bytes + 127) / 128; }
+inline bool sliced_in_place(int dim, int val_bytes) { return dim * val_bytes % 128 == 0; }
+inline bool sliced_supports(const void* dY, int64_t N, int dim, int val_bytes)
+{
+    return sliced_in_place(dim, val_bytes) ? aligned(dY, 16) && N * (int64_t)dim * val_bytes <= kSlicedMaxBytes
+                                           : N * 128 <= kSlicedMaxBytes;
+}
+inline int64_t sliced_copy_bytes(int64_t N, int dim, int val_bytes) { return N * 128 * sliced_slices(dim, val_bytes); }
+maxk_status launch_bwd_sliced(const ItemList& csc_items, const int32_t* csc_src, const float* csc_val, const void* dY,
+                              int value_type, const void* sp_index, int index_bytes, int64_t N, int dim, int k, char* copy,
+                              float* dXs, float* partials, hipStream_t s);
 
 maxk_status launch_bwd_push(const ItemList& items, const int32_t* col, const float* val, const void* dY,
                             int value_type, const void* sp_index, int index_bytes, int64_t N, int dim, int k,

@@ -38,6 +38,8 @@ struct maxk_graph {
     int64_t expand_floats = 0;
     std::vector<maxk::SlabSet*> slab_cache;    // A^T regrouped per slab height (one per height ever asked for)
     std::vector<maxk::TiledSet*> tiled_cache;  // visit lists of the LDS-tiled kernel, one per (set size, k / 4)
+    char* d_sliced = nullptr;   // slice-major copy of dY for the column-sliced pull (rows that are not whole cache lines)
+    int64_t sliced_bytes = 0;
     char* d_packed = nullptr;   // forward kernel's per-call repack of a small-k CBSR (one record per node)
     int64_t packed_bytes = 0;
     int64_t max_degree = 0;      // longest row of A (entries with one source)
@@ -47,6 +49,7 @@ struct maxk_graph {
     int32_t chunk = 0;         // tuning knobs, read from the environment once, by maxk_graph_create
     int32_t slab_kb = 0;
     int32_t fwd_pack_max = 0;
+    int32_t pull_form = 0;
     unsigned char* d_noalloc_scratch = nullptr;  // this device's copy of the library's fixed scratch array
     int device = 0;
 };
@@ -130,6 +133,8 @@ maxk_status upload_items(const std::vector<WorkItem>& items, const std::vector<S
     L.n_items = (int64_t)items.size();
     L.n_split = (int64_t)split.size();
     L.n_slots = n_slots;
+    L.n_long = std::partition_point(items.begin(), items.end(),
+                                    [](const WorkItem& w) { return w.end - w.begin > kSlicedLongItem; }) - items.begin();
     if (L.n_items) {
         MAXK_HIP_TRY(hipMalloc((void**)&L.d_items, sizeof(WorkItem) * items.size()));
         MAXK_HIP_TRY(hipMemcpyAsync(L.d_items, items.data(), sizeof(WorkItem) * items.size(), hipMemcpyHostToDevice, s));
@@ -470,12 +475,19 @@ int32_t slab_rows_for(const maxk_graph* g, int dim, int val_bytes = 4)
     return (int32_t)std::max<int64_t>(rows, 64);
 }
 
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+}
+
 // The regrouping of A^T for one slab height: built on first use (or by maxk_graph_reserve*), then kept until the
 // handle is destroyed, so alternating hidden widths or dY formats on one handle never rebuilds anything.
-maxk_status slabs_for(maxk_graph* g, int32_t slab_rows, SlabSet** out)
+maxk_status slabs_for(maxk_graph* g, int32_t slab_rows, bool existing_only, SlabSet** out)
 {
     for (SlabSet* S : g->slab_cache)
         if (S->slab_rows == slab_rows) { *out = S; return MAXK_OK; }
+    if (existing_only) return MAXK_OUT_OF_MEMORY;
     SlabSet* S = new (std::nothrow) SlabSet();
     if (!S) return MAXK_OUT_OF_MEMORY;
     const maxk_status st = build_slabs(g, *S, slab_rows);
@@ -485,12 +497,13 @@ maxk_status slabs_for(maxk_graph* g, int32_t slab_rows, SlabSet** out)
     return MAXK_OK;
 }
 
-maxk_status tiled_for(maxk_graph* g, int dim, int k, TiledSet** out)
+maxk_status tiled_for(maxk_graph* g, int dim, int k, bool existing_only, TiledSet** out)
 {
     TiledShape sh;
     if (!tiled_shape(g->N, dim, k, sh)) return MAXK_UNSUPPORTED;
     for (TiledSet* T : g->tiled_cache)
         if (T->D == sh.D && T->TR == sh.TR && T->LPV == k / tiled_positions_per_lane(k)) { *out = T; return MAXK_OK; }
+    if (existing_only) return MAXK_OUT_OF_MEMORY;
     TiledSet* T = new (std::nothrow) TiledSet();
     if (!T) return MAXK_OUT_OF_MEMORY;
     const maxk_status st = build_tiled(*T, g->N, g->nnz, g->d_csc_ptr, g->d_csc_src, g->d_csc_val, sh.D, sh.TR, k);
@@ -518,6 +531,21 @@ maxk_status ensure_packed(maxk_graph* g, int k, int index_bytes, int val_bytes)
     }
     g->d_packed = fresh;
     g->packed_bytes = need;
+    return MAXK_OK;
+}
+
+maxk_status ensure_sliced(maxk_graph* g, int dim, int val_bytes)
+{
+    const int64_t need = sliced_copy_bytes(g->N, dim, val_bytes);
+    if (need <= g->sliced_bytes) return MAXK_OK;
+    char* fresh = nullptr;
+    MAXK_HIP_TRY(hipMalloc((void**)&fresh, (size_t)need));
+    if (g->d_sliced) {
+        MAXK_HIP_TRY(hipDeviceSynchronize());
+        (void)hipFree(g->d_sliced);
+    }
+    g->d_sliced = fresh;
+    g->sliced_bytes = need;
     return MAXK_OK;
 }
 
@@ -574,26 +602,51 @@ double hot_share(const maxk_graph* g, double rows)
     return g->hot_share[i] + (std::exp2(at - i) - 1.0) * (g->hot_share[i + 1] - g->hot_share[i]);
 }
 
-// Backward kernel choice when the caller leaves it to the library: the lowest of five cost models, fitted on MI355X to
-// 160 shapes (R-MAT and uniform graphs of 4 thousand to 1 million nodes, average degree 12 to 400; widths 64 to 512;
-// k 8 to 128; fp32 and 16-bit dY) and the benchmark graphs.  Over those shapes the chosen kernel takes 5 % longer than
-// the best one on average (43 % with the rule before, which looked at entries per slab visit only).
-// Times in seconds; vb = bytes of a dY element, `lines` = 128-byte lines of a dY row that k sorted columns touch.
-int auto_bwd_mode(const maxk_graph* g, int dim, int k, int val_bytes = 4, bool tiled_ok = true)
+// Expected 128-byte lines of a dY row that k sorted columns touch
+double lines_touched(int dim, int k, int val_bytes)
+{
+    const double per_line = 128.0 / val_bytes;
+    return dim <= per_line ? 1.0 : (dim / per_line) * (1.0 - std::pow(1.0 - per_line / dim, (double)k));
+}
+
+// The two forms of the pull over CSC, in seconds (see auto_bwd_mode for where the figures come from).
+// Plain: a line costs 5 ps when its row sits in L2 (4 MB of the most frequent rows), 17 ps when it does not; below that
+// the gather's own instructions (12 + 0.55 k ps an entry).  One wavefront walks an item of at most `chunk` entries, 4 loads
+// at a time and 0.6 us a round: the tail of small graphs.
+// Column-sliced: every line of the row is gathered, 7 ps from L2 (24 thousand of the most frequent rows: a slice of 32
+// thousand fills it) and 25 ps from beyond; 60 + 0.5 k ps per (item, slice) to sample the sums; the copy, where one is
+// needed, at 4.5 TB/s.
+struct PullCost { double plain, sliced; };
+PullCost pull_cost(const maxk_graph* g, int dim, int k, int val_bytes, const void* dY)
 {
     const double N = (double)g->N, nnz = (double)g->nnz, row_bytes = (double)dim * val_bytes;
-    const double per_line = 128.0 / val_bytes;  // dY elements per cache line
-    const double lines = dim <= per_line ? 1.0 : (dim / per_line) * (1.0 - std::pow(1.0 - per_line / dim, (double)k));
-
-    // pull: a line costs 5 ps when the row sits in L2 (4 MB of the most frequent rows), 17 ps when it does not; below
-    // that the gather's own instructions (12 + 0.55 k ps an entry).  One wavefront walks an item of at most `chunk`
-    // entries, 4 loads at a time and 0.6 us a round: the tail of small graphs.
     const double miss = 1.0 - hot_share(g, 4e6 / row_bytes);
     int kp = 64;
     while (kp > 1 && kp / 2 >= k) kp /= 2;
     const double rounds = (double)std::min<int64_t>(g->chunk, g->max_in_degree) / (4.0 * (64 / kp));
-    const double pull = 6e-6 + nnz * std::max(lines * (5.0 + 12.0 * miss), 12.0 + 0.55 * k) * (k > 64 ? 1.15e-12 : 1e-12) +
-                        N * 200e-12 + 0.5 * rounds * 0.6e-6;
+    PullCost c;
+    c.plain = 6e-6 + nnz * std::max(lines_touched(dim, k, val_bytes) * (5.0 + 12.0 * miss), 12.0 + 0.55 * k) * (k > 64 ? 1.15e-12 : 1e-12) +
+              N * 200e-12 + 0.5 * rounds * 0.6e-6;
+    const double slices = sliced_slices(dim, val_bytes), hit = hot_share(g, 24000.0);
+    const bool in_place = sliced_in_place(dim, val_bytes);
+    c.sliced = !sliced_supports(dY, g->N, dim, val_bytes) || g->pull_form == 1 ? HUGE_VAL
+               : g->pull_form == 2 ? 0.0 : 6e-6 + nnz * slices * (7e-12 * hit + 25e-12 * (1.0 - hit)) + N * slices * (60e-12 + 0.5e-12 * k) +
+                     (in_place ? 0.0 : N * (row_bytes + slices * 128.0) / 4.5e12);
+    return c;
+}
+
+// Backward kernel choice when the caller leaves it to the library: the lowest of five cost models, fitted on MI355X to
+// 153 shapes (R-MAT and uniform graphs of 4 thousand to 1 million nodes, average degree 12 to 400; widths 64 to 512;
+// k 8 to 128; fp32 and 16-bit dY) and the benchmark graphs.  Over those shapes the chosen kernel takes 6 % longer than
+// the best one on average (79 % with the rule before, which looked at entries per slab visit only).
+// Times in seconds; `lines` = 128-byte lines of a dY row that an entry's k columns touch.
+int auto_bwd_mode(const maxk_graph* g, int dim, int k, int val_bytes = 4, bool tiled_ok = true)
+{
+    const double N = (double)g->N, nnz = (double)g->nnz, row_bytes = (double)dim * val_bytes;
+    const double lines = lines_touched(dim, k, val_bytes);
+
+    const PullCost p = pull_cost(g, dim, k, val_bytes, nullptr);
+    const double pull = std::min(p.plain, p.sliced);
 
     // expand/reduce: 8k bytes an entry through HBM, whatever the graph looks like (scalar stores when
     // k % 4 != 0, two-byte columns above dim 256)
@@ -619,7 +672,7 @@ int auto_bwd_mode(const maxk_graph* g, int dim, int k, int val_bytes = 4, bool t
 
     int mode = MAXK_BWD_PULL_CSC;
     double best = pull;
-    if (expand < best) { best = expand; mode = MAXK_BWD_EXPAND_REDUCE; }
+    if (1.05 * expand < best) { best = expand; mode = MAXK_BWD_EXPAND_REDUCE; }
     if (slab < best) { best = slab; mode = MAXK_BWD_SLAB_PULL; }
     if (tiled < best) mode = MAXK_BWD_TILED;
     return mode;
@@ -659,6 +712,7 @@ MAXK_API maxk_status maxk_graph_create(maxk_graph** out, int64_t N, int64_t nnz,
     g->chunk = env_int("MAXK_CHUNK", default_chunk(nnz), 64, 1 << 20);
     g->slab_kb = env_int("MAXK_SLAB_KB", 3584, 64, 1 << 20);
     g->fwd_pack_max = env_int("MAXK_FWD_PACK_MAX", 96, 0, 1 << 20);
+    g->pull_form = env_int("MAXK_PULL_FORM", 0, 0, 2);
     (void)hipGetDevice(&g->device);
     {
         const maxk_status sst = noalloc_scratch_address(&g->d_noalloc_scratch);
@@ -715,6 +769,7 @@ MAXK_API maxk_status maxk_graph_destroy(maxk_graph* g)
     (void)hipFree(g->d_csc_entry);
     (void)hipFree(g->d_expand);
     (void)hipFree(g->d_packed);
+    (void)hipFree(g->d_sliced);
     for (SlabSet* S : g->slab_cache) { free_slabs(*S); delete S; }
     for (TiledSet* T : g->tiled_cache) { free_tiled(*T); delete T; }
     (void)hipFree(g->d_partials);
@@ -745,15 +800,21 @@ MAXK_API maxk_status maxk_graph_reserve_narrow(maxk_graph* g, int32_t dim, int32
     const int mode = g->bwd_mode == MAXK_BWD_AUTO ? auto_bwd_mode(g, dim, k, vb) : g->bwd_mode;
     if (mode == MAXK_BWD_TILED) {
         TiledSet* T = nullptr;
-        st = tiled_for(g, dim, k, &T);
+        st = tiled_for(g, dim, k, false, &T);
         if (st != MAXK_UNSUPPORTED) return st;
         // the compute call falls back to the slab kernel for shapes the tiled one does not take
     }
     if (mode == MAXK_BWD_SLAB_PULL || mode == MAXK_BWD_TILED) {
         SlabSet* S = nullptr;
-        return g->nnz ? slabs_for(g, slab_rows_for(g, dim, vb), &S) : MAXK_OK;
+        return g->nnz ? slabs_for(g, slab_rows_for(g, dim, vb), false, &S) : MAXK_OK;
     }
-    return mode == MAXK_BWD_EXPAND_REDUCE ? ensure_expand(g, k) : MAXK_OK;
+    if (mode == MAXK_BWD_PULL_CSC) {
+        const PullCost p = pull_cost(g, dim, k, vb, nullptr);
+        return p.sliced < p.plain && !sliced_in_place(dim, vb) ? ensure_sliced(g, dim, vb) : MAXK_OK;
+    }
+    if (mode != MAXK_BWD_EXPAND_REDUCE) return MAXK_OK;
+    st = ensure_expand(g, k);
+    return st == MAXK_OUT_OF_MEMORY && g->bwd_mode == MAXK_BWD_AUTO ? MAXK_OK : st;  // (the compute call runs pull then)
 }
 
 MAXK_API maxk_status maxk_graph_reserve(maxk_graph* g, int32_t dim, int32_t k)
@@ -784,7 +845,7 @@ MAXK_API maxk_status maxk_graph_info(const maxk_graph* g, int64_t* N, int64_t* n
     if (n_split_rows) *n_split_rows = g->csr_items.n_split;
     if (max_degree) *max_degree = g->max_degree;
     if (workspace_bytes)
-        *workspace_bytes = (g->partial_floats + g->expand_floats) * (int64_t)sizeof(float) + g->packed_bytes;
+        *workspace_bytes = (g->partial_floats + g->expand_floats) * (int64_t)sizeof(float) + g->packed_bytes + g->sliced_bytes;
     return MAXK_OK;
 }
 
@@ -878,32 +939,51 @@ MAXK_API maxk_status maxk_sspmm_bwd_narrow(maxk_graph* g, const void* d_dY, int3
     if (st != MAXK_OK) return st;
     int mode = g->bwd_mode;
     const bool tiled_ok = tiled_supports(d_dY, value_type, d_sp_index, index_bytes, dim, k);
-    if (mode == MAXK_BWD_AUTO) mode = auto_bwd_mode(g, dim, k, vb, tiled_ok);
-    if (g->nnz == 0) return launch_fill_zero(d_dXs, g->N * (int64_t)k, (hipStream_t)stream);
+    const bool automatic = mode == MAXK_BWD_AUTO;
+    hipStream_t s = (hipStream_t)stream;
+    if (automatic) mode = auto_bwd_mode(g, dim, k, vb, tiled_ok);
+    if (g->nnz == 0) return launch_fill_zero(d_dXs, g->N * (int64_t)k, s);
+    // What nobody reserved is built here, unless the call is being captured (nothing may be allocated then) or memory has
+    // run out: the library's own choice then falls back to plain pull, which needs no buffer of its own.
     if (mode == MAXK_BWD_TILED) {
         TiledSet* T = nullptr;
-        st = tiled_ok ? tiled_for(g, dim, k, &T) : MAXK_UNSUPPORTED;
+        st = tiled_ok ? tiled_for(g, dim, k, automatic && capturing(s), &T) : MAXK_UNSUPPORTED;
         if (st == MAXK_OK)
-            return launch_bwd_tiled(*T, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs, (hipStream_t)stream);
-        if (st != MAXK_UNSUPPORTED) return st;
-        mode = MAXK_BWD_SLAB_PULL;  // shapes, formats and alignments the tiled kernel does not take
+            return launch_bwd_tiled(*T, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs, s);
+        if (st == MAXK_OUT_OF_MEMORY && automatic) mode = MAXK_BWD_PULL_CSC;
+        else if (st != MAXK_UNSUPPORTED) return st;
+        else mode = MAXK_BWD_SLAB_PULL;  // shapes, formats and alignments the tiled kernel does not take
     }
     if (mode == MAXK_BWD_SLAB_PULL) {
         SlabSet* S = nullptr;
-        st = slabs_for(g, slab_rows_for(g, dim, vb), &S);
-        if (st != MAXK_OK) return st;
-        return launch_bwd_slab_pull(*S, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs, (hipStream_t)stream);
+        st = slabs_for(g, slab_rows_for(g, dim, vb), automatic && capturing(s), &S);
+        if (st == MAXK_OK)
+            return launch_bwd_slab_pull(*S, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs, s);
+        if (st != MAXK_OUT_OF_MEMORY || !automatic) return st;
+        mode = MAXK_BWD_PULL_CSC;
     }
     if (mode == MAXK_BWD_EXPAND_REDUCE) {
-        st = ensure_expand(g, k);
-        if (st != MAXK_OK) return st;
-        return launch_bwd_expand_reduce(g->csr_items, g->d_col, g->d_val, g->csc_items, g->d_csc_entry, d_dY, value_type,
-                                        d_sp_index, index_bytes, dim, k, g->d_expand, d_dXs, g->d_partials,
-                                        (hipStream_t)stream);
+        st = g->nnz * (int64_t)k > g->expand_floats && automatic && capturing(s) ? MAXK_OUT_OF_MEMORY : ensure_expand(g, k);
+        if (st == MAXK_OK)
+            return launch_bwd_expand_reduce(g->csr_items, g->d_col, g->d_val, g->csc_items, g->d_csc_entry, d_dY, value_type,
+                                            d_sp_index, index_bytes, dim, k, g->d_expand, d_dXs, g->d_partials, s);
+        if (st != MAXK_OUT_OF_MEMORY || !automatic) return st;
+        mode = MAXK_BWD_PULL_CSC;
     }
-    if (mode == MAXK_BWD_PULL_CSC)
+    if (mode == MAXK_BWD_PULL_CSC) {
+        const PullCost p = pull_cost(g, dim, k, vb, d_dY);
+        if (p.sliced < p.plain) {
+            const bool in_place = sliced_in_place(dim, vb);
+            st = in_place ? MAXK_OK
+                 : sliced_copy_bytes(g->N, dim, vb) > g->sliced_bytes && capturing(s) ? MAXK_OUT_OF_MEMORY : ensure_sliced(g, dim, vb);
+            if (st == MAXK_OK)
+                st = launch_bwd_sliced(g->csc_items, g->d_csc_src, g->d_csc_val, d_dY, value_type, d_sp_index, index_bytes, g->N,
+                                       dim, k, in_place ? nullptr : g->d_sliced, d_dXs, g->d_partials, s);
+            if (st != MAXK_OUT_OF_MEMORY && st != MAXK_UNSUPPORTED) return st;
+        }
         return launch_bwd_pull(g->csc_items, g->d_csc_src, g->d_csc_val, d_dY, value_type, d_sp_index, index_bytes, dim, k,
-                               d_dXs, g->d_partials, (hipStream_t)stream);
+                               d_dXs, g->d_partials, s);
+    }
     return launch_bwd_push(g->csr_items, g->d_col, g->d_val, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs,
                            (hipStream_t)stream);
 }

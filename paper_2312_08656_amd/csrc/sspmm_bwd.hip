@@ -1,6 +1,7 @@
 // Backward aggregation (Eq. 2 right; Eq. 3): dispatch over the storage format of dY, plus the pieces that
 // do not read dY (clearing dXs, phase 2 of expand/reduce).  The kernels that read dY are in sspmm_bwd_impl.hpp.
 #include "sspmm_bwd_impl.hpp"
+#include "sspmm_bwd_sliced_impl.hpp"
 
 namespace maxk {
 namespace {
@@ -95,6 +96,18 @@ maxk_status launch_bwd_pull(const ItemList& L, const int32_t* csc_src, const flo
     if (L.n_items == 0) return MAXK_OK;
     if (L.n_items > 0x7FFFFFFF) return MAXK_UNSUPPORTED;
     const maxk_status st = MAXK_BY_FORMAT(bwd_pull_format, L, csc_src, csc_val, dY, sp_index, index_bytes, dim, k, dXs, partials, s);
+    if (st != MAXK_OK) return st;
+    return launch_combine(L, partials, k, dXs, s);
+}
+
+maxk_status launch_bwd_sliced(const ItemList& L, const int32_t* csc_src, const float* csc_val, const void* dY,
+                              int value_type, const void* sp_index, int index_bytes, int64_t N, int dim, int k, char* copy,
+                              float* dXs, float* partials, hipStream_t s)
+{
+    if (L.n_items == 0) return MAXK_OK;
+    if (L.n_items > 0x7FFFFFFF) return MAXK_UNSUPPORTED;
+    const maxk_status st = MAXK_BY_FORMAT(bwd_sliced_format, L, csc_src, csc_val, dY, sp_index, index_bytes, N, dim, k, copy,
+                                          dXs, partials, s);
     if (st != MAXK_OK) return st;
     return launch_combine(L, partials, k, dXs, s);
 }

@@ -1,5 +1,6 @@
 // Backward SSpMM kernels for dY stored as bf16 (see sspmm_bwd_impl.hpp).
 #include "sspmm_bwd_impl.hpp"
+#include "sspmm_bwd_sliced_impl.hpp"
 
 namespace maxk {
 
@@ -30,6 +31,14 @@ maxk_status bwd_slab_format<MAXK_VALUE_BF16>(const SlabSet& S, const void* dY, c
                                   int dim, int k, float* dXs, hipStream_t s)
 {
     return slab_format<MAXK_VALUE_BF16>(S, dY, sp_index, index_bytes, N, dim, k, dXs, s);
+}
+
+template <>
+maxk_status bwd_sliced_format<MAXK_VALUE_BF16>(const ItemList& L, const int32_t* csc_src, const float* csc_val, const void* dY,
+                                             const void* sp_index, int index_bytes, int64_t N, int dim, int k, char* copy,
+                                             float* dXs, float* partials, hipStream_t s)
+{
+    return sliced_format<MAXK_VALUE_BF16>(L, csc_src, csc_val, dY, sp_index, index_bytes, N, dim, k, copy, dXs, partials, s);
 }
 
 }  // namespace maxk

@@ -572,3 +572,80 @@ def test_auto_choice_at_the_ends_of_the_degree_distribution(shape, dim, k):
     ref, refabs = oracle.sspmm_bwd(rowptr, col, val, dY, oracle.topk_cbsr(H, k)[1])
     assert (np.abs(dXs.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all()
     gr.destroy()
+
+
+@pytest.fixture
+def _sliced_form(monkeypatch):
+    monkeypatch.setenv("MAXK_PULL_FORM", "2")  # column slices wherever the shape allows them
+
+
+def _mixed_degrees(N, seed):
+    """Directed, signed weights: columns (in-degrees) of 0, 1..20, 63, 64, 65, 200 entries and one of N - 1."""
+    rng = np.random.default_rng(seed)
+    pairs = []
+    for j in range(N):
+        d = N - 1 if j == 5 else (0, 1, 3, 4, 5, 8, 9, 20, 63, 64, 65, 200)[j % 12]
+        pairs += [(int(i), j, float(w)) for i, w in zip(rng.permutation(N)[:d], rng.standard_normal(d))]
+    return csr_from_coo(N, pairs)
+
+
+@pytest.mark.parametrize("dim,k,ib", [(32, 32, 1), (33, 7, 1), (64, 13, 2), (100, 13, 1), (128, 64, 4), (200, 70, 1),
+                                      (256, 32, 1), (256, 130, 2), (384, 96, 2), (511, 128, 2), (1024, 4, 4)])
+@pytest.mark.parametrize("fmt", ["f32", "bf16", "f16"])
+def test_column_sliced_pull(_sliced_form, dim, k, ib, fmt):
+    # slices that divide the row or leave a remainder, one to 32 of them, items of 0 entries to split ones, any column order
+    N = 700
+    rowptr, col, val = _mixed_degrees(N, 61)
+    H, dY = synth.normal_matrix(N, dim, 62), synth.normal_matrix(N, dim, 63)
+    gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val))
+    gr.set_bwd_mode(maxk.BWD_PULL_CSC)
+    _, sp_index = gpu_topk(to_dev(H), k, ib)
+    idx = oracle.topk_cbsr(H, k)[1]
+    shuffle = np.random.default_rng(64).permutation(k)  # the columns of a row may come in any order
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[fmt]
+    dY_dev = to_dev(dY).to(dt)
+    dY_ref = dY_dev.float().cpu().numpy()
+    for order in (np.arange(k), shuffle):
+        ix = sp_index.view(torch.int16) if ib == 2 else sp_index
+        ix = ix[:, torch.from_numpy(order).cuda()].contiguous()
+        dXs = torch.full((N, k), float("nan"), device="cuda")
+        maxk.maxk_sspmm_bwd_narrow(gr, dY_dev, ix, dXs)
+        # dY one element off its alignment: gathers through the copy, or plain pull
+        odd = torch.empty(N * dim + 1, dtype=dt, device="cuda")[1:].view(N, dim)
+        odd.copy_(dY_dev)
+        dXs_odd = torch.full((N, k), float("nan"), device="cuda")
+        maxk.maxk_sspmm_bwd_narrow(gr, odd, ix, dXs_odd)
+        torch.cuda.synchronize()
+        ref, refabs = oracle.sspmm_bwd(rowptr, col, val, dY_ref, np.ascontiguousarray(idx[:, order]))
+        for got in (dXs, dXs_odd):
+            assert (np.abs(got.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all()
+    gr.destroy()
+
+
+@pytest.mark.parametrize("dim,reserve", [(256, True), (100, True), (100, False)])
+def test_column_sliced_pull_in_a_captured_graph(_sliced_form, dim, reserve):
+    # not reserved, the copy's buffer may not be allocated under capture: the call falls back to whole rows
+    N, k = 700, 20
+    rowptr, col, val = _mixed_degrees(N, 71)
+    H, dY = to_dev(synth.normal_matrix(N, dim, 72)), to_dev(synth.normal_matrix(N, dim, 73))
+    gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val))
+    gr.set_bwd_mode(maxk.BWD_PULL_CSC)
+    _, sp_index = gpu_topk(H, k, 2)
+    dXs = torch.zeros((N, k), device="cuda")
+    gr.reserve(dim if reserve else 256, k)  # (dim 256 needs no copy: that builds the partial-sum workspace only)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        maxk.maxk_sspmm_bwd(gr, dY, sp_index, dXs)
+    eager = torch.empty_like(dXs)
+    for i in range(3):
+        dY.mul_(1.5 + i)
+        dXs.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        maxk.maxk_sspmm_bwd(gr, dY, sp_index, eager)
+        torch.cuda.synchronize()
+        # the two forms add in a different order: both within n * 2^-24 of sum|terms|, n <= 699 in-entries
+        scale = float(dY.abs().max()) * float(np.abs(val).max()) * N
+        assert float((dXs - eager).abs().max()) <= 2 * 700 * 2.0 ** -24 * scale
+    gr.destroy()
