@@ -78,6 +78,20 @@ struct TiledSet {
     uint32_t* d_progress = nullptr;  // [8 * ceil(n_dsets / 8) * 32] progress marks of the running workgroups (pacing)
 };
 
+// A regrouped for the forward sweep kernel: work items are dealt to bins of per_bin output rows with about the same number
+// of entries; a wavefront keeps a bin's rows in LDS and walks the entries of all of them in the order of their source node.
+// Entry e of a bin goes to lane group e % groups; a batch holds the next sweep_batch(k) entries of each group.
+struct SweepSet {
+    int32_t groups = 0, batch_len = 0, per_bin = 0;
+    int64_t n_bins = 0;
+    int2* d_ent = nullptr;         // {source node | row of the bin << kSweepRowShift, or -1 (padding); weight}
+    uint32_t* d_batch = nullptr;   // [n_bins + 1] first batch of every bin
+    int2* d_rows = nullptr;        // [n_bins * per_bin] {output row or -1, partial-sum slot or -1}
+};
+constexpr int kSweepRowShift = 26;  // source nodes below 2^26, at most 31 rows a bin
+__host__ __device__ constexpr int sweep_groups(int k) { return k < kWave ? kWave / k : 1; }  // k a power of two
+__host__ __device__ constexpr int sweep_batch(int k) { return k < 16 ? 8 : 16; }
+
 extern thread_local int32_t g_last_hip_error;
 
 inline maxk_status hip_fail(hipError_t e)
@@ -149,6 +163,10 @@ maxk_status launch_cbsr_scatter(const float* values, const void* sp_index, int i
 maxk_status launch_spgemm_fwd(const ItemList& items, const int32_t* col, const float* val, const void* sp_data,
                               int value_type, const void* sp_index, int index_bytes, int64_t N, char* packed, int dim,
                               int k, float* Y, float* partials, hipStream_t s);
+// the same on a regrouped A (k = 8, 16, 32, 64 or 128, sweep_groups(k) == sweep.groups)
+maxk_status launch_spgemm_fwd_sweep(const ItemList& items, const SweepSet& sweep, const void* sp_data, int value_type,
+                                    const void* sp_index, int index_bytes, int64_t N, char* packed, int dim, int k, float* Y,
+                                    float* partials, hipStream_t s);
 int fwd_packed_index_offset(int k, int index_bytes, int val_bytes);  // where a record's indices start
 int fwd_packed_record_bytes(int k, int index_bytes, int val_bytes);
 int fwd_private_copies(int k);  // output-row copies the forward kernel keeps for MaxK k

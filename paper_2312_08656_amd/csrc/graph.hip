@@ -14,7 +14,10 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <new>
+#include <queue>
+#include <utility>
 #include <vector>
 
 #include <rocprim/rocprim.hpp>
@@ -38,6 +41,7 @@ struct maxk_graph {
     int64_t expand_floats = 0;
     std::vector<maxk::SlabSet*> slab_cache;    // A^T regrouped per slab height (one per height ever asked for)
     std::vector<maxk::TiledSet*> tiled_cache;  // visit lists of the LDS-tiled kernel, one per (set size, k / 4)
+    std::vector<maxk::SweepSet*> sweep_cache;  // A regrouped for the forward sweep, one per (lane groups, rows of a bin)
     char* d_sliced = nullptr;   // slice-major copy of dY for the column-sliced pull (rows that are not whole cache lines)
     int64_t sliced_bytes = 0;
     char* d_packed = nullptr;   // forward kernel's per-call repack of a small-k CBSR (one record per node)
@@ -50,6 +54,8 @@ struct maxk_graph {
     int32_t slab_kb = 0;
     int32_t fwd_pack_max = 0;
     int32_t pull_form = 0;
+    int32_t fwd_sweep = 0;
+    bool reserved = false;     // maxk_graph_reserve* was called: forward calls build no tables any more
     unsigned char* d_noalloc_scratch = nullptr;  // this device's copy of the library's fixed scratch array
     int device = 0;
 };
@@ -513,6 +519,172 @@ maxk_status tiled_for(maxk_graph* g, int dim, int k, bool existing_only, TiledSe
     return MAXK_OK;
 }
 
+void free_sweep(SweepSet& W)
+{
+    (void)hipFree(W.d_ent);
+    (void)hipFree(W.d_batch);
+    (void)hipFree(W.d_rows);
+    W = SweepSet();
+}
+
+// key[p] = bin << 32 | source node, payload[p] = p, row_of[p] = row of the bin, for the entries of every work item
+__global__ __launch_bounds__(256) void sweep_keys_kernel(const WorkItem* __restrict__ items, const uint32_t* __restrict__ place,
+                                                         int per_bin, const int32_t* __restrict__ col, uint64_t* __restrict__ key,
+                                                         uint32_t* __restrict__ entry, uint8_t* __restrict__ row_of)
+{
+    const WorkItem it = items[blockIdx.x];
+    const uint32_t bin = place[blockIdx.x] / (uint32_t)per_bin, row = place[blockIdx.x] % (uint32_t)per_bin;
+    for (int p = it.begin + (int)threadIdx.x; p < it.end; p += blockDim.x) {
+        key[p] = (uint64_t)bin << 32 | (uint32_t)col[p];
+        entry[p] = (uint32_t)p;
+        row_of[p] = (uint8_t)row;
+    }
+}
+
+__global__ __launch_bounds__(256) void sweep_fill_kernel(int2* __restrict__ ent, int64_t n)
+{
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) ent[i] = make_int2(-1, 0);
+}
+
+__global__ __launch_bounds__(256) void sweep_entries_kernel(const uint64_t* __restrict__ key, const uint32_t* __restrict__ entry,
+                                                            const uint8_t* __restrict__ row_of, const float* __restrict__ val,
+                                                            int64_t nnz, const uint32_t* __restrict__ bin_first,
+                                                            const uint32_t* __restrict__ batch, uint32_t groups,
+                                                            uint32_t batch_len, int2* __restrict__ ent)
+{
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nnz; i += stride) {
+        const uint32_t bin = (uint32_t)(key[i] >> 32), p = entry[i], rank = (uint32_t)i - bin_first[bin];
+        const uint32_t g = rank % groups, n = rank / groups;
+        ent[(((int64_t)batch[bin] + n / batch_len) * groups + g) * batch_len + n % batch_len] =
+            make_int2((int)((uint32_t)key[i] | (uint32_t)row_of[p] << kSweepRowShift), __float_as_int(val[p]));
+    }
+}
+
+// Deals the work items to bins (longest first, each to the bin with the fewest entries so far that has a row left) and
+// lays the entries out.  Synchronises the device.
+maxk_status build_sweep(maxk_graph* g, SweepSet& W, int groups, int batch_len, int per_bin)
+{
+    MAXK_HIP_TRY(hipDeviceSynchronize());
+    const int64_t n_items = g->csr_items.n_items, nnz = g->nnz, n_bins = (n_items + per_bin - 1) / per_bin;
+    std::vector<WorkItem> items((size_t)n_items);
+    MAXK_HIP_TRY(hipMemcpy(items.data(), g->csr_items.d_items, sizeof(WorkItem) * (size_t)n_items, hipMemcpyDeviceToHost));
+    std::vector<uint32_t> place((size_t)n_items), load((size_t)n_bins, 0), batch((size_t)n_bins + 1, 0), first((size_t)n_bins, 0);
+    std::vector<int2> rows((size_t)(n_bins * per_bin), make_int2(-1, -1));
+    {
+        std::vector<uint8_t> used((size_t)n_bins, 0);
+        using slot = std::pair<uint32_t, uint32_t>;  // entries so far, bin
+        std::priority_queue<slot, std::vector<slot>, std::greater<slot>> open;
+        for (int64_t i = 0; i < n_bins; ++i) open.push({0u, (uint32_t)i});
+        for (int64_t i = 0; i < n_items; ++i) {
+            const uint32_t b = open.top().second;
+            open.pop();
+            place[(size_t)i] = b * (uint32_t)per_bin + used[b];
+            rows[(size_t)place[(size_t)i]] = make_int2(items[(size_t)i].row, items[(size_t)i].slot);
+            load[b] += (uint32_t)(items[(size_t)i].end - items[(size_t)i].begin);
+            if (++used[b] < per_bin) open.push({load[b], b});
+        }
+    }
+    uint32_t run = 0;
+    for (int64_t b = 0; b < n_bins; ++b) {
+        first[(size_t)b] = run;
+        run += load[(size_t)b];
+        const uint64_t per_batch = (uint64_t)groups * batch_len;
+        const uint64_t next = batch[(size_t)b] + (load[(size_t)b] + per_batch - 1) / per_batch;
+        if (next > 0x7FFFFFFFull) return MAXK_UNSUPPORTED;
+        batch[(size_t)b + 1] = (uint32_t)next;
+    }
+    hipStream_t s = nullptr;
+    uint64_t *d_key = nullptr, *d_key_sorted = nullptr;
+    uint32_t *d_entry = nullptr, *d_perm = nullptr, *d_place = nullptr, *d_first = nullptr;
+    uint8_t* d_row_of = nullptr;
+    void* d_tmp = nullptr;
+    auto cleanup = [&]() {
+        (void)hipFree(d_key); (void)hipFree(d_key_sorted); (void)hipFree(d_entry); (void)hipFree(d_perm);
+        (void)hipFree(d_place); (void)hipFree(d_first); (void)hipFree(d_row_of); (void)hipFree(d_tmp);
+    };
+#define MAXK_TRY_CLEAN(expr)                                                           \
+    do {                                                                               \
+        hipError_t _e = (expr);                                                        \
+        if (_e != hipSuccess) { cleanup(); free_sweep(W); return hip_fail(_e); }       \
+    } while (0)
+    const int64_t n_ent = (int64_t)batch[(size_t)n_bins] * groups * batch_len;
+    MAXK_TRY_CLEAN(hipMalloc((void**)&W.d_ent, sizeof(int2) * (size_t)std::max<int64_t>(n_ent, 1)));
+    MAXK_TRY_CLEAN(hipMalloc((void**)&W.d_batch, sizeof(uint32_t) * batch.size()));
+    MAXK_TRY_CLEAN(hipMalloc((void**)&W.d_rows, sizeof(int2) * rows.size()));
+    MAXK_TRY_CLEAN(hipMalloc((void**)&d_key, sizeof(uint64_t) * (size_t)nnz));
+    MAXK_TRY_CLEAN(hipMalloc((void**)&d_key_sorted, sizeof(uint64_t) * (size_t)nnz));
+    MAXK_TRY_CLEAN(hipMalloc((void**)&d_entry, sizeof(uint32_t) * (size_t)nnz));
+    MAXK_TRY_CLEAN(hipMalloc((void**)&d_perm, sizeof(uint32_t) * (size_t)nnz));
+    MAXK_TRY_CLEAN(hipMalloc((void**)&d_place, sizeof(uint32_t) * place.size()));
+    MAXK_TRY_CLEAN(hipMalloc((void**)&d_first, sizeof(uint32_t) * first.size()));
+    MAXK_TRY_CLEAN(hipMalloc((void**)&d_row_of, (size_t)nnz));
+    MAXK_TRY_CLEAN(hipMemcpy(W.d_batch, batch.data(), sizeof(uint32_t) * batch.size(), hipMemcpyHostToDevice));
+    MAXK_TRY_CLEAN(hipMemcpy(W.d_rows, rows.data(), sizeof(int2) * rows.size(), hipMemcpyHostToDevice));
+    MAXK_TRY_CLEAN(hipMemcpy(d_place, place.data(), sizeof(uint32_t) * place.size(), hipMemcpyHostToDevice));
+    MAXK_TRY_CLEAN(hipMemcpy(d_first, first.data(), sizeof(uint32_t) * first.size(), hipMemcpyHostToDevice));
+    const unsigned blocks = (unsigned)std::min<int64_t>((nnz + 255) / 256, 65536);
+    hipLaunchKernelGGL(sweep_keys_kernel, dim3((unsigned)n_items), dim3(256), 0, s, g->csr_items.d_items, d_place, per_bin,
+                       g->d_col, d_key, d_entry, d_row_of);
+    MAXK_TRY_CLEAN(hipGetLastError());
+    int end_bit = 33;
+    while (end_bit < 64 && ((uint64_t)1 << (end_bit - 32)) < (uint64_t)n_bins) ++end_bit;
+    size_t tmp_bytes = 0;
+    MAXK_TRY_CLEAN(rocprim::radix_sort_pairs(nullptr, tmp_bytes, d_key, d_key_sorted, d_entry, d_perm, (size_t)nnz, 0, (unsigned)end_bit, s));
+    MAXK_TRY_CLEAN(hipMalloc(&d_tmp, tmp_bytes ? tmp_bytes : 16));
+    MAXK_TRY_CLEAN(rocprim::radix_sort_pairs(d_tmp, tmp_bytes, d_key, d_key_sorted, d_entry, d_perm, (size_t)nnz, 0, (unsigned)end_bit, s));
+    hipLaunchKernelGGL(sweep_fill_kernel, dim3(blocks), dim3(256), 0, s, W.d_ent, n_ent);
+    hipLaunchKernelGGL(sweep_entries_kernel, dim3(blocks), dim3(256), 0, s, d_key_sorted, d_perm, d_row_of, g->d_val, nnz, d_first,
+                       W.d_batch, (uint32_t)groups, (uint32_t)batch_len, W.d_ent);
+    MAXK_TRY_CLEAN(hipGetLastError());
+    MAXK_TRY_CLEAN(hipStreamSynchronize(s));
+#undef MAXK_TRY_CLEAN
+    cleanup();
+    W.groups = groups;
+    W.batch_len = batch_len;
+    W.per_bin = per_bin;
+    W.n_bins = n_bins;
+    return MAXK_OK;
+}
+
+// Rows of a bin of the forward sweep for MaxK k, 0 where the row-by-row kernel is taken.  The sweep pays when the CBSR is
+// larger than an L2 (3 bytes a kept position at least), the bins fill the chip at least once (256 CUs x 32 wavefronts),
+// and a bin has enough entries for its padding to whole batches and its copies of the rows: 3 batches a lane group (us,
+// row by row / sweep: 43 M entries on 576 k nodes, k = 16, 19 a group 828 / 924; 2.5 M on 169 k, k = 32, 15 a group 91 /
+// 104; k = 64, 60 a group 124 / 119).  Rows of a bin: as many as leave two workgroups a CU (k = 64: 3 / 4 / 5 rows 3541 /
+// 3175 / 4010 us, k = 32: 1 / 2 2211 / 2085, k = 16: 1 / 2 / 3 1303 / 1369 / 1499).
+int sweep_rows(const maxk_graph* g, int dim, int k)
+{
+    if ((k & (k - 1)) != 0 || k < 8 || k > 128 || dim > 512 || g->N > (1 << kSweepRowShift) || g->nnz == 0 || g->fwd_sweep == 1)
+        return 0;
+    const int per_bin = k >= 64 ? 4 : k == 32 ? 2 : 1;
+    if (g->fwd_sweep == 2) return per_bin;
+    const double bins = (double)g->csr_items.n_items / per_bin;
+    const bool pays = (double)g->N * k * 3.0 > 4e6 && bins >= 8192.0 &&
+                      (double)g->nnz >= bins * sweep_groups(k) * 3.0 * sweep_batch(k);
+    return pays ? per_bin : 0;
+}
+
+maxk_status sweep_for(maxk_graph* g, int groups, int batch_len, int per_bin, bool existing_only, SweepSet** out)
+{
+    for (SweepSet* W : g->sweep_cache)
+        if (W->groups == groups && W->batch_len == batch_len && W->per_bin == per_bin) { *out = W; return MAXK_OK; }
+    if (existing_only) return MAXK_UNSUPPORTED;
+    SweepSet* W = new (std::nothrow) SweepSet();
+    if (!W) return MAXK_OUT_OF_MEMORY;
+    maxk_status st;
+    try {
+        st = build_sweep(g, *W, groups, batch_len, per_bin);
+        if (st == MAXK_OK) g->sweep_cache.push_back(W);
+    } catch (const std::bad_alloc&) {
+        st = MAXK_OUT_OF_MEMORY;
+    }
+    if (st != MAXK_OK) { free_sweep(*W); delete W; return st; }
+    *out = W;
+    return MAXK_OK;
+}
+
 // The forward kernel repacks the CBSR when a row of it is well below a cache line.
 bool fwd_uses_packed(const maxk_graph* g, int k, int index_bytes, int val_bytes)
 {
@@ -712,6 +884,7 @@ MAXK_API maxk_status maxk_graph_create(maxk_graph** out, int64_t N, int64_t nnz,
     g->chunk = env_int("MAXK_CHUNK", default_chunk(nnz), 64, 1 << 20);
     g->slab_kb = env_int("MAXK_SLAB_KB", 3584, 64, 1 << 20);
     g->fwd_pack_max = env_int("MAXK_FWD_PACK_MAX", 96, 0, 1 << 20);
+    g->fwd_sweep = env_int("MAXK_FWD_SWEEP", 0, 0, 2);
     g->pull_form = env_int("MAXK_PULL_FORM", 0, 0, 2);
     (void)hipGetDevice(&g->device);
     {
@@ -772,6 +945,7 @@ MAXK_API maxk_status maxk_graph_destroy(maxk_graph* g)
     (void)hipFree(g->d_sliced);
     for (SlabSet* S : g->slab_cache) { free_slabs(*S); delete S; }
     for (TiledSet* T : g->tiled_cache) { free_tiled(*T); delete T; }
+    for (SweepSet* W : g->sweep_cache) { free_sweep(*W); delete W; }
     (void)hipFree(g->d_partials);
     delete g;
     return MAXK_OK;
@@ -783,8 +957,14 @@ MAXK_API maxk_status maxk_graph_reserve_narrow(maxk_graph* g, int32_t dim, int32
     if (dy_value_type < MAXK_VALUE_F32 || dy_value_type > MAXK_VALUE_F16) return MAXK_INVALID_ARGUMENT;
     if (dim > MAXK_MAX_DIM) return MAXK_UNSUPPORTED;
     if (g->N == 0) return MAXK_OK;
+    g->reserved = true;
     maxk_status st = ensure_workspace(g, dim, k);
     if (st != MAXK_OK) return st;
+    if (const int per_bin = sweep_rows(g, dim, k)) {
+        SweepSet* W = nullptr;
+        st = sweep_for(g, sweep_groups(k), sweep_batch(k), per_bin, false, &W);
+        if (st != MAXK_OK && st != MAXK_UNSUPPORTED && st != MAXK_OUT_OF_MEMORY) return st;  // (else: row by row)
+    }
     for (int vb = 2; vb <= 4; vb += 2) {
         for (int ib = 1; ib <= 4; ib *= 2) {
             for (int kk = 1; kk <= k; ++kk) {  // the largest repacked record among k' <= k
@@ -890,6 +1070,14 @@ MAXK_API maxk_status maxk_spgemm_fwd_narrow(maxk_graph* g, const void* d_sp_data
         if (st != MAXK_OK) return st;
         packed = g->d_packed;
     }
+    if (const int per_bin = sweep_rows(g, dim, k)) {
+        SweepSet* W = nullptr;
+        st = sweep_for(g, sweep_groups(k), sweep_batch(k), per_bin, g->reserved || capturing((hipStream_t)stream), &W);
+        if (st == MAXK_OK)
+            return launch_spgemm_fwd_sweep(g->csr_items, *W, d_sp_data, value_type, d_sp_index, index_bytes, g->N, packed, dim, k,
+                                           d_Y, g->d_partials, (hipStream_t)stream);
+        if (st != MAXK_UNSUPPORTED && st != MAXK_OUT_OF_MEMORY) return st;
+    }
     return launch_spgemm_fwd(g->csr_items, g->d_col, g->d_val, d_sp_data, value_type, d_sp_index, index_bytes, g->N, packed,
                              dim, k, d_Y, g->d_partials, (hipStream_t)stream);
 }
@@ -920,6 +1108,12 @@ MAXK_API maxk_status maxk_spgemm_fwd_noalloc(maxk_graph* g, const float* d_sp_da
         partial_bytes + g->N * (int64_t)fwd_packed_record_bytes(k, index_bytes, 4) <= (int64_t)MAXK_NOALLOC_SCRATCH_BYTES)
         packed = reinterpret_cast<char*>(g->d_noalloc_scratch) + partial_bytes;
     // nothing in the array has to start at zero: the kernels write every partial row and every record they read
+    if (const int per_bin = sweep_rows(g, dim, k)) {  // where the regrouped A is there already
+        SweepSet* W = nullptr;
+        if (sweep_for(g, sweep_groups(k), sweep_batch(k), per_bin, true, &W) == MAXK_OK)
+            return launch_spgemm_fwd_sweep(g->csr_items, *W, d_sp_data, MAXK_VALUE_F32, d_sp_index, index_bytes, g->N, packed, dim,
+                                           k, d_Y, partials, (hipStream_t)stream);
+    }
     return launch_spgemm_fwd(g->csr_items, g->d_col, g->d_val, d_sp_data, MAXK_VALUE_F32, d_sp_index, index_bytes, g->N,
                              packed, dim, k, d_Y, partials, (hipStream_t)stream);
 }

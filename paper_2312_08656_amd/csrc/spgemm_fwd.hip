@@ -64,4 +64,19 @@ maxk_status launch_spgemm_fwd(const ItemList& L, const int32_t* col, const float
     return launch_combine(L, partials, dim, Y, s);
 }
 
+maxk_status launch_spgemm_fwd_sweep(const ItemList& L, const SweepSet& S, const void* sp_data, int value_type,
+                                    const void* sp_index, int index_bytes, int64_t N, char* packed, int dim, int k, float* Y,
+                                    float* partials, hipStream_t s)
+{
+    maxk_status st;
+    if (value_type == MAXK_VALUE_BF16)
+        st = launch_fwd_sweep_format<MAXK_VALUE_BF16>(S, sp_data, sp_index, index_bytes, N, packed, dim, k, Y, partials, s);
+    else if (value_type == MAXK_VALUE_F16)
+        st = launch_fwd_sweep_format<MAXK_VALUE_F16>(S, sp_data, sp_index, index_bytes, N, packed, dim, k, Y, partials, s);
+    else
+        st = launch_fwd_sweep_format<MAXK_VALUE_F32>(S, sp_data, sp_index, index_bytes, N, packed, dim, k, Y, partials, s);
+    if (st != MAXK_OK) return st;
+    return launch_combine(L, partials, dim, Y, s);
+}
+
 }  // namespace maxk

@@ -28,6 +28,8 @@
 #pragma once
 
 #include <algorithm>
+#include <type_traits>
+#include <utility>
 
 #include "common.hpp"
 
@@ -54,6 +56,10 @@ template <int VT>
 maxk_status launch_fwd_format(const ItemList& L, const int32_t* col, const float* val, const void* sp_data,
                               const void* sp_index, int index_bytes, int64_t N, char* packed, int dim, int k,
                               float* Y, float* partials, hipStream_t s);
+
+template <int VT>
+maxk_status launch_fwd_sweep_format(const SweepSet& S, const void* sp_data, const void* sp_index, int index_bytes, int64_t N,
+                                    char* packed, int dim, int k, float* Y, float* partials, hipStream_t s);
 
 namespace {
 
@@ -222,6 +228,201 @@ __global__ __launch_bounds__(kWave) void spgemm_fwd_rmw_kernel(const WorkItem* _
     }
 }
 
+
+// ---- forward sweep ----
+//
+// The kernel above has every wavefront gather from its own place in the CBSR, 37 MB of it on the dense workload (k = 32)
+// against 4 MB of L2 per XCD: nearly every record comes from beyond L2, and that fabric is what it waits for (7.4 TB/s).
+// Here a wavefront keeps a BIN of output rows in LDS and walks the entries of all its rows in the order of their source
+// node.  Bins hold about the same number of entries, so the wavefronts resident on an XCD pass over the source nodes at
+// about the same pace and share the records they gather through its L2.  As above, entries that share a wave instruction
+// add into private copies of the row (one per lane group of K lanes: the same number of partial sums per row), and LDS
+// operations of a wavefront execute in order.
+//
+// The LDS pipe bounds it next (a read-add-write pair is ~14 clocks a wave instruction), so entries do not go through LDS:
+// each row of 16 lanes holds the next 16 entries of its lane group (8 lanes the next 8 for K = 8) and hands them out by
+// data-parallel-primitive broadcasts.
+// Measured, us, kernel above / sweep: dense k = 8 1310 / 1161, k = 16 1563 / 1303, k = 32 2834 / 2085, k = 64 5200 / 3175,
+// k = 128 9276 / 6872, bf16 k = 64 3382 / 2985; 79 M entries on 132 k nodes k = 32 1572 / 1282; 43 M on 576 k k = 32
+// 1445 / 1336; 126 M on 2.4 M nodes k = 64 6181 / 4845.
+constexpr int kSweepWaves = 16;            // wavefronts of a workgroup, at most
+constexpr size_t kSweepLds = 64 * 1024;    // LDS of a workgroup, at most: two of them on a CU
+constexpr uint32_t kSweepMeet = 8;         // batches between barriers (k = 32: 1996 / 2028 / 2098 us at 4 / 8 / 16, bf16
+                                           // k = 64: 3109 / 3028 / 2988)
+
+template <int I>
+__device__ __forceinline__ uint32_t row16_lane(uint32_t x)  // lane I of the caller's 16 lanes
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x150 + I, 0xF, 0xF, true);
+}
+
+template <int I>
+__device__ __forceinline__ uint32_t row8_lane(uint32_t x)  // lane I of the caller's 8 lanes
+{
+    // the quad of the eight that holds lane I, moved into both; then lane I % 4 of the quad
+    const uint32_t half = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, I < 4 ? 0x114 : 0x104, 0xF, I < 4 ? 0xA : 0x5, false);
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)half, (I & 3) * 0x55, 0xF, 0xF, true);
+}
+
+// K: MaxK k (a power of two, 8..128).  A workgroup is up to 16 wavefronts with a bin each; they meet at a barrier every
+// kSweepMeet batches, which keeps a CU together on its way over the source nodes (k = 32: 2580 us without, 2100 with).
+template <int K, bool PACKED, int VT, typename IdxT>
+__global__ __launch_bounds__(kSweepWaves * kWave) void spgemm_fwd_sweep_kernel(
+    const int2* __restrict__ ent, const uint32_t* __restrict__ batch, const int2* __restrict__ bin_rows, int64_t n_bins,
+    int per_bin, const value_store_t<VT>* __restrict__ sp_data, const IdxT* __restrict__ sp_index,
+    const char* __restrict__ packed, int rec_bytes, int idx_off, int dim, int vec_out, float* __restrict__ Y,
+    float* __restrict__ partials)
+{
+    constexpr int GROUPS = sweep_groups(K), BATCH = sweep_batch(K);
+    constexpr int LANES = kWave / GROUPS;             // lanes of a group
+    constexpr int PASSES = K < kWave ? 1 : K / kWave;  // wave instructions per entry
+    constexpr int STEP = 8 / PASSES;                  // entries of a lane group in flight
+    extern __shared__ __attribute__((aligned(16))) float sweep_lds[];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int waves = blockDim.x / kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t bin0 = (int64_t)blockIdx.x * waves, bin = bin0 + wave;
+    const int copy = per_bin * dim, total = GROUPS * copy;  // floats of one copy of the bin's rows, and of all of them
+    float* __restrict__ rows = sweep_lds + wave * total;
+    if ((total & 3) == 0) {
+        for (int c = lane * 4; c < total; c += kWave * 4) *reinterpret_cast<float4*>(rows + c) = make_float4(0.f, 0.f, 0.f, 0.f);
+    } else {
+        for (int c = lane; c < total; c += kWave) rows[c] = 0.f;
+    }
+    const uint32_t b0 = bin < n_bins ? batch[bin] : 0u, b1 = bin < n_bins ? batch[bin + 1] : 0u;
+    uint32_t longest = 0;  // batches of the workgroup's longest bin: every wavefront meets every barrier
+    for (int i = 0; i < waves && bin0 + i < n_bins; ++i) longest = max(longest, batch[bin0 + i + 1] - batch[bin0 + i]);
+    const int t = lane % LANES;  // CBSR position
+    const int own = lane / LANES * copy;
+    constexpr int64_t kBatchEntries = GROUPS * BATCH;
+    const int2* __restrict__ mine = ent + lane / LANES * BATCH + lane % BATCH;
+    int2 next = b0 < b1 ? mine[b0 * kBatchEntries] : make_int2(-1, 0);
+    for (uint32_t i = 0; i < longest; ++i) {
+        if (i % kSweepMeet == 0) __syncthreads();
+        const uint32_t b = b0 + i;
+        if (b >= b1) continue;  // wave-uniform
+        const int2 cur = next;
+        if (b + 1 < b1) next = mine[(b + 1) * kBatchEntries];
+        const auto steps = [&](auto first) {
+            constexpr int F = decltype(first)::value;
+            float d[8], w[8];
+            int at[8];
+            bool ok[8];
+            const auto load = [&](auto idx) {
+                constexpr int R = decltype(idx)::value, E = F + R / PASSES, P = R % PASSES;
+                uint32_t x;
+                if constexpr (BATCH == 8) {
+                    x = row8_lane<E>((uint32_t)cur.x);
+                    w[R] = __uint_as_float(row8_lane<E>((uint32_t)cur.y));
+                } else {
+                    x = row16_lane<E>((uint32_t)cur.x);
+                    w[R] = __uint_as_float(row16_lane<E>((uint32_t)cur.y));
+                }
+                ok[R] = x != 0xFFFFFFFFu;
+                const uint32_t node = ok[R] ? x & ((1u << kSweepRowShift) - 1u) : 0u;  // (padding reads node 0 and drops it)
+                const int base = own + (int)(x >> kSweepRowShift) * dim;
+                if constexpr (PACKED) {
+                    const char* rec = packed + (int64_t)node * rec_bytes;
+                    d[R] = widen_value<VT>(reinterpret_cast<const value_store_t<VT>*>(rec)[t + P * kWave]);
+                    at[R] = base + (int)reinterpret_cast<const IdxT*>(rec + idx_off)[t + P * kWave];
+                } else {
+                    const int64_t off = (int64_t)node * K + (t + P * kWave);
+                    d[R] = widen_value<VT>(sp_data[off]);
+                    at[R] = base + (int)sp_index[off];
+                }
+            };
+            [&]<int... I>(std::integer_sequence<int, I...>) { (load(std::integral_constant<int, I>{}), ...); }
+            (std::make_integer_sequence<int, 8>{});
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                if (ok[r]) {
+                    const float old = rows[at[r]];
+                    rows[at[r]] = old + w[r] * d[r];
+                }
+            }
+        };
+        [&]<int... I>(std::integer_sequence<int, I...>) { (steps(std::integral_constant<int, I * STEP>{}), ...); }
+        (std::make_integer_sequence<int, BATCH / STEP>{});
+    }
+    if (bin >= n_bins) return;
+    // the wavefront's own LDS, whose operations execute in order: only the compiler has to keep it
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int i = 0; i < per_bin; ++i) {
+        const int2 to = bin_rows[bin * per_bin + i];
+        if (to.x < 0) continue;
+        float* __restrict__ out = to.y < 0 ? Y + (int64_t)to.x * dim : partials + (int64_t)to.y * dim;
+        const float* __restrict__ row = rows + i * dim;
+        if (vec_out) {
+            for (int c = lane * 4; c < dim; c += kWave * 4) {
+                float4 acc = *reinterpret_cast<const float4*>(row + c);
+#pragma unroll
+                for (int g = 1; g < GROUPS; ++g) {
+                    const float4 x = *reinterpret_cast<const float4*>(row + g * copy + c);
+                    acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
+                }
+                *reinterpret_cast<float4*>(out + c) = acc;
+            }
+        } else {
+            for (int c = lane; c < dim; c += kWave) {
+                float acc = row[c];
+#pragma unroll
+                for (int g = 1; g < GROUPS; ++g) acc += row[g * copy + c];
+                out[c] = acc;
+            }
+        }
+    }
+}
+
+template <bool PACKED, int VT, typename IdxT>
+maxk_status launch_sweep(const SweepSet& S, const value_store_t<VT>* sp_data, const IdxT* sp_index, const char* packed,
+                         int rec_bytes, int idx_off, int dim, int k, float* Y, float* partials, hipStream_t s)
+{
+    const size_t lds = sizeof(float) * (size_t)(S.groups * S.per_bin) * (size_t)dim;
+    int waves = kSweepWaves;
+    while (waves > 1 && lds * waves > kSweepLds) waves /= 2;
+    const int vec_out = dim % 4 == 0 && aligned(Y, 16) && aligned(partials, 16);
+    const dim3 grid((unsigned)((S.n_bins + waves - 1) / waves)), block((unsigned)(kWave * waves));
+#define MAXK_FWD_SWEEP(K)                                                                                               \
+    hipLaunchKernelGGL((spgemm_fwd_sweep_kernel<K, PACKED, VT, IdxT>), grid, block, lds * waves, s, S.d_ent, S.d_batch, \
+                       S.d_rows, S.n_bins, S.per_bin, sp_data, sp_index, packed, rec_bytes, idx_off, dim, vec_out, Y, partials)
+    switch (k) {
+        case 8: MAXK_FWD_SWEEP(8); break;
+        case 16: MAXK_FWD_SWEEP(16); break;
+        case 32: MAXK_FWD_SWEEP(32); break;
+        case 64: MAXK_FWD_SWEEP(64); break;
+        case 128: MAXK_FWD_SWEEP(128); break;
+        default: return MAXK_UNSUPPORTED;
+    }
+#undef MAXK_FWD_SWEEP
+    MAXK_LAUNCH_CHECK();
+    return MAXK_OK;
+}
+
+template <int VT, typename IdxT>
+maxk_status launch_sweep_i(const SweepSet& S, const value_store_t<VT>* sp_data, const IdxT* sp_index, int64_t N, char* packed,
+                           int dim, int k, float* Y, float* partials, hipStream_t s)
+{
+    if (!packed) return launch_sweep<false, VT>(S, sp_data, sp_index, nullptr, 0, 0, dim, k, Y, partials, s);
+    const int vb = (int)sizeof(value_store_t<VT>);
+    const int rec_bytes = fwd_packed_record_bytes(k, (int)sizeof(IdxT), vb), idx_off = fwd_packed_index_offset(k, (int)sizeof(IdxT), vb);
+    const int64_t n_units = N * (int64_t)k;
+    const unsigned blocks = (unsigned)std::min<int64_t>((n_units + 255) / 256, 65536);
+    hipLaunchKernelGGL((pack_cbsr_kernel<VT, IdxT>), dim3(blocks), dim3(256), 0, s, sp_data, sp_index, n_units, k, rec_bytes,
+                       idx_off, packed);
+    MAXK_LAUNCH_CHECK();
+    return launch_sweep<true, VT>(S, sp_data, sp_index, packed, rec_bytes, idx_off, dim, k, Y, partials, s);
+}
+
+template <int VT>
+maxk_status launch_fwd_sweep_vt(const SweepSet& S, const void* sp_data_v, const void* sp_index, int index_bytes, int64_t N,
+                                char* packed, int dim, int k, float* Y, float* partials, hipStream_t s)
+{
+    const auto* sp_data = (const value_store_t<VT>*)sp_data_v;
+    if (index_bytes == 1) return launch_sweep_i<VT>(S, sp_data, (const uint8_t*)sp_index, N, packed, dim, k, Y, partials, s);
+    if (index_bytes == 2) return launch_sweep_i<VT>(S, sp_data, (const uint16_t*)sp_index, N, packed, dim, k, Y, partials, s);
+    return launch_sweep_i<VT>(S, sp_data, (const int32_t*)sp_index, N, packed, dim, k, Y, partials, s);
+}
 
 template <int VT, typename IdxT>
 maxk_status launch_atomic(const ItemList& L, const int32_t* col, const float* val, const value_store_t<VT>* sp_data,

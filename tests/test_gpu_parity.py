@@ -649,3 +649,58 @@ def test_column_sliced_pull_in_a_captured_graph(_sliced_form, dim, reserve):
         scale = float(dY.abs().max()) * float(np.abs(val).max()) * N
         assert float((dXs - eager).abs().max()) <= 2 * 700 * 2.0 ** -24 * scale
     gr.destroy()
+
+
+@pytest.mark.parametrize("dim,k,ib", [(8, 8, 1), (100, 8, 1), (255, 16, 1), (256, 16, 2), (64, 32, 1), (256, 32, 4),
+                                      (130, 64, 1), (512, 64, 2), (128, 128, 1), (509, 128, 4)])
+@pytest.mark.parametrize("fmt", ["f32", "bf16", "f16"])
+def test_forward_sweep(monkeypatch, dim, k, ib, fmt):
+    # bins of 1, 2 and 4 rows (the last one not full), rows of 0 entries to split ones, any column order, Y misaligned
+    monkeypatch.setenv("MAXK_FWD_SWEEP", "2")
+    N = 701
+    rowptr, col, val = _mixed_degrees(N, 81)  # (column degrees; as rows of the transposed graph)
+    order = np.argsort(col, kind="stable")
+    rows = np.repeat(np.arange(N), np.diff(rowptr)).astype(np.int32)
+    rowptr, col, val = csr_from_coo(N, list(zip(col[order].tolist(), rows[order].tolist(), val[order].tolist())))
+    H = synth.normal_matrix(N, dim, 82)
+    gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val))
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[fmt]
+    sp_data = torch.empty((N, k), dtype=dt, device="cuda")
+    sp_index = torch.empty((N, k), dtype={1: torch.uint8, 2: torch.int16, 4: torch.int32}[ib], device="cuda")
+    maxk.maxk_topk_cbsr_narrow(to_dev(H), k, sp_data, sp_index)
+    data, idx = oracle.topk_cbsr(H, k)
+    data = sp_data.float().cpu().numpy()
+    shuffle = np.random.default_rng(83).permutation(k)
+    for perm in (np.arange(k), shuffle):
+        at = torch.from_numpy(perm).cuda()
+        d, ix = sp_data[:, at].contiguous(), sp_index[:, at].contiguous()
+        ref, refabs = oracle.spgemm_fwd(rowptr, col, val, np.ascontiguousarray(data[:, perm]), np.ascontiguousarray(idx[:, perm]), dim)
+        for offset in (0, 1):
+            Y = torch.full((N * dim + offset,), float("nan"), device="cuda")[offset:].view(N, dim)
+            maxk.maxk_spgemm_fwd_narrow(gr, d, ix, dim, Y)
+            torch.cuda.synchronize()
+            assert (np.abs(Y.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all()
+    if fmt == "f32":  # the regrouped graph is there now: the entry point that allocates nothing uses it too
+        Y2 = torch.full((N, dim), float("nan"), device="cuda")
+        maxk.maxk_spgemm_fwd_noalloc(gr, d, ix, dim, Y2)
+        torch.cuda.synchronize()
+        assert (np.abs(Y2.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all()
+    gr.destroy()
+
+
+def test_forward_sweep_keeps_infinities_in_their_rows(monkeypatch):
+    # padding entries read node 0: a value of infinity there must not reach rows that have no entry of node 0
+    monkeypatch.setenv("MAXK_FWD_SWEEP", "2")
+    N, dim, k = 40, 64, 32
+    rowptr, col, val = csr_from_coo(N, [(i, j, 1.0) for i in range(N) for j in range(1, 1 + i % 5)])
+    sp_data = torch.ones((N, k), device="cuda")
+    sp_data[0] = float("inf")
+    sp_index = torch.arange(k, dtype=torch.uint8, device="cuda").repeat(N, 1).contiguous()
+    gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val))
+    Y = torch.full((N, dim), float("nan"), device="cuda")
+    maxk.maxk_spgemm_fwd(gr, sp_data, sp_index, dim, Y)
+    torch.cuda.synchronize()
+    want = np.zeros((N, dim), np.float32)
+    want[:, :k] = (np.arange(N) % 5)[:, None]
+    assert np.array_equal(Y.cpu().numpy(), want)
+    gr.destroy()
