@@ -649,20 +649,24 @@ maxk_status build_sweep(maxk_graph* g, SweepSet& W, int groups, int batch_len, i
 }
 
 // Rows of a bin of the forward sweep for MaxK k, 0 where the row-by-row kernel is taken.  The sweep pays when the CBSR is
-// larger than an L2 (3 bytes a kept position at least), the bins fill the chip at least once (256 CUs x 32 wavefronts),
-// and a bin has enough entries for its padding to whole batches and its copies of the rows: 3 batches a lane group (us,
-// row by row / sweep: 43 M entries on 576 k nodes, k = 16, 19 a group 828 / 924; 2.5 M on 169 k, k = 32, 15 a group 91 /
-// 104; k = 64, 60 a group 124 / 119).  Rows of a bin: as many as leave two workgroups a CU (k = 64: 3 / 4 / 5 rows 3541 /
-// 3175 / 4010 us, k = 32: 1 / 2 2211 / 2085, k = 16: 1 / 2 / 3 1303 / 1369 / 1499).
-int sweep_rows(const maxk_graph* g, int dim, int k)
+// several times an L2, the bins fill the chip (256 CUs x 32 wavefronts), the rows in LDS leave enough wavefronts a CU, and
+// a bin has enough entries for its padding to whole batches and its copies of the rows.  us, row by row / sweep:
+//   CBSR size: k = 32, 100 k nodes (16 MB) 212 / 185, 40 k (6 MB) 60 / 62; k = 64, 100 k (32 MB) 377 / 345, 40 k (13 MB)
+//     273 / 287, bf16 values 100 k (19 MB) 825 / 872
+//   entries a lane group: k = 16, 123 1563 / 1303, 75 323 / 325, 19 828 / 924; k = 8, 62 1310 / 1161, 38 258 / 275; k = 32,
+//     101 618 / 583, 31 231 / 237
+//   width: k = 64, dim 400 706 / 685, dim 512 397 / 468; k = 128, dim 512 855 / 723
+// Rows of a bin: k = 64, 3 / 4 / 5 rows 3541 / 3175 / 4010 us; k = 32, 1 / 2 2211 / 2085; k = 16, 1 / 2 1303 / 1369.
+int sweep_rows(const maxk_graph* g, int dim, int k, int index_bytes, int val_bytes)
 {
     if ((k & (k - 1)) != 0 || k < 8 || k > 128 || dim > 512 || g->N > (1 << kSweepRowShift) || g->nnz == 0 || g->fwd_sweep == 1)
         return 0;
     const int per_bin = k >= 64 ? 4 : k == 32 ? 2 : 1;
     if (g->fwd_sweep == 2) return per_bin;
-    const double bins = (double)g->csr_items.n_items / per_bin;
-    const bool pays = (double)g->N * k * 3.0 > 4e6 && bins >= 8192.0 &&
-                      (double)g->nnz >= bins * sweep_groups(k) * 3.0 * sweep_batch(k);
+    const double bins = (double)g->csr_items.n_items / per_bin, table = (double)g->N * k * (val_bytes + index_bytes);
+    const double entries = (double)g->nnz / (bins * sweep_groups(k));  // of a lane group
+    const bool pays = table >= (k == 64 ? 30e6 : 10e6) && bins >= 8192.0 && entries >= (k == 16 ? 100.0 : 48.0) &&
+                      dim <= (k == 128 ? 512 : k >= 32 ? 400 : 256);
     return pays ? per_bin : 0;
 }
 
@@ -960,7 +964,7 @@ MAXK_API maxk_status maxk_graph_reserve_narrow(maxk_graph* g, int32_t dim, int32
     g->reserved = true;
     maxk_status st = ensure_workspace(g, dim, k);
     if (st != MAXK_OK) return st;
-    if (const int per_bin = sweep_rows(g, dim, k)) {
+    if (const int per_bin = sweep_rows(g, dim, k, dim <= 256 ? 1 : 2, 4)) {  // (narrower records may not need it)
         SweepSet* W = nullptr;
         st = sweep_for(g, sweep_groups(k), sweep_batch(k), per_bin, false, &W);
         if (st != MAXK_OK && st != MAXK_UNSUPPORTED && st != MAXK_OUT_OF_MEMORY) return st;  // (else: row by row)
@@ -1070,7 +1074,7 @@ MAXK_API maxk_status maxk_spgemm_fwd_narrow(maxk_graph* g, const void* d_sp_data
         if (st != MAXK_OK) return st;
         packed = g->d_packed;
     }
-    if (const int per_bin = sweep_rows(g, dim, k)) {
+    if (const int per_bin = sweep_rows(g, dim, k, index_bytes, vb)) {
         SweepSet* W = nullptr;
         st = sweep_for(g, sweep_groups(k), sweep_batch(k), per_bin, g->reserved || capturing((hipStream_t)stream), &W);
         if (st == MAXK_OK)
@@ -1108,7 +1112,7 @@ MAXK_API maxk_status maxk_spgemm_fwd_noalloc(maxk_graph* g, const float* d_sp_da
         partial_bytes + g->N * (int64_t)fwd_packed_record_bytes(k, index_bytes, 4) <= (int64_t)MAXK_NOALLOC_SCRATCH_BYTES)
         packed = reinterpret_cast<char*>(g->d_noalloc_scratch) + partial_bytes;
     // nothing in the array has to start at zero: the kernels write every partial row and every record they read
-    if (const int per_bin = sweep_rows(g, dim, k)) {  // where the regrouped A is there already
+    if (const int per_bin = sweep_rows(g, dim, k, index_bytes, 4)) {  // where the regrouped A is there already
         SweepSet* W = nullptr;
         if (sweep_for(g, sweep_groups(k), sweep_batch(k), per_bin, true, &W) == MAXK_OK)
             return launch_spgemm_fwd_sweep(g->csr_items, *W, d_sp_data, MAXK_VALUE_F32, d_sp_index, index_bytes, g->N, packed, dim,
