@@ -484,7 +484,9 @@ int32_t slab_rows_for(const maxk_graph* g, int dim, int val_bytes = 4)
 bool capturing(hipStream_t s)
 {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(s, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();  // the default stream while another one is being captured: nothing may be allocated either
+    return true;
 }
 
 // The regrouping of A^T for one slab height: built on first use (or by maxk_graph_reserve*), then kept until the
@@ -648,28 +650,6 @@ maxk_status build_sweep(maxk_graph* g, SweepSet& W, int groups, int batch_len, i
     return MAXK_OK;
 }
 
-// Rows of a bin of the forward sweep for MaxK k, 0 where the row-by-row kernel is taken.  The sweep pays when the CBSR is
-// several times an L2, the bins fill the chip (256 CUs x 32 wavefronts), the rows in LDS leave enough wavefronts a CU, and
-// a bin has enough entries for its padding to whole batches and its copies of the rows.  us, row by row / sweep:
-//   CBSR size: k = 32, 100 k nodes (16 MB) 212 / 185, 40 k (6 MB) 60 / 62; k = 64, 100 k (32 MB) 377 / 345, 40 k (13 MB)
-//     273 / 287, bf16 values 100 k (19 MB) 825 / 872
-//   entries a lane group: k = 16, 123 1563 / 1303, 75 323 / 325, 19 828 / 924; k = 8, 62 1310 / 1161, 38 258 / 275; k = 32,
-//     101 618 / 583, 31 231 / 237
-//   width: k = 64, dim 400 706 / 685, dim 512 397 / 468; k = 128, dim 512 855 / 723
-// Rows of a bin: k = 64, 3 / 4 / 5 rows 3541 / 3175 / 4010 us; k = 32, 1 / 2 2211 / 2085; k = 16, 1 / 2 1303 / 1369.
-int sweep_rows(const maxk_graph* g, int dim, int k, int index_bytes, int val_bytes)
-{
-    if ((k & (k - 1)) != 0 || k < 8 || k > 128 || dim > 512 || g->N > (1 << kSweepRowShift) || g->nnz == 0 || g->fwd_sweep == 1)
-        return 0;
-    const int per_bin = k >= 64 ? 4 : k == 32 ? 2 : 1;
-    if (g->fwd_sweep == 2) return per_bin;
-    const double bins = (double)g->csr_items.n_items / per_bin, table = (double)g->N * k * (val_bytes + index_bytes);
-    const double entries = (double)g->nnz / (bins * sweep_groups(k));  // of a lane group
-    const bool pays = table >= (k == 64 ? 30e6 : 10e6) && bins >= 8192.0 && entries >= (k == 16 ? 100.0 : 48.0) &&
-                      dim <= (k == 128 ? 512 : k >= 32 ? 400 : 256);
-    return pays ? per_bin : 0;
-}
-
 maxk_status sweep_for(maxk_graph* g, int groups, int batch_len, int per_bin, bool existing_only, SweepSet** out)
 {
     for (SweepSet* W : g->sweep_cache)
@@ -693,6 +673,30 @@ maxk_status sweep_for(maxk_graph* g, int groups, int batch_len, int per_bin, boo
 bool fwd_uses_packed(const maxk_graph* g, int k, int index_bytes, int val_bytes)
 {
     return k * (val_bytes + index_bytes) <= g->fwd_pack_max;
+}
+
+// Rows of a bin of the forward sweep for MaxK k, 0 where the row-by-row kernel is taken.  The sweep pays when the CBSR is
+// several times an L2, the bins fill the chip (256 CUs x 32 wavefronts), the rows in LDS leave enough wavefronts a CU, and
+// a bin has enough entries for its padding to whole batches and its copies of the rows.  us, row by row / sweep:
+//   CBSR size: k = 32, 100 k nodes (16 MB) 212 / 185, 40 k (6 MB) 60 / 62; k = 64, 100 k (32 MB) 377 / 345, 40 k (13 MB)
+//     273 / 287, bf16 values 100 k (19 MB) 825 / 872
+//   entries a lane group: k = 16, 123 1563 / 1303, 75 323 / 325, 19 828 / 924; k = 8, 62 1310 / 1161, 38 258 / 275; k = 32,
+//     101 618 / 583, 31 231 / 237
+//   width: k = 64, dim 400 706 / 685, dim 512 397 / 468; k = 128, dim 512 855 / 723
+// Rows of a bin: k = 64, 3 / 4 / 5 rows 3541 / 3175 / 4010 us; k = 32, 1 / 2 2211 / 2085; k = 16, 1 / 2 1303 / 1369.
+int sweep_rows(const maxk_graph* g, int dim, int k, int index_bytes, int val_bytes)
+{
+    if ((k & (k - 1)) != 0 || k < 8 || k > 128 || dim > 512 || g->N > (1 << kSweepRowShift) || g->nnz == 0 || g->fwd_sweep == 1)
+        return 0;
+    const int per_bin = k >= 64 ? 4 : k == 32 ? 2 : 1;
+    if (g->fwd_sweep == 2) return per_bin;
+    const int record = fwd_uses_packed(g, k, index_bytes, val_bytes) ? fwd_packed_record_bytes(k, index_bytes, val_bytes)
+                                                                     : k * (val_bytes + index_bytes);
+    const double bins = (double)g->csr_items.n_items / per_bin, table = (double)g->N * record;
+    const double entries = (double)g->nnz / (bins * sweep_groups(k));  // of a lane group
+    const bool pays = table >= (k == 64 ? 30e6 : 10e6) && bins >= 8192.0 && entries >= (k == 16 ? 100.0 : 48.0) &&
+                      dim <= (k == 128 ? 512 : k >= 32 ? 400 : 256);
+    return pays ? per_bin : 0;
 }
 
 maxk_status ensure_packed(maxk_graph* g, int k, int index_bytes, int val_bytes)
