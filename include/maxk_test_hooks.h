@@ -20,6 +20,9 @@ MAXK_API int32_t maxk_fwd_private_copies(int32_t k);
  * never go down and a repeated shape never adds one.  Either out pointer may be NULL. */
 MAXK_API maxk_status maxk_graph_cached_tables(const maxk_graph* g, int32_t* n_slab_tables, int32_t* n_tiled_tables);
 
+/* How many regroupings of A for the forward sweep the handle holds (kept like the tables above). */
+MAXK_API int32_t maxk_graph_sweep_tables(const maxk_graph* g);
+
 #ifdef __cplusplus
 }
 #endif

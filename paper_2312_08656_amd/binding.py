@@ -19,7 +19,7 @@ EXPORTS = (
     "maxk_graph_info",
     "maxk_topk_cbsr", "maxk_spgemm_fwd", "maxk_spgemm_fwd_noalloc", "maxk_topk_cbsr_narrow", "maxk_spgemm_fwd_narrow", "maxk_sspmm_bwd",
     "maxk_sspmm_bwd_narrow", "maxk_cbsr_scatter", "spmm_baseline", "maxk_status_string",
-    "maxk_last_hip_error", "maxk_version", "maxk_fwd_private_copies", "maxk_graph_cached_tables",
+    "maxk_last_hip_error", "maxk_version", "maxk_fwd_private_copies", "maxk_graph_cached_tables", "maxk_graph_sweep_tables",
 )
 
 
@@ -71,6 +71,8 @@ def load_library() -> ctypes.CDLL:
     lib.maxk_graph_cached_tables.argtypes = [vp, ctypes.POINTER(i32), ctypes.POINTER(i32)]
     lib.maxk_graph_cached_tables.restype = i32
     lib.maxk_fwd_private_copies.restype = i32
+    lib.maxk_graph_sweep_tables.argtypes = [vp]
+    lib.maxk_graph_sweep_tables.restype = i32
     lib.maxk_last_hip_error.argtypes = []
     lib.maxk_version.argtypes = []
     _LIB = lib
@@ -151,6 +153,10 @@ class MaxKGraph:
         _check(load_library().maxk_graph_cached_tables(self.handle, ctypes.byref(a), ctypes.byref(b)),
                "maxk_graph_cached_tables")
         return int(a.value), int(b.value)
+
+    def sweep_tables(self) -> int:
+        """Regroupings of A for the forward sweep that the handle holds -- a test hook."""
+        return int(load_library().maxk_graph_sweep_tables(self.handle))
 
     def destroy(self) -> None:
         if self._h:

@@ -529,17 +529,21 @@ void free_sweep(SweepSet& W)
     W = SweepSet();
 }
 
-// key[p] = bin << 32 | source node, payload[p] = p, row_of[p] = row of the bin, for the entries of every work item
+// key[p] = bin << 32 | source node, payload[p] = p, row_of[p] = row of the bin, for the entries of every work item.
+// Workgroups stride over the items: one each would be 2^32 threads, more than a launch holds, from 2^24 items up.
 __global__ __launch_bounds__(256) void sweep_keys_kernel(const WorkItem* __restrict__ items, const uint32_t* __restrict__ place,
-                                                         int per_bin, const int32_t* __restrict__ col, uint64_t* __restrict__ key,
-                                                         uint32_t* __restrict__ entry, uint8_t* __restrict__ row_of)
+                                                         int64_t n_items, int per_bin, const int32_t* __restrict__ col,
+                                                         uint64_t* __restrict__ key, uint32_t* __restrict__ entry,
+                                                         uint8_t* __restrict__ row_of)
 {
-    const WorkItem it = items[blockIdx.x];
-    const uint32_t bin = place[blockIdx.x] / (uint32_t)per_bin, row = place[blockIdx.x] % (uint32_t)per_bin;
-    for (int p = it.begin + (int)threadIdx.x; p < it.end; p += blockDim.x) {
-        key[p] = (uint64_t)bin << 32 | (uint32_t)col[p];
-        entry[p] = (uint32_t)p;
-        row_of[p] = (uint8_t)row;
+    for (int64_t i = blockIdx.x; i < n_items; i += gridDim.x) {
+        const WorkItem it = items[i];
+        const uint32_t bin = place[i] / (uint32_t)per_bin, row = place[i] % (uint32_t)per_bin;
+        for (int p = it.begin + (int)threadIdx.x; p < it.end; p += blockDim.x) {
+            key[p] = (uint64_t)bin << 32 | (uint32_t)col[p];
+            entry[p] = (uint32_t)p;
+            row_of[p] = (uint8_t)row;
+        }
     }
 }
 
@@ -627,8 +631,8 @@ maxk_status build_sweep(maxk_graph* g, SweepSet& W, int groups, int batch_len, i
     MAXK_TRY_CLEAN(hipMemcpy(d_place, place.data(), sizeof(uint32_t) * place.size(), hipMemcpyHostToDevice));
     MAXK_TRY_CLEAN(hipMemcpy(d_first, first.data(), sizeof(uint32_t) * first.size(), hipMemcpyHostToDevice));
     const unsigned blocks = (unsigned)std::min<int64_t>((nnz + 255) / 256, 65536);
-    hipLaunchKernelGGL(sweep_keys_kernel, dim3((unsigned)n_items), dim3(256), 0, s, g->csr_items.d_items, d_place, per_bin,
-                       g->d_col, d_key, d_entry, d_row_of);
+    hipLaunchKernelGGL(sweep_keys_kernel, dim3((unsigned)std::min<int64_t>(n_items, 1 << 20)), dim3(256), 0, s,
+                       g->csr_items.d_items, d_place, n_items, per_bin, g->d_col, d_key, d_entry, d_row_of);
     MAXK_TRY_CLEAN(hipGetLastError());
     int end_bit = 33;
     while (end_bit < 64 && ((uint64_t)1 << (end_bit - 32)) < (uint64_t)n_bins) ++end_bit;
@@ -689,6 +693,8 @@ int sweep_rows(const maxk_graph* g, int dim, int k, int index_bytes, int val_byt
     if ((k & (k - 1)) != 0 || k < 8 || k > 128 || dim > 512 || g->N > (1 << kSweepRowShift) || g->nnz == 0 || g->fwd_sweep == 1)
         return 0;
     const int per_bin = k >= 64 ? 4 : k == 32 ? 2 : 1;
+    // a wavefront per bin, rounded up to whole workgroups, is below the 2^32 threads of a launch
+    if ((g->csr_items.n_items + per_bin - 1) / per_bin > (1 << 26) - 64) return 0;
     if (g->fwd_sweep == 2) return per_bin;
     const int record = fwd_uses_packed(g, k, index_bytes, val_bytes) ? fwd_packed_record_bytes(k, index_bytes, val_bytes)
                                                                      : k * (val_bytes + index_bytes);
@@ -970,8 +976,7 @@ MAXK_API maxk_status maxk_graph_reserve_narrow(maxk_graph* g, int32_t dim, int32
     if (st != MAXK_OK) return st;
     if (const int per_bin = sweep_rows(g, dim, k, dim <= 256 ? 1 : 2, 4)) {  // (narrower records may not need it)
         SweepSet* W = nullptr;
-        st = sweep_for(g, sweep_groups(k), sweep_batch(k), per_bin, false, &W);
-        if (st != MAXK_OK && st != MAXK_UNSUPPORTED && st != MAXK_OUT_OF_MEMORY) return st;  // (else: row by row)
+        (void)sweep_for(g, sweep_groups(k), sweep_batch(k), per_bin, false, &W);  // (not built: row by row)
     }
     for (int vb = 2; vb <= 4; vb += 2) {
         for (int ib = 1; ib <= 4; ib *= 2) {
@@ -1084,7 +1089,6 @@ MAXK_API maxk_status maxk_spgemm_fwd_narrow(maxk_graph* g, const void* d_sp_data
         if (st == MAXK_OK)
             return launch_spgemm_fwd_sweep(g->csr_items, *W, d_sp_data, value_type, d_sp_index, index_bytes, g->N, packed, dim, k,
                                            d_Y, g->d_partials, (hipStream_t)stream);
-        if (st != MAXK_UNSUPPORTED && st != MAXK_OUT_OF_MEMORY) return st;
     }
     return launch_spgemm_fwd(g->csr_items, g->d_col, g->d_val, d_sp_data, value_type, d_sp_index, index_bytes, g->N, packed,
                              dim, k, d_Y, g->d_partials, (hipStream_t)stream);
@@ -1242,6 +1246,8 @@ MAXK_API maxk_status maxk_graph_cached_tables(const maxk_graph* g, int32_t* n_sl
     if (n_tiled_tables) *n_tiled_tables = (int32_t)g->tiled_cache.size();
     return MAXK_OK;
 }
+
+MAXK_API int32_t maxk_graph_sweep_tables(const maxk_graph* g) { return g ? (int32_t)g->sweep_cache.size() : MAXK_INVALID_ARGUMENT; }
 
 int32_t maxk_last_hip_error(void) { return g_last_hip_error; }
 

@@ -704,3 +704,27 @@ def test_forward_sweep_keeps_infinities_in_their_rows(monkeypatch):
     want[:, :k] = (np.arange(N) % 5)[:, None]
     assert np.array_equal(Y.cpu().numpy(), want)
     gr.destroy()
+
+
+def test_forward_sweep_of_more_than_2_to_the_24_rows(monkeypatch):
+    # the regrouping of A strides over its work items: a workgroup each would be more threads than a launch holds.
+    # Whole numbers below 2^24, so every order of the sums gives the same bits
+    monkeypatch.setenv("MAXK_FWD_SWEEP", "2")
+    N, dim, k = (1 << 24) + 77, 8, 8
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    rows = torch.sort(torch.randint(N, (N + 5000,), generator=gen, device="cuda")).values
+    rows[-3:] = N - 1
+    rowptr = torch.zeros(N + 1, dtype=torch.int32, device="cuda")
+    rowptr[1:] = torch.cumsum(torch.bincount(rows, minlength=N), 0)
+    col = torch.randint(N, rows.shape, generator=gen, device="cuda", dtype=torch.int32)
+    val = torch.randint(-3, 4, rows.shape, generator=gen, device="cuda").float()
+    sp_data = torch.randint(-5, 6, (N, k), generator=gen, device="cuda").float()
+    sp_index = torch.arange(k, dtype=torch.uint8, device="cuda").repeat(N, 1)
+    gr = maxk.maxk_graph_create(rowptr, col, val)
+    gr.reserve(dim, k)
+    assert gr.sweep_tables() == 1
+    Y = torch.full((N, dim), float("nan"), device="cuda")
+    maxk.maxk_spgemm_fwd(gr, sp_data, sp_index, dim, Y)
+    want = torch.zeros_like(Y).index_add_(0, rows, sp_data[col.long()] * val[:, None])
+    assert torch.equal(Y, want)
+    gr.destroy()
