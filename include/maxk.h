@@ -111,6 +111,9 @@ MAXK_API maxk_status maxk_graph_destroy(maxk_graph* g);
  * so alternating several (dim, k) or dY formats never rebuilds one.  Without a reserve, the first compute call that
  * needs a table or a larger workspace builds it (synchronous allocations; the tables also sort A^T), later ones
  * reuse it; the same holds for a backward call whose pointers turn out too misaligned for the reserved kernel.
+ * A call captured into a HIP graph keeps the addresses of what it used.  Tables and the slice-major copy stay where
+ * they are until maxk_graph_destroy; the partial-sum workspace, the repack buffer and the expand/reduce buffer are
+ * replaced when a later call or reserve on the handle needs a larger one, so reserve the largest shapes before capturing.
  * Synchronises the device.  maxk_graph_reserve is the fp32-dY form.
  */
 MAXK_API maxk_status maxk_graph_reserve(maxk_graph* g, int32_t dim, int32_t k);

@@ -44,6 +44,8 @@ struct maxk_graph {
     std::vector<maxk::SweepSet*> sweep_cache;  // A regrouped for the forward sweep, one per (lane groups, rows of a bin)
     char* d_sliced = nullptr;   // slice-major copy of dY for the column-sliced pull (rows that are not whole cache lines)
     int64_t sliced_bytes = 0;
+    std::vector<char*> sliced_before;  // smaller ones: a captured backward pass may still hold their address
+    int64_t sliced_before_bytes = 0;
     char* d_packed = nullptr;   // forward kernel's per-call repack of a small-k CBSR (one record per node)
     int64_t packed_bytes = 0;
     int64_t max_degree = 0;      // longest row of A (entries with one source)
@@ -720,15 +722,22 @@ maxk_status ensure_packed(maxk_graph* g, int k, int index_bytes, int val_bytes)
     return MAXK_OK;
 }
 
+// A copy that has become too small is kept until the handle is destroyed: pull needs no other buffer on a graph without
+// split rows, and a captured backward pass of a narrower dY may be replayed after this.
 maxk_status ensure_sliced(maxk_graph* g, int dim, int val_bytes)
 {
     const int64_t need = sliced_copy_bytes(g->N, dim, val_bytes);
     if (need <= g->sliced_bytes) return MAXK_OK;
+    try {
+        g->sliced_before.reserve(g->sliced_before.size() + 1);
+    } catch (const std::bad_alloc&) {
+        return MAXK_OUT_OF_MEMORY;
+    }
     char* fresh = nullptr;
     MAXK_HIP_TRY(hipMalloc((void**)&fresh, (size_t)need));
     if (g->d_sliced) {
-        MAXK_HIP_TRY(hipDeviceSynchronize());
-        (void)hipFree(g->d_sliced);
+        g->sliced_before.push_back(g->d_sliced);
+        g->sliced_before_bytes += g->sliced_bytes;
     }
     g->d_sliced = fresh;
     g->sliced_bytes = need;
@@ -957,6 +966,7 @@ MAXK_API maxk_status maxk_graph_destroy(maxk_graph* g)
     (void)hipFree(g->d_expand);
     (void)hipFree(g->d_packed);
     (void)hipFree(g->d_sliced);
+    for (char* p : g->sliced_before) (void)hipFree(p);
     for (SlabSet* S : g->slab_cache) { free_slabs(*S); delete S; }
     for (TiledSet* T : g->tiled_cache) { free_tiled(*T); delete T; }
     for (SweepSet* W : g->sweep_cache) { free_sweep(*W); delete W; }
@@ -1038,7 +1048,8 @@ MAXK_API maxk_status maxk_graph_info(const maxk_graph* g, int64_t* N, int64_t* n
     if (n_split_rows) *n_split_rows = g->csr_items.n_split;
     if (max_degree) *max_degree = g->max_degree;
     if (workspace_bytes)
-        *workspace_bytes = (g->partial_floats + g->expand_floats) * (int64_t)sizeof(float) + g->packed_bytes + g->sliced_bytes;
+        *workspace_bytes = (g->partial_floats + g->expand_floats) * (int64_t)sizeof(float) + g->packed_bytes + g->sliced_bytes +
+                           g->sliced_before_bytes;
     return MAXK_OK;
 }
 

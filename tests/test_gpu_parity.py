@@ -651,6 +651,35 @@ def test_column_sliced_pull_in_a_captured_graph(_sliced_form, dim, reserve):
     gr.destroy()
 
 
+def test_captured_column_sliced_pull_outlives_a_wider_reserve(_sliced_form):
+    # the captured pass gathers from the slice-major copy it was captured with; a wider dY needs a larger one
+    N, dim, k = 700, 100, 20
+    rowptr, col, val = _mixed_degrees(N, 74)
+    H, dY = to_dev(synth.normal_matrix(N, dim, 75)), to_dev(synth.normal_matrix(N, dim, 76))
+    gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val))
+    gr.set_bwd_mode(maxk.BWD_PULL_CSC)
+    _, sp_index = gpu_topk(H, k, 2)
+    idx = index_to_numpy(sp_index)
+    dXs = torch.zeros((N, k), device="cuda")
+    gr.reserve(dim, k)
+    before = gr.info()["workspace_bytes"]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        maxk.maxk_sspmm_bwd(gr, dY, sp_index, dXs)
+    copies = lambda d: N * 128 * -(-4 * d // 128)
+    gr.reserve(300, k)
+    assert gr.info()["workspace_bytes"] - before >= copies(300), "the narrower copy is meant to stay"
+    for i in range(3):
+        dY.mul_(1.5 + i)
+        dXs.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        ref, refabs = oracle.sspmm_bwd(rowptr, col, val, dY.cpu().numpy(), idx)
+        assert (np.abs(dXs.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all()
+    gr.destroy()
+
+
 @pytest.mark.parametrize("dim,k,ib", [(8, 8, 1), (100, 8, 1), (255, 16, 1), (256, 16, 2), (64, 32, 1), (256, 32, 4),
                                       (130, 64, 1), (512, 64, 2), (128, 128, 1), (509, 128, 4)])
 @pytest.mark.parametrize("fmt", ["f32", "bf16", "f16"])
