@@ -89,8 +89,9 @@ typedef struct maxk_graph maxk_graph;
  * Sec. 4.2).  Takes A in CSR on the device: d_rowptr int32[N+1], d_colidx
  * int32[nnz], d_val fp32[nnz]; rows may be empty, columns need not be sorted,
  * duplicates add.  Builds and owns: the degree-ordered work-item lists with hub
- * rows split into bounded chunks, and A^T as CSC (value-carrying) for the
- * backward pull kernel.  Synchronises `stream` (it copies rowptr to the host).
+ * rows split into bounded chunks, A^T as CSC (value-carrying) for the
+ * backward pull kernel, and on graphs below 8 million entries the partial-sum
+ * workspace of split rows for every width (at most 32 MiB).  Synchronises `stream` (it copies rowptr to the host).
  * Not part of the timed path.
  */
 MAXK_API maxk_status maxk_graph_create(maxk_graph** out, int64_t N, int64_t nnz, const int32_t* d_rowptr,
@@ -112,8 +113,9 @@ MAXK_API maxk_status maxk_graph_destroy(maxk_graph* g);
  * needs a table or a larger workspace builds it (synchronous allocations; the tables also sort A^T), later ones
  * reuse it; the same holds for a backward call whose pointers turn out too misaligned for the reserved kernel.
  * A call captured into a HIP graph keeps the addresses of what it used.  Tables and the slice-major copy stay where
- * they are until maxk_graph_destroy; the partial-sum workspace, the repack buffer and the expand/reduce buffer are
- * replaced when a later call or reserve on the handle needs a larger one, so reserve the largest shapes before capturing.
+ * they are until maxk_graph_destroy; the partial-sum workspace (of graphs from 8 million entries up), the repack
+ * buffer and the expand/reduce buffer are replaced when a later call or reserve on the handle needs a larger one, so
+ * reserve the largest shapes before capturing.
  * Synchronises the device.  maxk_graph_reserve is the fp32-dY form.
  */
 MAXK_API maxk_status maxk_graph_reserve(maxk_graph* g, int32_t dim, int32_t k);

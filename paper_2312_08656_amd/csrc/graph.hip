@@ -268,6 +268,23 @@ maxk_status build_csc(maxk_graph* g, std::vector<int32_t>& h_csc_ptr, hipStream_
     return st;
 }
 
+// Partial rows of the items that default_chunk made shorter than 2048 entries, at the widest row (at most 32 MiB; see
+// there), allocated by maxk_graph_create: most of these rows are whole at 2048 entries, and a call on such a graph needs
+// no buffer then, so it may come for the first time while its stream is being captured.  Without the memory, later calls
+// allocate what they need.
+void short_item_workspace(maxk_graph* g)
+{
+    const int64_t slots = std::max(g->csr_items.n_slots, g->csc_items.n_slots);
+    if (g->chunk >= 2048 || slots == 0 || slots > 8192) return;
+    float* fresh = nullptr;
+    if (hipMalloc((void**)&fresh, sizeof(float) * (size_t)(slots * MAXK_MAX_DIM)) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    g->d_partials = fresh;
+    g->partial_floats = slots * MAXK_MAX_DIM;
+}
+
 maxk_status ensure_workspace(maxk_graph* g, int dim, int k)
 {
     const int64_t need = std::max<int64_t>(g->csr_items.n_slots * (int64_t)dim, g->csc_items.n_slots * (int64_t)k);
@@ -945,6 +962,7 @@ MAXK_API maxk_status maxk_graph_create(maxk_graph** out, int64_t N, int64_t nnz,
         st = MAXK_OUT_OF_MEMORY;
         goto fail;
     }
+    short_item_workspace(g);
     *out = g;
     return MAXK_OK;
 fail:

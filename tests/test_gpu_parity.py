@@ -455,6 +455,43 @@ def test_step_captured_in_a_hip_graph_replays_correctly():
     dg.close()
 
 
+def test_first_calls_on_a_graph_with_split_rows_may_be_captured():
+    # nothing reserved, nothing called before: rows of 129 to 2047 entries are split on a small graph, and their partial
+    # sums must not need an allocation under capture (k = 20: no repacked records either)
+    N, dim, k = 1500, 64, 20
+    rng = np.random.default_rng(91)
+    lens = rng.integers(0, 20, N)
+    lens[::50], lens[7] = 300, 1400
+    cols = [rng.permutation(N)[:n] for n in lens]
+    rowptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    col = np.concatenate(cols).astype(np.int32)
+    val = rng.standard_normal(col.size).astype(np.float32)
+    H, dY = to_dev(synth.normal_matrix(N, dim, 92)), to_dev(synth.normal_matrix(N, dim, 93))
+    sp_data, sp_index = gpu_topk(H, k, 1)
+    gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val))
+    gr.set_bwd_mode(maxk.BWD_PULL_CSC)
+    Y, Z, dXs = torch.empty((N, dim), device="cuda"), torch.empty((N, dim), device="cuda"), torch.empty((N, k), device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        maxk.maxk_spgemm_fwd(gr, sp_data, sp_index, dim, Y)
+        maxk.spmm_baseline(gr, H, Z)
+        maxk.maxk_sspmm_bwd(gr, dY, sp_index, dXs)
+    idx = index_to_numpy(sp_index)
+    for rep in range(3):
+        dY.mul_(0.5 + rep)
+        sp_data.mul_(0.5 + rep)
+        for t in (Y, Z, dXs):
+            t.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        for got, (ref, refabs) in ((Y, oracle.spgemm_fwd(rowptr, col, val, sp_data.cpu().numpy(), idx, dim)),
+                                   (Z, oracle.spmm(rowptr, col, val, H.cpu().numpy())),
+                                   (dXs, oracle.sspmm_bwd(rowptr, col, val, dY.cpu().numpy(), idx))):
+            assert (np.abs(got.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all()
+    gr.destroy()
+
+
 @pytest.mark.parametrize("vt,dtype", [("bf16", "bfloat16"), ("f16", "float16")])
 def test_narrow_values_round_like_the_oracle_on_special_values(vt, dtype):
     """Halfway cases, the fp16 subnormal range, overflow to infinity, signed zeros: with k = dim the
