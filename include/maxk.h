@@ -109,9 +109,10 @@ MAXK_API maxk_status maxk_graph_destroy(maxk_graph* g);
  * slice-major copy of dY that the pull kernel's column-sliced form keeps for rows that are not whole cache lines).
  * After it, compute calls with the same dim and k (forward, SpMM: any dim' <= dim, k' <= k) allocate nothing,
  * do not synchronise and read no environment variable.  Tables are cached per shape for the life of the handle,
- * so alternating several (dim, k) or dY formats never rebuilds one.  Without a reserve, the first compute call that
- * needs a table or a larger workspace builds it (synchronous allocations; the tables also sort A^T), later ones
- * reuse it; the same holds for a backward call whose pointers turn out too misaligned for the reserved kernel.
+ * so alternating several (dim, k) or dY formats never rebuilds one.  Beyond the reserved shapes, the first compute call
+ * that needs a table or a larger workspace builds it (synchronous allocations; the tables also sort A or A^T), later ones
+ * reuse it; the same holds for a backward call whose pointers turn out too misaligned for the reserved kernel.  (Within
+ * a reserved (dim, k), a forward call with a k' < k whose own regrouped copy nobody built runs row by row.)
  * A call captured into a HIP graph keeps the addresses of what it used.  Tables and the slice-major copy stay where
  * they are until maxk_graph_destroy; the partial-sum workspace (of graphs from 8 million entries up), the repack
  * buffer and the expand/reduce buffer are replaced when a later call or reserve on the handle needs a larger one, so

@@ -23,6 +23,10 @@ MAXK_API maxk_status maxk_graph_cached_tables(const maxk_graph* g, int32_t* n_sl
 /* How many regroupings of A for the forward sweep the handle holds (kept like the tables above). */
 MAXK_API int32_t maxk_graph_sweep_tables(const maxk_graph* g);
 
+/* From here on the handle's tables, the slice-major copy and the expand/reduce buffer are refused, as if memory had run
+ * out, when they take more than `bytes` (a table: 8 an entry); negative: no limit.  Returns how many were refused so far. */
+MAXK_API int64_t maxk_graph_limit_allocations(maxk_graph* g, int64_t bytes);
+
 #ifdef __cplusplus
 }
 #endif

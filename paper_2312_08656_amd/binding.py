@@ -20,6 +20,7 @@ EXPORTS = (
     "maxk_topk_cbsr", "maxk_spgemm_fwd", "maxk_spgemm_fwd_noalloc", "maxk_topk_cbsr_narrow", "maxk_spgemm_fwd_narrow", "maxk_sspmm_bwd",
     "maxk_sspmm_bwd_narrow", "maxk_cbsr_scatter", "spmm_baseline", "maxk_status_string",
     "maxk_last_hip_error", "maxk_version", "maxk_fwd_private_copies", "maxk_graph_cached_tables", "maxk_graph_sweep_tables",
+    "maxk_graph_limit_allocations",
 )
 
 
@@ -73,6 +74,8 @@ def load_library() -> ctypes.CDLL:
     lib.maxk_fwd_private_copies.restype = i32
     lib.maxk_graph_sweep_tables.argtypes = [vp]
     lib.maxk_graph_sweep_tables.restype = i32
+    lib.maxk_graph_limit_allocations.argtypes = [vp, i64]
+    lib.maxk_graph_limit_allocations.restype = i64
     lib.maxk_last_hip_error.argtypes = []
     lib.maxk_version.argtypes = []
     _LIB = lib
@@ -157,6 +160,10 @@ class MaxKGraph:
     def sweep_tables(self) -> int:
         """Regroupings of A for the forward sweep that the handle holds -- a test hook."""
         return int(load_library().maxk_graph_sweep_tables(self.handle))
+
+    def limit_allocations(self, limit: int) -> int:
+        """Refuses larger tables and buffers as if memory had run out; refusals so far -- a test hook."""
+        return int(load_library().maxk_graph_limit_allocations(self.handle, limit))
 
     def destroy(self) -> None:
         if self._h:

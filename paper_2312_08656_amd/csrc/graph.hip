@@ -57,7 +57,9 @@ struct maxk_graph {
     int32_t fwd_pack_max = 0;
     int32_t pull_form = 0;
     int32_t fwd_sweep = 0;
-    bool reserved = false;     // maxk_graph_reserve* was called: forward calls build no tables any more
+    std::vector<std::pair<int32_t, int32_t>> reserved;  // (dim, k) of maxk_graph_reserve*, none within another
+    int64_t test_alloc_limit = -1;  // test hook: tables and buffers of more bytes are refused (-1: none)
+    int64_t test_denied = 0;        // how many were
     unsigned char* d_noalloc_scratch = nullptr;  // this device's copy of the library's fixed scratch array
     int device = 0;
 };
@@ -266,6 +268,14 @@ maxk_status build_csc(maxk_graph* g, std::vector<int32_t>& h_csc_ptr, hipStream_
 #undef MAXK_TRY_CLEAN
     cleanup();
     return st;
+}
+
+// The test hook's stand-in for a device without room for `bytes` more
+bool denied(maxk_graph* g, int64_t bytes)
+{
+    if (g->test_alloc_limit < 0 || bytes <= g->test_alloc_limit) return false;
+    ++g->test_denied;
+    return true;
 }
 
 // Partial rows of the items that default_chunk made shorter than 2048 entries, at the widest row (at most 32 MiB; see
@@ -514,7 +524,7 @@ maxk_status slabs_for(maxk_graph* g, int32_t slab_rows, bool existing_only, Slab
 {
     for (SlabSet* S : g->slab_cache)
         if (S->slab_rows == slab_rows) { *out = S; return MAXK_OK; }
-    if (existing_only) return MAXK_OUT_OF_MEMORY;
+    if (existing_only || denied(g, g->nnz * 8)) return MAXK_OUT_OF_MEMORY;
     SlabSet* S = new (std::nothrow) SlabSet();
     if (!S) return MAXK_OUT_OF_MEMORY;
     const maxk_status st = build_slabs(g, *S, slab_rows);
@@ -530,7 +540,7 @@ maxk_status tiled_for(maxk_graph* g, int dim, int k, bool existing_only, TiledSe
     if (!tiled_shape(g->N, dim, k, sh)) return MAXK_UNSUPPORTED;
     for (TiledSet* T : g->tiled_cache)
         if (T->D == sh.D && T->TR == sh.TR && T->LPV == k / tiled_positions_per_lane(k)) { *out = T; return MAXK_OK; }
-    if (existing_only) return MAXK_OUT_OF_MEMORY;
+    if (existing_only || denied(g, g->nnz * 8)) return MAXK_OUT_OF_MEMORY;
     TiledSet* T = new (std::nothrow) TiledSet();
     if (!T) return MAXK_OUT_OF_MEMORY;
     const maxk_status st = build_tiled(*T, g->N, g->nnz, g->d_csc_ptr, g->d_csc_src, g->d_csc_val, sh.D, sh.TR, k);
@@ -673,11 +683,30 @@ maxk_status build_sweep(maxk_graph* g, SweepSet& W, int groups, int batch_len, i
     return MAXK_OK;
 }
 
+// Forward calls within a reserved shape build nothing; the others build what they need on first use.
+bool reserved_for(const maxk_graph* g, int dim, int k)
+{
+    return std::any_of(g->reserved.begin(), g->reserved.end(), [=](const auto& r) { return dim <= r.first && k <= r.second; });
+}
+
+maxk_status note_reserved(maxk_graph* g, int dim, int k)
+{
+    if (reserved_for(g, dim, k)) return MAXK_OK;
+    try {
+        std::erase_if(g->reserved, [=](const auto& r) { return r.first <= dim && r.second <= k; });
+        g->reserved.emplace_back(dim, k);
+    } catch (const std::bad_alloc&) {
+        return MAXK_OUT_OF_MEMORY;
+    }
+    return MAXK_OK;
+}
+
 maxk_status sweep_for(maxk_graph* g, int groups, int batch_len, int per_bin, bool existing_only, SweepSet** out)
 {
     for (SweepSet* W : g->sweep_cache)
         if (W->groups == groups && W->batch_len == batch_len && W->per_bin == per_bin) { *out = W; return MAXK_OK; }
     if (existing_only) return MAXK_UNSUPPORTED;
+    if (denied(g, g->nnz * 8)) return MAXK_OUT_OF_MEMORY;
     SweepSet* W = new (std::nothrow) SweepSet();
     if (!W) return MAXK_OUT_OF_MEMORY;
     maxk_status st;
@@ -745,6 +774,7 @@ maxk_status ensure_sliced(maxk_graph* g, int dim, int val_bytes)
 {
     const int64_t need = sliced_copy_bytes(g->N, dim, val_bytes);
     if (need <= g->sliced_bytes) return MAXK_OK;
+    if (denied(g, need)) return MAXK_OUT_OF_MEMORY;
     try {
         g->sliced_before.reserve(g->sliced_before.size() + 1);
     } catch (const std::bad_alloc&) {
@@ -765,6 +795,7 @@ maxk_status ensure_expand(maxk_graph* g, int k)
 {
     const int64_t need = g->nnz * (int64_t)k;
     if (need <= g->expand_floats) return MAXK_OK;
+    if (denied(g, need * (int64_t)sizeof(float))) return MAXK_OUT_OF_MEMORY;
     float* fresh = nullptr;
     MAXK_HIP_TRY(hipMalloc((void**)&fresh, sizeof(float) * (size_t)need));
     if (g->d_expand) {
@@ -890,6 +921,46 @@ int auto_bwd_mode(const maxk_graph* g, int dim, int k, int val_bytes = 4, bool t
     return mode;
 }
 
+maxk_status reserve_shape(maxk_graph* g, int dim, int k, int dy_value_type)
+{
+    maxk_status st = ensure_workspace(g, dim, k);
+    if (st != MAXK_OK) return st;
+    if (const int per_bin = sweep_rows(g, dim, k, dim <= 256 ? 1 : 2, 4)) {  // (narrower records may not need it)
+        SweepSet* W = nullptr;
+        (void)sweep_for(g, sweep_groups(k), sweep_batch(k), per_bin, false, &W);  // (not built: row by row)
+    }
+    for (int vb = 2; vb <= 4; vb += 2) {
+        for (int ib = 1; ib <= 4; ib *= 2) {
+            for (int kk = 1; kk <= k; ++kk) {  // the largest repacked record among k' <= k
+                if (!fwd_uses_packed(g, kk, ib, vb)) break;
+                if (kk == k || !fwd_uses_packed(g, kk + 1, ib, vb)) {
+                    st = ensure_packed(g, kk, ib, vb);
+                    if (st != MAXK_OK) return st;
+                }
+            }
+        }
+    }
+    const int vb = value_bytes(dy_value_type);
+    const int mode = g->bwd_mode == MAXK_BWD_AUTO ? auto_bwd_mode(g, dim, k, vb) : g->bwd_mode;
+    if (mode == MAXK_BWD_TILED) {
+        TiledSet* T = nullptr;
+        st = tiled_for(g, dim, k, false, &T);
+        if (st != MAXK_UNSUPPORTED) return st;
+        // the compute call falls back to the slab kernel for shapes the tiled one does not take
+    }
+    if (mode == MAXK_BWD_SLAB_PULL || mode == MAXK_BWD_TILED) {
+        SlabSet* S = nullptr;
+        return g->nnz ? slabs_for(g, slab_rows_for(g, dim, vb), false, &S) : MAXK_OK;
+    }
+    if (mode == MAXK_BWD_PULL_CSC) {
+        const PullCost p = pull_cost(g, dim, k, vb, nullptr);
+        return p.sliced < p.plain && !sliced_in_place(dim, vb) ? ensure_sliced(g, dim, vb) : MAXK_OK;
+    }
+    if (mode != MAXK_BWD_EXPAND_REDUCE) return MAXK_OK;
+    st = ensure_expand(g, k);
+    return st == MAXK_OUT_OF_MEMORY && g->bwd_mode == MAXK_BWD_AUTO ? MAXK_OK : st;  // (the compute call runs pull then)
+}
+
 bool bad_index_bytes(int index_bytes, int dim)
 {
     if (index_bytes == 1) return dim > 256;
@@ -999,43 +1070,8 @@ MAXK_API maxk_status maxk_graph_reserve_narrow(maxk_graph* g, int32_t dim, int32
     if (dy_value_type < MAXK_VALUE_F32 || dy_value_type > MAXK_VALUE_F16) return MAXK_INVALID_ARGUMENT;
     if (dim > MAXK_MAX_DIM) return MAXK_UNSUPPORTED;
     if (g->N == 0) return MAXK_OK;
-    g->reserved = true;
-    maxk_status st = ensure_workspace(g, dim, k);
-    if (st != MAXK_OK) return st;
-    if (const int per_bin = sweep_rows(g, dim, k, dim <= 256 ? 1 : 2, 4)) {  // (narrower records may not need it)
-        SweepSet* W = nullptr;
-        (void)sweep_for(g, sweep_groups(k), sweep_batch(k), per_bin, false, &W);  // (not built: row by row)
-    }
-    for (int vb = 2; vb <= 4; vb += 2) {
-        for (int ib = 1; ib <= 4; ib *= 2) {
-            for (int kk = 1; kk <= k; ++kk) {  // the largest repacked record among k' <= k
-                if (!fwd_uses_packed(g, kk, ib, vb)) break;
-                if (kk == k || !fwd_uses_packed(g, kk + 1, ib, vb)) {
-                    st = ensure_packed(g, kk, ib, vb);
-                    if (st != MAXK_OK) return st;
-                }
-            }
-        }
-    }
-    const int vb = value_bytes(dy_value_type);
-    const int mode = g->bwd_mode == MAXK_BWD_AUTO ? auto_bwd_mode(g, dim, k, vb) : g->bwd_mode;
-    if (mode == MAXK_BWD_TILED) {
-        TiledSet* T = nullptr;
-        st = tiled_for(g, dim, k, false, &T);
-        if (st != MAXK_UNSUPPORTED) return st;
-        // the compute call falls back to the slab kernel for shapes the tiled one does not take
-    }
-    if (mode == MAXK_BWD_SLAB_PULL || mode == MAXK_BWD_TILED) {
-        SlabSet* S = nullptr;
-        return g->nnz ? slabs_for(g, slab_rows_for(g, dim, vb), false, &S) : MAXK_OK;
-    }
-    if (mode == MAXK_BWD_PULL_CSC) {
-        const PullCost p = pull_cost(g, dim, k, vb, nullptr);
-        return p.sliced < p.plain && !sliced_in_place(dim, vb) ? ensure_sliced(g, dim, vb) : MAXK_OK;
-    }
-    if (mode != MAXK_BWD_EXPAND_REDUCE) return MAXK_OK;
-    st = ensure_expand(g, k);
-    return st == MAXK_OUT_OF_MEMORY && g->bwd_mode == MAXK_BWD_AUTO ? MAXK_OK : st;  // (the compute call runs pull then)
+    const maxk_status st = reserve_shape(g, dim, k, dy_value_type);
+    return st == MAXK_OK ? note_reserved(g, dim, k) : st;
 }
 
 MAXK_API maxk_status maxk_graph_reserve(maxk_graph* g, int32_t dim, int32_t k)
@@ -1114,7 +1150,7 @@ MAXK_API maxk_status maxk_spgemm_fwd_narrow(maxk_graph* g, const void* d_sp_data
     }
     if (const int per_bin = sweep_rows(g, dim, k, index_bytes, vb)) {
         SweepSet* W = nullptr;
-        st = sweep_for(g, sweep_groups(k), sweep_batch(k), per_bin, g->reserved || capturing((hipStream_t)stream), &W);
+        st = sweep_for(g, sweep_groups(k), sweep_batch(k), per_bin, reserved_for(g, dim, k) || capturing((hipStream_t)stream), &W);
         if (st == MAXK_OK)
             return launch_spgemm_fwd_sweep(g->csr_items, *W, d_sp_data, value_type, d_sp_index, index_bytes, g->N, packed, dim, k,
                                            d_Y, g->d_partials, (hipStream_t)stream);
@@ -1277,6 +1313,13 @@ MAXK_API maxk_status maxk_graph_cached_tables(const maxk_graph* g, int32_t* n_sl
 }
 
 MAXK_API int32_t maxk_graph_sweep_tables(const maxk_graph* g) { return g ? (int32_t)g->sweep_cache.size() : MAXK_INVALID_ARGUMENT; }
+
+MAXK_API int64_t maxk_graph_limit_allocations(maxk_graph* g, int64_t bytes)
+{
+    if (!g) return MAXK_INVALID_ARGUMENT;
+    g->test_alloc_limit = bytes;
+    return g->test_denied;
+}
 
 int32_t maxk_last_hip_error(void) { return g_last_hip_error; }
 

@@ -794,3 +794,36 @@ def test_forward_sweep_of_more_than_2_to_the_24_rows(monkeypatch):
     want = torch.zeros_like(Y).index_add_(0, rows, sp_data[col.long()] * val[:, None])
     assert torch.equal(Y, want)
     gr.destroy()
+
+
+# ------------------------------------------------------------------ what a handle builds, for which shapes, and when not
+
+
+def _aggregation_case(N, M, dim, k, seed):
+    g = synth.make_graph(N, M, 0, directed=True, self_loops=True, seed=seed, weights="normal")
+    H, dY = synth.normal_matrix(N, dim, seed + 1), synth.normal_matrix(N, dim, seed + 2)
+    gr = maxk.maxk_graph_create(to_dev(g.rowptr), to_dev(g.col), to_dev(g.val))
+    sp_data, sp_index = gpu_topk(to_dev(H), k, 2)
+    return g, dY, gr, sp_data, sp_index
+
+
+def _forward(g, gr, sp_data, sp_index, dim):
+    Y = torch.full((g.N, dim), float("nan"), device="cuda")
+    maxk.maxk_spgemm_fwd(gr, sp_data, sp_index, dim, Y)
+    ref, refabs = oracle.spgemm_fwd(g.rowptr, g.col, g.val, sp_data.cpu().numpy(), index_to_numpy(sp_index), dim)
+    assert (np.abs(Y.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all()
+
+
+def test_reserving_one_shape_leaves_the_sweep_to_the_others(monkeypatch):
+    monkeypatch.setenv("MAXK_FWD_SWEEP", "2")
+    N, dim = 900, 64
+    g, _, gr, _, _ = _aggregation_case(N, 9000, dim, 8, 101)
+    gr.reserve(dim, 16)
+    assert gr.sweep_tables() == 1
+    H = to_dev(synth.normal_matrix(N, 96, 104))
+    for width, k, tables in ((dim, 16, 1), (32, 16, 1), (dim, 8, 1), (dim, 32, 2), (dim, 32, 2), (96, 8, 3), (dim, 13, 3)):
+        # within the reserved shape nothing is built (k = 8 runs row by row); beyond it the first call builds what it needs
+        sp_data, sp_index = gpu_topk(H[:, :width].contiguous(), k, 2)
+        _forward(g, gr, sp_data, sp_index, width)
+        assert gr.sweep_tables() == tables, (width, k)
+    gr.destroy()
