@@ -11,6 +11,7 @@
 //     its work-item list, for the pull backward kernel;
 //   - one partial-sum workspace shared by all kernels of the handle.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -58,6 +59,7 @@ struct maxk_graph {
     int32_t pull_form = 0;
     int32_t fwd_sweep = 0;
     std::vector<std::pair<int32_t, int32_t>> reserved;  // (dim, k) of maxk_graph_reserve*, none within another
+    std::vector<std::array<int64_t, 4>> refused;  // tables that could not be built: {kind, shape}; a reserve tries them again
     int64_t test_alloc_limit = -1;  // test hook: tables and buffers of more bytes are refused (-1: none)
     int64_t test_denied = 0;        // how many were
     unsigned char* d_noalloc_scratch = nullptr;  // this device's copy of the library's fixed scratch array
@@ -277,6 +279,27 @@ bool denied(maxk_graph* g, int64_t bytes)
     ++g->test_denied;
     return true;
 }
+
+// A table or buffer that could not be built is not asked for again by compute calls: each try synchronises the device
+// and may allocate most of what it needs before it fails, and one that succeeds later would change the kernel mid-run.
+using RefusedKey = std::array<int64_t, 4>;
+enum : int64_t { kRefusedSweep };
+
+bool is_refused(const maxk_graph* g, const RefusedKey& key)
+{
+    return std::find(g->refused.begin(), g->refused.end(), key) != g->refused.end();
+}
+
+void note_refused(maxk_graph* g, const RefusedKey& key)
+{
+    if (is_refused(g, key)) return;
+    try {
+        g->refused.push_back(key);
+    } catch (const std::bad_alloc&) {  // then the next call tries again
+    }
+}
+
+void forget_refused(maxk_graph* g, const RefusedKey& key) { std::erase(g->refused, key); }
 
 // Partial rows of the items that default_chunk made shorter than 2048 entries, at the widest row (at most 32 MiB; see
 // there), allocated by maxk_graph_create: most of these rows are whole at 2048 entries, and a call on such a graph needs
@@ -701,22 +724,29 @@ maxk_status note_reserved(maxk_graph* g, int dim, int k)
     return MAXK_OK;
 }
 
+// existing_only: nothing is built, and a refusal is not remembered (the call is being captured, or was reserved)
 maxk_status sweep_for(maxk_graph* g, int groups, int batch_len, int per_bin, bool existing_only, SweepSet** out)
 {
     for (SweepSet* W : g->sweep_cache)
         if (W->groups == groups && W->batch_len == batch_len && W->per_bin == per_bin) { *out = W; return MAXK_OK; }
-    if (existing_only) return MAXK_UNSUPPORTED;
-    if (denied(g, g->nnz * 8)) return MAXK_OUT_OF_MEMORY;
+    const RefusedKey key = {kRefusedSweep, groups, batch_len, per_bin};
+    if (existing_only || is_refused(g, key)) return MAXK_UNSUPPORTED;
     SweepSet* W = new (std::nothrow) SweepSet();
-    if (!W) return MAXK_OUT_OF_MEMORY;
-    maxk_status st;
-    try {
-        st = build_sweep(g, *W, groups, batch_len, per_bin);
-        if (st == MAXK_OK) g->sweep_cache.push_back(W);
-    } catch (const std::bad_alloc&) {
-        st = MAXK_OUT_OF_MEMORY;
+    maxk_status st = MAXK_OUT_OF_MEMORY;
+    if (W && !denied(g, g->nnz * 8)) {
+        try {
+            st = build_sweep(g, *W, groups, batch_len, per_bin);
+            if (st == MAXK_OK) g->sweep_cache.push_back(W);
+        } catch (const std::bad_alloc&) {
+            st = MAXK_OUT_OF_MEMORY;
+        }
     }
-    if (st != MAXK_OK) { free_sweep(*W); delete W; return st; }
+    if (st != MAXK_OK) {
+        if (W) free_sweep(*W);
+        delete W;
+        note_refused(g, key);
+        return st;
+    }
     *out = W;
     return MAXK_OK;
 }
@@ -927,6 +957,7 @@ maxk_status reserve_shape(maxk_graph* g, int dim, int k, int dy_value_type)
     if (st != MAXK_OK) return st;
     if (const int per_bin = sweep_rows(g, dim, k, dim <= 256 ? 1 : 2, 4)) {  // (narrower records may not need it)
         SweepSet* W = nullptr;
+        forget_refused(g, {kRefusedSweep, sweep_groups(k), sweep_batch(k), per_bin});
         (void)sweep_for(g, sweep_groups(k), sweep_batch(k), per_bin, false, &W);  // (not built: row by row)
     }
     for (int vb = 2; vb <= 4; vb += 2) {

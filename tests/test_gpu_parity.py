@@ -827,3 +827,18 @@ def test_reserving_one_shape_leaves_the_sweep_to_the_others(monkeypatch):
         _forward(g, gr, sp_data, sp_index, width)
         assert gr.sweep_tables() == tables, (width, k)
     gr.destroy()
+
+
+def test_a_sweep_table_that_does_not_fit_is_tried_once(monkeypatch):
+    monkeypatch.setenv("MAXK_FWD_SWEEP", "2")
+    N, dim, k = 900, 64, 32
+    g, _, gr, sp_data, sp_index = _aggregation_case(N, 9000, dim, k, 111)
+    gr.limit_allocations(0)
+    for _ in range(3):
+        _forward(g, gr, sp_data, sp_index, dim)
+    assert gr.limit_allocations(-1) == 1
+    _forward(g, gr, sp_data, sp_index, dim)  # memory is there again: a call still builds nothing, a reserve does
+    assert gr.sweep_tables() == 0
+    gr.reserve(dim, k)
+    assert gr.sweep_tables() == 1
+    gr.destroy()
