@@ -113,7 +113,9 @@ MAXK_API maxk_status maxk_graph_destroy(maxk_graph* g);
  * that needs a table or a larger workspace builds it (synchronous allocations; the tables also sort A or A^T), later ones
  * reuse it; the same holds for a backward call whose pointers turn out too misaligned for the reserved kernel.  (Within
  * a reserved (dim, k), a forward call with a k' < k whose own regrouped copy nobody built runs row by row.)
- * A forward call whose regrouped copy could not be built runs row by row; it is asked for again by a reserve only.
+ * When memory runs out, MAXK_BWD_AUTO moves on to the next best backward kernel that fits (the last one, pull, needs no
+ * buffer), and a forward call whose regrouped copy could not be built runs row by row, in the compute call and in
+ * the reserve alike; what was refused is asked for again by a reserve of its shape only.
  * A call captured into a HIP graph keeps the addresses of what it used.  Tables and the slice-major copy stay where
  * they are until maxk_graph_destroy; the partial-sum workspace (of graphs from 8 million entries up), the repack
  * buffer and the expand/reduce buffer are replaced when a later call or reserve on the handle needs a larger one, so

@@ -283,7 +283,7 @@ bool denied(maxk_graph* g, int64_t bytes)
 // A table or buffer that could not be built is not asked for again by compute calls: each try synchronises the device
 // and may allocate most of what it needs before it fails, and one that succeeds later would change the kernel mid-run.
 using RefusedKey = std::array<int64_t, 4>;
-enum : int64_t { kRefusedSweep };
+enum : int64_t { kRefusedSweep, kRefusedSlab, kRefusedTiled, kRefusedExpand, kRefusedSliced };
 
 bool is_refused(const maxk_graph* g, const RefusedKey& key)
 {
@@ -300,6 +300,18 @@ void note_refused(maxk_graph* g, const RefusedKey& key)
 }
 
 void forget_refused(maxk_graph* g, const RefusedKey& key) { std::erase(g->refused, key); }
+
+maxk_status allocate(maxk_graph* g, void** out, int64_t bytes, const RefusedKey& key)
+{
+    const maxk_status st = denied(g, bytes) ? MAXK_OUT_OF_MEMORY : [&] {
+        const hipError_t e = hipMalloc(out, (size_t)bytes);
+        return e == hipSuccess ? MAXK_OK : hip_fail(e);
+    }();
+    if (st == MAXK_OUT_OF_MEMORY) note_refused(g, key);
+    return st;
+}
+
+RefusedKey sliced_key(const maxk_graph* g, int dim, int val_bytes) { return {kRefusedSliced, sliced_copy_bytes(g->N, dim, val_bytes)}; }
 
 // Partial rows of the items that default_chunk made shorter than 2048 entries, at the widest row (at most 32 MiB; see
 // there), allocated by maxk_graph_create: most of these rows are whole at 2048 entries, and a call on such a graph needs
@@ -500,7 +512,7 @@ maxk_status build_slabs(maxk_graph* g, SlabSet& S, int32_t slab_rows)
                                   hipMemcpyDeviceToHost, s));
     MAXK_TRY_CLEAN(hipStreamSynchronize(s));
     // long visits (hub destinations inside one slab): listed per slab on the host
-    {
+    try {
         std::vector<int32_t> h_begin((size_t)n_visits + 1), h_long;
         MAXK_TRY_CLEAN(hipMemcpy(h_begin.data(), S.d_visit_begin, sizeof(int32_t) * (size_t)(n_visits + 1),
                                  hipMemcpyDeviceToHost));
@@ -517,7 +529,10 @@ maxk_status build_slabs(maxk_graph* g, SlabSet& S, int32_t slab_rows)
             MAXK_TRY_CLEAN(hipMalloc((void**)&S.d_long_visit, sizeof(int32_t) * h_long.size()));
             MAXK_TRY_CLEAN(hipMemcpy(S.d_long_visit, h_long.data(), sizeof(int32_t) * h_long.size(), hipMemcpyHostToDevice));
         }
-
+    } catch (const std::bad_alloc&) {
+        cleanup();
+        free_slabs(S);
+        return MAXK_OUT_OF_MEMORY;
     }
 #undef MAXK_TRY_CLEAN
     cleanup();
@@ -543,32 +558,59 @@ bool capturing(hipStream_t s)
 
 // The regrouping of A^T for one slab height: built on first use (or by maxk_graph_reserve*), then kept until the
 // handle is destroyed, so alternating hidden widths or dY formats on one handle never rebuilds anything.
-maxk_status slabs_for(maxk_graph* g, int32_t slab_rows, bool existing_only, SlabSet** out)
+// existing_only(): asked where the table is missing; nothing is built then, and that is not remembered as a refusal.
+template <class F>
+maxk_status slabs_for(maxk_graph* g, int32_t slab_rows, const F& existing_only, SlabSet** out)
 {
     for (SlabSet* S : g->slab_cache)
         if (S->slab_rows == slab_rows) { *out = S; return MAXK_OK; }
-    if (existing_only || denied(g, g->nnz * 8)) return MAXK_OUT_OF_MEMORY;
+    if (existing_only()) return MAXK_OUT_OF_MEMORY;
     SlabSet* S = new (std::nothrow) SlabSet();
-    if (!S) return MAXK_OUT_OF_MEMORY;
-    const maxk_status st = build_slabs(g, *S, slab_rows);
-    if (st != MAXK_OK) { delete S; return st; }
-    try { g->slab_cache.push_back(S); } catch (const std::bad_alloc&) { free_slabs(*S); delete S; return MAXK_OUT_OF_MEMORY; }
+    maxk_status st = MAXK_OUT_OF_MEMORY;
+    if (S && !denied(g, g->nnz * 8)) {
+        try {
+            st = build_slabs(g, *S, slab_rows);
+            if (st == MAXK_OK) g->slab_cache.push_back(S);
+        } catch (const std::bad_alloc&) {
+            st = MAXK_OUT_OF_MEMORY;
+        }
+    }
+    if (st != MAXK_OK) {
+        if (S) free_slabs(*S);
+        delete S;
+        if (st == MAXK_OUT_OF_MEMORY) note_refused(g, {kRefusedSlab, slab_rows});
+        return st;
+    }
     *out = S;
     return MAXK_OK;
 }
 
-maxk_status tiled_for(maxk_graph* g, int dim, int k, bool existing_only, TiledSet** out)
+RefusedKey tiled_key(const TiledShape& sh, int k) { return {kRefusedTiled, sh.D, sh.TR, k / tiled_positions_per_lane(k)}; }
+
+template <class F>
+maxk_status tiled_for(maxk_graph* g, int dim, int k, const F& existing_only, TiledSet** out)
 {
     TiledShape sh;
     if (!tiled_shape(g->N, dim, k, sh)) return MAXK_UNSUPPORTED;
     for (TiledSet* T : g->tiled_cache)
         if (T->D == sh.D && T->TR == sh.TR && T->LPV == k / tiled_positions_per_lane(k)) { *out = T; return MAXK_OK; }
-    if (existing_only || denied(g, g->nnz * 8)) return MAXK_OUT_OF_MEMORY;
+    if (existing_only()) return MAXK_OUT_OF_MEMORY;
     TiledSet* T = new (std::nothrow) TiledSet();
-    if (!T) return MAXK_OUT_OF_MEMORY;
-    const maxk_status st = build_tiled(*T, g->N, g->nnz, g->d_csc_ptr, g->d_csc_src, g->d_csc_val, sh.D, sh.TR, k);
-    if (st != MAXK_OK) { delete T; return st; }
-    try { g->tiled_cache.push_back(T); } catch (const std::bad_alloc&) { free_tiled(*T); delete T; return MAXK_OUT_OF_MEMORY; }
+    maxk_status st = MAXK_OUT_OF_MEMORY;
+    if (T && !denied(g, g->nnz * 8)) {
+        try {
+            st = build_tiled(*T, g->N, g->nnz, g->d_csc_ptr, g->d_csc_src, g->d_csc_val, sh.D, sh.TR, k);
+            if (st == MAXK_OK) g->tiled_cache.push_back(T);
+        } catch (const std::bad_alloc&) {
+            st = MAXK_OUT_OF_MEMORY;
+        }
+    }
+    if (st != MAXK_OK) {
+        if (T) free_tiled(*T);
+        delete T;
+        if (st == MAXK_OUT_OF_MEMORY) note_refused(g, tiled_key(sh, k));
+        return st;
+    }
     *out = T;
     return MAXK_OK;
 }
@@ -804,14 +846,14 @@ maxk_status ensure_sliced(maxk_graph* g, int dim, int val_bytes)
 {
     const int64_t need = sliced_copy_bytes(g->N, dim, val_bytes);
     if (need <= g->sliced_bytes) return MAXK_OK;
-    if (denied(g, need)) return MAXK_OUT_OF_MEMORY;
     try {
         g->sliced_before.reserve(g->sliced_before.size() + 1);
     } catch (const std::bad_alloc&) {
         return MAXK_OUT_OF_MEMORY;
     }
     char* fresh = nullptr;
-    MAXK_HIP_TRY(hipMalloc((void**)&fresh, (size_t)need));
+    const maxk_status st = allocate(g, (void**)&fresh, need, sliced_key(g, dim, val_bytes));
+    if (st != MAXK_OK) return st;
     if (g->d_sliced) {
         g->sliced_before.push_back(g->d_sliced);
         g->sliced_before_bytes += g->sliced_bytes;
@@ -825,9 +867,9 @@ maxk_status ensure_expand(maxk_graph* g, int k)
 {
     const int64_t need = g->nnz * (int64_t)k;
     if (need <= g->expand_floats) return MAXK_OK;
-    if (denied(g, need * (int64_t)sizeof(float))) return MAXK_OUT_OF_MEMORY;
     float* fresh = nullptr;
-    MAXK_HIP_TRY(hipMalloc((void**)&fresh, sizeof(float) * (size_t)need));
+    const maxk_status st = allocate(g, (void**)&fresh, need * (int64_t)sizeof(float), {kRefusedExpand, k});
+    if (st != MAXK_OK) return st;
     if (g->d_expand) {
         MAXK_HIP_TRY(hipDeviceSynchronize());
         (void)hipFree(g->d_expand);
@@ -902,7 +944,8 @@ PullCost pull_cost(const maxk_graph* g, int dim, int k, int val_bytes, const voi
               N * 200e-12 + 0.5 * rounds * 0.6e-6;
     const double slices = sliced_slices(dim, val_bytes), hit = hot_share(g, 24000.0);
     const bool in_place = sliced_in_place(dim, val_bytes);
-    c.sliced = !sliced_supports(dY, g->N, dim, val_bytes) || g->pull_form == 1 ? HUGE_VAL
+    c.sliced = !sliced_supports(dY, g->N, dim, val_bytes) || g->pull_form == 1 ||
+                       (!in_place && is_refused(g, sliced_key(g, dim, val_bytes)) && sliced_copy_bytes(g->N, dim, val_bytes) > g->sliced_bytes) ? HUGE_VAL
                : g->pull_form == 2 ? 0.0 : 6e-6 + nnz * slices * (7e-12 * hit + 25e-12 * (1.0 - hit)) + N * slices * (60e-12 + 0.5e-12 * k) +
                      (in_place ? 0.0 : N * (row_bytes + slices * 128.0) / 4.5e12);
     return c;
@@ -921,22 +964,24 @@ int auto_bwd_mode(const maxk_graph* g, int dim, int k, int val_bytes = 4, bool t
     const PullCost p = pull_cost(g, dim, k, val_bytes, nullptr);
     const double pull = std::min(p.plain, p.sliced);
 
+    // what was refused memory is out of the race until a reserve gets it
     // expand/reduce: 8k bytes an entry through HBM, whatever the graph looks like (scalar stores when
     // k % 4 != 0, two-byte columns above dim 256)
-    const double expand = nnz * k * 4.0 > 96e9 ? HUGE_VAL
+    const double expand = nnz * k * 4.0 > 96e9 || (is_refused(g, {kRefusedExpand, k}) && g->nnz * (int64_t)k > g->expand_floats) ? HUGE_VAL
                           : 8e-6 + nnz * (18e-12 + (dim > 256 ? 1.75e-12 : 1.5e-12) * k) * (k % 4 ? 1.7 : 1.0) +
                                 N * (400e-12 + 0.22e-12 * row_bytes);
 
     // slab pull: lines from L2 at 5.2 ps (plus ~0.35 lines an entry of streamed arrays) and one launch a slab, ~22 us
     // with its ramp and tail
-    const double n_slabs = std::ceil(N / slab_rows_for(g, dim, val_bytes));
-    const double slab = n_slabs * N >= 1.8e19 ? HUGE_VAL : 5e-6 + nnz * (lines + 0.35) * 5.2e-12 + n_slabs * 22e-6;
+    const int32_t slab_rows = slab_rows_for(g, dim, val_bytes);
+    const double n_slabs = std::ceil(N / slab_rows);
+    const double slab = n_slabs * N >= 1.8e19 || is_refused(g, {kRefusedSlab, slab_rows}) ? HUGE_VAL : 5e-6 + nnz * (lines + 0.35) * 5.2e-12 + n_slabs * 22e-6;
 
     // LDS-tiled: a (destination set, tile) step on each CU (the dim = 256 specialization is 3-5 times cheaper than the
     // general one), the entries, and fp32 atomics when the source rows are cut into ranges
     double tiled = HUGE_VAL;
     TiledShape sh;
-    if (tiled_ok && val_bytes == 4 && tiled_shape(g->N, dim, k, sh)) {
+    if (tiled_ok && val_bytes == 4 && tiled_shape(g->N, dim, k, sh) && !is_refused(g, tiled_key(sh, k))) {
         const double n_tiles = std::ceil(N / sh.TR);
         if (sh.n_dsets * n_tiles < 2.6e8)
             tiled = 15e-6 + (dim == 256 ? 0.2e-6 : 0.5e-6 + 1.2e-9 * dim) * sh.n_dsets * n_tiles / 256.0 +
@@ -949,6 +994,52 @@ int auto_bwd_mode(const maxk_graph* g, int dim, int k, int val_bytes = 4, bool t
     if (slab < best) { best = slab; mode = MAXK_BWD_SLAB_PULL; }
     if (tiled < best) mode = MAXK_BWD_TILED;
     return mode;
+}
+
+// The backward kernel of a call and the tables it walks, which are built where they are missing.
+struct BwdPlan {
+    int mode = MAXK_BWD_PULL_CSC;
+    bool sliced = false;  // the pull's column-sliced form
+    TiledSet* T = nullptr;
+    SlabSet* S = nullptr;
+};
+
+// Chooses the kernel and builds what it lacks, for a reserve (stream = nullptr) and for a compute call alike.  The
+// library's own choice goes on to the next best kernel when memory runs out, down to plain pull, which needs no buffer of
+// its own; while the call is being captured nothing may be allocated, and plain pull stands in for what is missing.
+maxk_status plan_bwd(maxk_graph* g, int dim, int k, int vb, bool tiled_ok, const void* dY, const hipStream_t* stream, BwdPlan& plan)
+{
+    const bool automatic = g->bwd_mode == MAXK_BWD_AUTO;
+    const auto captured = [&] { return stream && capturing(*stream); };
+    const auto existing_only = [&] { return automatic && captured(); };
+    int mode = automatic ? auto_bwd_mode(g, dim, k, vb, tiled_ok) : g->bwd_mode;
+    for (;;) {
+        maxk_status st = MAXK_OK;
+        plan = BwdPlan();
+        plan.mode = mode;
+        if (mode == MAXK_BWD_TILED) {
+            st = tiled_ok ? tiled_for(g, dim, k, existing_only, &plan.T) : MAXK_UNSUPPORTED;
+            if (st == MAXK_UNSUPPORTED) plan.mode = MAXK_BWD_SLAB_PULL;  // shapes, formats and alignments the tiled kernel does not take
+        }
+        if (plan.mode == MAXK_BWD_SLAB_PULL) st = slabs_for(g, slab_rows_for(g, dim, vb), existing_only, &plan.S);
+        if (mode == MAXK_BWD_EXPAND_REDUCE) {
+            st = g->nnz * (int64_t)k > g->expand_floats && existing_only() ? MAXK_OUT_OF_MEMORY : ensure_expand(g, k);
+        }
+        if (mode == MAXK_BWD_PULL_CSC) {
+            const PullCost p = pull_cost(g, dim, k, vb, dY);
+            plan.sliced = p.sliced < p.plain;
+            if (plan.sliced && !sliced_in_place(dim, vb)) {
+                st = sliced_copy_bytes(g->N, dim, vb) > g->sliced_bytes && captured() ? MAXK_OUT_OF_MEMORY : ensure_sliced(g, dim, vb);
+                if (st == MAXK_OUT_OF_MEMORY) {
+                    plan.sliced = false;
+                    st = MAXK_OK;
+                }
+            }
+        }
+        if (st != MAXK_OUT_OF_MEMORY || !automatic) return st;
+        const int next = auto_bwd_mode(g, dim, k, vb, tiled_ok);
+        mode = next == mode ? MAXK_BWD_PULL_CSC : next;  // (the same again: nothing was refused, the call is being captured)
+    }
 }
 
 maxk_status reserve_shape(maxk_graph* g, int dim, int k, int dy_value_type)
@@ -972,24 +1063,13 @@ maxk_status reserve_shape(maxk_graph* g, int dim, int k, int dy_value_type)
         }
     }
     const int vb = value_bytes(dy_value_type);
-    const int mode = g->bwd_mode == MAXK_BWD_AUTO ? auto_bwd_mode(g, dim, k, vb) : g->bwd_mode;
-    if (mode == MAXK_BWD_TILED) {
-        TiledSet* T = nullptr;
-        st = tiled_for(g, dim, k, false, &T);
-        if (st != MAXK_UNSUPPORTED) return st;
-        // the compute call falls back to the slab kernel for shapes the tiled one does not take
-    }
-    if (mode == MAXK_BWD_SLAB_PULL || mode == MAXK_BWD_TILED) {
-        SlabSet* S = nullptr;
-        return g->nnz ? slabs_for(g, slab_rows_for(g, dim, vb), false, &S) : MAXK_OK;
-    }
-    if (mode == MAXK_BWD_PULL_CSC) {
-        const PullCost p = pull_cost(g, dim, k, vb, nullptr);
-        return p.sliced < p.plain && !sliced_in_place(dim, vb) ? ensure_sliced(g, dim, vb) : MAXK_OK;
-    }
-    if (mode != MAXK_BWD_EXPAND_REDUCE) return MAXK_OK;
-    st = ensure_expand(g, k);
-    return st == MAXK_OUT_OF_MEMORY && g->bwd_mode == MAXK_BWD_AUTO ? MAXK_OK : st;  // (the compute call runs pull then)
+    forget_refused(g, {kRefusedExpand, k});
+    forget_refused(g, {kRefusedSlab, slab_rows_for(g, dim, vb)});
+    forget_refused(g, sliced_key(g, dim, vb));
+    TiledShape sh;
+    if (tiled_shape(g->N, dim, k, sh)) forget_refused(g, tiled_key(sh, k));
+    BwdPlan plan;
+    return g->nnz ? plan_bwd(g, dim, k, vb, true, nullptr, nullptr, plan) : MAXK_OK;
 }
 
 bool bad_index_bytes(int index_bytes, int dim)
@@ -1239,55 +1319,28 @@ MAXK_API maxk_status maxk_sspmm_bwd_narrow(maxk_graph* g, const void* d_dY, int3
         return MAXK_INVALID_ARGUMENT;
     maxk_status st = ensure_workspace(g, dim, k);
     if (st != MAXK_OK) return st;
-    int mode = g->bwd_mode;
-    const bool tiled_ok = tiled_supports(d_dY, value_type, d_sp_index, index_bytes, dim, k);
-    const bool automatic = mode == MAXK_BWD_AUTO;
     hipStream_t s = (hipStream_t)stream;
-    if (automatic) mode = auto_bwd_mode(g, dim, k, vb, tiled_ok);
     if (g->nnz == 0) return launch_fill_zero(d_dXs, g->N * (int64_t)k, s);
-    // What nobody reserved is built here, unless the call is being captured (nothing may be allocated then) or memory has
-    // run out: the library's own choice then falls back to plain pull, which needs no buffer of its own.
-    if (mode == MAXK_BWD_TILED) {
-        TiledSet* T = nullptr;
-        st = tiled_ok ? tiled_for(g, dim, k, automatic && capturing(s), &T) : MAXK_UNSUPPORTED;
-        if (st == MAXK_OK)
-            return launch_bwd_tiled(*T, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs, s);
-        if (st == MAXK_OUT_OF_MEMORY && automatic) mode = MAXK_BWD_PULL_CSC;
-        else if (st != MAXK_UNSUPPORTED) return st;
-        else mode = MAXK_BWD_SLAB_PULL;  // shapes, formats and alignments the tiled kernel does not take
-    }
-    if (mode == MAXK_BWD_SLAB_PULL) {
-        SlabSet* S = nullptr;
-        st = slabs_for(g, slab_rows_for(g, dim, vb), automatic && capturing(s), &S);
-        if (st == MAXK_OK)
-            return launch_bwd_slab_pull(*S, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs, s);
-        if (st != MAXK_OUT_OF_MEMORY || !automatic) return st;
-        mode = MAXK_BWD_PULL_CSC;
-    }
-    if (mode == MAXK_BWD_EXPAND_REDUCE) {
-        st = g->nnz * (int64_t)k > g->expand_floats && automatic && capturing(s) ? MAXK_OUT_OF_MEMORY : ensure_expand(g, k);
-        if (st == MAXK_OK)
-            return launch_bwd_expand_reduce(g->csr_items, g->d_col, g->d_val, g->csc_items, g->d_csc_entry, d_dY, value_type,
-                                            d_sp_index, index_bytes, dim, k, g->d_expand, d_dXs, g->d_partials, s);
-        if (st != MAXK_OUT_OF_MEMORY || !automatic) return st;
-        mode = MAXK_BWD_PULL_CSC;
-    }
-    if (mode == MAXK_BWD_PULL_CSC) {
-        const PullCost p = pull_cost(g, dim, k, vb, d_dY);
-        if (p.sliced < p.plain) {
-            const bool in_place = sliced_in_place(dim, vb);
-            st = in_place ? MAXK_OK
-                 : sliced_copy_bytes(g->N, dim, vb) > g->sliced_bytes && capturing(s) ? MAXK_OUT_OF_MEMORY : ensure_sliced(g, dim, vb);
-            if (st == MAXK_OK)
-                st = launch_bwd_sliced(g->csc_items, g->d_csc_src, g->d_csc_val, d_dY, value_type, d_sp_index, index_bytes, g->N,
-                                       dim, k, in_place ? nullptr : g->d_sliced, d_dXs, g->d_partials, s);
-            if (st != MAXK_OUT_OF_MEMORY && st != MAXK_UNSUPPORTED) return st;
+    BwdPlan plan;
+    st = plan_bwd(g, dim, k, vb, tiled_supports(d_dY, value_type, d_sp_index, index_bytes, dim, k), d_dY, &s, plan);
+    if (st != MAXK_OK) return st;
+    if (plan.mode == MAXK_BWD_TILED)
+        return launch_bwd_tiled(*plan.T, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs, s);
+    if (plan.mode == MAXK_BWD_SLAB_PULL)
+        return launch_bwd_slab_pull(*plan.S, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs, s);
+    if (plan.mode == MAXK_BWD_EXPAND_REDUCE)
+        return launch_bwd_expand_reduce(g->csr_items, g->d_col, g->d_val, g->csc_items, g->d_csc_entry, d_dY, value_type,
+                                        d_sp_index, index_bytes, dim, k, g->d_expand, d_dXs, g->d_partials, s);
+    if (plan.mode == MAXK_BWD_PULL_CSC) {
+        if (plan.sliced) {
+            st = launch_bwd_sliced(g->csc_items, g->d_csc_src, g->d_csc_val, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k,
+                                   sliced_in_place(dim, vb) ? nullptr : g->d_sliced, d_dXs, g->d_partials, s);
+            if (st != MAXK_UNSUPPORTED) return st;
         }
         return launch_bwd_pull(g->csc_items, g->d_csc_src, g->d_csc_val, d_dY, value_type, d_sp_index, index_bytes, dim, k,
                                d_dXs, g->d_partials, s);
     }
-    return launch_bwd_push(g->csr_items, g->d_col, g->d_val, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs,
-                           (hipStream_t)stream);
+    return launch_bwd_push(g->csr_items, g->d_col, g->d_val, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs, s);
 }
 
 MAXK_API maxk_status maxk_sspmm_bwd(maxk_graph* g, const float* d_dY, const void* d_sp_index, int32_t index_bytes, int32_t dim,

@@ -842,3 +842,42 @@ def test_a_sweep_table_that_does_not_fit_is_tried_once(monkeypatch):
     gr.reserve(dim, k)
     assert gr.sweep_tables() == 1
     gr.destroy()
+
+
+_CHOICES = [("expand_reduce", 3001, 300_000, 384, 16), ("tiled", 3001, 900_000, 256, 16), ("slab_pull", 10007, 3_000_000, 256, 13),
+            ("pull", 3001, 90_000, 100, 50)]
+
+
+@pytest.mark.parametrize("reserve", [False, True])
+@pytest.mark.parametrize("choice,N,M,dim,k", _CHOICES)
+def test_a_backward_kernel_that_does_not_fit_is_given_up_once(monkeypatch, choice, N, M, dim, k, reserve):
+    # the library's choice moves on to a kernel that fits, with or without a reserve, and stays there
+    monkeypatch.delenv("MAXK_SLAB_KB", raising=False)
+    if choice == "pull":
+        monkeypatch.setenv("MAXK_PULL_FORM", "2")  # width 100: the column slices need a copy of dY
+    g, dY, gr, _, sp_index = _aggregation_case(N, M, dim, k, 121)
+    if choice == "pull":
+        gr.set_bwd_mode(maxk.BWD_PULL_CSC)
+    assert gr.bwd_choice(dim, k) == choice
+    gr.limit_allocations(0)
+    if reserve:
+        gr.reserve(dim, k)
+    ref, refabs = oracle.sspmm_bwd(g.rowptr, g.col, g.val, dY, index_to_numpy(sp_index))
+    dY_dev, dXs = to_dev(dY), torch.empty((N, k), device="cuda")
+    seen = []
+    for i in range(3):
+        if i == 2:
+            gr.limit_allocations(-1)  # memory is there again: the kernel does not change under the caller
+        before = torch.cuda.mem_get_info()[0]
+        dXs.fill_(float("nan"))
+        maxk.maxk_sspmm_bwd(gr, dY_dev, sp_index, dXs)
+        torch.cuda.synchronize()
+        assert (np.abs(dXs.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all()
+        assert gr.cached_tables() == (0, 0)
+        assert i == 0 or torch.cuda.mem_get_info()[0] == before
+        seen.append((gr.bwd_choice(dim, k), gr.limit_allocations(0 if i < 1 else -1)))
+    assert len(set(seen)) == 1 and seen[0][1] >= 1, seen
+    assert seen[0][0] == "pull"
+    gr.reserve(dim, k)  # asks for the memory again
+    assert gr.bwd_choice(dim, k) == choice
+    gr.destroy()
