@@ -944,10 +944,11 @@ PullCost pull_cost(const maxk_graph* g, int dim, int k, int val_bytes, const voi
               N * 200e-12 + 0.5 * rounds * 0.6e-6;
     const double slices = sliced_slices(dim, val_bytes), hit = hot_share(g, 24000.0);
     const bool in_place = sliced_in_place(dim, val_bytes);
-    c.sliced = !sliced_supports(dY, g->N, dim, val_bytes) || g->pull_form == 1 ||
-                       (!in_place && is_refused(g, sliced_key(g, dim, val_bytes)) && sliced_copy_bytes(g->N, dim, val_bytes) > g->sliced_bytes) ? HUGE_VAL
-               : g->pull_form == 2 ? 0.0 : 6e-6 + nnz * slices * (7e-12 * hit + 25e-12 * (1.0 - hit)) + N * slices * (60e-12 + 0.5e-12 * k) +
-                     (in_place ? 0.0 : N * (row_bytes + slices * 128.0) / 4.5e12);
+    c.sliced = !sliced_supports(dY, g->N, dim, val_bytes) ||
+                       (!in_place && is_refused(g, sliced_key(g, dim, val_bytes)) && sliced_copy_bytes(g->N, dim, val_bytes) > g->sliced_bytes)
+                   ? HUGE_VAL
+                   : 6e-6 + nnz * slices * (7e-12 * hit + 25e-12 * (1.0 - hit)) + N * slices * (60e-12 + 0.5e-12 * k) +
+                         (in_place ? 0.0 : N * (row_bytes + slices * 128.0) / 4.5e12);
     return c;
 }
 
@@ -1027,7 +1028,7 @@ maxk_status plan_bwd(maxk_graph* g, int dim, int k, int vb, bool tiled_ok, const
         }
         if (mode == MAXK_BWD_PULL_CSC) {
             const PullCost p = pull_cost(g, dim, k, vb, dY);
-            plan.sliced = p.sliced < p.plain;
+            plan.sliced = g->pull_form == 0 ? p.sliced < p.plain : g->pull_form == 2 && p.sliced < HUGE_VAL;
             if (plan.sliced && !sliced_in_place(dim, vb)) {
                 st = sliced_copy_bytes(g->N, dim, vb) > g->sliced_bytes && captured() ? MAXK_OUT_OF_MEMORY : ensure_sliced(g, dim, vb);
                 if (st == MAXK_OUT_OF_MEMORY) {

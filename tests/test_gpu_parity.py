@@ -881,3 +881,13 @@ def test_a_backward_kernel_that_does_not_fit_is_given_up_once(monkeypatch, choic
     gr.reserve(dim, k)  # asks for the memory again
     assert gr.bwd_choice(dim, k) == choice
     gr.destroy()
+
+
+def test_the_form_of_the_pull_does_not_move_the_automatic_choice(monkeypatch):
+    monkeypatch.delenv("MAXK_SLAB_KB", raising=False)
+    for form in ("0", "1", "2"):
+        monkeypatch.setenv("MAXK_PULL_FORM", form)
+        for choice, N, M, dim, k in _CHOICES[:2]:
+            gr = _aggregation_case(N, M, dim, k, 121)[2]
+            assert gr.bwd_choice(dim, k) == choice, form
+            gr.destroy()
