@@ -891,3 +891,37 @@ def test_the_form_of_the_pull_does_not_move_the_automatic_choice(monkeypatch):
             gr = _aggregation_case(N, M, dim, k, 121)[2]
             assert gr.bwd_choice(dim, k) == choice, form
             gr.destroy()
+
+
+# ------------------------------------------------------------------ how many sums a result is added up in
+
+
+def _one_large_many_ones(N, large):
+    """dY rows of ones, `large` in row 0: node 1 receives from nodes 0..119, node 2 from 0..63, the others from 0 only."""
+    ins = [(i, 1) for i in range(120)] + [(i, 2) for i in range(64)] + [(0, j) for j in range(3, N)]
+    rowptr, col, val = csr_from_coo(N, [(i, j, 1.0) for i, j in sorted(ins)])
+    return rowptr, col, val, {1: 120, 2: 64}
+
+
+@pytest.mark.parametrize("form", ["1"])
+@pytest.mark.parametrize("dim,k", [(64, 8), (64, 13), (128, 32), (128, 64), (256, 100)])
+@pytest.mark.parametrize("fmt", ["f32", "bf16", "f16"])
+def test_pull_adds_up_in_short_sums(monkeypatch, form, dim, k, fmt):
+    # One in-entry adds L, every other adds 1, and L + 1 rounds to L: a running sum that holds L loses all that follow.
+    # Products are added four at a time before they reach a running sum, so at most the 3 ones beside L are lost; the
+    # sums above L are even numbers, which rounds by 1 at most, twice
+    monkeypatch.setenv("MAXK_PULL_FORM", form)
+    N, large = 130, {"f32": 2.0 ** 24, "bf16": 2.0 ** 24, "f16": 2.0 ** 12}[fmt]
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[fmt]
+    rowptr, col, val, degree = _one_large_many_ones(N, large)
+    gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val * (2.0 ** 24 / large)))  # (f16 ends at 65504)
+    gr.set_bwd_mode(maxk.BWD_PULL_CSC)
+    dY = torch.full((N, dim), large / 2.0 ** 24, dtype=dt, device="cuda")
+    dY[0] = large
+    sp_index = torch.arange(k, dtype=torch.uint8, device="cuda").repeat(N, 1)
+    dXs = torch.empty((N, k), device="cuda")
+    maxk.maxk_sspmm_bwd_narrow(gr, dY, sp_index, dXs)
+    got = dXs.cpu().numpy()
+    for node, n in degree.items():
+        assert np.abs(got[node] - 2.0 ** 24 - (n - 1)).max() <= 3 + 2, (node, got[node][:4] - 2.0 ** 24)
+    gr.destroy()
