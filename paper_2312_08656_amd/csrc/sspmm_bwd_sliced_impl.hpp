@@ -75,24 +75,28 @@ __device__ __forceinline__ uint32_t upper_four(uint32_t x)
     return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x104, 0xF, 0x5, false);
 }
 
-template <int VT, int N>
-__device__ __forceinline__ void sliced_fma(float (&acc)[N], float w, u32x4 x)
+// sum = w * x for the first entry of a sum, sum += w * x for the others
+template <int VT, bool FIRST, int N>
+__device__ __forceinline__ void sliced_fma(float (&sum)[N], float w, u32x4 x)
 {
     const uint32_t d[4] = {x.x, x.y, x.z, x.w};
+    const auto add = [&](float& to, float v) { to = FIRST ? w * v : to + w * v; };
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         if constexpr (VT == MAXK_VALUE_F32) {
-            acc[i] += w * __uint_as_float(d[i]);
+            add(sum[i], __uint_as_float(d[i]));
         } else {
-            acc[2 * i] += w * widen_value<VT>((uint16_t)(d[i] & 0xFFFFu));
-            acc[2 * i + 1] += w * widen_value<VT>((uint16_t)(d[i] >> 16));
+            add(sum[2 * i], widen_value<VT>((uint16_t)(d[i] & 0xFFFFu)));
+            add(sum[2 * i + 1], widen_value<VT>((uint16_t)(d[i] >> 16)));
         }
     }
 }
 
-// VEC: consecutive sp_index entries fetched with one load (4 or 1), for the short items
+// VEC: consecutive sp_index entries fetched with one load (4 or 1), for the short items.
+// fp32 in registers for 8 wavefronts a SIMD (66 registers otherwise: the first shape below 1370 us instead of 1232); the
+// 16-bit formats as they come (74 registers, 6 wavefronts: 617 us; held to 8 they spill: 1090).
 template <int VT, int VEC, typename IdxT>
-__global__ __launch_bounds__(kSlicedWaves * kWave) void bwd_sliced_kernel(SlicedArgs a)
+__global__ __launch_bounds__(kSlicedWaves * kWave, VT == MAXK_VALUE_F32 ? 8 : 1) void bwd_sliced_kernel(SlicedArgs a)
 {
     constexpr int EPL = VT == MAXK_VALUE_F32 ? 4 : 8;  // columns per lane
     constexpr int W = 8 * EPL;                         // columns of a slice
@@ -124,9 +128,14 @@ __global__ __launch_bounds__(kSlicedWaves * kWave) void bwd_sliced_kernel(Sliced
         e = min(e, p + share);
     }
     const uint32_t lane_off = (uint32_t)q * 16u;
-    float acc[EPL];
+    // Entries are added up in fours, which go to two running sums in turn.  One running sum over all entries of a lane group
+    // came out up to twice as far from 64 bits as the kernels whose calls come here (runs of 64 entries, 2-norm: 1.4e-7 with
+    // one sum, 7.4e-8 so, plain pull 6.8e-8 .. 8.7e-8, expand/reduce 7.1e-8 .. 1.1e-7; of 16: 7.4e-8, 5.6e-8, 5.6e-8 and
+    // 6.0e-8).  us, one sum / fours: fp32 60 k nodes, degree 240, k = 64 1223 / 1232; 100 k, degree 60, dim 101, k = 50
+    // 332 / 335; bf16 60 k, degree 240, k = 64 627 / 617.
+    float first[EPL], second[EPL], four[EPL];
 #pragma unroll
-    for (int i = 0; i < EPL; ++i) acc[i] = 0.f;
+    for (int i = 0; i < EPL; ++i) first[i] = second[i] = 0.f;
 
     constexpr uint32_t kNowhere = 0xFFFF0000u;  // past every buffer (kSlicedMaxBytes), also with lane_off added
     int n = e - p;                              // entries left of this group; <= 0: none
@@ -140,10 +149,12 @@ __global__ __launch_bounds__(kSlicedWaves * kWave) void bwd_sliced_kernel(Sliced
         const uint32_t off_0 = lower_four(off), w_0 = lower_four(w);
 #define MAXK_SLICED_LOAD(H, U) \
     x[H * 4 + U] = __builtin_amdgcn_raw_buffer_load_b128(rows, (int)(quad_lane<U>(off_##H) + lane_off), 0, 0);
-#define MAXK_SLICED_FMA(H, U) sliced_fma<VT>(acc, __uint_as_float(quad_lane<U>(w_##H)), x[H * 4 + U]);
+#define MAXK_SLICED_FMA(H, U) sliced_fma<VT, U == 0>(four, __uint_as_float(quad_lane<U>(w_##H)), x[H * 4 + U]);
         if (!__any(n > 4)) {  // the last four or fewer
             MAXK_SLICED_LOAD(0, 0) MAXK_SLICED_LOAD(0, 1) MAXK_SLICED_LOAD(0, 2) MAXK_SLICED_LOAD(0, 3)
             MAXK_SLICED_FMA(0, 0) MAXK_SLICED_FMA(0, 1) MAXK_SLICED_FMA(0, 2) MAXK_SLICED_FMA(0, 3)
+#pragma unroll
+            for (int i = 0; i < EPL; ++i) first[i] += four[i];
             break;
         }
         const uint32_t off_1 = upper_four(off), w_1 = upper_four(w);
@@ -154,7 +165,11 @@ __global__ __launch_bounds__(kSlicedWaves * kWave) void bwd_sliced_kernel(Sliced
         row = a.src[entry(p)];
         weight = a.val[entry(p)];
         MAXK_SLICED_FMA(0, 0) MAXK_SLICED_FMA(0, 1) MAXK_SLICED_FMA(0, 2) MAXK_SLICED_FMA(0, 3)
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) first[i] += four[i];
         MAXK_SLICED_FMA(1, 0) MAXK_SLICED_FMA(1, 1) MAXK_SLICED_FMA(1, 2) MAXK_SLICED_FMA(1, 3)
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) second[i] += four[i];
 #undef MAXK_SLICED_LOAD
 #undef MAXK_SLICED_FMA
     }
@@ -163,7 +178,8 @@ __global__ __launch_bounds__(kSlicedWaves * kWave) void bwd_sliced_kernel(Sliced
     // destination's columns that lie in the slice
 #pragma unroll
     for (int i = 0; i < EPL; i += 4)
-        *reinterpret_cast<float4*>(sums + g * W + q * EPL + i) = make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]);
+        *reinterpret_cast<float4*>(sums + g * W + q * EPL + i) =
+            make_float4(first[i] + second[i], first[i + 1] + second[i + 1], first[i + 2] + second[i + 2], first[i + 3] + second[i + 3]);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");

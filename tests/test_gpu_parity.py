@@ -903,7 +903,7 @@ def _one_large_many_ones(N, large):
     return rowptr, col, val, {1: 120, 2: 64}
 
 
-@pytest.mark.parametrize("form", ["1"])
+@pytest.mark.parametrize("form", ["1", "2"])
 @pytest.mark.parametrize("dim,k", [(64, 8), (64, 13), (128, 32), (128, 64), (256, 100)])
 @pytest.mark.parametrize("fmt", ["f32", "bf16", "f16"])
 def test_pull_adds_up_in_short_sums(monkeypatch, form, dim, k, fmt):
