@@ -6,7 +6,7 @@
 namespace maxk {
 namespace {
 
-constexpr int kReduceUnroll = 4;
+constexpr int kReduceUnroll = 4;  // added up in pairs before the running sum, for its rounding (as in pull_sum)
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(float* __restrict__ p, int64_t n)
 {
@@ -48,9 +48,7 @@ __global__ __launch_bounds__(kWave) void bwd_reduce_kernel(const WorkItem* __res
                 }
             }
 #pragma unroll
-            for (int u = 0; u < kReduceUnroll; ++u)
-#pragma unroll
-                for (int j = 0; j < VEC; ++j) acc[j] += v[u][j];
+            for (int j = 0; j < VEC; ++j) acc[j] += (v[0][j] + v[1][j]) + (v[2][j] + v[3][j]);
         }
 #pragma unroll
         for (int off = LPE; off < kWave; off <<= 1)

@@ -590,10 +590,24 @@ __device__ __forceinline__ void rowacc_batch(float (&acc)[RC][row_piece<VT>::n],
             }
         }
     }
+    // A batch is added up by itself before it reaches the running sum (9.0 M entries, 30 k nodes, dim 64, k = 16: 2-norm error
+    // against 64 bits 2.15e-7 -> 1.04e-7; times within 1 %).  Not for rows of more than 768 columns: the registers for it
+    // cost wavefronts (dim 1024, fp32: 1864 -> 2049 us).
+    if constexpr (RC < 4) {
 #pragma unroll
-    for (int uu = 0; uu < CNT; ++uu)
+        for (int c = 0; c < RC; ++c) {
+            float sum[EPL] = {};
 #pragma unroll
-        for (int c = 0; c < RC; ++c) fma_piece<VT>(acc[c], en.w[uu], x[uu][c]);
+            for (int uu = 0; uu < CNT; ++uu) fma_piece<VT>(sum, en.w[uu], x[uu][c]);
+#pragma unroll
+            for (int i = 0; i < EPL; ++i) acc[c][i] += sum[i];
+        }
+    } else {
+#pragma unroll
+        for (int uu = 0; uu < CNT; ++uu)
+#pragma unroll
+            for (int c = 0; c < RC; ++c) fma_piece<VT>(acc[c], en.w[uu], x[uu][c]);
+    }
 }
 
 // RC: chunks of 64 row pieces (256 columns) that cover a row

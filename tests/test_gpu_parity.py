@@ -903,6 +903,32 @@ def _one_large_many_ones(N, large):
     return rowptr, col, val, {1: 120, 2: 64}
 
 
+def _large_sum_pass(mode, dim, k, fmt):
+    N, large = 130, {"f32": 2.0 ** 24, "bf16": 2.0 ** 24, "f16": 2.0 ** 12}[fmt]
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[fmt]
+    rowptr, col, val, degree = _one_large_many_ones(N, large)
+    gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val * (2.0 ** 24 / large)))  # (f16 ends at 65504)
+    gr.set_bwd_mode(mode)
+    dY = torch.full((N, dim), large / 2.0 ** 24, dtype=dt, device="cuda")
+    dY[0] = large
+    sp_index = torch.arange(k, dtype=torch.uint8, device="cuda").repeat(N, 1)
+    dXs = torch.empty((N, k), device="cuda")
+    maxk.maxk_sspmm_bwd_narrow(gr, dY, sp_index, dXs)
+    got = dXs.cpu().numpy()
+    gr.destroy()
+    return got, degree
+
+
+@pytest.mark.parametrize("dim,k", [(64, 32), (128, 64), (256, 100)])
+@pytest.mark.parametrize("fmt", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("mode", ["expand_reduce", "slab_pull"])
+def test_expand_reduce_and_slab_pull_add_up_in_short_sums(mode, dim, k, fmt):
+    # as below: expand/reduce adds product rows in pairs of pairs, slab pull adds dY rows in batches of eight
+    got, degree = _large_sum_pass(maxk.BWD_EXPAND_REDUCE if mode == "expand_reduce" else maxk.BWD_SLAB_PULL, dim, k, fmt)
+    for node, n in degree.items():
+        assert np.abs(got[node] - 2.0 ** 24 - (n - 1)).max() <= (3 if mode == "expand_reduce" else 7) + 2, got[node][:4] - 2.0 ** 24
+
+
 @pytest.mark.parametrize("form", ["1", "2"])
 @pytest.mark.parametrize("dim,k", [(64, 8), (64, 13), (128, 32), (128, 64), (256, 100)])
 @pytest.mark.parametrize("fmt", ["f32", "bf16", "f16"])
@@ -911,17 +937,6 @@ def test_pull_adds_up_in_short_sums(monkeypatch, form, dim, k, fmt):
     # Products are added four at a time before they reach a running sum, so at most the 3 ones beside L are lost; the
     # sums above L are even numbers, which rounds by 1 at most, twice
     monkeypatch.setenv("MAXK_PULL_FORM", form)
-    N, large = 130, {"f32": 2.0 ** 24, "bf16": 2.0 ** 24, "f16": 2.0 ** 12}[fmt]
-    dt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[fmt]
-    rowptr, col, val, degree = _one_large_many_ones(N, large)
-    gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val * (2.0 ** 24 / large)))  # (f16 ends at 65504)
-    gr.set_bwd_mode(maxk.BWD_PULL_CSC)
-    dY = torch.full((N, dim), large / 2.0 ** 24, dtype=dt, device="cuda")
-    dY[0] = large
-    sp_index = torch.arange(k, dtype=torch.uint8, device="cuda").repeat(N, 1)
-    dXs = torch.empty((N, k), device="cuda")
-    maxk.maxk_sspmm_bwd_narrow(gr, dY, sp_index, dXs)
-    got = dXs.cpu().numpy()
+    got, degree = _large_sum_pass(maxk.BWD_PULL_CSC, dim, k, fmt)
     for node, n in degree.items():
-        assert np.abs(got[node] - 2.0 ** 24 - (n - 1)).max() <= 3 + 2, (node, got[node][:4] - 2.0 ** 24)
-    gr.destroy()
+        assert np.abs(got[node] - 2.0 ** 24 - (n - 1)).max() <= 3 + 2, got[node][:4] - 2.0 ** 24
