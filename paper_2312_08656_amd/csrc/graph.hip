@@ -987,6 +987,15 @@ int auto_bwd_mode(const maxk_graph* g, int dim, int k, int val_bytes = 4, bool t
         if (sh.n_dsets * n_tiles < 2.6e8)
             tiled = 15e-6 + (dim == 256 ? 0.2e-6 : 0.5e-6 + 1.2e-9 * dim) * sh.n_dsets * n_tiles / 256.0 +
                     nnz * (3e-12 + 0.6e-12 * k) + (sh.R > 1 ? sh.R * N * k / 330e9 : 0.0);
+        // It keeps one running sum an element and source range, pull and slab pull short ones.  On graphs of more than a few
+        // thousand nodes it also has to win against slab pull by the models that were fitted on the dense and the
+        // ogbn-proteins-like graph alone (within 10 % there; the ones above run high for slab pull where no hub ends its
+        // launches), or it takes calls it is not faster for.  30 k nodes, width 256, k = 64, us (2-norm error against 64
+        // bits) tiled / slab pull / pull: uniform, degree 300 405 (1.62e-7) / 395 (0.93e-7) / 693; degree 100 201 (1.01e-7)
+        // / 193 / 219 (0.72e-7); R-MAT, degree 300 865 (4.9e-8) / 1074 / 584 (2.7e-8).
+        if (sh.n_dsets * n_tiles >= 65536.0 &&
+            1.05 * (150e-9 * sh.n_dsets * n_tiles / 256.0 + nnz * (3e-12 + 0.73e-12 * k)) >= nnz * (lines + 0.35) * 5.2e-12 + n_slabs * 10e-6)
+            tiled = HUGE_VAL;
     }
 
     int mode = MAXK_BWD_PULL_CSC;

@@ -940,3 +940,17 @@ def test_pull_adds_up_in_short_sums(monkeypatch, form, dim, k, fmt):
     got, degree = _large_sum_pass(maxk.BWD_PULL_CSC, dim, k, fmt)
     for node, n in degree.items():
         assert np.abs(got[node] - 2.0 ** 24 - (n - 1)).max() <= 3 + 2, got[node][:4] - 2.0 ** 24
+
+
+@pytest.mark.parametrize("skewed", [False, True])
+def test_auto_leaves_close_calls_to_the_kernels_with_short_sums(monkeypatch, skewed):
+    # width 256, k = 64, 9 M entries: the tiled kernel is no faster than slab pull or pull, and less exact than both
+    monkeypatch.delenv("MAXK_SLAB_KB", raising=False)
+    N, nnz, gen = 30011, 9_000_000, torch.Generator(device="cuda").manual_seed(3)
+    u = torch.rand((2, nnz), generator=gen, device="cuda", dtype=torch.float64)
+    src, col = ((u ** 2 if skewed else u) * N).long()
+    rowptr = torch.zeros(N + 1, dtype=torch.int32, device="cuda")
+    rowptr[1:] = torch.cumsum(torch.bincount(src, minlength=N), 0)
+    gr = maxk.maxk_graph_create(rowptr, col.int(), torch.ones(nnz, device="cuda"))
+    assert gr.bwd_choice(256, 64) in ("pull", "slab_pull")
+    gr.destroy()
