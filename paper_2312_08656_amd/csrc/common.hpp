@@ -80,7 +80,8 @@ struct TiledSet {
 
 // A regrouped for the forward sweep kernel: work items are dealt to bins of per_bin output rows with about the same number
 // of entries; a wavefront keeps a bin's rows in LDS and walks the entries of all of them in the order of their source node.
-// Entry e of a bin goes to lane group e % groups; a batch holds the next sweep_batch(k) entries of each group.
+// Entry e of a row goes to lane group (e + place of the row in the bin) % groups; a batch holds the next sweep_batch(k)
+// entries of each group.
 struct SweepSet {
     int32_t groups = 0, batch_len = 0, per_bin = 0;
     int64_t n_bins = 0;

@@ -623,18 +623,20 @@ void free_sweep(SweepSet& W)
     W = SweepSet();
 }
 
-// key[p] = bin << 32 | source node, payload[p] = p, row_of[p] = row of the bin, for the entries of every work item.
+// key[p] = (bin, lane group) << 32 | source node, payload[p] = p, row_of[p] = row of the bin, for the entries of every work
+// item.  Each row's own entries take the lane groups in turn: dealt by their place in the bin, the entries of two rows with the
+// same neighbours alternate and each row would end up in one lane group, one running sum.
 // Workgroups stride over the items: one each would be 2^32 threads, more than a launch holds, from 2^24 items up.
 __global__ __launch_bounds__(256) void sweep_keys_kernel(const WorkItem* __restrict__ items, const uint32_t* __restrict__ place,
-                                                         int64_t n_items, int per_bin, const int32_t* __restrict__ col,
-                                                         uint64_t* __restrict__ key, uint32_t* __restrict__ entry,
+                                                         int64_t n_items, int per_bin, uint32_t groups,
+                                                         const int32_t* __restrict__ col, uint64_t* __restrict__ key, uint32_t* __restrict__ entry,
                                                          uint8_t* __restrict__ row_of)
 {
     for (int64_t i = blockIdx.x; i < n_items; i += gridDim.x) {
         const WorkItem it = items[i];
         const uint32_t bin = place[i] / (uint32_t)per_bin, row = place[i] % (uint32_t)per_bin;
         for (int p = it.begin + (int)threadIdx.x; p < it.end; p += blockDim.x) {
-            key[p] = (uint64_t)bin << 32 | (uint32_t)col[p];
+            key[p] = ((uint64_t)bin * groups + ((uint32_t)(p - it.begin) + row) % groups) << 32 | (uint32_t)col[p];
             entry[p] = (uint32_t)p;
             row_of[p] = (uint8_t)row;
         }
@@ -649,14 +651,14 @@ __global__ __launch_bounds__(256) void sweep_fill_kernel(int2* __restrict__ ent,
 
 __global__ __launch_bounds__(256) void sweep_entries_kernel(const uint64_t* __restrict__ key, const uint32_t* __restrict__ entry,
                                                             const uint8_t* __restrict__ row_of, const float* __restrict__ val,
-                                                            int64_t nnz, const uint32_t* __restrict__ bin_first,
+                                                            int64_t nnz, const uint32_t* __restrict__ list_first,
                                                             const uint32_t* __restrict__ batch, uint32_t groups,
                                                             uint32_t batch_len, int2* __restrict__ ent)
 {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nnz; i += stride) {
-        const uint32_t bin = (uint32_t)(key[i] >> 32), p = entry[i], rank = (uint32_t)i - bin_first[bin];
-        const uint32_t g = rank % groups, n = rank / groups;
+        const uint32_t list = (uint32_t)(key[i] >> 32), bin = list / groups, g = list % groups, p = entry[i];
+        const uint32_t n = (uint32_t)i - list_first[list];
         ent[(((int64_t)batch[bin] + n / batch_len) * groups + g) * batch_len + n % batch_len] =
             make_int2((int)((uint32_t)key[i] | (uint32_t)row_of[p] << kSweepRowShift), __float_as_int(val[p]));
     }
@@ -670,7 +672,8 @@ maxk_status build_sweep(maxk_graph* g, SweepSet& W, int groups, int batch_len, i
     const int64_t n_items = g->csr_items.n_items, nnz = g->nnz, n_bins = (n_items + per_bin - 1) / per_bin;
     std::vector<WorkItem> items((size_t)n_items);
     MAXK_HIP_TRY(hipMemcpy(items.data(), g->csr_items.d_items, sizeof(WorkItem) * (size_t)n_items, hipMemcpyDeviceToHost));
-    std::vector<uint32_t> place((size_t)n_items), load((size_t)n_bins, 0), batch((size_t)n_bins + 1, 0), first((size_t)n_bins, 0);
+    std::vector<uint32_t> place((size_t)n_items), load((size_t)n_bins, 0), batch((size_t)n_bins + 1, 0);
+    std::vector<uint32_t> first((size_t)n_bins * groups, 0);  // entries of every (bin, lane group), then its first one
     std::vector<int2> rows((size_t)(n_bins * per_bin), make_int2(-1, -1));
     {
         std::vector<uint8_t> used((size_t)n_bins, 0);
@@ -682,16 +685,22 @@ maxk_status build_sweep(maxk_graph* g, SweepSet& W, int groups, int batch_len, i
             open.pop();
             place[(size_t)i] = b * (uint32_t)per_bin + used[b];
             rows[(size_t)place[(size_t)i]] = make_int2(items[(size_t)i].row, items[(size_t)i].slot);
-            load[b] += (uint32_t)(items[(size_t)i].end - items[(size_t)i].begin);
+            const uint32_t len = (uint32_t)(items[(size_t)i].end - items[(size_t)i].begin);
+            load[b] += len;
+            for (uint32_t j = 0; j < (uint32_t)groups; ++j)  // entries j, j + groups, ... of the row
+                first[(size_t)b * groups + (j + used[b]) % groups] += (len + (uint32_t)groups - 1 - j) / (uint32_t)groups;
             if (++used[b] < per_bin) open.push({load[b], b});
         }
     }
     uint32_t run = 0;
     for (int64_t b = 0; b < n_bins; ++b) {
-        first[(size_t)b] = run;
-        run += load[(size_t)b];
-        const uint64_t per_batch = (uint64_t)groups * batch_len;
-        const uint64_t next = batch[(size_t)b] + (load[(size_t)b] + per_batch - 1) / per_batch;
+        uint32_t longest = 0;
+        for (int l = 0; l < groups; ++l) {
+            uint32_t& f = first[(size_t)b * groups + l];
+            longest = std::max(longest, f);
+            run += std::exchange(f, run);
+        }
+        const uint64_t next = (uint64_t)batch[(size_t)b] + (longest + (uint32_t)batch_len - 1) / (uint32_t)batch_len;
         if (next > 0x7FFFFFFFull) return MAXK_UNSUPPORTED;
         batch[(size_t)b + 1] = (uint32_t)next;
     }
@@ -726,10 +735,10 @@ maxk_status build_sweep(maxk_graph* g, SweepSet& W, int groups, int batch_len, i
     MAXK_TRY_CLEAN(hipMemcpy(d_first, first.data(), sizeof(uint32_t) * first.size(), hipMemcpyHostToDevice));
     const unsigned blocks = (unsigned)std::min<int64_t>((nnz + 255) / 256, 65536);
     hipLaunchKernelGGL(sweep_keys_kernel, dim3((unsigned)std::min<int64_t>(n_items, 1 << 20)), dim3(256), 0, s,
-                       g->csr_items.d_items, d_place, n_items, per_bin, g->d_col, d_key, d_entry, d_row_of);
+                       g->csr_items.d_items, d_place, n_items, per_bin, (uint32_t)groups, g->d_col, d_key, d_entry, d_row_of);
     MAXK_TRY_CLEAN(hipGetLastError());
     int end_bit = 33;
-    while (end_bit < 64 && ((uint64_t)1 << (end_bit - 32)) < (uint64_t)n_bins) ++end_bit;
+    while (end_bit < 64 && ((uint64_t)1 << (end_bit - 32)) < (uint64_t)n_bins * groups) ++end_bit;
     size_t tmp_bytes = 0;
     MAXK_TRY_CLEAN(rocprim::radix_sort_pairs(nullptr, tmp_bytes, d_key, d_key_sorted, d_entry, d_perm, (size_t)nnz, 0, (unsigned)end_bit, s));
     MAXK_TRY_CLEAN(hipMalloc(&d_tmp, tmp_bytes ? tmp_bytes : 16));

@@ -954,3 +954,24 @@ def test_auto_leaves_close_calls_to_the_kernels_with_short_sums(monkeypatch, ske
     gr = maxk.maxk_graph_create(rowptr, col.int(), torch.ones(nnz, device="cuda"))
     assert gr.bwd_choice(256, 64) in ("pull", "slab_pull")
     gr.destroy()
+
+
+@pytest.mark.parametrize("sweep", ["1", "2"])
+@pytest.mark.parametrize("k", [8, 16, 32])
+def test_forward_shares_a_row_out_over_its_lane_groups(monkeypatch, sweep, k):
+    # Every row has the same neighbours, the first of them with the value L, the others 1, and L + 1 rounds to L: only the
+    # entries beside the first one's lane group count.  G = 64 / k groups: at most ceil(n / G) entries are lost.  Adding the
+    # G sums up rounds to an even number G - 1 times, by 1 at most
+    monkeypatch.setenv("MAXK_FWD_SWEEP", sweep)
+    N, n, dim = 120, 100, 64
+    rowptr, col, val = csr_from_coo(N, [(i, j, 1.0) for i in range(N) for j in range(n)])
+    gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val))
+    sp_data = torch.ones((N, k), device="cuda")
+    sp_data[0] = 2.0 ** 24
+    sp_index = torch.arange(k, dtype=torch.uint8, device="cuda").repeat(N, 1)
+    Y = torch.empty((N, dim), device="cuda")
+    maxk.maxk_spgemm_fwd(gr, sp_data, sp_index, dim, Y)
+    got = Y.cpu().numpy()[:, :k]
+    lost, G = 2.0 ** 24 + (n - 1) - got, 64 // k
+    assert lost.min() >= -(G - 1) and lost.max() <= -(-n // G) + G - 1, (lost.min(), lost.max())
+    gr.destroy()
