@@ -15,9 +15,9 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
-#include <functional>
+#include <deque>
+#include <map>
 #include <new>
-#include <queue>
 #include <utility>
 #include <vector>
 
@@ -31,6 +31,7 @@ struct maxk_graph {
     const int32_t* d_col = nullptr;
     const float* d_val = nullptr;
     maxk::ItemList csr_items;  // over rows of A
+    std::vector<std::pair<int32_t, int64_t>> csr_lengths;  // entries of a work item of csr_items, how many such items; longest first
     maxk::ItemList csc_items;  // over columns of A (rows of A^T)
     int32_t* d_csc_ptr = nullptr;
     int32_t* d_csc_src = nullptr;
@@ -623,20 +624,100 @@ void free_sweep(SweepSet& W)
     W = SweepSet();
 }
 
+// `count` consecutive work items that become row `row` of consecutive bins
+struct SweepRun { uint32_t item, bin, count, row; };
+
+// Deals the work items to bins of per_bin rows, longest first, each to the bin with the fewest entries so far that has a row
+// left (in rounds of one item a bin the fullest bins stay up to 20 % above the mean, and the forward pass takes 5 % longer
+// at four rows a bin).  Bins of equal load are moved a run at a time, so the work follows the number of different lengths
+// and not of items.  The runs come in the order of their items.
+void sweep_deal(const std::vector<std::pair<int32_t, int64_t>>& lengths, int64_t n_bins, int per_bin, std::vector<SweepRun>& runs)
+{
+    std::map<int64_t, std::deque<SweepRun>> open;  // by load: bins in runs, `row` = rows taken so far
+    open[0].push_back({0, 0, (uint32_t)n_bins, 0});
+    uint32_t item = 0;
+    for (const auto& [len, times] : lengths) {
+        for (int64_t left = times; left > 0;) {
+            const auto least = open.begin();
+            const int64_t load = least->first;
+            SweepRun& bins = least->second.front();
+            const SweepRun run = {item, bins.bin, (uint32_t)std::min<int64_t>(left, bins.count), bins.row};
+            bins.bin += run.count;
+            bins.count -= run.count;
+            if (bins.count == 0) {
+                least->second.pop_front();
+                if (least->second.empty()) open.erase(least);
+            }
+            if ((int)run.row + 1 < per_bin) open[load + len].push_back({0, run.bin, run.count, run.row + 1});
+            runs.push_back(run);
+            item += run.count;
+            left -= run.count;
+        }
+    }
+}
+
+// item_at[place] = the work item of every row of every bin (place = bin * per_bin + row; -1 from the caller: none), and back
+__global__ __launch_bounds__(256) void sweep_places_kernel(const SweepRun* __restrict__ runs, int n_runs, int64_t n_items,
+                                                           int per_bin, uint32_t* __restrict__ place, uint32_t* __restrict__ item_at)
+{
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_items; i += stride) {
+        int lo = 0, hi = n_runs;  // the last run that starts at or before item i
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if ((int64_t)runs[mid].item <= i) lo = mid; else hi = mid;
+        }
+        const SweepRun r = runs[lo];
+        const uint32_t at = (r.bin + ((uint32_t)i - r.item)) * (uint32_t)per_bin + r.row;
+        place[i] = at;
+        item_at[at] = (uint32_t)i;
+    }
+}
+
+__global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t* __restrict__ p, int64_t n, uint32_t x)
+{
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = x;
+}
+
+// Rows and partial-sum slots of every bin, entries of every (bin, lane group), batches of every bin.  Each row's own entries
+// take the lane groups in turn: dealt by their place in the bin, the entries of two rows with the same neighbours alternate
+// and each row would end up in one lane group, one running sum.
+__global__ __launch_bounds__(256) void sweep_bins_kernel(const WorkItem* __restrict__ items, const uint32_t* __restrict__ item_at,
+                                                         int64_t n_bins, int per_bin, uint32_t groups, uint32_t batch_len,
+                                                         int2* __restrict__ rows, uint32_t* __restrict__ list_len,
+                                                         uint32_t* __restrict__ batches)
+{
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < n_bins; b += stride) {
+        for (uint32_t g = 0; g < groups; ++g) list_len[b * groups + g] = 0;
+        for (int r = 0; r < per_bin; ++r) {
+            const uint32_t i = item_at[b * per_bin + r];
+            const WorkItem it = i != 0xFFFFFFFFu ? items[i] : WorkItem{-1, 0, 0, -1};
+            rows[b * per_bin + r] = make_int2(it.row, it.slot);
+            const uint32_t len = (uint32_t)(it.end - it.begin);
+            for (uint32_t j = 0; j < groups; ++j)  // entries j, j + groups, ... of the row
+                list_len[b * groups + (j + (uint32_t)r) % groups] += (len + groups - 1 - j) / groups;
+        }
+        uint32_t longest = 0;
+        for (uint32_t g = 0; g < groups; ++g) longest = max(longest, list_len[b * groups + g]);
+        batches[b] = (longest + batch_len - 1) / batch_len;
+    }
+}
+
 // key[p] = (bin, lane group) << 32 | source node, payload[p] = p, row_of[p] = row of the bin, for the entries of every work
-// item.  Each row's own entries take the lane groups in turn: dealt by their place in the bin, the entries of two rows with the
-// same neighbours alternate and each row would end up in one lane group, one running sum.
-// Workgroups stride over the items: one each would be 2^32 threads, more than a launch holds, from 2^24 items up.
+// item.  Workgroups stride over the items: one each would be 2^32 threads, more than a launch holds, from 2^24 items up.
 __global__ __launch_bounds__(256) void sweep_keys_kernel(const WorkItem* __restrict__ items, const uint32_t* __restrict__ place,
-                                                         int64_t n_items, int per_bin, uint32_t groups,
-                                                         const int32_t* __restrict__ col, uint64_t* __restrict__ key, uint32_t* __restrict__ entry,
-                                                         uint8_t* __restrict__ row_of)
+                                                         int64_t n_items, uint32_t per_bin, uint32_t groups,
+                                                         const int32_t* __restrict__ col, uint64_t* __restrict__ key,
+                                                         uint32_t* __restrict__ entry, uint8_t* __restrict__ row_of)
 {
     for (int64_t i = blockIdx.x; i < n_items; i += gridDim.x) {
         const WorkItem it = items[i];
-        const uint32_t bin = place[i] / (uint32_t)per_bin, row = place[i] % (uint32_t)per_bin;
+        const uint32_t row = place[i] % per_bin;
+        const uint64_t bin = place[i] / per_bin;
         for (int p = it.begin + (int)threadIdx.x; p < it.end; p += blockDim.x) {
-            key[p] = ((uint64_t)bin * groups + ((uint32_t)(p - it.begin) + row) % groups) << 32 | (uint32_t)col[p];
+            key[p] = (bin * groups + ((uint32_t)(p - it.begin) + row) % groups) << 32 | (uint32_t)col[p];
             entry[p] = (uint32_t)p;
             row_of[p] = (uint8_t)row;
         }
@@ -664,87 +745,79 @@ __global__ __launch_bounds__(256) void sweep_entries_kernel(const uint64_t* __re
     }
 }
 
-// Deals the work items to bins (longest first, each to the bin with the fewest entries so far that has a row left) and
-// lays the entries out.  Synchronises the device.
+// Deals the work items to bins and lays their entries out.  Synchronises the device.
 maxk_status build_sweep(maxk_graph* g, SweepSet& W, int groups, int batch_len, int per_bin)
 {
     MAXK_HIP_TRY(hipDeviceSynchronize());
-    const int64_t n_items = g->csr_items.n_items, nnz = g->nnz, n_bins = (n_items + per_bin - 1) / per_bin;
-    std::vector<WorkItem> items((size_t)n_items);
-    MAXK_HIP_TRY(hipMemcpy(items.data(), g->csr_items.d_items, sizeof(WorkItem) * (size_t)n_items, hipMemcpyDeviceToHost));
-    std::vector<uint32_t> place((size_t)n_items), load((size_t)n_bins, 0), batch((size_t)n_bins + 1, 0);
-    std::vector<uint32_t> first((size_t)n_bins * groups, 0);  // entries of every (bin, lane group), then its first one
-    std::vector<int2> rows((size_t)(n_bins * per_bin), make_int2(-1, -1));
-    {
-        std::vector<uint8_t> used((size_t)n_bins, 0);
-        using slot = std::pair<uint32_t, uint32_t>;  // entries so far, bin
-        std::priority_queue<slot, std::vector<slot>, std::greater<slot>> open;
-        for (int64_t i = 0; i < n_bins; ++i) open.push({0u, (uint32_t)i});
-        for (int64_t i = 0; i < n_items; ++i) {
-            const uint32_t b = open.top().second;
-            open.pop();
-            place[(size_t)i] = b * (uint32_t)per_bin + used[b];
-            rows[(size_t)place[(size_t)i]] = make_int2(items[(size_t)i].row, items[(size_t)i].slot);
-            const uint32_t len = (uint32_t)(items[(size_t)i].end - items[(size_t)i].begin);
-            load[b] += len;
-            for (uint32_t j = 0; j < (uint32_t)groups; ++j)  // entries j, j + groups, ... of the row
-                first[(size_t)b * groups + (j + used[b]) % groups] += (len + (uint32_t)groups - 1 - j) / (uint32_t)groups;
-            if (++used[b] < per_bin) open.push({load[b], b});
-        }
-    }
-    uint32_t run = 0;
-    for (int64_t b = 0; b < n_bins; ++b) {
-        uint32_t longest = 0;
-        for (int l = 0; l < groups; ++l) {
-            uint32_t& f = first[(size_t)b * groups + l];
-            longest = std::max(longest, f);
-            run += std::exchange(f, run);
-        }
-        const uint64_t next = (uint64_t)batch[(size_t)b] + (longest + (uint32_t)batch_len - 1) / (uint32_t)batch_len;
-        if (next > 0x7FFFFFFFull) return MAXK_UNSUPPORTED;
-        batch[(size_t)b + 1] = (uint32_t)next;
-    }
+    const int64_t n_items = g->csr_items.n_items, nnz = g->nnz, n_bins = (n_items + per_bin - 1) / per_bin, n_lists = n_bins * groups;
+    std::vector<SweepRun> runs;
+    sweep_deal(g->csr_lengths, n_bins, per_bin, runs);
     hipStream_t s = nullptr;
     uint64_t *d_key = nullptr, *d_key_sorted = nullptr;
-    uint32_t *d_entry = nullptr, *d_perm = nullptr, *d_place = nullptr, *d_first = nullptr;
+    uint32_t *d_entry = nullptr, *d_perm = nullptr, *d_list_len = nullptr, *d_list_first = nullptr, *d_batches = nullptr,
+             *d_place = nullptr, *d_item_at = nullptr;
+    SweepRun* d_runs = nullptr;
     uint8_t* d_row_of = nullptr;
     void* d_tmp = nullptr;
     auto cleanup = [&]() {
         (void)hipFree(d_key); (void)hipFree(d_key_sorted); (void)hipFree(d_entry); (void)hipFree(d_perm);
-        (void)hipFree(d_place); (void)hipFree(d_first); (void)hipFree(d_row_of); (void)hipFree(d_tmp);
+        (void)hipFree(d_list_len); (void)hipFree(d_list_first); (void)hipFree(d_batches); (void)hipFree(d_row_of); (void)hipFree(d_tmp);
+        (void)hipFree(d_place); (void)hipFree(d_item_at); (void)hipFree(d_runs);
     };
 #define MAXK_TRY_CLEAN(expr)                                                           \
     do {                                                                               \
         hipError_t _e = (expr);                                                        \
         if (_e != hipSuccess) { cleanup(); free_sweep(W); return hip_fail(_e); }       \
     } while (0)
-    const int64_t n_ent = (int64_t)batch[(size_t)n_bins] * groups * batch_len;
+    // (fewer than 2^31 / 8 + 2 * 2^26 batches: a bin has at most one more than its entries fill)
+    MAXK_TRY_CLEAN(hipMalloc((void**)&W.d_batch, sizeof(uint32_t) * (size_t)(n_bins + 1)));
+    MAXK_TRY_CLEAN(hipMalloc((void**)&W.d_rows, sizeof(int2) * (size_t)(n_bins * per_bin)));
+    MAXK_TRY_CLEAN(hipMalloc((void**)&d_batches, sizeof(uint32_t) * (size_t)(n_bins + 1)));
+    MAXK_TRY_CLEAN(hipMalloc((void**)&d_list_len, sizeof(uint32_t) * (size_t)n_lists));
+    MAXK_TRY_CLEAN(hipMalloc((void**)&d_list_first, sizeof(uint32_t) * (size_t)n_lists));
+    MAXK_TRY_CLEAN(hipMalloc((void**)&d_place, sizeof(uint32_t) * (size_t)n_items));
+    MAXK_TRY_CLEAN(hipMalloc((void**)&d_item_at, sizeof(uint32_t) * (size_t)(n_bins * per_bin)));
+    MAXK_TRY_CLEAN(hipMalloc((void**)&d_runs, sizeof(SweepRun) * runs.size()));
+    MAXK_TRY_CLEAN(hipMemcpy(d_runs, runs.data(), sizeof(SweepRun) * runs.size(), hipMemcpyHostToDevice));
+    size_t tmp_bytes = 0, scan_bytes = 0;
+    MAXK_TRY_CLEAN(rocprim::exclusive_scan(nullptr, tmp_bytes, d_batches, W.d_batch, 0u, (size_t)(n_bins + 1), rocprim::plus<uint32_t>(), s));
+    MAXK_TRY_CLEAN(rocprim::exclusive_scan(nullptr, scan_bytes, d_list_len, d_list_first, 0u, (size_t)n_lists, rocprim::plus<uint32_t>(), s));
+    tmp_bytes = std::max<size_t>({tmp_bytes, scan_bytes, 16});
+    MAXK_TRY_CLEAN(hipMalloc(&d_tmp, tmp_bytes));
+    const dim3 bin_blocks((unsigned)std::min<int64_t>((n_bins + 255) / 256, 65536));
+    hipLaunchKernelGGL(fill_u32_kernel, bin_blocks, dim3(256), 0, s, d_item_at, n_bins * per_bin, 0xFFFFFFFFu);
+    hipLaunchKernelGGL(sweep_places_kernel, bin_blocks, dim3(256), 0, s, d_runs, (int)runs.size(), n_items, per_bin, d_place, d_item_at);
+    MAXK_TRY_CLEAN(hipGetLastError());
+    hipLaunchKernelGGL(sweep_bins_kernel, bin_blocks, dim3(256), 0, s, g->csr_items.d_items, d_item_at, n_bins, per_bin,
+                       (uint32_t)groups, (uint32_t)batch_len, W.d_rows, d_list_len, d_batches);
+    MAXK_TRY_CLEAN(hipGetLastError());
+    scan_bytes = tmp_bytes;
+    MAXK_TRY_CLEAN(rocprim::exclusive_scan(d_tmp, scan_bytes, d_batches, W.d_batch, 0u, (size_t)(n_bins + 1), rocprim::plus<uint32_t>(), s));
+    scan_bytes = tmp_bytes;
+    MAXK_TRY_CLEAN(rocprim::exclusive_scan(d_tmp, scan_bytes, d_list_len, d_list_first, 0u, (size_t)n_lists, rocprim::plus<uint32_t>(), s));
+    uint32_t n_batches = 0;
+    MAXK_TRY_CLEAN(hipMemcpyAsync(&n_batches, W.d_batch + n_bins, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    MAXK_TRY_CLEAN(hipStreamSynchronize(s));
+    (void)hipFree(d_tmp); d_tmp = nullptr;
+    const int64_t n_ent = (int64_t)n_batches * groups * batch_len;
     MAXK_TRY_CLEAN(hipMalloc((void**)&W.d_ent, sizeof(int2) * (size_t)std::max<int64_t>(n_ent, 1)));
-    MAXK_TRY_CLEAN(hipMalloc((void**)&W.d_batch, sizeof(uint32_t) * batch.size()));
-    MAXK_TRY_CLEAN(hipMalloc((void**)&W.d_rows, sizeof(int2) * rows.size()));
     MAXK_TRY_CLEAN(hipMalloc((void**)&d_key, sizeof(uint64_t) * (size_t)nnz));
     MAXK_TRY_CLEAN(hipMalloc((void**)&d_key_sorted, sizeof(uint64_t) * (size_t)nnz));
     MAXK_TRY_CLEAN(hipMalloc((void**)&d_entry, sizeof(uint32_t) * (size_t)nnz));
     MAXK_TRY_CLEAN(hipMalloc((void**)&d_perm, sizeof(uint32_t) * (size_t)nnz));
-    MAXK_TRY_CLEAN(hipMalloc((void**)&d_place, sizeof(uint32_t) * place.size()));
-    MAXK_TRY_CLEAN(hipMalloc((void**)&d_first, sizeof(uint32_t) * first.size()));
     MAXK_TRY_CLEAN(hipMalloc((void**)&d_row_of, (size_t)nnz));
-    MAXK_TRY_CLEAN(hipMemcpy(W.d_batch, batch.data(), sizeof(uint32_t) * batch.size(), hipMemcpyHostToDevice));
-    MAXK_TRY_CLEAN(hipMemcpy(W.d_rows, rows.data(), sizeof(int2) * rows.size(), hipMemcpyHostToDevice));
-    MAXK_TRY_CLEAN(hipMemcpy(d_place, place.data(), sizeof(uint32_t) * place.size(), hipMemcpyHostToDevice));
-    MAXK_TRY_CLEAN(hipMemcpy(d_first, first.data(), sizeof(uint32_t) * first.size(), hipMemcpyHostToDevice));
     const unsigned blocks = (unsigned)std::min<int64_t>((nnz + 255) / 256, 65536);
     hipLaunchKernelGGL(sweep_keys_kernel, dim3((unsigned)std::min<int64_t>(n_items, 1 << 20)), dim3(256), 0, s,
-                       g->csr_items.d_items, d_place, n_items, per_bin, (uint32_t)groups, g->d_col, d_key, d_entry, d_row_of);
+                       g->csr_items.d_items, d_place, n_items, (uint32_t)per_bin, (uint32_t)groups, g->d_col, d_key, d_entry, d_row_of);
     MAXK_TRY_CLEAN(hipGetLastError());
     int end_bit = 33;
-    while (end_bit < 64 && ((uint64_t)1 << (end_bit - 32)) < (uint64_t)n_bins * groups) ++end_bit;
-    size_t tmp_bytes = 0;
+    while (end_bit < 64 && ((uint64_t)1 << (end_bit - 32)) < (uint64_t)n_lists) ++end_bit;
+    tmp_bytes = 0;
     MAXK_TRY_CLEAN(rocprim::radix_sort_pairs(nullptr, tmp_bytes, d_key, d_key_sorted, d_entry, d_perm, (size_t)nnz, 0, (unsigned)end_bit, s));
     MAXK_TRY_CLEAN(hipMalloc(&d_tmp, tmp_bytes ? tmp_bytes : 16));
     MAXK_TRY_CLEAN(rocprim::radix_sort_pairs(d_tmp, tmp_bytes, d_key, d_key_sorted, d_entry, d_perm, (size_t)nnz, 0, (unsigned)end_bit, s));
     hipLaunchKernelGGL(sweep_fill_kernel, dim3(blocks), dim3(256), 0, s, W.d_ent, n_ent);
-    hipLaunchKernelGGL(sweep_entries_kernel, dim3(blocks), dim3(256), 0, s, d_key_sorted, d_perm, d_row_of, g->d_val, nnz, d_first,
+    hipLaunchKernelGGL(sweep_entries_kernel, dim3(blocks), dim3(256), 0, s, d_key_sorted, d_perm, d_row_of, g->d_val, nnz, d_list_first,
                        W.d_batch, (uint32_t)groups, (uint32_t)batch_len, W.d_ent);
     MAXK_TRY_CLEAN(hipGetLastError());
     MAXK_TRY_CLEAN(hipStreamSynchronize(s));
@@ -1148,6 +1221,11 @@ MAXK_API maxk_status maxk_graph_create(maxk_graph** out, int64_t N, int64_t nnz,
         int64_t n_slots = 0, max_len = 0;
         build_items(h_rowptr, N, g->chunk, items, split, n_slots, max_len);
         g->max_degree = max_len;
+        for (const WorkItem& w : items) {
+            const int32_t len = w.end - w.begin;
+            if (g->csr_lengths.empty() || g->csr_lengths.back().first != len) g->csr_lengths.emplace_back(len, 0);
+            ++g->csr_lengths.back().second;
+        }
         hot_source_shares(h_rowptr, N, nnz, g->hot_share);
         st = upload_items(items, split, n_slots, g->csr_items, s);
         if (st != MAXK_OK) goto fail;
