@@ -975,3 +975,80 @@ def test_forward_shares_a_row_out_over_its_lane_groups(monkeypatch, sweep, k):
     lost, G = 2.0 ** 24 + (n - 1) - got, 64 // k
     assert lost.min() >= -(G - 1) and lost.max() <= -(-n // G) + G - 1, (lost.min(), lost.max())
     gr.destroy()
+
+
+# ------------------------------------------------------------------ which path a call took
+
+
+@pytest.mark.parametrize("k", [8, 32, 64])
+def test_sweep_tables_are_shared_and_built_once(monkeypatch, k):
+    monkeypatch.setenv("MAXK_FWD_SWEEP", "2")
+    N, dim = 900, 200
+    g, _, gr, sp_data, sp_index = _aggregation_case(N, 9000, dim, k, 131)
+    _forward(g, gr, sp_data, sp_index, dim)
+    assert gr.sweep_tables() == 1
+    Y = torch.full((N, dim), float("nan"), device="cuda")
+    maxk.maxk_spgemm_fwd_noalloc(gr, sp_data, sp_index, dim, Y)
+    ref, refabs = oracle.spgemm_fwd(g.rowptr, g.col, g.val, sp_data.cpu().numpy(), index_to_numpy(sp_index), dim)
+    assert (np.abs(Y.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all()
+    gr.reserve(512, k)  # other widths walk the same table
+    _forward(g, gr, sp_data, sp_index, dim + 7)
+    assert gr.sweep_tables() == 1
+    fresh = _aggregation_case(N, 9000, dim, k, 131)[2]
+    maxk.maxk_spgemm_fwd_noalloc(fresh, sp_data, sp_index, dim, Y)
+    assert fresh.sweep_tables() == 0  # that entry point builds nothing
+    monkeypatch.setenv("MAXK_FWD_SWEEP", "1")
+    rows = _aggregation_case(N, 9000, dim, k, 131)[2]
+    _forward(g, rows, sp_data, sp_index, dim)
+    assert rows.sweep_tables() == 0
+    for h in (gr, fresh, rows):
+        h.destroy()
+
+
+@pytest.mark.parametrize("k,tables", [(32, 1), (64, 0)])
+def test_forward_sweep_in_a_captured_graph(monkeypatch, k, tables):
+    # reserved, the captured call walks the table; at a k that nobody reserved it builds nothing and runs row by row
+    monkeypatch.setenv("MAXK_FWD_SWEEP", "2")
+    N, dim = 900, 128
+    g, _, gr, sp_data, sp_index = _aggregation_case(N, 9000, dim, k, 141)
+    if tables:
+        gr.reserve(dim, k)
+    Y = torch.empty((N, dim), device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        maxk.maxk_spgemm_fwd(gr, sp_data, sp_index, dim, Y)
+    assert gr.sweep_tables() == tables
+    idx = index_to_numpy(sp_index)
+    for rep in range(3):
+        sp_data.mul_(0.5 + rep)
+        Y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        ref, refabs = oracle.spgemm_fwd(g.rowptr, g.col, g.val, sp_data.cpu().numpy(), idx, dim)
+        assert (np.abs(Y.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all()
+    gr.destroy()
+
+
+@pytest.mark.parametrize("N,dim", [(3_000_000, 256), (17_000_000, 20)])
+def test_column_sliced_pull_with_offsets_above_2_gib(_sliced_form, N, dim):
+    # dY itself (2.9 GiB, gathered in place) and its slice-major copy (2.0 GiB) through 32-bit offsets.  Whole numbers below
+    # 2^24, so every order of the sums gives the same bits
+    k, gen = 8, torch.Generator(device="cuda").manual_seed(9)
+    rows = torch.sort(torch.randint(N, (N // 2,), generator=gen, device="cuda")).values
+    rows[-200_000:] = torch.arange(N - 200_000, N, device="cuda")  # the highest offsets
+    rows = torch.sort(rows).values
+    rowptr = torch.zeros(N + 1, dtype=torch.int32, device="cuda")
+    rowptr[1:] = torch.cumsum(torch.bincount(rows, minlength=N), 0)
+    col = torch.randint(N, rows.shape, generator=gen, device="cuda", dtype=torch.int32)
+    val = torch.randint(-3, 4, rows.shape, generator=gen, device="cuda").float()
+    dY = torch.randint(-5, 6, (N, dim), generator=gen, device="cuda", dtype=torch.int8).float()
+    at = torch.arange(k, device="cuda") * (dim // k)
+    sp_index = at.to(torch.uint8).repeat(N, 1)
+    gr = maxk.maxk_graph_create(rowptr, col, val)
+    gr.set_bwd_mode(maxk.BWD_PULL_CSC)
+    dXs = torch.full((N, k), float("nan"), device="cuda")
+    maxk.maxk_sspmm_bwd(gr, dY, sp_index, dXs)
+    want = torch.zeros_like(dXs).index_add_(0, col.long(), dY[:, at][rows] * val[:, None])
+    assert torch.equal(dXs, want)
+    gr.destroy()
