@@ -390,9 +390,11 @@ maxk_status launch_sweep(const SweepSet& S, const value_store_t<VT>* sp_data, co
         case 8: MAXK_FWD_SWEEP(8); break;
         case 16: MAXK_FWD_SWEEP(16); break;
         case 32: MAXK_FWD_SWEEP(32); break;
-        case 64: MAXK_FWD_SWEEP(64); break;
-        case 128: MAXK_FWD_SWEEP(128); break;
-        default: return MAXK_UNSUPPORTED;
+        default:
+            if constexpr (PACKED) return MAXK_UNSUPPORTED;
+            else if (k == 64) MAXK_FWD_SWEEP(64);
+            else if (k == 128) MAXK_FWD_SWEEP(128);
+            else return MAXK_UNSUPPORTED;
     }
 #undef MAXK_FWD_SWEEP
     MAXK_LAUNCH_CHECK();
@@ -403,7 +405,8 @@ template <int VT, typename IdxT>
 maxk_status launch_sweep_i(const SweepSet& S, const value_store_t<VT>* sp_data, const IdxT* sp_index, int64_t N, char* packed,
                            int dim, int k, float* Y, float* partials, hipStream_t s)
 {
-    if (!packed) return launch_sweep<false, VT>(S, sp_data, sp_index, nullptr, 0, 0, dim, k, Y, partials, s);
+    // (a CBSR row of 64 positions is whole cache lines in both arrays: nothing to gain from a record, whatever the knob says)
+    if (!packed || k >= kWave) return launch_sweep<false, VT>(S, sp_data, sp_index, nullptr, 0, 0, dim, k, Y, partials, s);
     const int vb = (int)sizeof(value_store_t<VT>);
     const int rec_bytes = fwd_packed_record_bytes(k, (int)sizeof(IdxT), vb), idx_off = fwd_packed_index_offset(k, (int)sizeof(IdxT), vb);
     const int64_t n_units = N * (int64_t)k;

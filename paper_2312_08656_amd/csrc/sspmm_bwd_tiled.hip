@@ -736,9 +736,6 @@ void free_tiled(TiledSet& T)
     T = TiledSet();
 }
 
-// Destination-set size for (N, dim, k): as many nodes as LDS holds accumulators for beside two row buffers, rounded
-// so that the number of sets is a power of two (the 32 CUs of an XCD then hold whole groups of sets).  Tiles of 16
-// rows: taller ones (32, 48 rows, with correspondingly smaller sets) were measured slower at every k.
 // An XCD holds G destination sets and runs 32 workgroups at a time; the source rows are cut into R ranges so that
 // its G * R workgroups fill whole rounds of 32 (as nearly as a small R allows).
 void tiled_ranges(int n_dsets, int n_tiles, int& G, int& R, int& tiles_per_range)
@@ -756,6 +753,9 @@ void tiled_ranges(int n_dsets, int n_tiles, int& G, int& R, int& tiles_per_range
     R = (n_tiles + tiles_per_range - 1) / tiles_per_range;
 }
 
+// Destination-set size for (N, dim, k): as many nodes as LDS holds accumulators for beside two row buffers, rounded
+// so that the number of sets is a power of two (the 32 CUs of an XCD then hold whole groups of sets).  Tiles of 16
+// rows: taller ones (32, 48 rows, with correspondingly smaller sets) were measured slower at every k.
 bool tiled_shape(int64_t N, int dim, int k, TiledShape& sh)
 {
     if (N < 1 || k % 4 != 0 || k < 4 || k > 256 || dim % 4 != 0 || dim > 512) return false;
