@@ -883,13 +883,19 @@ bool fwd_uses_packed(const maxk_graph* g, int k, int index_bytes, int val_bytes)
 
 // Rows of a bin of the forward sweep for MaxK k, 0 where the row-by-row kernel is taken.  The sweep pays when the CBSR is
 // several times an L2, the bins fill the chip (256 CUs x 32 wavefronts), the rows in LDS leave enough wavefronts a CU, and
-// a bin has enough entries for its padding to whole batches and its copies of the rows.  us, row by row / sweep:
-//   CBSR size: k = 32, 100 k nodes (16 MB) 212 / 185, 40 k (6 MB) 60 / 62; k = 64, 100 k (32 MB) 377 / 345, 40 k (13 MB)
-//     273 / 287, bf16 values 100 k (19 MB) 825 / 872
+// a bin has enough entries for its padding to whole batches and its copies of the rows.  The lines are drawn by k where both
+// sides were measured, over 16 graphs (profiles/forward_sweep_rule_over_graphs.txt: the kernel taken is 0.7 % above the
+// better one on average, row by row 3.7 %); us, row by row / sweep:
+//   CBSR size: k = 32, 100 k nodes (16 MB) 212 / 185, 40 k (6 MB) 60 / 62; k = 64, 100 k (32 MB) 366 / 333, 40 k (13 MB)
+//     277 / 283, bf16 values 100 k (19 MB) 825 / 860 and 320 / 307; k = 128, 40 k (26 MB) 540 / 438 and 178 / 163
 //   entries a lane group: k = 16, 123 1563 / 1303, 75 323 / 325, 19 828 / 924; k = 8, 62 1310 / 1161, 38 258 / 275; k = 32,
 //     101 618 / 583, 31 231 / 237
-//   width: k = 64, dim 400 706 / 685, dim 512 397 / 468; k = 128, dim 512 855 / 723
-// Rows of a bin: k = 64, 3 / 4 / 5 rows 3541 / 3175 / 4010 us; k = 32, 1 / 2 2211 / 2085; k = 16, 1 / 2 1303 / 1369.
+//   width: k = 16, dim 400 334 / 360; k = 32, dim 400 468 / 448, dim 512 238 / 276; k = 64, dim 400 710 / 666, dim 512
+//     388 / 442; k = 128, dim 512 841 / 724
+// Rows of a bin, us: k = 64, 3 / 4 / 5 rows 3541 / 3175 / 4010 (dense workload); k = 32, 1 / 2 / 3 rows 2211 / 2085 / 1922
+// there, 1312 / 1282 / 1326 on 79 M entries and 132 k nodes, 1 / 2 / 4 rows 1425 / 1336 / 1264 on 43 M and 576 k: two are ahead of
+// one on each, three and four are faster where the rows are long resp. the nodes many; k = 16, 1 / 2 1303 / 1369 (dense),
+// 805 / 917 (79 M), 924 / 825 (43 M, below the entries line: row by row 828).
 int sweep_rows(const maxk_graph* g, int dim, int k, int index_bytes, int val_bytes)
 {
     if ((k & (k - 1)) != 0 || k < 8 || k > 128 || dim > 512 || g->N > (1 << kSweepRowShift) || g->nnz == 0 || g->fwd_sweep == 1)
@@ -1037,7 +1043,8 @@ PullCost pull_cost(const maxk_graph* g, int dim, int k, int val_bytes, const voi
 // Backward kernel choice when the caller leaves it to the library: the lowest of five cost models, fitted on MI355X to
 // 153 shapes (R-MAT and uniform graphs of 4 thousand to 1 million nodes, average degree 12 to 400; widths 64 to 512;
 // k 8 to 128; fp32 and 16-bit dY) and the benchmark graphs.  Over those shapes the chosen kernel takes 6 % longer than
-// the best one on average (79 % with the rule before, which looked at entries per slab visit only).
+// the best one on average (profiles/backward_choice_over_shapes.txt; the largest misses, 2.2 times, are 16-bit dY on
+// 60 k nodes of degree 240, where hub visits end the launches of slab pull later than the model has it).
 // Times in seconds; `lines` = 128-byte lines of a dY row that an entry's k columns touch.
 int auto_bwd_mode(const maxk_graph* g, int dim, int k, int val_bytes = 4, bool tiled_ok = true)
 {
