@@ -680,10 +680,29 @@ __global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t* __restrict__ p,
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = x;
 }
 
+// The entries that a sweep gives a work item: first, first + stride, ...  A piece of a split row takes every n-th entry of the
+// row and not a run of them: a run covers a part of the source nodes only, and its bin would be ahead of or behind the others
+// on their way over them all along.  us, runs / every n-th: 115 M entries on 233 k nodes k = 32 2059 / 2020, k = 64
+// 3149 / 2979, k = 128 6811 / 6022; 43 M on 576 k k = 64 2060 / 1918; 126 M on 2.4 M k = 64 4838 / 4561.
+struct SweepItem { int32_t first, stride, count; };
+__device__ SweepItem sweep_item(const WorkItem it, const SplitRow* __restrict__ split, int n_split, const int32_t* __restrict__ ptr)
+{
+    if (it.slot < 0) return {it.begin, 1, it.end - it.begin};
+    int lo = 0, hi = n_split;  // the last split row that starts at or before the slot
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (split[mid].slot_begin <= it.slot) lo = mid; else hi = mid;
+    }
+    const int32_t pieces = split[lo].slot_count, piece = it.slot - split[lo].slot_begin, begin = ptr[it.row];
+    return {begin + piece, pieces, (ptr[it.row + 1] - begin - piece + pieces - 1) / pieces};
+}
+
 // Rows and partial-sum slots of every bin, entries of every (bin, lane group), batches of every bin.  Each row's own entries
 // take the lane groups in turn: dealt by their place in the bin, the entries of two rows with the same neighbours alternate
 // and each row would end up in one lane group, one running sum.
-__global__ __launch_bounds__(256) void sweep_bins_kernel(const WorkItem* __restrict__ items, const uint32_t* __restrict__ item_at,
+__global__ __launch_bounds__(256) void sweep_bins_kernel(const WorkItem* __restrict__ items, const SplitRow* __restrict__ split,
+                                                         int n_split, const int32_t* __restrict__ ptr,
+                                                         const uint32_t* __restrict__ item_at,
                                                          int64_t n_bins, int per_bin, uint32_t groups, uint32_t batch_len,
                                                          int2* __restrict__ rows, uint32_t* __restrict__ list_len,
                                                          uint32_t* __restrict__ batches)
@@ -695,7 +714,7 @@ __global__ __launch_bounds__(256) void sweep_bins_kernel(const WorkItem* __restr
             const uint32_t i = item_at[b * per_bin + r];
             const WorkItem it = i != 0xFFFFFFFFu ? items[i] : WorkItem{-1, 0, 0, -1};
             rows[b * per_bin + r] = make_int2(it.row, it.slot);
-            const uint32_t len = (uint32_t)(it.end - it.begin);
+            const uint32_t len = (uint32_t)sweep_item(it, split, n_split, ptr).count;
             for (uint32_t j = 0; j < groups; ++j)  // entries j, j + groups, ... of the row
                 list_len[b * groups + (j + (uint32_t)r) % groups] += (len + groups - 1 - j) / groups;
         }
@@ -707,17 +726,20 @@ __global__ __launch_bounds__(256) void sweep_bins_kernel(const WorkItem* __restr
 
 // key[p] = (bin, lane group) << 32 | source node, payload[p] = p, row_of[p] = row of the bin, for the entries of every work
 // item.  Workgroups stride over the items: one each would be 2^32 threads, more than a launch holds, from 2^24 items up.
-__global__ __launch_bounds__(256) void sweep_keys_kernel(const WorkItem* __restrict__ items, const uint32_t* __restrict__ place,
+__global__ __launch_bounds__(256) void sweep_keys_kernel(const WorkItem* __restrict__ items, const SplitRow* __restrict__ split,
+                                                         int n_split, const int32_t* __restrict__ ptr,
+                                                         const uint32_t* __restrict__ place,
                                                          int64_t n_items, uint32_t per_bin, uint32_t groups,
                                                          const int32_t* __restrict__ col, uint64_t* __restrict__ key,
                                                          uint32_t* __restrict__ entry, uint8_t* __restrict__ row_of)
 {
     for (int64_t i = blockIdx.x; i < n_items; i += gridDim.x) {
-        const WorkItem it = items[i];
+        const SweepItem it = sweep_item(items[i], split, n_split, ptr);
         const uint32_t row = place[i] % per_bin;
         const uint64_t bin = place[i] / per_bin;
-        for (int p = it.begin + (int)threadIdx.x; p < it.end; p += blockDim.x) {
-            key[p] = (bin * groups + ((uint32_t)(p - it.begin) + row) % groups) << 32 | (uint32_t)col[p];
+        for (int e = (int)threadIdx.x; e < it.count; e += blockDim.x) {
+            const int64_t p = it.first + (int64_t)e * it.stride;
+            key[p] = (bin * groups + ((uint32_t)e + row) % groups) << 32 | (uint32_t)col[p];
             entry[p] = (uint32_t)p;
             row_of[p] = (uint8_t)row;
         }
@@ -788,8 +810,8 @@ maxk_status build_sweep(maxk_graph* g, SweepSet& W, int groups, int batch_len, i
     hipLaunchKernelGGL(fill_u32_kernel, bin_blocks, dim3(256), 0, s, d_item_at, n_bins * per_bin, 0xFFFFFFFFu);
     hipLaunchKernelGGL(sweep_places_kernel, bin_blocks, dim3(256), 0, s, d_runs, (int)runs.size(), n_items, per_bin, d_place, d_item_at);
     MAXK_TRY_CLEAN(hipGetLastError());
-    hipLaunchKernelGGL(sweep_bins_kernel, bin_blocks, dim3(256), 0, s, g->csr_items.d_items, d_item_at, n_bins, per_bin,
-                       (uint32_t)groups, (uint32_t)batch_len, W.d_rows, d_list_len, d_batches);
+    hipLaunchKernelGGL(sweep_bins_kernel, bin_blocks, dim3(256), 0, s, g->csr_items.d_items, g->csr_items.d_split,
+                       (int)g->csr_items.n_split, g->d_rowptr, d_item_at, n_bins, per_bin, (uint32_t)groups, (uint32_t)batch_len, W.d_rows, d_list_len, d_batches);
     MAXK_TRY_CLEAN(hipGetLastError());
     scan_bytes = tmp_bytes;
     MAXK_TRY_CLEAN(rocprim::exclusive_scan(d_tmp, scan_bytes, d_batches, W.d_batch, 0u, (size_t)(n_bins + 1), rocprim::plus<uint32_t>(), s));
@@ -808,7 +830,8 @@ maxk_status build_sweep(maxk_graph* g, SweepSet& W, int groups, int batch_len, i
     MAXK_TRY_CLEAN(hipMalloc((void**)&d_row_of, (size_t)nnz));
     const unsigned blocks = (unsigned)std::min<int64_t>((nnz + 255) / 256, 65536);
     hipLaunchKernelGGL(sweep_keys_kernel, dim3((unsigned)std::min<int64_t>(n_items, 1 << 20)), dim3(256), 0, s,
-                       g->csr_items.d_items, d_place, n_items, (uint32_t)per_bin, (uint32_t)groups, g->d_col, d_key, d_entry, d_row_of);
+                       g->csr_items.d_items, g->csr_items.d_split, (int)g->csr_items.n_split, g->d_rowptr, d_place, n_items,
+                       (uint32_t)per_bin, (uint32_t)groups, g->d_col, d_key, d_entry, d_row_of);
     MAXK_TRY_CLEAN(hipGetLastError());
     int end_bit = 33;
     while (end_bit < 64 && ((uint64_t)1 << (end_bit - 32)) < (uint64_t)n_lists) ++end_bit;
