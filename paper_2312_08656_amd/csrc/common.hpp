@@ -10,6 +10,24 @@ namespace maxk {
 
 constexpr int kWave = 64;  // CDNA wavefront width
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Streams that a kernel reads or writes once pass by the L2's replacement order, so that the records it gathers stay.
+__device__ __forceinline__ void store_once(float* p, float4 x)
+{
+    __builtin_nontemporal_store(f32x4{x.x, x.y, x.z, x.w}, reinterpret_cast<f32x4*>(p));
+}
+__device__ __forceinline__ float4 load_once(const float4* p)
+{
+    const f32x4 x = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
+    return make_float4(x.x, x.y, x.z, x.w);
+}
+__device__ __forceinline__ int2 load_once(const int2* p)  // 8 bytes, aligned
+{
+    const uint64_t x = __builtin_nontemporal_load(reinterpret_cast<const uint64_t*>(p));
+    return make_int2((int)(uint32_t)x, (int)(uint32_t)(x >> 32));
+}
+
 // One unit of scheduled work: a contiguous run of stored entries of one row
 // (forward / push backward / dense SpMM) or of one column of A^T (pull backward).
 // The paper's "edge group" (Sec. 4.1), sized for a 64-wide wavefront.

@@ -375,6 +375,19 @@ def test_cbsr_scatter_is_exact(dim, k, ib):
     assert np.array_equal(dense.cpu().numpy().view(np.uint32), oracle.cbsr_scatter(vals, ri, dim).view(np.uint32))
 
 
+# rows per wavefront 1, 2 and 4 with a last wavefront that has fewer; 16-byte and 4-byte stores; k above a wavefront
+@pytest.mark.parametrize("N,dim,k,shift", [(1, 4, 4, 0), (5, 33, 32, 0), (16387, 36, 9, 0), (32771, 60, 7, 0), (32771, 60, 7, 1),
+                                           (32773, 61, 61, 0), (32770, 260, 130, 0), (9, 1024, 200, 0)])
+def test_cbsr_scatter_row_groups(N, dim, k, shift):
+    gen = torch.Generator(device="cuda").manual_seed(N + dim)
+    values = torch.randn(N, k, generator=gen, device="cuda")
+    index = torch.rand(N, dim, generator=gen, device="cuda").topk(k, dim=1).indices.sort(dim=1).values
+    buf = torch.full((N * dim + shift,), float("nan"), device="cuda")  # shift: `dense` not 16-byte aligned
+    dense = buf[shift:].view(N, dim)
+    maxk.maxk_cbsr_scatter(values, index.to(torch.int32), dense)
+    assert torch.equal(dense, torch.zeros(N, dim, device="cuda").scatter_(1, index, values))
+
+
 def test_autograd_function_matches_the_oracle_chain():
     name = "tiny_directed"
     g = synth.graph(name)
