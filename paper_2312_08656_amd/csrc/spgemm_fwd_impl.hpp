@@ -217,7 +217,7 @@ __global__ __launch_bounds__(kWave) void spgemm_fwd_rmw_kernel(const WorkItem* _
                 const float4 x = *reinterpret_cast<const float4*>(row_buf + b * cs + c);
                 acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
             }
-            *reinterpret_cast<float4*>(out + c) = acc;
+            store_once(out + c, acc);
         }
     } else {
         for (int c = lane; c < dim; c += kWave) {
@@ -245,6 +245,11 @@ __global__ __launch_bounds__(kWave) void spgemm_fwd_rmw_kernel(const WorkItem* _
 // Measured, us, kernel above / sweep: dense k = 8 1310 / 1161, k = 16 1563 / 1303, k = 32 2834 / 2085, k = 64 5200 / 3175,
 // k = 128 9276 / 6872, bf16 k = 64 3382 / 2985; 79 M entries on 132 k nodes k = 32 1572 / 1282; 43 M on 576 k k = 32
 // 1445 / 1336; 126 M on 2.4 M nodes k = 64 6181 / 4845.
+//
+// The entries are read once and Y is written once: both pass by L2's replacement order and leave its 4 MB to the records.
+// us, plain / so: 43 M entries on 577 k nodes k = 32 1311 / 1276; 115 M on 233 k k = 32 2078 / 2054, bf16 k = 64
+// 3449 / 3437; 126 M on 2.4 M k = 64 4650 / 4547.  Y of the kernel above: 14.7 M on 717 k, dim 384, k = 96 1169 / 1139; 79 M
+// on 133 k k = 8 692 / 682.
 constexpr int kSweepWaves = 16;            // wavefronts of a workgroup, at most
 constexpr size_t kSweepLds = 64 * 1024;    // LDS of a workgroup, at most: two of them on a CU
 constexpr uint32_t kSweepMeet = 8;         // batches between barriers (k = 32: 1996 / 2028 / 2098 us at 4 / 8 / 16, bf16
@@ -295,13 +300,13 @@ __global__ __launch_bounds__(kSweepWaves * kWave) void spgemm_fwd_sweep_kernel(
     const int own = lane / LANES * copy;
     constexpr int64_t kBatchEntries = GROUPS * BATCH;
     const int2* __restrict__ mine = ent + lane / LANES * BATCH + lane % BATCH;
-    int2 next = b0 < b1 ? mine[b0 * kBatchEntries] : make_int2(-1, 0);
+    int2 next = b0 < b1 ? load_once(mine + b0 * kBatchEntries) : make_int2(-1, 0);
     for (uint32_t i = 0; i < longest; ++i) {
         if (i % kSweepMeet == 0) __syncthreads();
         const uint32_t b = b0 + i;
         if (b >= b1) continue;  // wave-uniform
         const int2 cur = next;
-        if (b + 1 < b1) next = mine[(b + 1) * kBatchEntries];
+        if (b + 1 < b1) next = load_once(mine + (b + 1) * kBatchEntries);
         const auto steps = [&](auto first) {
             constexpr int F = decltype(first)::value;
             float d[8], w[8];
@@ -361,7 +366,7 @@ __global__ __launch_bounds__(kSweepWaves * kWave) void spgemm_fwd_sweep_kernel(
                     const float4 x = *reinterpret_cast<const float4*>(row + g * copy + c);
                     acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
                 }
-                *reinterpret_cast<float4*>(out + c) = acc;
+                store_once(out + c, acc);
             }
         } else {
             for (int c = lane; c < dim; c += kWave) {
