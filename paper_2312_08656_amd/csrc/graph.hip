@@ -11,6 +11,7 @@
 //     its work-item list, for the pull backward kernel;
 //   - one partial-sum workspace shared by all kernels of the handle.
 #include <algorithm>
+#include <bit>
 #include <array>
 #include <cmath>
 #include <cstdlib>
@@ -514,7 +515,7 @@ maxk_status build_slabs(maxk_graph* g, SlabSet& S, int32_t slab_rows)
     MAXK_TRY_CLEAN(hipStreamSynchronize(s));
     // long visits (hub destinations inside one slab): listed per slab on the host
     try {
-        std::vector<int32_t> h_begin((size_t)n_visits + 1), h_long;
+        std::vector<int32_t> h_begin((size_t)n_visits + 1), h_long, in_order;
         MAXK_TRY_CLEAN(hipMemcpy(h_begin.data(), S.d_visit_begin, sizeof(int32_t) * (size_t)(n_visits + 1),
                                  hipMemcpyDeviceToHost));
         S.h_slab_long = (int64_t*)std::calloc((size_t)n_slabs + 1, sizeof(int64_t));
@@ -523,6 +524,15 @@ maxk_status build_slabs(maxk_graph* g, SlabSet& S, int32_t slab_rows)
             S.h_slab_long[sl] = (int64_t)h_long.size();
             for (int64_t v = S.h_slab_visit[sl]; v < S.h_slab_visit[sl + 1]; ++v)
                 if (h_begin[(size_t)v + 1] - h_begin[(size_t)v] > kSlabLongVisit) h_long.push_back((int32_t)v);
+            // longest first, by powers of two (a list that is walked from its front by as many wavefronts as there are)
+            const auto first = h_long.begin() + S.h_slab_long[sl], last = h_long.end();
+            const auto size_class = [&](int32_t v) { return std::countl_zero((uint32_t)(h_begin[(size_t)v + 1] - h_begin[(size_t)v])); };
+            size_t at[33] = {};
+            for (auto v = first; v != last; ++v) ++at[size_class(*v) + 1];
+            for (int c = 0; c < 32; ++c) at[c + 1] += at[c];
+            in_order.resize((size_t)(last - first));
+            for (auto v = first; v != last; ++v) in_order[at[size_class(*v)]++] = *v;
+            std::copy(in_order.begin(), in_order.end(), first);
         }
         S.h_slab_long[n_slabs] = (int64_t)h_long.size();
         S.n_long = (int64_t)h_long.size();

@@ -612,12 +612,19 @@ __device__ __forceinline__ void rowacc_batch(float (&acc)[RC][row_piece<VT>::n],
     }
 }
 
-// RC: chunks of 64 row pieces (256 columns) that cover a row
+// RC: chunks of 64 row pieces (256 columns) that cover a row.
+// The first workgroups take one visit of more than kSlabLongVisit entries each, longest first; the others the rest, in
+// destination order.  Left in that order, long visits that begin late ended the launch: eight rows of a visit are in flight
+// at a time, so one of 600 entries takes half as long as a launch.  us, all in destination order / so: 115 M entries on 233 k
+// nodes, dim 256, k = 64 bf16 dY 4420 / 3960, fp32 5826 / 5371, k = 128 6754 / 6275; 79 M on 133 k, k = 64 3778 / 3268; R-MAT 40 M on
+// 100 k, dim 300, k = 100, bf16 4290 / 3514; 14 M on 60 k, k = 64 bf16 1932 / 1942, fp32 1925 / 1908 (there one visit outlasts
+// the rest).  Visits from 64 or 128 entries up instead: 3952 / 4039, 5509 / 5627 on the first two.
 template <int RC, bool FULL, int VT, typename IdxT>
 __global__ __launch_bounds__(kWave) void bwd_slab_rowacc_kernel(const int32_t* __restrict__ visit_node,
                                                                 const int32_t* __restrict__ visit_begin,
                                                                 int64_t v_begin, int64_t v_end, int visits_per_wave,
-                                                                int64_t tasks_per_xcd,
+                                                                const int32_t* __restrict__ long_visit, int n_long,
+                                                                int long_pad, int64_t tasks_per_xcd,
                                                                 const int32_t* __restrict__ slab_src,
                                                                 const float* __restrict__ slab_val,
                                                                 const value_store_t<VT>* __restrict__ dY,
@@ -629,11 +636,19 @@ __global__ __launch_bounds__(kWave) void bwd_slab_rowacc_kernel(const int32_t* _
     constexpr int U = kRowAccInFlight;
     __shared__ __attribute__((aligned(16))) float row_acc[RC * CHUNK];
     const int lane = threadIdx.x;
-    const int64_t wg = blockIdx.x;  // workgroup b runs on XCD b % 8: each XCD takes a contiguous range of visits
-    if ((wg >> 3) >= tasks_per_xcd) return;
-    const int64_t v0 = v_begin + ((wg & 7) * tasks_per_xcd + (wg >> 3)) * visits_per_wave;
-    if (v0 >= v_end) return;
-    const int nv = (int)min((int64_t)visits_per_wave, v_end - v0);  // <= 32
+    const bool alone = (int)blockIdx.x < long_pad;
+    int64_t v0;
+    int nv = 1;
+    if (alone) {
+        if ((int)blockIdx.x >= n_long) return;  // (long_pad: n_long rounded up to the XCDs, so that the ranges line up)
+        v0 = long_visit[blockIdx.x];
+    } else {
+        const int64_t wg = (int)blockIdx.x - long_pad;  // workgroup b runs on XCD b % 8: each XCD takes a contiguous range of visits
+        if ((wg >> 3) >= tasks_per_xcd) return;
+        v0 = v_begin + ((wg & 7) * tasks_per_xcd + (wg >> 3)) * visits_per_wave;
+        if (v0 >= v_end) return;
+        nv = (int)min((int64_t)visits_per_wave, v_end - v0);  // <= 32
+    }
     const int hdr_begin = (lane <= nv) ? visit_begin[v0 + lane] : 0;
     const int hdr_node = (lane < nv) ? visit_node[v0 + lane] : 0;
     bool col_ok[RC];
@@ -646,6 +661,11 @@ __global__ __launch_bounds__(kWave) void bwd_slab_rowacc_kernel(const int32_t* _
     for (int n = 0; n < nv; ++n) {
         const int64_t j = __builtin_amdgcn_readfirstlane(__shfl(hdr_node, n));
         const int e = __builtin_amdgcn_readfirstlane(__shfl(hdr_begin, n + 1));
+        if (!alone && e - pos > kSlabLongVisit) {  // a wavefront of its own has it
+            pos = e;
+            cur = load_entry_batch(slab_src, slab_val, pos);
+            continue;
+        }
         // the destination's columns and its dXs values are asked for now and used after the rows (k <= 128: two
         // per lane are held in registers; beyond that the tail is fetched at the end)
         int col_t[2];
@@ -748,15 +768,18 @@ maxk_status launch_slab_rowacc(const SlabSet& S, const value_store_t<VT>* dY, co
         if (vb >= ve) continue;
         const int64_t tasks = (ve - vb + vpw - 1) / vpw;
         const int64_t per_xcd = (tasks + 7) / 8;
-        if (per_xcd * 8 > 0x7FFFFFFFll) return MAXK_UNSUPPORTED;
+        const int32_t* longs = S.d_long_visit + S.h_slab_long[sl];
+        const int64_t n_long = S.h_slab_long[sl + 1] - S.h_slab_long[sl], long_pad = (n_long + 7) & ~(int64_t)7;
+        if (per_xcd * 8 + long_pad > 0x7FFFFFFFll) return MAXK_UNSUPPORTED;
+        const dim3 grid((unsigned)(per_xcd * 8 + long_pad));
         if (dim == RC * 256)
-            hipLaunchKernelGGL((bwd_slab_rowacc_kernel<RC, true, VT, IdxT>), dim3((unsigned)(per_xcd * 8)), dim3(kWave), 0,
-                               s, S.d_visit_node, S.d_visit_begin, vb, ve, vpw, per_xcd, S.d_src, S.d_val, dY, sp_index,
-                               dim, k, dXs);
+            hipLaunchKernelGGL((bwd_slab_rowacc_kernel<RC, true, VT, IdxT>), grid, dim3(kWave), 0, s, S.d_visit_node,
+                               S.d_visit_begin, vb, ve, vpw, longs, (int)n_long, (int)long_pad, per_xcd, S.d_src, S.d_val, dY,
+                               sp_index, dim, k, dXs);
         else
-            hipLaunchKernelGGL((bwd_slab_rowacc_kernel<RC, false, VT, IdxT>), dim3((unsigned)(per_xcd * 8)), dim3(kWave),
-                               0, s, S.d_visit_node, S.d_visit_begin, vb, ve, vpw, per_xcd, S.d_src, S.d_val, dY, sp_index,
-                               dim, k, dXs);
+            hipLaunchKernelGGL((bwd_slab_rowacc_kernel<RC, false, VT, IdxT>), grid, dim3(kWave), 0, s, S.d_visit_node,
+                               S.d_visit_begin, vb, ve, vpw, longs, (int)n_long, (int)long_pad, per_xcd, S.d_src, S.d_val, dY,
+                               sp_index, dim, k, dXs);
     }
     MAXK_LAUNCH_CHECK();
     return MAXK_OK;

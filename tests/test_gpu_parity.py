@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
     import paper_2312_08656_amd as maxk
-    from gpu_common import (DeviceGraph, check_backward, check_forward, check_spmm, check_topk, full_pass, gpu_topk,
+    from gpu_common import (DeviceGraph, check_backward, check_forward, check_narrow, check_spmm, check_topk, full_pass, gpu_topk,
                             index_to_numpy, say, to_dev)
 
 
@@ -93,6 +93,34 @@ def test_small_dense_graph_with_long_slab_visits(dim, k, ib):
     dg = DeviceGraph(g)
     H, dY = synth.normal_matrix(g.N, dim, 5), synth.normal_matrix(g.N, dim, 6)
     full_pass(dg, H, dY, k, ib, sampled=False)
+    dg.close()
+
+
+@pytest.mark.parametrize("dim,k,last", [(64, 8, 200), (64, 64, 33), (256, 32, 60), (260, 130, 32), (60, 20, 0)])
+def test_slab_visits_around_the_long_one(dim, k, last):
+    # row-accumulating slab pull: visits of 31 .. 33 and of many more entries, several long ones in a row, slabs that end on
+    # one, a slab of long visits only, nodes without any
+    N, slab = 601, 64 * 1024 // (dim * 4)
+    lengths = [0, 31, 32, 33, 60, 61, 1, 64]
+    rng = np.random.default_rng(dim + k)
+    rows, cols = [], []
+    for s in range(0, N, slab):
+        top = min(slab, N - s)
+        for j in range(N):
+            n = last if j == N - 1 else 40 if s == slab else lengths[(j + s // slab) % 8]
+            src = s + rng.permutation(top)[:min(n, top)]
+            rows.append(src)
+            cols.append(np.full(src.size, j))
+    rows, cols = np.concatenate(rows), np.concatenate(cols)
+    order = np.lexsort((cols, rows))
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=N))]).astype(np.int32)
+    g = synth.Graph(N, rowptr, cols[order].astype(np.int32), rng.standard_normal(rows.size).astype(np.float32))
+    dg = DeviceGraph(g)
+    H, dY = synth.normal_matrix(N, dim, 5), synth.normal_matrix(N, dim, 6)
+    ref = oracle.topk_cbsr(H, k)
+    _, sp_index = gpu_topk(to_dev(H), k, 2)
+    check_backward(dg, ref, dY, to_dev(dY), sp_index, maxk.BWD_SLAB_PULL)
+    check_narrow(dg, to_dev(H), dY, k, 2, ref, dim)
     dg.close()
 
 
