@@ -18,7 +18,8 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(float* __restrict__ p, i
 // LPE = lanes per entry (power of two >= k / VEC, at most 64); 64 / LPE entries per wave instruction.
 // Bound by the read of `expand`, each row of which is wanted once.  43 M entries, 577 k nodes, k = 32: plain loads 1121 us,
 // loads that leave nothing in L2 1031 us (5.5 GB: 5.4 TB/s).
-template <int VEC, int LPE>
+// ONCE: product rows are whole 64-byte sectors
+template <int VEC, int LPE, bool ONCE>
 __global__ __launch_bounds__(kWave) void bwd_reduce_kernel(const WorkItem* __restrict__ items,
                                                            const uint32_t* __restrict__ csc_entry,
                                                            const float* __restrict__ expand, int k,
@@ -43,10 +44,11 @@ __global__ __launch_bounds__(kWave) void bwd_reduce_kernel(const WorkItem* __res
                 const bool ok = active && p < it.end;
                 const float* __restrict__ src = expand + (int64_t)csc_entry[ok ? p : it.begin] * k + (ok ? qq : 0) * VEC;
                 if constexpr (VEC == 4) {
-                    const float4 x = ok ? load_once(reinterpret_cast<const float4*>(src)) : make_float4(0.f, 0.f, 0.f, 0.f);
+                    const float4* __restrict__ row = reinterpret_cast<const float4*>(src);
+                    const float4 x = !ok ? make_float4(0.f, 0.f, 0.f, 0.f) : ONCE ? load_once(row) : *row;
                     v[u][0] = x.x; v[u][1] = x.y; v[u][2] = x.z; v[u][3] = x.w;
                 } else {
-                    v[u][0] = ok ? __builtin_nontemporal_load(src) : 0.f;
+                    v[u][0] = ok ? *src : 0.f;
                 }
             }
 #pragma unroll
@@ -63,14 +65,14 @@ __global__ __launch_bounds__(kWave) void bwd_reduce_kernel(const WorkItem* __res
     }
 }
 
-template <int VEC>
+template <int VEC, bool ONCE>
 maxk_status launch_reduce_v(const ItemList& L, const uint32_t* csc_entry, const float* expand, int k, float* dXs,
                             float* partials, hipStream_t s)
 {
     dim3 grid((unsigned)L.n_items), block(kWave);
     const int kq = k / VEC;
 #define MAXK_REDUCE(LPE) \
-    hipLaunchKernelGGL((bwd_reduce_kernel<VEC, LPE>), grid, block, 0, s, L.d_items, csc_entry, expand, k, dXs, partials)
+    hipLaunchKernelGGL((bwd_reduce_kernel<VEC, LPE, ONCE>), grid, block, 0, s, L.d_items, csc_entry, expand, k, dXs, partials)
     if (kq <= 1) MAXK_REDUCE(1);
     else if (kq <= 2) MAXK_REDUCE(2);
     else if (kq <= 4) MAXK_REDUCE(4);
@@ -134,8 +136,10 @@ maxk_status launch_bwd_expand_reduce(const ItemList& csr_items, const int32_t* c
         st = MAXK_BY_FORMAT(bwd_expand_format, csr_items, col, val, dY, sp_index, index_bytes, dim, k, expand, s);
         if (st != MAXK_OK) return st;
     }
-    if (k % 4 == 0 && aligned(dXs, 16) && aligned(expand, 16)) st = launch_reduce_v<4>(csc_items, csc_entry, expand, k, dXs, partials, s);
-    else st = launch_reduce_v<1>(csc_items, csc_entry, expand, k, dXs, partials, s);
+    const bool vec = k % 4 == 0 && aligned(dXs, 16) && aligned(expand, 16);
+    if (vec && k % 16 == 0) st = launch_reduce_v<4, true>(csc_items, csc_entry, expand, k, dXs, partials, s);
+    else if (vec) st = launch_reduce_v<4, false>(csc_items, csc_entry, expand, k, dXs, partials, s);
+    else st = launch_reduce_v<1, false>(csc_items, csc_entry, expand, k, dXs, partials, s);
     if (st != MAXK_OK) return st;
     return launch_combine(csc_items, partials, k, dXs, s);
 }

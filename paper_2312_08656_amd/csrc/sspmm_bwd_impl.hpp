@@ -240,7 +240,9 @@ constexpr int kExpandRounds = 8;
 // Phase 1: expand[p*k + t] = val[p] * dY[row(p), sp_index[col[p]*k + t]] for every stored entry p.
 // VEC = CBSR positions per lane (4: one packed index load + one float4 store per lane; else 1).
 // Bound by the write of `expand` and by the sp_index rows that come from beyond L2; the products are stored so that they do
-// not push those rows out.  43 M entries, 577 k nodes, k = 32: 1974 -> 1874 us.
+// not push those rows out.  43 M entries, 577 k nodes, k = 32: 1974 -> 1874 us.  Only where a product row is whole 64-byte
+// sectors: others share theirs, which then move twice (both kernels, us, plain / so: 1.7 M entries, 45 k nodes, k = 13 92 / 123;
+// 25 M on 592 k, k = 8 1109 / 1142; 3.4 M on 282 k, k = 16 239 / 214; 3.3 M on 42 k, k = 32 260 / 191).
 template <int K, int VEC, int VT, typename IdxT>
 __global__ __launch_bounds__(kWave) void bwd_expand_kernel(const WorkItem* __restrict__ items,
                                                            const int32_t* __restrict__ col,
@@ -286,11 +288,12 @@ __global__ __launch_bounds__(kWave) void bwd_expand_kernel(const WorkItem* __res
                 if (ok[r]) {
                     const int u = u0 + r * kWave + lane;
                     if constexpr (VEC == 4) {
-                        store_once(dst + (int64_t)u * 4,
-                                   make_float4(a[r] * g_row[ix[r].get(0)], a[r] * g_row[ix[r].get(1)],
-                                               a[r] * g_row[ix[r].get(2)], a[r] * g_row[ix[r].get(3)]));
+                        const float4 x = make_float4(a[r] * g_row[ix[r].get(0)], a[r] * g_row[ix[r].get(1)],
+                                                     a[r] * g_row[ix[r].get(2)], a[r] * g_row[ix[r].get(3)]);
+                        if (k % 16 == 0) store_once(dst + (int64_t)u * 4, x);
+                        else *reinterpret_cast<float4*>(dst + (int64_t)u * 4) = x;
                     } else {
-                        __builtin_nontemporal_store(a[r] * g_row[ix[r].get(0)], dst + u);
+                        dst[u] = a[r] * g_row[ix[r].get(0)];
                     }
                 }
             }
