@@ -153,7 +153,7 @@ __global__ __launch_bounds__(kWave) void spgemm_fwd_rmw_kernel(const WorkItem* _
                                                                int dim, int k_rt, int nb_rt, int vec_out,
                                                                float* __restrict__ Y, float* __restrict__ partials)
 {
-    // vec_out: dim % 4 == 0 and Y / partials 16-byte aligned, so that a row is written with 16-byte stores
+    // vec_out: dim % 4 == 0 and Y / partials 16-byte aligned, so that a row is written with 16-byte stores; 2: past L2
     extern __shared__ __attribute__((aligned(16))) float lds[];
     const int k = K ? K : k_rt;
     const int nb = K ? private_copies(K) : nb_rt;
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(kWave) void spgemm_fwd_rmw_kernel(const WorkItem* _
                 const float4 x = *reinterpret_cast<const float4*>(row_buf + b * cs + c);
                 acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
             }
-            store_once(out + c, acc);
+            if (vec_out == 2) store_once(out + c, acc); else *reinterpret_cast<float4*>(out + c) = acc;
         }
     } else {
         for (int c = lane; c < dim; c += kWave) {
@@ -366,7 +366,7 @@ __global__ __launch_bounds__(kSweepWaves * kWave) void spgemm_fwd_sweep_kernel(
                     const float4 x = *reinterpret_cast<const float4*>(row + g * copy + c);
                     acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
                 }
-                store_once(out + c, acc);
+                if (vec_out == 2) store_once(out + c, acc); else *reinterpret_cast<float4*>(out + c) = acc;
             }
         } else {
             for (int c = lane; c < dim; c += kWave) {
@@ -381,12 +381,12 @@ __global__ __launch_bounds__(kSweepWaves * kWave) void spgemm_fwd_sweep_kernel(
 
 template <bool PACKED, int VT, typename IdxT>
 maxk_status launch_sweep(const SweepSet& S, const value_store_t<VT>* sp_data, const IdxT* sp_index, const char* packed,
-                         int rec_bytes, int idx_off, int dim, int k, float* Y, float* partials, hipStream_t s)
+                         int rec_bytes, int idx_off, int64_t N, int dim, int k, float* Y, float* partials, hipStream_t s)
 {
     const size_t lds = sizeof(float) * (size_t)(S.groups * S.per_bin) * (size_t)dim;
     int waves = kSweepWaves;
     while (waves > 1 && lds * waves > kSweepLds) waves /= 2;
-    const int vec_out = dim % 4 == 0 && aligned(Y, 16) && aligned(partials, 16);
+    const int vec_out = dim % 4 == 0 && aligned(Y, 16) && aligned(partials, 16) ? (past_l2(N * dim * 4) ? 2 : 1) : 0;
     const dim3 grid((unsigned)((S.n_bins + waves - 1) / waves)), block((unsigned)(kWave * waves));
 #define MAXK_FWD_SWEEP(K)                                                                                               \
     hipLaunchKernelGGL((spgemm_fwd_sweep_kernel<K, PACKED, VT, IdxT>), grid, block, lds * waves, s, S.d_ent, S.d_batch, \
@@ -411,7 +411,7 @@ maxk_status launch_sweep_i(const SweepSet& S, const value_store_t<VT>* sp_data, 
                            int dim, int k, float* Y, float* partials, hipStream_t s)
 {
     // (a CBSR row of 64 positions is whole cache lines in both arrays: nothing to gain from a record, whatever the knob says)
-    if (!packed || k >= kWave) return launch_sweep<false, VT>(S, sp_data, sp_index, nullptr, 0, 0, dim, k, Y, partials, s);
+    if (!packed || k >= kWave) return launch_sweep<false, VT>(S, sp_data, sp_index, nullptr, 0, 0, N, dim, k, Y, partials, s);
     const int vb = (int)sizeof(value_store_t<VT>);
     const int rec_bytes = fwd_packed_record_bytes(k, (int)sizeof(IdxT), vb), idx_off = fwd_packed_index_offset(k, (int)sizeof(IdxT), vb);
     const int64_t n_units = N * (int64_t)k;
@@ -419,7 +419,7 @@ maxk_status launch_sweep_i(const SweepSet& S, const value_store_t<VT>* sp_data, 
     hipLaunchKernelGGL((pack_cbsr_kernel<VT, IdxT>), dim3(blocks), dim3(256), 0, s, sp_data, sp_index, n_units, k, rec_bytes,
                        idx_off, packed);
     MAXK_LAUNCH_CHECK();
-    return launch_sweep<true, VT>(S, sp_data, sp_index, packed, rec_bytes, idx_off, dim, k, Y, partials, s);
+    return launch_sweep<true, VT>(S, sp_data, sp_index, packed, rec_bytes, idx_off, N, dim, k, Y, partials, s);
 }
 
 template <int VT>
@@ -445,14 +445,14 @@ maxk_status launch_atomic(const ItemList& L, const int32_t* col, const float* va
 
 template <bool PACKED, int VT, typename IdxT>
 maxk_status launch_rmw(const ItemList& L, const int32_t* col, const float* val, const value_store_t<VT>* sp_data,
-                       const IdxT* sp_index, const char* packed, int rec_bytes, int idx_off, int dim, int k, float* Y,
+                       const IdxT* sp_index, const char* packed, int rec_bytes, int idx_off, int64_t N, int dim, int k, float* Y,
                        float* partials, hipStream_t s)
 {
     if (L.n_items > 0x7FFFFFFF) return MAXK_UNSUPPORTED;
     dim3 grid((unsigned)L.n_items), block(kWave);
     const int nb = private_copies(k);
     const size_t lds = sizeof(float) * (size_t)((nb * (dim + kCopyPad) + 1) & ~1) + sizeof(int2) * kWave;
-    const int vec_out = dim % 4 == 0 && aligned(Y, 16) && aligned(partials, 16);
+    const int vec_out = dim % 4 == 0 && aligned(Y, 16) && aligned(partials, 16) ? (past_l2(N * dim * 4) ? 2 : 1) : 0;
 #define MAXK_FWD_RMW(K, R)                                                                                        \
     hipLaunchKernelGGL((spgemm_fwd_rmw_kernel<K, R, PACKED, VT, IdxT>), grid, block, lds, s, L.d_items, col, val, \
                        sp_data, sp_index, packed, rec_bytes, idx_off, dim, k, nb, vec_out, Y, partials)
@@ -485,9 +485,9 @@ maxk_status launch_rmw_i(const ItemList& L, const int32_t* col, const float* val
         hipLaunchKernelGGL((pack_cbsr_kernel<VT, IdxT>), dim3(blocks), dim3(256), 0, s, sp_data, sp_index, n_units, k,
                            rec_bytes, idx_off, packed);
         MAXK_LAUNCH_CHECK();
-        return launch_rmw<true, VT>(L, col, val, sp_data, sp_index, packed, rec_bytes, idx_off, dim, k, Y, partials, s);
+        return launch_rmw<true, VT>(L, col, val, sp_data, sp_index, packed, rec_bytes, idx_off, N, dim, k, Y, partials, s);
     }
-    return launch_rmw<false, VT>(L, col, val, sp_data, sp_index, nullptr, 0, 0, dim, k, Y, partials, s);
+    return launch_rmw<false, VT>(L, col, val, sp_data, sp_index, nullptr, 0, 0, N, dim, k, Y, partials, s);
 }
 
 // everything but the final sum of split rows, for one storage format of the values

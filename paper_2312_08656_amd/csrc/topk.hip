@@ -337,7 +337,7 @@ constexpr int kScatterRows = 4;
 template <int V, typename IdxT>
 __global__ __launch_bounds__(256) void cbsr_scatter_kernel(const float* __restrict__ values,
                                                            const IdxT* __restrict__ sp_index, int64_t N, int dim,
-                                                           int k, int rows_per_wave, float* __restrict__ dense)
+                                                           int k, int rows_per_wave, int once, float* __restrict__ dense)
 {
     extern __shared__ __attribute__((aligned(16))) float rows[];  // 4 rows of dim floats
     const int lane = threadIdx.x & (kWave - 1);
@@ -375,7 +375,10 @@ __global__ __launch_bounds__(256) void cbsr_scatter_kernel(const float* __restri
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         float* __restrict__ out = dense + row * (int64_t)dim;
         if constexpr (V == 4) {
-            for (int c = lane * 4; c < dim; c += kWave * 4) store_once(out + c, *reinterpret_cast<const float4*>(buf + c));
+            for (int c = lane * 4; c < dim; c += kWave * 4) {
+                const float4 x4 = *reinterpret_cast<const float4*>(buf + c);
+                if (once) store_once(out + c, x4); else *reinterpret_cast<float4*>(out + c) = x4;
+            }
         } else {
             for (int c = lane; c < dim; c += kWave) out[c] = buf[c];
         }
@@ -434,7 +437,7 @@ maxk_status launch_cbsr_scatter(const float* values, const void* sp_index, int i
     const size_t lds = sizeof(float) * 4 * (size_t)dim;
     const bool vec = dim % 4 == 0 && aligned(dense, 16);
 #define MAXK_SCATTER(V, IDX) \
-    hipLaunchKernelGGL((cbsr_scatter_kernel<V, IDX>), grid, block, lds, s, values, (const IDX*)sp_index, N, dim, k, rows_per_wave, dense)
+    hipLaunchKernelGGL((cbsr_scatter_kernel<V, IDX>), grid, block, lds, s, values, (const IDX*)sp_index, N, dim, k, rows_per_wave, (int)past_l2(N * dim * 4), dense)
     if (index_bytes == 1) { if (vec) MAXK_SCATTER(4, uint8_t); else MAXK_SCATTER(1, uint8_t); }
     else if (index_bytes == 2) { if (vec) MAXK_SCATTER(4, uint16_t); else MAXK_SCATTER(1, uint16_t); }
     else { if (vec) MAXK_SCATTER(4, int32_t); else MAXK_SCATTER(1, int32_t); }
