@@ -16,6 +16,21 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // Output below the size of the eight L2s together is better left there: its way out would add to the end of a short kernel
 // (forward, 2.1 M entries on 4 k nodes 28.1 us plain / 29.0; 1.2 M on 40 k 40.0 / 40.9; 169 k nodes, 173 MB of Y 99.9 / 98.9).
 inline bool past_l2(int64_t bytes) { return bytes > (32 << 20); }
+
+// The products of expand/reduce, which one kernel writes and the next one reads.  They pass by L2 where the call does not fit
+// the Infinity Cache (256 MiB): products, entries, dY, columns and result.  Within it the plain ones come back from there and
+// a store past L2 only delays them.  us, plain / past L2, k = 32, width 256 on 6 k nodes 76 / 87 (225 MB of products), 97 / 92 (240),
+// 118 / 99 (260); on 40 k 69 / 70 (160), 92 / 80 (190); on 150 k 132 / 114 (120); k = 96, width 384, 6 k nodes 79 / 99 (225),
+// 148 / 130 (300); k = 128, 4 k nodes 69 / 91 (164); the sides cross at 236 to 286 MB of everything on 14 series of graphs
+// (the largest loss of this line on them is 13 %: k = 32, width 256, 40 k nodes, 190 MB of products).  Below 40 MB the
+// two are within 3 us, plain ahead by 5 % on 2.5 k and 25 k nodes, behind by up to 15 % on 8 k.  Product rows
+// that are not whole 64-byte sectors share them, and they then move twice (1.7 M entries, 45 k nodes, k = 13 92 / 123; 25 M on
+// 592 k, k = 8 1109 / 1142).
+constexpr double kInfinityCache = 256.0 * (1 << 20);
+inline bool products_past_l2(int64_t N, int64_t nnz, int dim, int k, int index_bytes, int val_bytes)
+{
+    return k % 16 == 0 && (double)nnz * (4.0 * k + 12.0) + (double)N * ((double)dim * val_bytes + (4.0 + index_bytes) * k) > kInfinityCache;
+}
 __device__ __forceinline__ void store_once(float* p, float4 x)
 {
     __builtin_nontemporal_store(f32x4{x.x, x.y, x.z, x.w}, reinterpret_cast<f32x4*>(p));
@@ -222,9 +237,10 @@ maxk_status launch_bwd_push(const ItemList& items, const int32_t* col, const flo
                             int value_type, const void* sp_index, int index_bytes, int64_t N, int dim, int k,
                             float* dXs, hipStream_t s);
 
+// once: the products pass by L2
 maxk_status launch_bwd_expand_reduce(const ItemList& csr_items, const int32_t* col, const float* val,
                                      const ItemList& csc_items, const uint32_t* csc_entry, const void* dY,
-                                     int value_type, const void* sp_index, int index_bytes, int dim, int k,
+                                     int value_type, const void* sp_index, int index_bytes, int dim, int k, bool once,
                                      float* expand, float* dXs, float* partials, hipStream_t s);
 
 maxk_status launch_bwd_slab_pull(const SlabSet& S, const void* dY, int value_type, const void* sp_index,

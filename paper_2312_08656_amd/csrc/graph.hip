@@ -1467,7 +1467,8 @@ MAXK_API maxk_status maxk_sspmm_bwd_narrow(maxk_graph* g, const void* d_dY, int3
         return launch_bwd_slab_pull(*plan.S, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs, s);
     if (plan.mode == MAXK_BWD_EXPAND_REDUCE)
         return launch_bwd_expand_reduce(g->csr_items, g->d_col, g->d_val, g->csc_items, g->d_csc_entry, d_dY, value_type,
-                                        d_sp_index, index_bytes, dim, k, g->d_expand, d_dXs, g->d_partials, s);
+                                        d_sp_index, index_bytes, dim, k, products_past_l2(g->N, g->nnz, dim, k, index_bytes, vb),
+                                        g->d_expand, d_dXs, g->d_partials, s);
     if (plan.mode == MAXK_BWD_PULL_CSC) {
         if (plan.sliced) {
             st = launch_bwd_sliced(g->csc_items, g->d_csc_src, g->d_csc_val, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k,
@@ -1524,6 +1525,11 @@ MAXK_API const char* maxk_status_string(maxk_status s)
 }
 
 MAXK_API int32_t maxk_fwd_private_copies(int32_t k) { return k < 1 ? MAXK_INVALID_ARGUMENT : fwd_private_copies(k); }
+
+MAXK_API int32_t maxk_expand_past_l2(int64_t N, int64_t nnz, int32_t dim, int32_t k, int32_t index_bytes, int32_t dy_value_type)
+{
+    return products_past_l2(N, nnz, dim, k, index_bytes, value_bytes(dy_value_type));
+}
 
 MAXK_API maxk_status maxk_graph_cached_tables(const maxk_graph* g, int32_t* n_slab_tables, int32_t* n_tiled_tables)
 {

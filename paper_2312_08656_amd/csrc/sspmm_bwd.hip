@@ -18,7 +18,7 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(float* __restrict__ p, i
 // LPE = lanes per entry (power of two >= k / VEC, at most 64); 64 / LPE entries per wave instruction.
 // Bound by the read of `expand`, each row of which is wanted once.  43 M entries, 577 k nodes, k = 32: plain loads 1121 us,
 // loads that leave nothing in L2 1031 us (5.5 GB: 5.4 TB/s).
-// ONCE: product rows are whole 64-byte sectors
+// ONCE: see products_past_l2
 template <int VEC, int LPE, bool ONCE>
 __global__ __launch_bounds__(kWave) void bwd_reduce_kernel(const WorkItem* __restrict__ items,
                                                            const uint32_t* __restrict__ csc_entry,
@@ -126,18 +126,18 @@ maxk_status launch_bwd_push(const ItemList& L, const int32_t* col, const float* 
 
 maxk_status launch_bwd_expand_reduce(const ItemList& csr_items, const int32_t* col, const float* val,
                                      const ItemList& csc_items, const uint32_t* csc_entry, const void* dY,
-                                     int value_type, const void* sp_index, int index_bytes, int dim, int k,
+                                     int value_type, const void* sp_index, int index_bytes, int dim, int k, bool once,
                                      float* expand, float* dXs, float* partials, hipStream_t s)
 {
     if (csc_items.n_items == 0) return MAXK_OK;
     if (csr_items.n_items > 0x7FFFFFFF || csc_items.n_items > 0x7FFFFFFF) return MAXK_UNSUPPORTED;
     maxk_status st = MAXK_OK;
     if (csr_items.n_items) {
-        st = MAXK_BY_FORMAT(bwd_expand_format, csr_items, col, val, dY, sp_index, index_bytes, dim, k, expand, s);
+        st = MAXK_BY_FORMAT(bwd_expand_format, csr_items, col, val, dY, sp_index, index_bytes, dim, k, once, expand, s);
         if (st != MAXK_OK) return st;
     }
     const bool vec = k % 4 == 0 && aligned(dXs, 16) && aligned(expand, 16);
-    if (vec && k % 16 == 0) st = launch_reduce_v<4, true>(csc_items, csc_entry, expand, k, dXs, partials, s);
+    if (vec && once) st = launch_reduce_v<4, true>(csc_items, csc_entry, expand, k, dXs, partials, s);
     else if (vec) st = launch_reduce_v<4, false>(csc_items, csc_entry, expand, k, dXs, partials, s);
     else st = launch_reduce_v<1, false>(csc_items, csc_entry, expand, k, dXs, partials, s);
     if (st != MAXK_OK) return st;

@@ -21,9 +21,9 @@ maxk_status bwd_push_format<MAXK_VALUE_BF16>(const ItemList& L, const int32_t* c
 
 template <>
 maxk_status bwd_expand_format<MAXK_VALUE_BF16>(const ItemList& L, const int32_t* col, const float* val, const void* dY,
-                                    const void* sp_index, int index_bytes, int dim, int k, float* expand, hipStream_t s)
+                                    const void* sp_index, int index_bytes, int dim, int k, bool once, float* expand, hipStream_t s)
 {
-    return expand_format<MAXK_VALUE_BF16>(L, col, val, dY, sp_index, index_bytes, dim, k, expand, s);
+    return expand_format<MAXK_VALUE_BF16>(L, col, val, dY, sp_index, index_bytes, dim, k, once, expand, s);
 }
 
 template <>

@@ -58,8 +58,8 @@ template <int VT>
 maxk_status bwd_push_format(const ItemList& L, const int32_t* col, const float* val, const void* dY,
                             const void* sp_index, int index_bytes, int dim, int k, float* dXs, hipStream_t s);
 template <int VT>
-maxk_status bwd_expand_format(const ItemList& L, const int32_t* col, const float* val, const void* dY,
-                              const void* sp_index, int index_bytes, int dim, int k, float* expand, hipStream_t s);
+maxk_status bwd_expand_format(const ItemList& L, const int32_t* col, const float* val, const void* dY, const void* sp_index,
+                              int index_bytes, int dim, int k, bool once, float* expand, hipStream_t s);
 template <int VT>
 maxk_status bwd_slab_format(const SlabSet& S, const void* dY, const void* sp_index, int index_bytes, int64_t N,
                             int dim, int k, float* dXs, hipStream_t s);
@@ -239,11 +239,10 @@ constexpr int kExpandRounds = 8;
 
 // Phase 1: expand[p*k + t] = val[p] * dY[row(p), sp_index[col[p]*k + t]] for every stored entry p.
 // VEC = CBSR positions per lane (4: one packed index load + one float4 store per lane; else 1).
-// Bound by the write of `expand` and by the sp_index rows that come from beyond L2; the products are stored so that they do
-// not push those rows out.  43 M entries, 577 k nodes, k = 32: 1974 -> 1874 us.  Only where a product row is whole 64-byte
-// sectors: others share theirs, which then move twice (both kernels, us, plain / so: 1.7 M entries, 45 k nodes, k = 13 92 / 123;
-// 25 M on 592 k, k = 8 1109 / 1142; 3.4 M on 282 k, k = 16 239 / 214; 3.3 M on 42 k, k = 32 260 / 191).
-template <int K, int VEC, int VT, typename IdxT>
+// Bound by the write of `expand` and by the sp_index rows that come from beyond L2; where the call does not fit the Infinity
+// Cache (ONCE, see products_past_l2) the products are stored so that they do not push those rows out.  43 M entries, 577 k
+// nodes, k = 32: 1974 -> 1874 us; both kernels, 3.4 M on 282 k, k = 16 240 -> 210; 3.4 M on 42 k, k = 32 263 -> 195.
+template <int K, int VEC, bool ONCE, int VT, typename IdxT>
 __global__ __launch_bounds__(kWave) void bwd_expand_kernel(const WorkItem* __restrict__ items,
                                                            const int32_t* __restrict__ col,
                                                            const float* __restrict__ val, const value_store_t<VT>* __restrict__ dY,
@@ -290,7 +289,7 @@ __global__ __launch_bounds__(kWave) void bwd_expand_kernel(const WorkItem* __res
                     if constexpr (VEC == 4) {
                         const float4 x = make_float4(a[r] * g_row[ix[r].get(0)], a[r] * g_row[ix[r].get(1)],
                                                      a[r] * g_row[ix[r].get(2)], a[r] * g_row[ix[r].get(3)]);
-                        if (k % 16 == 0) store_once(dst + (int64_t)u * 4, x);
+                        if constexpr (ONCE) store_once(dst + (int64_t)u * 4, x);
                         else *reinterpret_cast<float4*>(dst + (int64_t)u * 4) = x;
                     } else {
                         dst[u] = a[r] * g_row[ix[r].get(0)];
@@ -301,14 +300,15 @@ __global__ __launch_bounds__(kWave) void bwd_expand_kernel(const WorkItem* __res
     }
 }
 
-template <int VEC, int VT, typename IdxT>
+template <int VEC, bool ONCE, int VT, typename IdxT>
 maxk_status launch_expand_t(const ItemList& L, const int32_t* col, const float* val, const value_store_t<VT>* dY,
                             const IdxT* sp_index, int dim, int k, float* expand, hipStream_t s)
 {
     dim3 grid((unsigned)L.n_items), block(kWave);
     const size_t lds = sizeof(float) * (size_t)((dim + 1) & ~1) + sizeof(int2) * kWave;
 #define MAXK_EXPAND(K) \
-    hipLaunchKernelGGL((bwd_expand_kernel<K, VEC, VT, IdxT>), grid, block, lds, s, L.d_items, col, val, dY, sp_index, dim, k, expand)
+    hipLaunchKernelGGL((bwd_expand_kernel<K, VEC, ONCE && K % 16 == 0, VT, IdxT>), grid, block, lds, s, L.d_items, col, val, dY, sp_index, \
+                       dim, k, expand)
     switch (k) {
         case 8: MAXK_EXPAND(8); break;
         case 16: MAXK_EXPAND(16); break;
@@ -326,11 +326,12 @@ maxk_status launch_expand_t(const ItemList& L, const int32_t* col, const float* 
 
 template <int VT, typename IdxT>
 maxk_status launch_expand_i(const ItemList& L, const int32_t* col, const float* val, const value_store_t<VT>* dY,
-                            const IdxT* sp_index, int dim, int k, float* expand, hipStream_t s)
+                            const IdxT* sp_index, int dim, int k, bool once, float* expand, hipStream_t s)
 {
     const bool vec = (k % 4 == 0) && aligned(sp_index, 4 * sizeof(IdxT)) && aligned(expand, 16);
-    return vec ? launch_expand_t<4, VT>(L, col, val, dY, sp_index, dim, k, expand, s)
-               : launch_expand_t<1, VT>(L, col, val, dY, sp_index, dim, k, expand, s);
+    if (vec && once) return launch_expand_t<4, true, VT>(L, col, val, dY, sp_index, dim, k, expand, s);
+    return vec ? launch_expand_t<4, false, VT>(L, col, val, dY, sp_index, dim, k, expand, s)
+               : launch_expand_t<1, false, VT>(L, col, val, dY, sp_index, dim, k, expand, s);
 }
 
 // ------------------------------------------------------------- slab pull ----
@@ -888,12 +889,12 @@ maxk_status push_format(const ItemList& L, const int32_t* col, const float* val,
 
 template <int VT>
 maxk_status expand_format(const ItemList& L, const int32_t* col, const float* val, const void* dY_v,
-                          const void* sp_index, int index_bytes, int dim, int k, float* expand, hipStream_t s)
+                          const void* sp_index, int index_bytes, int dim, int k, bool once, float* expand, hipStream_t s)
 {
     const auto* dY = (const value_store_t<VT>*)dY_v;
-    if (index_bytes == 1) return launch_expand_i<VT>(L, col, val, dY, (const uint8_t*)sp_index, dim, k, expand, s);
-    if (index_bytes == 2) return launch_expand_i<VT>(L, col, val, dY, (const uint16_t*)sp_index, dim, k, expand, s);
-    return launch_expand_i<VT>(L, col, val, dY, (const int32_t*)sp_index, dim, k, expand, s);
+    if (index_bytes == 1) return launch_expand_i<VT>(L, col, val, dY, (const uint8_t*)sp_index, dim, k, once, expand, s);
+    if (index_bytes == 2) return launch_expand_i<VT>(L, col, val, dY, (const uint16_t*)sp_index, dim, k, once, expand, s);
+    return launch_expand_i<VT>(L, col, val, dY, (const int32_t*)sp_index, dim, k, once, expand, s);
 }
 
 template <int VT>

@@ -416,6 +416,33 @@ def test_cbsr_scatter_row_groups(N, dim, k, shift):
     assert torch.equal(dense, torch.zeros(N, dim, device="cuda").scatter_(1, index, values))
 
 
+# products past L2 (everything the call touches above 256 MiB) and not, whole 64-byte product rows and others
+@pytest.mark.parametrize("nnz,dim,k,fmt,past", [(610_000, 130, 128, "f32", 1), (610_000, 130, 128, "bf16", 1), (610_000, 130, 124, "f32", 0),
+                                                (310_000, 130, 128, "f16", 0), (1_000_003, 64, 64, "f32", 1)])
+def test_expand_reduce_either_side_of_the_infinity_cache(nnz, dim, k, fmt, past):
+    N = 20011
+    gen = torch.Generator(device="cuda").manual_seed(nnz + k)
+    row = torch.randint(N, (nnz,), generator=gen, device="cuda").sort().values
+    col = torch.randint(N, (nnz,), generator=gen, device="cuda")
+    col[::7] = 3  # one destination of many entries: split over work items
+    val = torch.randn(nnz, generator=gen, device="cuda")
+    rowptr = torch.zeros(N + 1, dtype=torch.int32, device="cuda")
+    rowptr[1:] = torch.bincount(row, minlength=N).cumsum(0)
+    gr = maxk.maxk_graph_create(rowptr, col.to(torch.int32), val)
+    dY = torch.randn(N, dim, generator=gen, device="cuda").to({"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[fmt])
+    assert maxk.load_library().maxk_expand_past_l2(N, nnz, dim, k, 4, 0 if fmt == "f32" else 1) == past
+    index = torch.rand(N, dim, generator=gen, device="cuda").topk(k, dim=1).indices.sort(dim=1).values
+    gr.set_bwd_mode(maxk.BWD_EXPAND_REDUCE)
+    dXs = torch.full((N, k), float("nan"), device="cuda")
+    maxk.maxk_sspmm_bwd_narrow(gr, dY, index.to(torch.int32), dXs)
+    want, size = (torch.zeros(N, dim, dtype=torch.float64, device="cuda") for _ in range(2))
+    terms = val.double()[:, None] * dY.double()[row]
+    want.index_add_(0, col, terms)
+    size.index_add_(0, col, terms.abs())
+    assert bool(((dXs - want.gather(1, index)).abs() <= 1e-5 * size.gather(1, index) + 1e-6).all())
+    gr.destroy()
+
+
 def test_autograd_function_matches_the_oracle_chain():
     name = "tiny_directed"
     g = synth.graph(name)
