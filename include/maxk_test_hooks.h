@@ -18,6 +18,9 @@ MAXK_API int32_t maxk_fwd_private_copies(int32_t k);
 /* Whether the expand/reduce backward kernels write and read their products past L2 at this shape (0 or 1). */
 MAXK_API int32_t maxk_expand_past_l2(int64_t N, int64_t nnz, int32_t dim, int32_t k, int32_t index_bytes, int32_t dy_value_type);
 
+/* The same for the rows that the gradient scatter writes. */
+MAXK_API int32_t maxk_scatter_past_l2(int64_t N, int32_t dim, int32_t k, int32_t index_bytes);
+
 /* How many regroupings of A^T the handle holds: slab tables (one per slab height ever needed) and visit lists of the
  * LDS-tiled backward kernel (one per destination-set size and k / 4).  They are built once and kept, so the counts
  * never go down and a repeated shape never adds one.  Either out pointer may be NULL. */

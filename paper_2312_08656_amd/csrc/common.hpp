@@ -13,7 +13,7 @@ constexpr int kWave = 64;  // CDNA wavefront width
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // Streams that a kernel reads or writes once pass by the L2's replacement order, so that the records it gathers stay.
-// Output below the size of the eight L2s together is better left there: its way out would add to the end of a short kernel
+// Forward output below the size of the eight L2s together is better left there: its way out would add to the end of a short kernel
 // (forward, 2.1 M entries on 4 k nodes 28.1 us plain / 29.0; 1.2 M on 40 k 40.0 / 40.9; 169 k nodes, 173 MB of Y 99.9 / 98.9).
 inline bool past_l2(int64_t bytes) { return bytes > (32 << 20); }
 
@@ -30,6 +30,15 @@ constexpr double kInfinityCache = 256.0 * (1 << 20);
 inline bool products_past_l2(int64_t N, int64_t nnz, int dim, int k, int index_bytes, int val_bytes)
 {
     return k % 16 == 0 && (double)nnz * (4.0 * k + 12.0) + (double)N * ((double)dim * val_bytes + (4.0 + index_bytes) * k) > kInfinityCache;
+}
+// The rows that the gradient scatter writes.  Past L2 where they and the CBSR do not fit the Infinity Cache: below it the
+// kernel itself is up to 33 % slower so where k is small (width 304, k = 19, 236 MB 1.33, 256, k = 16 1.16; k of a quarter of the
+// width and more 0.79 to 1.0), and a kernel that reads the rows next waits up to 13 % longer; above it 0.6 to 0.9.  Rows that are not
+// whole 64-byte sectors stay plain unless they are narrow.  us, plain / past L2: width 300, 60 MB 12.4 / 17.7, 180 MB
+// 31.5 / 47.9, 600 MB 144 / 159; width 260 14.5 / 17.5, 37.0 / 48.3, 156 / 169; width 100 16.1 / 15.9, 37.4 / 43.2, 184 / 167.
+inline bool scatter_past_l2(int64_t N, int dim, int k, int index_bytes)
+{
+    return (dim % 16 == 0 || dim <= 128) && (double)N * (4.0 * dim + (4.0 + index_bytes) * k) > kInfinityCache;
 }
 __device__ __forceinline__ void store_once(float* p, float4 x)
 {

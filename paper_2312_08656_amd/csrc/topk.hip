@@ -328,10 +328,11 @@ __global__ __launch_bounds__(256) void topk_cbsr_kernel(const float* __restrict_
 
 // MaxK backward: dense[row, sp_index[row,t]] = values[row,t], zeros elsewhere.  A row is assembled in LDS so that it
 // leaves the CU as coalesced 4*V-byte stores.  Bound by the write of `dense`.  A wavefront owns up to kScatterRows
-// consecutive rows and has the loads of all of them in flight before the first leaves (with one row it waited for them
-// with nothing to write); the rows are its own, and LDS operations of one wavefront execute in order, so there is no
-// barrier.  us, one row a wavefront, 4-byte stores and a barrier / this: 169 k nodes, dim 256, k = 32 37 / 29; 577 k, k = 32
-// 139 / 99; 717 k, dim 384, k = 96 290 / 265; 2.4 M, k = 64 631 / 548 (3.3 GB: 6.0 TB/s).
+// consecutive rows and has the loads of the first 64 positions of all of them in flight before the first leaves (with one
+// row it waited for them with nothing to write; positions from 64 on are loaded with their row); the rows are its own, and
+// LDS operations of one wavefront execute in order, so there is no barrier.  us, one row a wavefront, 4-byte stores and a
+// barrier / this: 9 k nodes, dim 256, k = 64 (one row a wavefront) 8.2 / 5.7; 577 k, k = 32 139 / 99; 717 k, dim 384, k = 96
+// 300 / 263, k = 128 296 / 282; 2.4 M, dim 256, k = 64 634 / 541 (3.3 GB: 6.1 TB/s).
 constexpr int kScatterRows = 4;
 
 template <int V, typename IdxT>
@@ -437,7 +438,7 @@ maxk_status launch_cbsr_scatter(const float* values, const void* sp_index, int i
     const size_t lds = sizeof(float) * 4 * (size_t)dim;
     const bool vec = dim % 4 == 0 && aligned(dense, 16);
 #define MAXK_SCATTER(V, IDX) \
-    hipLaunchKernelGGL((cbsr_scatter_kernel<V, IDX>), grid, block, lds, s, values, (const IDX*)sp_index, N, dim, k, rows_per_wave, (int)past_l2(N * dim * 4), dense)
+    hipLaunchKernelGGL((cbsr_scatter_kernel<V, IDX>), grid, block, lds, s, values, (const IDX*)sp_index, N, dim, k, rows_per_wave, (int)scatter_past_l2(N, dim, k, index_bytes), dense)
     if (index_bytes == 1) { if (vec) MAXK_SCATTER(4, uint8_t); else MAXK_SCATTER(1, uint8_t); }
     else if (index_bytes == 2) { if (vec) MAXK_SCATTER(4, uint16_t); else MAXK_SCATTER(1, uint16_t); }
     else { if (vec) MAXK_SCATTER(4, int32_t); else MAXK_SCATTER(1, int32_t); }

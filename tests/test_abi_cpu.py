@@ -115,6 +115,15 @@ def test_products_that_fit_the_infinity_cache_stay_in_l2s_order(lib):
         assert past(592423, 24888335, 256, k, 1, 0) == 0
 
 
+def test_scattered_rows_leave_l2_whole_and_above_the_infinity_cache(lib):
+    past = lib.maxk_scatter_past_l2
+    for N, dim, k, ib in ((576289, 256, 32, 1), (716847, 384, 96, 2), (232965, 256, 32, 1), (2449029, 256, 64, 1), (750000, 100, 13, 1)):
+        assert past(N, dim, k, ib) == 1, (N, dim)
+    for N, dim, k, ib in ((132534, 256, 8, 1), (169343, 256, 32, 1), (190000, 304, 19, 2), (40013, 100, 13, 1), (1024, 64, 8, 1),
+                          (500000, 300, 40, 2), (600000, 260, 64, 2), (600000, 200, 25, 1)):
+        assert past(N, dim, k, ib) == 0, (N, dim)
+
+
 def test_every_kernel_source_is_in_the_build():
     """A .hip file that the build script does not list would silently drop its kernels from libmaxk.so."""
     from pathlib import Path
