@@ -153,7 +153,8 @@ __global__ __launch_bounds__(kWave) void spgemm_fwd_rmw_kernel(const WorkItem* _
                                                                int dim, int k_rt, int nb_rt, int vec_out,
                                                                float* __restrict__ Y, float* __restrict__ partials)
 {
-    // vec_out: dim % 4 == 0 and Y / partials 16-byte aligned, so that a row is written with 16-byte stores; 2: past L2
+    // vec_out: dim % 4 == 0 and Y / partials 16-byte aligned, so that a row is written with 16-byte stores; 2: past
+    // L2, but for the partial rows of split ones, which combine_kernel reads next
     extern __shared__ __attribute__((aligned(16))) float lds[];
     const int k = K ? K : k_rt;
     const int nb = K ? private_copies(K) : nb_rt;
@@ -211,13 +212,14 @@ __global__ __launch_bounds__(kWave) void spgemm_fwd_rmw_kernel(const WorkItem* _
 
     float* __restrict__ out = (it.slot < 0) ? Y + (int64_t)it.row * dim : partials + (int64_t)it.slot * dim;
     if (vec_out) {
+        const bool once = vec_out == 2 && it.slot < 0;
         for (int c = lane * 4; c < dim; c += kWave * 4) {
             float4 acc = *reinterpret_cast<const float4*>(row_buf + c);
             for (int b = 1; b < nb; ++b) {
                 const float4 x = *reinterpret_cast<const float4*>(row_buf + b * cs + c);
                 acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
             }
-            if (vec_out == 2) store_once(out + c, acc); else *reinterpret_cast<float4*>(out + c) = acc;
+            if (once) store_once(out + c, acc); else *reinterpret_cast<float4*>(out + c) = acc;
         }
     } else {
         for (int c = lane; c < dim; c += kWave) {
@@ -249,7 +251,10 @@ __global__ __launch_bounds__(kWave) void spgemm_fwd_rmw_kernel(const WorkItem* _
 // The entries are read once and Y is written once: both pass by L2's replacement order and leave its 4 MB to the records.
 // us, plain / so: 43 M entries on 577 k nodes k = 32 1311 / 1276; 115 M on 233 k k = 32 2078 / 2054, bf16 k = 64
 // 3449 / 3437; 126 M on 2.4 M k = 64 4650 / 4547.  Y of the kernel above: 14.7 M on 717 k, dim 384, k = 96 1169 / 1139; 79 M
-// on 133 k k = 8 692 / 682.
+// on 133 k k = 8 692 / 682.  Partial rows of split rows are read by the next kernel and stay plain (2.5 M on 169 k k = 32, all plain /
+// partial rows past L2 as well / so 89.8 / 91.0 / 89.3).  With a kernel behind it that reads Y the call keeps the gain: 43 M on
+// 577 k k = 32 1476 / 1450 for both, 14.7 M on 717 k, dim 384, k = 96 1481 / 1439; rows of 100 or 300 floats too (8.5 M on
+// 500 k 336 / 307, 6.2 M on 200 k 286 / 261).
 constexpr int kSweepWaves = 16;            // wavefronts of a workgroup, at most
 constexpr size_t kSweepLds = 64 * 1024;    // LDS of a workgroup, at most: two of them on a CU
 constexpr uint32_t kSweepMeet = 8;         // batches between barriers (k = 32: 1996 / 2028 / 2098 us at 4 / 8 / 16, bf16
@@ -359,6 +364,7 @@ __global__ __launch_bounds__(kSweepWaves * kWave) void spgemm_fwd_sweep_kernel(
         float* __restrict__ out = to.y < 0 ? Y + (int64_t)to.x * dim : partials + (int64_t)to.y * dim;
         const float* __restrict__ row = rows + i * dim;
         if (vec_out) {
+            const bool once = vec_out == 2 && to.y < 0;
             for (int c = lane * 4; c < dim; c += kWave * 4) {
                 float4 acc = *reinterpret_cast<const float4*>(row + c);
 #pragma unroll
@@ -366,7 +372,7 @@ __global__ __launch_bounds__(kSweepWaves * kWave) void spgemm_fwd_sweep_kernel(
                     const float4 x = *reinterpret_cast<const float4*>(row + g * copy + c);
                     acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
                 }
-                if (vec_out == 2) store_once(out + c, acc); else *reinterpret_cast<float4*>(out + c) = acc;
+                if (once) store_once(out + c, acc); else *reinterpret_cast<float4*>(out + c) = acc;
             }
         } else {
             for (int c = lane; c < dim; c += kWave) {

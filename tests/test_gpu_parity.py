@@ -842,6 +842,31 @@ def test_forward_sweep_keeps_infinities_in_their_rows(monkeypatch):
     gr.destroy()
 
 
+@pytest.mark.parametrize("sweep", ["1", "2"])
+@pytest.mark.parametrize("dim,k", [(256, 64), (300, 16), (255, 32)])
+def test_forward_output_past_l2_with_split_rows(monkeypatch, sweep, dim, k):
+    # Y above 32 MiB, rows cut into 157 and 24 pieces of uneven length.  Whole numbers below 2^24: any order, the same bits
+    monkeypatch.setenv("MAXK_FWD_SWEEP", sweep)
+    N = 40_009
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    rows = torch.cat([torch.arange(N, device="cuda").repeat_interleave(2), torch.full((20_001,), 3, device="cuda"),
+                      torch.full((3_000,), N - 1, device="cuda")]).sort().values
+    rowptr = torch.zeros(N + 1, dtype=torch.int32, device="cuda")
+    rowptr[1:] = torch.cumsum(torch.bincount(rows, minlength=N), 0)
+    col = torch.randint(N, rows.shape, generator=gen, device="cuda")
+    val = torch.randint(-3, 4, rows.shape, generator=gen, device="cuda").float()
+    sp_data = torch.randint(-5, 6, (N, k), generator=gen, device="cuda").float()
+    index = torch.rand(N, dim, generator=gen, device="cuda").topk(k, dim=1).indices.sort(dim=1).values
+    gr = maxk.maxk_graph_create(rowptr, col.to(torch.int32), val)
+    assert gr.info()["n_split_rows"] == 2
+    Y = torch.full((N, dim), float("nan"), device="cuda")
+    maxk.maxk_spgemm_fwd(gr, sp_data, index.to(torch.int32), dim, Y)
+    assert gr.sweep_tables() == (sweep == "2")
+    X = torch.zeros(N, dim, device="cuda").scatter_(1, index, sp_data)
+    assert torch.equal(Y, torch.zeros(N, dim, device="cuda").index_add_(0, rows, val[:, None] * X[col]))
+    gr.destroy()
+
+
 def test_forward_sweep_of_more_than_2_to_the_24_rows(monkeypatch):
     # the regrouping of A strides over its work items: a workgroup each would be more threads than a launch holds.
     # Whole numbers below 2^24, so every order of the sums gives the same bits
