@@ -95,7 +95,10 @@ def _check(status: int, what: str) -> None:
 
 def _stream() -> int:
     # (the handle alone: torch.cuda.current_stream() makes a Stream object around it, 2.6 us a call against 0.2)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    except AttributeError:  # not a public name
+        return int(torch.cuda.current_stream().cuda_stream)
 
 
 def _dev(t: torch.Tensor, dtype, what: str) -> int:

@@ -85,6 +85,22 @@ def test_binding_refuses_cpu_tensors():
         maxk.maxk_topk_cbsr(H, 2, torch.zeros(4, 2), torch.zeros(4, 2, dtype=torch.uint8))
 
 
+@pytest.mark.parametrize("has_raw", [True, False])
+def test_the_current_stream_is_found_with_and_without_the_raw_handle(monkeypatch, has_raw):
+    # torch's call for the bare handle is not a public one; without it the public stream object has the same handle
+    import torch
+    from types import SimpleNamespace
+
+    from paper_2312_08656_amd import binding
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    if has_raw:
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", {3: 0x5678}.__getitem__, raising=False)
+    else:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=0x1234))
+    assert binding._stream() == (0x5678 if has_raw else 0x1234)
+
+
 def test_forward_private_copies_never_collide(lib):
     # The forward kernel walks flat units u = entry * k + position, 64 per wave instruction (aligned to
     # multiples of 64 within a batch of 64 entries), and lets entry e accumulate into copy e % NB without
