@@ -26,6 +26,9 @@ MAXK_API int32_t maxk_scatter_past_l2(int64_t N, int32_t dim, int32_t k, int32_t
  * never go down and a repeated shape never adds one.  Either out pointer may be NULL. */
 MAXK_API maxk_status maxk_graph_cached_tables(const maxk_graph* g, int32_t* n_slab_tables, int32_t* n_tiled_tables);
 
+/* From how many entries on a visit gets a wavefront of its own (32: above 32) in a slab of `entries` whose longest has `longest`. */
+MAXK_API int32_t maxk_lone_visit_line(int32_t longest, int64_t entries);
+
 /* How many regroupings of A for the forward sweep the handle holds (kept like the tables above). */
 MAXK_API int32_t maxk_graph_sweep_tables(const maxk_graph* g);
 

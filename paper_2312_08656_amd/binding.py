@@ -20,7 +20,7 @@ EXPORTS = (
     "maxk_topk_cbsr", "maxk_spgemm_fwd", "maxk_spgemm_fwd_noalloc", "maxk_topk_cbsr_narrow", "maxk_spgemm_fwd_narrow", "maxk_sspmm_bwd",
     "maxk_sspmm_bwd_narrow", "maxk_cbsr_scatter", "spmm_baseline", "maxk_status_string",
     "maxk_last_hip_error", "maxk_version", "maxk_fwd_private_copies", "maxk_graph_cached_tables", "maxk_graph_sweep_tables",
-    "maxk_graph_limit_allocations", "maxk_expand_past_l2", "maxk_scatter_past_l2",
+    "maxk_graph_limit_allocations", "maxk_expand_past_l2", "maxk_scatter_past_l2", "maxk_lone_visit_line",
 )
 
 
@@ -80,6 +80,8 @@ def load_library() -> ctypes.CDLL:
     lib.maxk_expand_past_l2.restype = i32
     lib.maxk_scatter_past_l2.argtypes = [i64, i32, i32, i32]
     lib.maxk_scatter_past_l2.restype = i32
+    lib.maxk_lone_visit_line.argtypes = [i32, i64]
+    lib.maxk_lone_visit_line.restype = i32
     lib.maxk_last_hip_error.argtypes = []
     lib.maxk_version.argtypes = []
     _LIB = lib

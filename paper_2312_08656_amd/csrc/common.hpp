@@ -86,6 +86,10 @@ struct ItemList {
 // 8 lanes each (16 / 32 / 64 measured within 3 % of each other, 64 best on graphs of 40 k nodes and more)
 constexpr int kSlicedLongItem = 64;
 
+// The visits of a slab that the row-accumulating kernel gives a wavefront each: the first `count` of its long ones, of more
+// than `over` entries.
+struct LoneVisits { int32_t over, count; };
+
 // A^T regrouped for the L2-tiled pull kernel: source rows are cut into slabs of `slab_rows`
 // rows (a slab of dY fits one XCD's L2); in-entries are ordered by (slab of source, destination,
 // source) and every non-empty (slab, destination) pair is one "visit".
@@ -102,6 +106,7 @@ struct SlabSet {
     int64_t n_long = 0;
     int32_t* d_long_visit = nullptr;   // [n_long] visit numbers, grouped by slab
     int64_t* h_slab_long = nullptr;    // host [n_slabs + 1] first long visit of each slab
+    LoneVisits* h_slab_lone = nullptr; // host [n_slabs]
 };
 
 constexpr int kSlabLongVisit = 32;

@@ -356,6 +356,7 @@ void free_slabs(SlabSet& S)
     (void)hipFree(S.d_long_visit);
     std::free(S.h_slab_visit);
     std::free(S.h_slab_long);
+    std::free(S.h_slab_lone);
     S = SlabSet();
 }
 
@@ -428,6 +429,22 @@ __global__ __launch_bounds__(256) void fill_i64_kernel(int64_t* __restrict__ p, 
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = value;
+}
+
+// From how many entries on the row-accumulating slab kernel gives a visit a wavefront of its own: kSlabLongVisit or a power of
+// two above it.  Lone visits fill the chip from the start of a launch on, which shortens it where its end was long visits that
+// began late; but the longest visit then shares its CU with other long ones, and where it takes most of a launch by itself they
+// delay it.  So the line follows its share: r = its entries over a resident wavefront's share (7168 of them) of the slab's; 0.04 r
+// of its length, at most 0.3.  us, dim 256, k = 64, r: visits from 33 / 64 / 256 / 512 / 1024 / no visit alone: 115 M entries on 233 k nodes,
+// fp32, 1.2 5384 / 5492 / 5806 / 5831 / 5827 / 5855; 60 M on 180 k, bf16, 5.3 3742 / 3738 / 3666 / 3633 / 3671 / 4375; 24 M on 60 k,
+// bf16, 5.7 1516 / 1464 / 1427 / 1400 / 1391 / 1437; 28 M on 90 k, bf16, 11 3194 / 3142 / 3073 / 3051 / 2960 / 3134; 14 M on 60 k, fp32, 14.5
+// 1893 / 1842 / 1789 / 1769 / 1772 / 1921.  Over 18 graphs in fp32 and bf16 the line is within 3 % of the best of these, 33 up to 9 % off.
+int32_t lone_visit_line(int32_t longest, int64_t entries)
+{
+    const double share = 7168.0 * longest / (double)std::max<int64_t>(entries, 1), line = std::min(0.3, 0.04 * share) * longest;
+    int32_t n = kSlabLongVisit;
+    while (2.0 * n <= line) n *= 2;
+    return n;
 }
 
 // Regroups A^T by slabs of `slab_rows` source rows (see SlabSet) into the empty set S.  Synchronises the device.
@@ -519,17 +536,27 @@ maxk_status build_slabs(maxk_graph* g, SlabSet& S, int32_t slab_rows)
         MAXK_TRY_CLEAN(hipMemcpy(h_begin.data(), S.d_visit_begin, sizeof(int32_t) * (size_t)(n_visits + 1),
                                  hipMemcpyDeviceToHost));
         S.h_slab_long = (int64_t*)std::calloc((size_t)n_slabs + 1, sizeof(int64_t));
-        if (!S.h_slab_long) { cleanup(); free_slabs(S); return MAXK_OUT_OF_MEMORY; }
+        S.h_slab_lone = (LoneVisits*)std::calloc((size_t)n_slabs, sizeof(LoneVisits));
+        if (!S.h_slab_long || !S.h_slab_lone) { cleanup(); free_slabs(S); return MAXK_OUT_OF_MEMORY; }
         for (int32_t sl = 0; sl < n_slabs; ++sl) {
             S.h_slab_long[sl] = (int64_t)h_long.size();
             for (int64_t v = S.h_slab_visit[sl]; v < S.h_slab_visit[sl + 1]; ++v)
                 if (h_begin[(size_t)v + 1] - h_begin[(size_t)v] > kSlabLongVisit) h_long.push_back((int32_t)v);
-            // longest first, by powers of two (a list that is walked from its front by as many wavefronts as there are)
+            // longest first, by powers of two (a list that is walked from its front by as many wavefronts as there are).  us of
+            // the sampled kernel, in destination order / so: 79 M entries on 133 k nodes, k = 16 3578 / 3468; 7 M on 63 k,
+            // width 99, k = 32 562 / 540; 14 M on 60 k, k = 16 1806 / 1756, but bf16, k = 8 1067 / 1093; 115 M on 233 k within 1 %.
+            // Of the row-accumulating one: 18 M on 60 k, k = 32, bf16 839 / 720; 40 M on 100 k, dim 300, k = 100, bf16 3650 / 3518;
+            // 14 M on 60 k, k = 64, bf16 1864 / 1941 (every long visit alone; the line of lone visits mends that).
             const auto first = h_long.begin() + S.h_slab_long[sl], last = h_long.end();
             const auto size_class = [&](int32_t v) { return std::countl_zero((uint32_t)(h_begin[(size_t)v + 1] - h_begin[(size_t)v])); };
             size_t at[33] = {};
             for (auto v = first; v != last; ++v) ++at[size_class(*v) + 1];
             for (int c = 0; c < 32; ++c) at[c + 1] += at[c];
+            int32_t longest = 0;
+            for (auto v = first; v != last; ++v) longest = std::max(longest, h_begin[(size_t)*v + 1] - h_begin[(size_t)*v]);
+            const int32_t line = lone_visit_line(longest, h_begin[(size_t)S.h_slab_visit[sl + 1]] - h_begin[(size_t)S.h_slab_visit[sl]]);
+            S.h_slab_lone[sl] = line <= kSlabLongVisit ? LoneVisits{kSlabLongVisit, (int32_t)(last - first)}
+                                                       : LoneVisits{line - 1, (int32_t)at[std::countl_zero((uint32_t)line) + 1]};
             in_order.resize((size_t)(last - first));
             for (auto v = first; v != last; ++v) in_order[at[size_class(*v)]++] = *v;
             std::copy(in_order.begin(), in_order.end(), first);
@@ -1543,6 +1570,8 @@ MAXK_API maxk_status maxk_graph_cached_tables(const maxk_graph* g, int32_t* n_sl
     if (n_tiled_tables) *n_tiled_tables = (int32_t)g->tiled_cache.size();
     return MAXK_OK;
 }
+
+MAXK_API int32_t maxk_lone_visit_line(int32_t longest, int64_t entries) { return lone_visit_line(longest, entries); }
 
 MAXK_API int32_t maxk_graph_sweep_tables(const maxk_graph* g) { return g ? (int32_t)g->sweep_cache.size() : MAXK_INVALID_ARGUMENT; }
 

@@ -617,18 +617,19 @@ __device__ __forceinline__ void rowacc_batch(float (&acc)[RC][row_piece<VT>::n],
 }
 
 // RC: chunks of 64 row pieces (256 columns) that cover a row.
-// The first workgroups take one visit of more than kSlabLongVisit entries each, longest first; the others the rest, in
-// destination order.  Left in that order, long visits that begin late ended the launch: eight rows of a visit are in flight
-// at a time, so one of 600 entries takes half as long as a launch.  us, all in destination order / so: 115 M entries on 233 k
-// nodes, dim 256, k = 64 bf16 dY 4420 / 3960, fp32 5826 / 5371, k = 128 6754 / 6275; 79 M on 133 k, k = 64 3778 / 3268; R-MAT 40 M on
-// 100 k, dim 300, k = 100, bf16 4290 / 3514; 14 M on 60 k, k = 64 bf16 1932 / 1942, fp32 1925 / 1908 (there one visit outlasts
-// the rest).  Visits from 64 or 128 entries up instead: 3952 / 4039, 5509 / 5627 on the first two.
+// The first workgroups take one visit of more than `over` entries each, longest first (by powers of two); the others the rest,
+// in destination order.  Left in that order, long visits that begin late ended the launch: eight rows of a visit are in flight
+// at a time, so one of 600 entries takes half as long as a launch.  Where the line lies: lone_visit_line.
+// us, all in destination order / from 33 entries on everywhere / so: 115 M entries on 233 k nodes, dim 256, k = 64 bf16 dY 4390 / 3940 /
+// 3940, fp32 5820 / 5370 / 5385, k = 128 6745 / 6265 / 6230; 79 M on 133 k, k = 64 3740 / 3262 / 3262; R-MAT 40 M on 100 k, dim 300, k = 100,
+// bf16 4245 / 3511 / 3471; 28 M on 90 k, k = 64, bf16 3087 / 3185 / 2967; 24 M on 60 k, bf16 1407 / 1494 / 1412; 14 M on 60 k, bf16
+// 1861 / 1938 / 1803, fp32 1883 / 1879 / 1751; 9 M on 30 k, fp32 1085 / 1130 / 1058.
 template <int RC, bool FULL, int VT, typename IdxT>
 __global__ __launch_bounds__(kWave) void bwd_slab_rowacc_kernel(const int32_t* __restrict__ visit_node,
                                                                 const int32_t* __restrict__ visit_begin,
                                                                 int64_t v_begin, int64_t v_end, int visits_per_wave,
                                                                 const int32_t* __restrict__ long_visit, int n_long,
-                                                                int long_pad, int64_t tasks_per_xcd,
+                                                                int long_pad, int over, int64_t tasks_per_xcd,
                                                                 const int32_t* __restrict__ slab_src,
                                                                 const float* __restrict__ slab_val,
                                                                 const value_store_t<VT>* __restrict__ dY,
@@ -665,7 +666,7 @@ __global__ __launch_bounds__(kWave) void bwd_slab_rowacc_kernel(const int32_t* _
     for (int n = 0; n < nv; ++n) {
         const int64_t j = __builtin_amdgcn_readfirstlane(__shfl(hdr_node, n));
         const int e = __builtin_amdgcn_readfirstlane(__shfl(hdr_begin, n + 1));
-        if (!alone && e - pos > kSlabLongVisit) {  // a wavefront of its own has it
+        if (!alone && e - pos > over) {  // a wavefront of its own has it
             pos = e;
             cur = load_entry_batch(slab_src, slab_val, pos);
             continue;
@@ -773,16 +774,17 @@ maxk_status launch_slab_rowacc(const SlabSet& S, const value_store_t<VT>* dY, co
         const int64_t tasks = (ve - vb + vpw - 1) / vpw;
         const int64_t per_xcd = (tasks + 7) / 8;
         const int32_t* longs = S.d_long_visit + S.h_slab_long[sl];
-        const int64_t n_long = S.h_slab_long[sl + 1] - S.h_slab_long[sl], long_pad = (n_long + 7) & ~(int64_t)7;
+        const auto [over, n_lone] = S.h_slab_lone[sl];
+        const int64_t long_pad = ((int64_t)n_lone + 7) & ~(int64_t)7;
         if (per_xcd * 8 + long_pad > 0x7FFFFFFFll) return MAXK_UNSUPPORTED;
         const dim3 grid((unsigned)(per_xcd * 8 + long_pad));
         if (dim == RC * 256)
             hipLaunchKernelGGL((bwd_slab_rowacc_kernel<RC, true, VT, IdxT>), grid, dim3(kWave), 0, s, S.d_visit_node,
-                               S.d_visit_begin, vb, ve, vpw, longs, (int)n_long, (int)long_pad, per_xcd, S.d_src, S.d_val, dY,
+                               S.d_visit_begin, vb, ve, vpw, longs, n_lone, (int)long_pad, over, per_xcd, S.d_src, S.d_val, dY,
                                sp_index, dim, k, dXs);
         else
             hipLaunchKernelGGL((bwd_slab_rowacc_kernel<RC, false, VT, IdxT>), grid, dim3(kWave), 0, s, S.d_visit_node,
-                               S.d_visit_begin, vb, ve, vpw, longs, (int)n_long, (int)long_pad, per_xcd, S.d_src, S.d_val, dY,
+                               S.d_visit_begin, vb, ve, vpw, longs, n_lone, (int)long_pad, over, per_xcd, S.d_src, S.d_val, dY,
                                sp_index, dim, k, dXs);
     }
     MAXK_LAUNCH_CHECK();

@@ -140,6 +140,17 @@ def test_scattered_rows_leave_l2_whole_and_above_the_infinity_cache(lib):
         assert past(N, dim, k, ib) == 0, (N, dim)
 
 
+def test_the_line_of_lone_visits_follows_the_longest_one(lib):
+    line = lib.maxk_lone_visit_line
+    # (entries of the longest visit, of the slab): where no visit stands out, every long one is alone
+    for longest, entries in ((0, 0), (33, 100), (286, 1762775), (564, 3536890), (490, 2144031), (72, 1798635)):
+        assert line(longest, entries) == 32, (longest, entries)
+    # one visit takes most of a launch
+    assert line(1137, 1442198) == 256 and line(2277, 2884617) == 512
+    assert line(1730, 861040) == 512 and line(3466, 1730281) == 1024 and line(3445, 2218819) == 1024
+    assert line(10**6, 10**6) == 262144
+
+
 def test_every_kernel_source_is_in_the_build():
     """A .hip file that the build script does not list would silently drop its kernels from libmaxk.so."""
     from pathlib import Path

@@ -124,6 +124,39 @@ def test_slab_visits_around_the_long_one(dim, k, last):
     dg.close()
 
 
+@pytest.mark.parametrize("dim,k,fmt", [(16, 8, "f32"), (16, 16, "bf16"), (12, 5, "f32")])
+def test_lone_visits_of_slabs_with_one_that_stands_out(dim, k, fmt):
+    # lines of 256, 128, 64 and 32 entries in four slabs, visits at each of them and one entry off, the longest's neighbours short
+    slab = 64 * 1024 // (dim * (4 if fmt == "f32" else 2))
+    longest, N = [860, 430, 214, 40], 3 * slab + 100
+    rng = np.random.default_rng(dim + k)
+    rows, cols = [], []
+    for s, top in enumerate(longest):
+        lengths = [n for n in (1, 0, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 2) if n <= top]
+        for j in range(N):
+            n = top if j == 7 else lengths[j % len(lengths)] if j < 97 else j % 3
+            src = s * slab + rng.permutation(min(slab, N - s * slab))[:n]
+            rows.append(src)
+            cols.append(np.full(src.size, j))
+        entries = sum(r.size for r in rows[-N:])
+        assert maxk.load_library().maxk_lone_visit_line(top, entries) == [256, 128, 64, 32][s]
+    rows, cols = np.concatenate(rows), np.concatenate(cols)
+    order = np.lexsort((cols, rows))
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=N))]).astype(np.int32)
+    g = synth.Graph(N, rowptr, cols[order].astype(np.int32), rng.standard_normal(rows.size).astype(np.float32))
+    dg = DeviceGraph(g)
+    H, dY = synth.normal_matrix(N, dim, 5), synth.normal_matrix(N, dim, 6)
+    dY_dev = to_dev(dY).to({"f32": torch.float32, "bf16": torch.bfloat16}[fmt])
+    ref = oracle.topk_cbsr(H, k)
+    _, sp_index = gpu_topk(to_dev(H), k, 1)
+    dg.handle.set_bwd_mode(maxk.BWD_SLAB_PULL)
+    dXs = torch.full((N, k), float("nan"), device="cuda")
+    maxk.maxk_sspmm_bwd_narrow(dg.handle, dY_dev, sp_index, dXs)
+    want, size = oracle.sspmm_bwd(g.rowptr, g.col, g.val, dY_dev.float().cpu().numpy(), ref[1])
+    assert (np.abs(dXs.cpu().numpy() - want) <= 1e-5 * size + 1e-6).all()
+    dg.close()
+
+
 def test_topk_ties_signed_zero_and_infinities():
     H = synth.normal_matrix(5000, 384, seed=5)
     synth.add_tie_rows(H, seed=5, percent=40, pool=16, const_every=8)
