@@ -19,7 +19,7 @@ MAXK_API int32_t maxk_fwd_private_copies(int32_t k);
 MAXK_API int32_t maxk_expand_past_l2(int64_t N, int64_t nnz, int32_t dim, int32_t k, int32_t index_bytes, int32_t dy_value_type);
 
 /* The same for the rows that the gradient scatter writes. */
-MAXK_API int32_t maxk_scatter_past_l2(int64_t N, int32_t dim, int32_t k, int32_t index_bytes);
+MAXK_API int32_t maxk_scatter_past_l2(int64_t N, int32_t dim);
 
 /* How many regroupings of A^T the handle holds: slab tables (one per slab height ever needed) and visit lists of the
  * LDS-tiled backward kernel (one per destination-set size and k / 4).  They are built once and kept, so the counts

@@ -78,7 +78,7 @@ def load_library() -> ctypes.CDLL:
     lib.maxk_graph_limit_allocations.restype = i64
     lib.maxk_expand_past_l2.argtypes = [i64, i64, i32, i32, i32, i32]
     lib.maxk_expand_past_l2.restype = i32
-    lib.maxk_scatter_past_l2.argtypes = [i64, i32, i32, i32]
+    lib.maxk_scatter_past_l2.argtypes = [i64, i32]
     lib.maxk_scatter_past_l2.restype = i32
     lib.maxk_lone_visit_line.argtypes = [i32, i64]
     lib.maxk_lone_visit_line.restype = i32

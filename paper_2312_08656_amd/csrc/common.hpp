@@ -31,15 +31,15 @@ inline bool products_past_l2(int64_t N, int64_t nnz, int dim, int k, int index_b
 {
     return k % 16 == 0 && (double)nnz * (4.0 * k + 12.0) + (double)N * ((double)dim * val_bytes + (4.0 + index_bytes) * k) > kInfinityCache;
 }
-// The rows that the gradient scatter writes.  Past L2 where they and the CBSR do not fit the Infinity Cache: below it the
-// kernel itself is up to 33 % slower so where k is small (width 304, k = 19, 236 MB 1.33, 256, k = 16 1.16; k of a quarter of the
-// width and more 0.79 to 1.0), and a kernel that reads the rows next waits up to 13 % longer; above it 0.6 to 0.9.  Rows that are not
-// whole 64-byte sectors stay plain unless they are narrow.  us, plain / past L2: width 300, 60 MB 12.4 / 17.7, 180 MB
-// 31.5 / 47.9, 600 MB 144 / 159; width 260 14.5 / 17.5, 37.0 / 48.3, 156 / 169; width 100 16.1 / 15.9, 37.4 / 43.2, 184 / 167.
-inline bool scatter_past_l2(int64_t N, int dim, int k, int index_bytes)
-{
-    return (dim % 16 == 0 || dim <= 128) && (double)N * (4.0 * dim + (4.0 + index_bytes) * k) > kInfinityCache;
-}
+// The rows that the gradient scatter writes.  Past L2 from 32 MiB up where they are whole 64-byte sectors: the kernel by itself
+// gains above the Infinity Cache only and is up to 33 % slower below it where k is small, but the pass around it keeps H, Y
+// and dY closer.  us of a whole pass, plain / past L2 (with kernels behind it that read Y and dH): 169 k nodes, width 256, k = 32 440 / 422
+// (556 / 540); 117 k, k = 16 295 / 278 (397 / 392); 78 k, width 384, k = 96 479 / 463 (563 / 557); 133 k, k = 8 1710 / 1702 (1810 /
+// 1801); 59 k, k = 16 133.5 / 133.9 (191.5 / 190.3).  Other rows share their sectors, which then move twice, up to 1.6 times
+// the kernel's time; only larger ones gain over the pass: width 300, 60 MB 227 / 228 (274 / 276), 190 MB 755 / 753 (895 / 887), 320 MB
+// 1304 / 1294; width 500, 60 MB 138 / 136 (183 / 188), 120 MB 265 / 263 (350 / 354), 190 MB 416 / 407; width 260, 60 MB 281 / 284
+// (324 / 329), 190 MB 870 / 872 (988 / 988); width 100, 60 MB 338 / 333 (380 / 381), 190 MB 1147 / 1131.
+inline bool scatter_past_l2(int64_t N, int dim) { return (double)N * dim * 4.0 > (dim % 16 == 0 ? 32.0 * (1 << 20) : 160e6); }
 __device__ __forceinline__ void store_once(float* p, float4 x)
 {
     __builtin_nontemporal_store(f32x4{x.x, x.y, x.z, x.w}, reinterpret_cast<f32x4*>(p));

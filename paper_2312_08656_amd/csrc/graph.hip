@@ -1558,10 +1558,7 @@ MAXK_API int32_t maxk_expand_past_l2(int64_t N, int64_t nnz, int32_t dim, int32_
     return products_past_l2(N, nnz, dim, k, index_bytes, value_bytes(dy_value_type));
 }
 
-MAXK_API int32_t maxk_scatter_past_l2(int64_t N, int32_t dim, int32_t k, int32_t index_bytes)
-{
-    return scatter_past_l2(N, dim, k, index_bytes);
-}
+MAXK_API int32_t maxk_scatter_past_l2(int64_t N, int32_t dim) { return scatter_past_l2(N, dim); }
 
 MAXK_API maxk_status maxk_graph_cached_tables(const maxk_graph* g, int32_t* n_slab_tables, int32_t* n_tiled_tables)
 {

@@ -438,7 +438,7 @@ maxk_status launch_cbsr_scatter(const float* values, const void* sp_index, int i
     const size_t lds = sizeof(float) * 4 * (size_t)dim;
     const bool vec = dim % 4 == 0 && aligned(dense, 16);
 #define MAXK_SCATTER(V, IDX) \
-    hipLaunchKernelGGL((cbsr_scatter_kernel<V, IDX>), grid, block, lds, s, values, (const IDX*)sp_index, N, dim, k, rows_per_wave, (int)scatter_past_l2(N, dim, k, index_bytes), dense)
+    hipLaunchKernelGGL((cbsr_scatter_kernel<V, IDX>), grid, block, lds, s, values, (const IDX*)sp_index, N, dim, k, rows_per_wave, (int)scatter_past_l2(N, dim), dense)
     if (index_bytes == 1) { if (vec) MAXK_SCATTER(4, uint8_t); else MAXK_SCATTER(1, uint8_t); }
     else if (index_bytes == 2) { if (vec) MAXK_SCATTER(4, uint16_t); else MAXK_SCATTER(1, uint16_t); }
     else { if (vec) MAXK_SCATTER(4, int32_t); else MAXK_SCATTER(1, int32_t); }

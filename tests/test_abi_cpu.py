@@ -131,13 +131,12 @@ def test_products_that_fit_the_infinity_cache_stay_in_l2s_order(lib):
         assert past(592423, 24888335, 256, k, 1, 0) == 0
 
 
-def test_scattered_rows_leave_l2_whole_and_above_the_infinity_cache(lib):
+def test_scattered_rows_leave_l2_whole_or_many(lib):
     past = lib.maxk_scatter_past_l2
-    for N, dim, k, ib in ((576289, 256, 32, 1), (716847, 384, 96, 2), (232965, 256, 32, 1), (2449029, 256, 64, 1), (750000, 100, 13, 1)):
-        assert past(N, dim, k, ib) == 1, (N, dim)
-    for N, dim, k, ib in ((132534, 256, 8, 1), (169343, 256, 32, 1), (190000, 304, 19, 2), (40013, 100, 13, 1), (1024, 64, 8, 1),
-                          (500000, 300, 40, 2), (600000, 260, 64, 2), (600000, 200, 25, 1)):
-        assert past(N, dim, k, ib) == 0, (N, dim)
+    for N, dim in ((169343, 256), (132534, 256), (716847, 384), (190000, 304), (500000, 300), (600000, 100)):
+        assert past(N, dim) == 1, (N, dim)
+    for N, dim in ((1024, 64), (40013, 100), (32768, 256), (100000, 300), (115384, 260), (60000, 500), (190000, 200)):
+        assert past(N, dim) == 0, (N, dim)
 
 
 def test_the_line_of_lone_visits_follows_the_longest_one(lib):

@@ -439,8 +439,8 @@ def test_cbsr_scatter_is_exact(dim, k, ib):
 # rows per wavefront 1, 2 and 4 with a last wavefront that has fewer; 16-byte and 4-byte stores; k above a wavefront
 @pytest.mark.parametrize("N,dim,k,shift", [(1, 4, 4, 0), (5, 33, 32, 0), (16387, 36, 9, 0), (32771, 60, 7, 0), (32771, 60, 7, 1),
                                            (32773, 61, 61, 0), (32770, 260, 130, 0), (9, 1024, 200, 0),
-                                           # above 256 MiB: past L2 (narrow rows, whole sectors), plain ones, misaligned
-                                           (700_001, 100, 13, 0), (262_147, 272, 9, 0), (262_147, 256, 70, 1), (262_147, 300, 7, 0)])
+                                           # past L2 by their size, misaligned, just below it
+                                           (700_001, 100, 13, 0), (262_147, 272, 9, 0), (262_147, 256, 70, 1), (131_071, 300, 7, 0)])
 def test_cbsr_scatter_row_groups(N, dim, k, shift):
     gen = torch.Generator(device="cuda").manual_seed(N + dim)
     values = torch.randn(N, k, generator=gen, device="cuda")
