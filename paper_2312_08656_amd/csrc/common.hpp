@@ -17,20 +17,20 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // (forward, 2.1 M entries on 4 k nodes 28.1 us plain / 29.0; 1.2 M on 40 k 40.0 / 40.9; 169 k nodes, 173 MB of Y 99.9 / 98.9).
 inline bool past_l2(int64_t bytes) { return bytes > (32 << 20); }
 
-// The products of expand/reduce, which one kernel writes and the next one reads.  They pass by L2 where the call does not fit
-// the Infinity Cache (256 MiB): products, entries, dY, columns and result.  Within it the plain ones come back from there and
-// a store past L2 only delays them.  us, plain / past L2, k = 32, width 256 on 6 k nodes 76 / 87 (225 MB of products), 97 / 92 (240),
-// 118 / 99 (260); on 40 k 69 / 70 (160), 92 / 80 (190); on 150 k 132 / 114 (120); k = 96, width 384, 6 k nodes 79 / 99 (225),
-// 148 / 130 (300); k = 128, 4 k nodes 69 / 91 (164); the sides cross at 236 to 286 MB of everything on 14 series of graphs
-// (the largest loss of this line on them is 13 %: k = 32, width 256, 40 k nodes, 190 MB of products).  Below 40 MB the
-// two are within 3 us, plain ahead by 5 % on 2.5 k and 25 k nodes, behind by up to 15 % on 8 k.  Product rows
-// that are not whole 64-byte sectors share them, and they then move twice (1.7 M entries, 45 k nodes, k = 13 92 / 123; 25 M on
-// 592 k, k = 8 1109 / 1142).
+// The products of expand/reduce, which one kernel writes and the next one reads.  They pass by L2 where they do not fit the
+// Infinity Cache (256 MiB) with the rest of the pass: entries, dY, columns, result, and H, Y and dH around the call.  Within it the
+// plain ones come back from there and a store past L2 only delays them.  The two kernels alone, us, plain / past L2, width 256: 4 k nodes,
+// 0.3 M entries, k = 128 69 / 91; 6 k nodes, k = 32 70 / 81 (205 MB of products), 118 / 99 (260); 150 k, k = 32 132 / 114 (120); alone the
+// sides cross at 236 to 286 MB of what the call itself touches (14 series of graphs), below 40 MB of products they are within 3 us.  A whole pass
+// (with kernels behind it that read Y and dH): 25 k nodes, k = 16, 42 MB of products 67.3 / 69.0 (84.0 / 86.0); 40 k, k = 32, 128 MB 108.5 / 111.2
+// (152.9 / 141.2), 164 MB 136.5 / 126.5 (176 / 156); 117 k, k = 16, 157 MB 285 / 278 (376 / 392).  Product rows that are not whole 64-byte
+// sectors share them, and they then move twice (1.7 M entries, 45 k nodes, k = 13 92 / 123; 25 M on 592 k, k = 8 1109 / 1142).
 constexpr double kInfinityCache = 256.0 * (1 << 20);
 inline bool products_past_l2(int64_t N, int64_t nnz, int dim, int k, int index_bytes, int val_bytes)
 {
-    return k % 16 == 0 && (double)nnz * (4.0 * k + 12.0) + (double)N * ((double)dim * val_bytes + (4.0 + index_bytes) * k) > kInfinityCache;
+    return k % 16 == 0 && (double)nnz * (4.0 * k + 12.0) + (double)N * (dim * (val_bytes + 12.0) + (4.0 + index_bytes) * k) > kInfinityCache;
 }
+
 // The rows that the gradient scatter writes.  Past L2 from 32 MiB up where they are whole 64-byte sectors: the kernel by itself
 // gains above the Infinity Cache only and is up to 33 % slower below it where k is small, but the pass around it keeps H, Y
 // and dY closer.  us of a whole pass, plain / past L2 (with kernels behind it that read Y and dH): 169 k nodes, width 256, k = 32 440 / 422

@@ -239,7 +239,7 @@ constexpr int kExpandRounds = 8;
 
 // Phase 1: expand[p*k + t] = val[p] * dY[row(p), sp_index[col[p]*k + t]] for every stored entry p.
 // VEC = CBSR positions per lane (4: one packed index load + one float4 store per lane; else 1).
-// Bound by the write of `expand` and by the sp_index rows that come from beyond L2; where the call does not fit the Infinity
+// Bound by the write of `expand` and by the sp_index rows that come from beyond L2; where the pass does not fit the Infinity
 // Cache (ONCE, see products_past_l2) the products are stored so that they do not push those rows out.  43 M entries, 577 k
 // nodes, k = 32: 1974 -> 1874 us; both kernels, 3.4 M on 282 k, k = 16 240 -> 210; 3.4 M on 42 k, k = 32 263 -> 195.
 template <int K, int VEC, bool ONCE, int VT, typename IdxT>

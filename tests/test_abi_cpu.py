@@ -118,14 +118,14 @@ def test_forward_private_copies_never_collide(lib):
 
 
 def test_products_that_fit_the_infinity_cache_stay_in_l2s_order(lib):
-    # (N, nnz, dim, k, index bytes, dY format) either side of 256 MiB of everything the call touches, and odd product rows
+    # (N, nnz, dim, k, index bytes, dY format) either side of 256 MiB of everything the pass touches, and odd product rows
     past = lib.maxk_expand_past_l2
-    for shape in ((15882, 1925544, 100, 16, 1, 0), (3823, 320487, 256, 128, 1, 0), (6000, 1757000, 256, 32, 1, 0),
-                  (4029, 300881, 256, 96, 1, 0), (40000, 1250000, 256, 32, 1, 0), (1024, 17408, 64, 16, 1, 0),
-                  (150000, 937500, 256, 32, 1, 1)):
+    for shape in ((15882, 1925544, 100, 16, 1, 0), (3823, 320487, 256, 128, 1, 0), (6000, 1601000, 256, 32, 1, 0),
+                  (4029, 300881, 256, 96, 1, 0), (25000, 650000, 256, 16, 1, 0), (1024, 17408, 64, 16, 1, 0),
+                  (33000, 1000000, 256, 32, 1, 1)):
         assert past(*shape) == 0, shape
     for shape in ((576289, 43040151, 256, 32, 1, 0), (42015, 3374557, 256, 32, 1, 0), (281571, 3382179, 128, 16, 1, 0),
-                  (6000, 2030000, 256, 32, 1, 0), (40000, 1600000, 256, 32, 1, 0), (150000, 937500, 256, 32, 1, 0)):
+                  (6000, 2030000, 256, 32, 1, 0), (40000, 1280000, 256, 32, 1, 0), (33000, 1000000, 256, 32, 1, 0)):
         assert past(*shape) == 1, shape
     for k in (8, 13, 24, 100):  # not whole 64-byte sectors
         assert past(592423, 24888335, 256, k, 1, 0) == 0

@@ -451,7 +451,7 @@ def test_cbsr_scatter_row_groups(N, dim, k, shift):
     assert torch.equal(dense, torch.zeros(N, dim, device="cuda").scatter_(1, index, values))
 
 
-# products past L2 (everything the call touches above 256 MiB) and not, whole 64-byte product rows and others
+# products past L2 (everything the pass touches above 256 MiB) and not, whole 64-byte product rows and others
 @pytest.mark.parametrize("nnz,dim,k,fmt,past", [(610_000, 130, 128, "f32", 1), (610_000, 130, 128, "bf16", 1), (610_000, 130, 124, "f32", 0),
                                                 (310_000, 130, 128, "f16", 0), (1_000_003, 64, 64, "f32", 1)])
 def test_expand_reduce_either_side_of_the_infinity_cache(nnz, dim, k, fmt, past):
