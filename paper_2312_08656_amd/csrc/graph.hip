@@ -944,15 +944,15 @@ bool fwd_uses_packed(const maxk_graph* g, int k, int index_bytes, int val_bytes)
 // Rows of a bin of the forward sweep for MaxK k, 0 where the row-by-row kernel is taken.  The sweep pays when the CBSR is
 // several times an L2, the bins fill the chip (256 CUs x 32 wavefronts), the rows in LDS leave enough wavefronts a CU, and
 // a bin has enough entries for its padding to whole batches and its copies of the rows.  The lines are drawn by k where both
-// sides were measured, over 16 graphs (profiles/forward_sweep_rule_over_graphs.txt: the kernel taken is 0.7 % above the
-// better one on average, row by row 3.7 %); us, row by row / sweep:
-//   CBSR size: k = 32, 100 k nodes (16 MB) 212 / 185, 40 k (6 MB) 60 / 62; k = 64, 100 k (32 MB) 366 / 333, 40 k (13 MB)
-//     277 / 283, bf16 values 100 k (19 MB) 825 / 860 and 320 / 307; k = 128, 40 k (26 MB) 540 / 438 and 178 / 163
-//   entries a lane group: k = 16, 123 1563 / 1303, 75 323 / 325, 19 828 / 924; k = 8, 62 1310 / 1161, 38 258 / 275; k = 32,
-//     101 618 / 583, 31 231 / 237
-//   width: k = 16, dim 400 334 / 360; k = 32, dim 400 468 / 448, dim 512 238 / 276; k = 64, dim 400 710 / 666, dim 512
-//     388 / 442; k = 128, dim 512 841 / 724
-// Rows of a bin, us: k = 64, 3 / 4 / 5 rows 3541 / 3175 / 4010 (dense workload); k = 32, 1 / 2 / 3 rows 2211 / 2085 / 1922
+// sides were measured, over 16 graphs (profiles/forward_sweep_rule_over_graphs.txt: the kernel taken is 0.4 % above the
+// better one on average, 15 % at most, row by row 3.2 %); us, row by row / sweep:
+//   CBSR size: k = 32, 100 k nodes (16 MB) 191 / 197 and 531 / 500, 40 k (6 MB) 57 / 66; k = 64, 100 k (32 MB) 357 / 342, 40 k
+//     (13 MB) 259 / 291, bf16 values 100 k (19 MB) 756 / 825 and 303 / 315; k = 128, 40 k (26 MB) 524 / 441 and 171 / 163
+//   entries a lane group: k = 16, 123 1549 / 1245, 75 306 / 311, 19 795 / 842; k = 8, 62 1264 / 1126, 38 218 / 268; k = 32,
+//     101 597 / 555, 31 188 / 217; k = 64, 124 291 / 332 (250 k nodes, skewed, the largest miss) and 132 / 134
+//   width: k = 16, dim 400 271 / 332; k = 32, dim 400 441 / 429, dim 512 215 / 269; k = 64, dim 400 705 / 650, dim 512
+//     382 / 439; k = 128, dim 512 845 / 713
+// Rows of a bin, us, when the lines were drawn (the sweep was 2 to 13 % slower then): k = 64, 3 / 4 / 5 rows 3541 / 3175 / 4010 (dense workload); k = 32, 1 / 2 / 3 rows 2211 / 2085 / 1922
 // there, 1312 / 1282 / 1326 on 79 M entries and 132 k nodes, 1 / 2 / 4 rows 1425 / 1336 / 1264 on 43 M and 576 k: two are ahead of
 // one on each, three and four are faster where the rows are long resp. the nodes many; k = 16, 1 / 2 1303 / 1369 (dense),
 // 805 / 917 (79 M), 924 / 825 (43 M, below the entries line: row by row 828).
@@ -1102,9 +1102,12 @@ PullCost pull_cost(const maxk_graph* g, int dim, int k, int val_bytes, const voi
 
 // Backward kernel choice when the caller leaves it to the library: the lowest of five cost models, fitted on MI355X to
 // 153 shapes (R-MAT and uniform graphs of 4 thousand to 1 million nodes, average degree 12 to 400; widths 64 to 512;
-// k 8 to 128; fp32 and 16-bit dY) and the benchmark graphs.  Over those shapes the chosen kernel takes 6 % longer than
-// the best one on average (profiles/backward_choice_over_shapes.txt; the largest misses, 2.2 times, are 16-bit dY on
-// 60 k nodes of degree 240, where hub visits end the launches of slab pull later than the model has it).
+// k 8 to 128; fp32 and 16-bit dY) and the benchmark graphs.  Over those shapes the chosen kernel takes 5 % longer than
+// the best one on average (profiles/backward_choice_over_shapes.txt; the largest misses, 2 times, are 16-bit dY on
+// 60 k nodes of degree 240, where hub visits end the launches of slab pull later than the model has it).  The lines of expand/reduce
+// and slab pull were fitted before product rows passed by L2 and long visits began a launch, and run high for both now: pull is
+// taken on 42 k nodes, 3.3 M entries, k = 32 (243 us, expand/reduce 191), 40 k, 1.6 M, k = 32 (136 / 100), 118 k, 1.7 M, k = 64
+// (241 / 208), 282 k, 3.4 M, k = 16 (247 / 214) and 169 k, 2.5 M, k = 32 (230 / 216; a whole pass 424 / 414).
 // Times in seconds; `lines` = 128-byte lines of a dY row that an entry's k columns touch.
 int auto_bwd_mode(const maxk_graph* g, int dim, int k, int val_bytes = 4, bool tiled_ok = true)
 {

@@ -244,13 +244,13 @@ __global__ __launch_bounds__(kWave) void spgemm_fwd_rmw_kernel(const WorkItem* _
 // The LDS pipe bounds it next (a read-add-write pair is ~14 clocks a wave instruction), so entries do not go through LDS:
 // each row of 16 lanes holds the next 16 entries of its lane group (8 lanes the next 8 for K = 8) and hands them out by
 // data-parallel-primitive broadcasts.
-// Measured, us, kernel above / sweep: dense k = 8 1310 / 1161, k = 16 1563 / 1303, k = 32 2834 / 2085, k = 64 5200 / 3175,
-// k = 128 9276 / 6872, bf16 k = 64 3382 / 2985; 79 M entries on 132 k nodes k = 32 1572 / 1282; 43 M on 576 k k = 32
-// 1445 / 1336; 126 M on 2.4 M nodes k = 64 6181 / 4845.
+// Measured, us, kernel above / sweep: dense k = 8 1264 / 1126, k = 16 1549 / 1245, k = 32 2809 / 1995, k = 64 5262 / 2986,
+// k = 128 9239 / 5944, bf16 k = 64 3251 / 2893; 79 M entries on 132 k nodes k = 32 1513 / 1171; 43 M on 576 k k = 32
+// 1428 / 1270; 126 M on 2.4 M nodes k = 64 6079 / 4491.
 //
 // The entries are read once and Y is written once: both pass by L2's replacement order and leave its 4 MB to the records.
-// us, plain / so: 43 M entries on 577 k nodes k = 32 1311 / 1276; 115 M on 233 k k = 32 2078 / 2054, bf16 k = 64
-// 3449 / 3437; 126 M on 2.4 M k = 64 4650 / 4547.  Y of the kernel above: 14.7 M on 717 k, dim 384, k = 96 1169 / 1139; 79 M
+// us, both plain / so: 43 M entries on 577 k nodes k = 32 1311 / 1276; 126 M on 2.4 M k = 64 4650 / 4547.  Y alone: 115 M on 233 k
+// k = 32 2017 / 2005, bf16 k = 64 2935 / 2896; of the kernel above 14.7 M on 717 k, dim 384, k = 96 1169 / 1139; 79 M
 // on 133 k k = 8 692 / 682.  Partial rows of split rows are read by the next kernel and stay plain (2.5 M on 169 k k = 32, all plain /
 // partial rows past L2 as well / so 89.8 / 91.0 / 89.3).  With a kernel behind it that reads Y the call keeps the gain: 43 M on
 // 577 k k = 32 1476 / 1450 for both, 14.7 M on 717 k, dim 384, k = 96 1481 / 1439; rows of 100 or 300 floats too (8.5 M on

@@ -798,6 +798,8 @@ maxk_status launch_slab_i(const SlabSet& S, const value_store_t<VT>* dY, const I
     // Row-accumulating form from the k where it was measured faster on the dense workload (dim 256; ms, sampled /
     // row-accumulating): fp32 k=24 5.26 / 5.39, k=32 5.42 / 5.41, k=64 6.64 / 5.76, k=128 9.62 / 6.70;
     // 16-bit dY k=8 3.1 / 4.3, k=16 4.1 / 4.2, k=32 5.8 / 4.3, k=128 11.5 / 4.8.  Other widths use the same ratios.
+    // (Before long visits began a launch: the row-accumulating form now takes 5.05 / 5.38 / 6.25 at k=32 / 64 / 128, with 16-bit dY
+    // 3.87 / 3.95 / 4.38, so at k=24 and, in 16 bits, k=16 it may be ahead of the sampled form's 5.25 and 4.0.)
     const bool rowacc = sizeof(value_store_t<VT>) == 4 ? 8 * k >= dim : 16 * k > dim;
     if (rowacc && dim % 4 == 0 && aligned(dY, 16)) {
         if (dim <= 256) return launch_slab_rowacc<1, VT>(S, dY, sp_index, dim, k, dXs, s);
