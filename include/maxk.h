@@ -29,7 +29,9 @@
  *     backward kernel, default 3584), MAXK_FWD_PACK_MAX (largest CBSR row in bytes that the forward pass
  *     repacks into one record per node, default 96), MAXK_PULL_FORM (form of the CSC pull: 0 = by cost, 1 = whole
  *     rows, 2 = column slices wherever the shape allows them; default 0), MAXK_FWD_SWEEP (forward kernel: 0 = by
- *     size, 1 = row by row, 2 = the sweep wherever the shape allows it; default 0).
+ *     size, 1 = row by row, 2 = the sweep wherever the shape allows it; default 0), MAXK_BWD_REGS (register-tiled
+ *     backward kernel in MAXK_BWD_AUTO: 0 = by cost, 1 = never, 2 = wherever the shape allows it, 3 = the same, its
+ *     destination sets by degree; default 0).
  */
 #ifndef MAXK_H
 #define MAXK_H
@@ -61,7 +63,11 @@ enum {
 
 /* Which kernel maxk_sspmm_bwd runs (see maxk_graph_set_bwd_mode). */
 enum {
-    MAXK_BWD_AUTO = 0,    /* library's choice (the faster one on MI355X) */
+    MAXK_BWD_AUTO = 0,    /* library's choice (the faster one on MI355X).  Where it is faster than the kernel that this would
+                             take, and its sums are no longer, the register-tiled kernel stands in for it: a workgroup keeps
+                             the dXs rows of a set of destination nodes in registers and takes the dY rows that they need
+                             through LDS; deterministic, no atomics.  k <= 128, rows of dY of at most 2048 bytes and whole
+                             16-byte units, 16-byte aligned dY */
     MAXK_BWD_PULL_CSC = 1,/* owner-computes over A^T stored as CSC: deterministic, no atomics */
     MAXK_BWD_PUSH_CSR = 2,/* Alg. 2's dataflow: stage dY[i,:] on chip, push along row i of A with fp32 atomics */
     MAXK_BWD_EXPAND_REDUCE = 3,/* Alg. 2's staging without atomics: write each entry's k products to a per-graph
@@ -106,6 +112,7 @@ MAXK_API maxk_status maxk_graph_destroy(maxk_graph* g);
  * copy of A that the forward sweep walks (k = 8, 16, 32, 64, 128 on large graphs; 8 bytes an entry), and
  * what the backward kernel that would run needs (the nnz*k float buffer of expand/reduce, the slab regrouping
  * of A^T for the slab height of (dim, dy_value_type), the visit lists of the LDS-tiled kernel for (dim, k), the
+ * regrouping of A^T and the partial sums of the register-tiled kernel, the
  * slice-major copy of dY that the pull kernel's column-sliced form keeps for rows that are not whole cache lines).
  * After it, compute calls with the same dim and k (forward, SpMM: any dim' <= dim, k' <= k) allocate nothing,
  * do not synchronise and read no environment variable.  Tables are cached per shape for the life of the handle,
@@ -129,7 +136,7 @@ MAXK_API maxk_status maxk_graph_reserve_narrow(maxk_graph* g, int32_t dim, int32
 MAXK_API maxk_status maxk_graph_set_bwd_mode(maxk_graph* g, int32_t mode);
 
 /* The MAXK_BWD_* kernel maxk_sspmm_bwd would run for (dim, k) with the handle's current mode
- * (resolves MAXK_BWD_AUTO); negative maxk_status on bad arguments. */
+ * (resolves MAXK_BWD_AUTO; the register-tiled kernel may stand in for what this names); negative maxk_status on bad arguments. */
 MAXK_API int32_t maxk_graph_bwd_choice(const maxk_graph* g, int32_t dim, int32_t k);
 
 /* Reads back sizes: any out pointer may be NULL. */

@@ -32,6 +32,9 @@ MAXK_API int32_t maxk_lone_visit_line(int32_t longest, int64_t entries);
 /* How many regroupings of A for the forward sweep the handle holds (kept like the tables above). */
 MAXK_API int32_t maxk_graph_sweep_tables(const maxk_graph* g);
 
+/* How many regroupings of A^T for the register-tiled backward kernel the handle holds (kept like the tables above). */
+MAXK_API int32_t maxk_graph_regs_tables(const maxk_graph* g);
+
 /* From here on the handle's tables, the slice-major copy and the expand/reduce buffer are refused, as if memory had run
  * out, when they take more than `bytes` (a table: 8 an entry); negative: no limit.  Returns how many were refused so far. */
 MAXK_API int64_t maxk_graph_limit_allocations(maxk_graph* g, int64_t bytes);

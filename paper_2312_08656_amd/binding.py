@@ -20,6 +20,7 @@ EXPORTS = (
     "maxk_topk_cbsr", "maxk_spgemm_fwd", "maxk_spgemm_fwd_noalloc", "maxk_topk_cbsr_narrow", "maxk_spgemm_fwd_narrow", "maxk_sspmm_bwd",
     "maxk_sspmm_bwd_narrow", "maxk_cbsr_scatter", "spmm_baseline", "maxk_status_string",
     "maxk_last_hip_error", "maxk_version", "maxk_fwd_private_copies", "maxk_graph_cached_tables", "maxk_graph_sweep_tables",
+    "maxk_graph_regs_tables",
     "maxk_graph_limit_allocations", "maxk_expand_past_l2", "maxk_scatter_past_l2", "maxk_lone_visit_line",
 )
 
@@ -74,6 +75,8 @@ def load_library() -> ctypes.CDLL:
     lib.maxk_fwd_private_copies.restype = i32
     lib.maxk_graph_sweep_tables.argtypes = [vp]
     lib.maxk_graph_sweep_tables.restype = i32
+    lib.maxk_graph_regs_tables.argtypes = [vp]
+    lib.maxk_graph_regs_tables.restype = i32
     lib.maxk_graph_limit_allocations.argtypes = [vp, i64]
     lib.maxk_graph_limit_allocations.restype = i64
     lib.maxk_expand_past_l2.argtypes = [i64, i64, i32, i32, i32, i32]
@@ -170,6 +173,10 @@ class MaxKGraph:
     def sweep_tables(self) -> int:
         """Regroupings of A for the forward sweep that the handle holds -- a test hook."""
         return int(load_library().maxk_graph_sweep_tables(self.handle))
+
+    def regs_tables(self) -> int:
+        """Regroupings of A^T for the register-tiled backward kernel that the handle holds."""
+        return int(load_library().maxk_graph_regs_tables(self.handle))
 
     def limit_allocations(self, limit: int) -> int:
         """Refuses larger tables and buffers as if memory had run out; refusals so far -- a test hook."""

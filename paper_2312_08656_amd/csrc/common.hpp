@@ -128,6 +128,53 @@ struct TiledSet {
     uint32_t* d_progress = nullptr;  // [8 * ceil(n_dsets / 8) * 32] progress marks of the running workgroups (pacing)
 };
 
+// A^T regrouped for the register-tiled backward kernel (sspmm_bwd_regs.hip).  The head of the destinations, most in-entries first, is
+// dealt to sets; a workgroup holds the accumulators of a set in its registers and takes the source rows that the set has
+// entries from through LDS, a tile at a time.  A step is a tile and up to kRegsListRecords records for each wavefront.
+constexpr int kRegsWaves = 8;            // wavefronts of a workgroup, one workgroup a CU
+constexpr int kRegsListRecords = 32;     // 16-byte records (two entries each) of a wavefront's list in one step
+constexpr int kRegsTileBuffers = 3;
+constexpr int regs_slots(int kr) { return kr == 2 ? 55 : 111; }  // destinations (per lane group) of a wavefront; one more takes the padding
+struct RegsLayout { int rows, head; };   // rows that a wavefront brings per step; 4-byte words of its header
+constexpr RegsLayout regs_layout(int pitch)
+{
+    return pitch == 256 ? RegsLayout{24, 32} : pitch == 512 ? RegsLayout{12, 16} : pitch == 1024 ? RegsLayout{6, 8} : pitch == 1536 ? RegsLayout{4, 8} : RegsLayout{3, 8};
+}
+constexpr int regs_batch_records(int groups, int kr) { return kr == 2 ? 1 : groups == 1 ? 2 : 4; }  // a list is whole batches
+struct RegsUnit { int32_t set, begin, end, part_begin, part_end; };  // steps [begin, end) of a set, and its parts (none: the set is one part)
+struct RegsSum { int32_t set, part_begin, part_end; };  // the parts of a set
+struct RegsSplit { int32_t node, row_begin, row_end; };  // a destination that is several ones: their rows of `extra`
+struct RegsPart { int32_t end, slots; };  // step behind its last; the sums of that many slots leave then, kRegsHotSlots or all
+// Destinations are dealt to slots most in-entries first: the sums of the first slots get long first.
+constexpr int kRegsHotSlots = 16;  // (a multiple of the four registers that leave at a time)
+struct RegsShape {
+    int32_t pitch = 0, groups = 0, kr = 0;  // bytes of a row in LDS; destinations that share a register; registers a destination
+    int32_t n_sets = 0, spread = 0;         // sets; sets that a run of destinations is dealt over (1: sets by falling degree)
+    int32_t ranges = 0;                     // units a set (0: by cost)
+    int32_t run = 0;                        // entries that a destination adds up before its sum leaves the registers, about (0: a unit's)
+    int64_t cap = 0;                        // in-entries of a destination above which it is several ones, with every n-th entry each
+    int64_t head = 0;                       // destinations in the sets; the others have the fewest in-entries
+    bool operator==(const RegsShape&) const = default;
+};
+struct RegsSet {
+    RegsShape shape;
+    int64_t n_units = 0, n_steps = 0, n_records = 0;
+    uint4* d_rec = nullptr;
+    uint32_t* d_hdr = nullptr;
+    int32_t* d_node = nullptr;     // destination of every accumulator, or -1
+    int32_t* d_row = nullptr;      // the row its sum goes to: of dXs, from N on of `extra`
+    float* d_extra = nullptr;
+    int64_t extra_floats = 0;
+    RegsSplit* d_split = nullptr;
+    int64_t n_split = 0, n_tail = 0;  // destinations that are several ones; destinations behind the head
+    RegsUnit* d_unit = nullptr;
+    RegsPart* d_part = nullptr;
+    float* d_parts = nullptr;      // partial sums of sets in several parts (a call's workspace)
+    int64_t part_floats = 0;
+    RegsSum* d_sum = nullptr;      // the sets in several parts
+    int64_t n_sums = 0;
+};
+
 // A regrouped for the forward sweep kernel: work items are dealt to bins of per_bin output rows with about the same number
 // of entries; a wavefront keeps a bin's rows in LDS and walks the entries of all of them in the order of their source node.
 // Entry e of a row goes to lane group (e + place of the row in the bin) % groups; a batch holds the next sweep_batch(k)
@@ -270,6 +317,16 @@ maxk_status build_tiled(TiledSet& T, int64_t N, int64_t nnz, const int32_t* d_cs
 void free_tiled(TiledSet& T);
 maxk_status launch_bwd_tiled(const TiledSet& T, const void* dY, int value_type, const void* sp_index, int index_bytes,
                              int64_t N, int dim, int k, float* dXs, hipStream_t s);
+
+bool regs_fits(int dim, int val_bytes, int k, RegsShape& sh);  // pitch, groups and kr; false: (dim, format, k) not supported
+maxk_status build_regs(RegsSet& T, const RegsShape& shape, int64_t N, int64_t nnz, const int32_t* d_rowptr, const int32_t* d_csc_ptr, const int32_t* d_csc_src,
+                       const float* d_csc_val);
+void free_regs(RegsSet& T);
+maxk_status launch_bwd_regs(const RegsSet& T, const void* dY, int value_type, const void* sp_index, int index_bytes, int64_t N, int dim,
+                            int k, float* dXs, hipStream_t s);
+template <int VT>
+maxk_status launch_regs_format(const RegsSet& T, const void* dY, const void* sp_index, int index_bytes, int64_t N, int dim, int k, float* dXs,
+                               hipStream_t s);
 
 // shared by the push and slab kernels: p[0..n) = 0
 maxk_status launch_fill_zero(float* p, int64_t n, hipStream_t s);

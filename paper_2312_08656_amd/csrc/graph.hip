@@ -14,6 +14,7 @@
 #include <bit>
 #include <array>
 #include <cmath>
+#include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <deque>
@@ -44,6 +45,11 @@ struct maxk_graph {
     int64_t expand_floats = 0;
     std::vector<maxk::SlabSet*> slab_cache;    // A^T regrouped per slab height (one per height ever asked for)
     std::vector<maxk::TiledSet*> tiled_cache;  // visit lists of the LDS-tiled kernel, one per (set size, k / 4)
+    std::vector<maxk::RegsSet*> regs_cache;    // A^T regrouped for the register-tiled kernel, one per shape
+    struct RegsChoice { int32_t dim, val_bytes, k; maxk::RegsShape shape; };
+    std::vector<RegsChoice> regs_choices;      // what regs_choice found, per shape
+    int32_t bwd_regs = 0;
+    std::vector<std::pair<int32_t, int64_t>> in_degrees;  // in-entries of a node, how many such nodes; most first
     std::vector<maxk::SweepSet*> sweep_cache;  // A regrouped for the forward sweep, one per (lane groups, rows of a bin)
     char* d_sliced = nullptr;   // slice-major copy of dY for the column-sliced pull (rows that are not whole cache lines)
     int64_t sliced_bytes = 0;
@@ -285,7 +291,7 @@ bool denied(maxk_graph* g, int64_t bytes)
 // A table or buffer that could not be built is not asked for again by compute calls: each try synchronises the device
 // and may allocate most of what it needs before it fails, and one that succeeds later would change the kernel mid-run.
 using RefusedKey = std::array<int64_t, 4>;
-enum : int64_t { kRefusedSweep, kRefusedSlab, kRefusedTiled, kRefusedExpand, kRefusedSliced };
+enum : int64_t { kRefusedSweep, kRefusedSlab, kRefusedTiled, kRefusedRegs, kRefusedExpand, kRefusedSliced };
 
 bool is_refused(const maxk_graph* g, const RefusedKey& key)
 {
@@ -647,6 +653,34 @@ maxk_status tiled_for(maxk_graph* g, int dim, int k, const F& existing_only, Til
         if (T) free_tiled(*T);
         delete T;
         if (st == MAXK_OUT_OF_MEMORY) note_refused(g, tiled_key(sh, k));
+        return st;
+    }
+    *out = T;
+    return MAXK_OK;
+}
+
+RefusedKey regs_key(const RegsShape& sh) { return {kRefusedRegs, sh.pitch, sh.groups + 16 * sh.kr, sh.head}; }
+
+template <class F>
+maxk_status regs_for(maxk_graph* g, const RegsShape& sh, const F& existing_only, RegsSet** out)
+{
+    for (RegsSet* T : g->regs_cache)
+        if (T->shape == sh) { *out = T; return MAXK_OK; }
+    if (existing_only()) return MAXK_OUT_OF_MEMORY;
+    RegsSet* T = new (std::nothrow) RegsSet();
+    maxk_status st = MAXK_OUT_OF_MEMORY;
+    if (T && !denied(g, g->nnz * 8)) {
+        try {
+            st = build_regs(*T, sh, g->N, g->nnz, g->d_rowptr, g->d_csc_ptr, g->d_csc_src, g->d_csc_val);
+            if (st == MAXK_OK) g->regs_cache.push_back(T);
+        } catch (const std::bad_alloc&) {
+            st = MAXK_OUT_OF_MEMORY;
+        }
+    }
+    if (st != MAXK_OK) {
+        if (T) free_regs(*T);
+        delete T;
+        note_refused(g, regs_key(sh));
         return st;
     }
     *out = T;
@@ -1109,7 +1143,7 @@ PullCost pull_cost(const maxk_graph* g, int dim, int k, int val_bytes, const voi
 // taken on 42 k nodes, 3.3 M entries, k = 32 (243 us, expand/reduce 191), 40 k, 1.6 M, k = 32 (136 / 100), 118 k, 1.7 M, k = 64
 // (241 / 208), 282 k, 3.4 M, k = 16 (247 / 214) and 169 k, 2.5 M, k = 32 (230 / 216; a whole pass 424 / 414).
 // Times in seconds; `lines` = 128-byte lines of a dY row that an entry's k columns touch.
-int auto_bwd_mode(const maxk_graph* g, int dim, int k, int val_bytes = 4, bool tiled_ok = true)
+int auto_bwd_mode(const maxk_graph* g, int dim, int k, int val_bytes = 4, bool tiled_ok = true, double* seconds = nullptr)
 {
     const double N = (double)g->N, nnz = (double)g->nnz, row_bytes = (double)dim * val_bytes;
     const double lines = lines_touched(dim, k, val_bytes);
@@ -1154,8 +1188,141 @@ int auto_bwd_mode(const maxk_graph* g, int dim, int k, int val_bytes = 4, bool t
     double best = pull;
     if (1.05 * expand < best) { best = expand; mode = MAXK_BWD_EXPAND_REDUCE; }
     if (slab < best) { best = slab; mode = MAXK_BWD_SLAB_PULL; }
-    if (tiled < best) mode = MAXK_BWD_TILED;
+    if (tiled < best) { best = tiled; mode = MAXK_BWD_TILED; }
+    if (seconds) *seconds = best;
     return mode;
+}
+
+// ---- the register-tiled kernel: how its sets are laid out, and where it stands in for the kernels above ----
+
+// Rows that `sets` sets with a share x of the entries each use: a source of d entries is used by one with 1 - exp(-d x).
+double regs_rows(const maxk_graph* g, double x)
+{
+    double rows = 0.0, before = 0.0;
+    for (int i = 0; i < 33 && before < (double)g->N; ++i) {
+        const double last = std::min((double)g->N, std::exp2(i)), count = last - before;
+        const double entries = (g->hot_share[i] - (i ? g->hot_share[i - 1] : 0.f)) * (double)g->nnz;
+        if (count > 0.0) rows += count * -std::expm1(-entries / count * x);
+        before = last;
+    }
+    return rows;
+}
+
+// Seconds of a call with the sets of `sh`, the destinations behind its head by plain pull.  A step costs its instructions
+// (0.37 us, and 3.9 to 6.5 ns an entry) or its rows: 0.65 us where they come from L2, 2.5 us more where each comes from
+// beyond (even sets: an XCD's 32 CUs bring what one of them uses; by degree: 1.5 us); rows of two copies 1.5 times.
+double regs_cost(const maxk_graph* g, const std::vector<std::pair<int32_t, int64_t>>& degrees, const RegsShape& sh, int dim, int val_bytes, int k)
+{
+    const double N = (double)g->N, nnz = (double)g->nnz, room = (double)regs_slots(sh.kr) * sh.groups * kRegsWaves * sh.spread;
+    const double tile = regs_layout(sh.pitch).rows * kRegsWaves, rows_factor = sh.pitch > 1024 ? 1.5 : 1.0;
+    const double b = sh.kr == 2 ? 6.5e-9 : sh.groups == 1 ? 4.4e-9 : sh.groups == 2 ? 3.9e-9 : 5e-9;
+    const double hot = room * kRegsHotSlots / regs_slots(sh.kr);
+    const bool even = sh.ranges > 0;
+    int64_t shares = 0;
+    for (const auto& [degree, n] : degrees) shares += n;
+    double seconds = even ? 60e-6 : 180e-6, all_entries = 0.0, work = 0.0, copies = 0.0;
+    auto run = degrees.begin();
+    double nodes = run == degrees.end() ? 0.0 : (double)run->second, left = (double)sh.head;
+    while (left > 0.0 && run != degrees.end()) {  // a run of `spread` sets at a time
+        double in_run = std::min(room, left), at = 0.0, entries = 0.0, cold = 0.0, cold_squares = 0.0;
+        left -= in_run;
+        while (in_run > 0.0 && run != degrees.end()) {
+            const double now = std::min(nodes, in_run), d = (double)run->first, behind = std::max(0.0, at + now - std::max(at, hot));
+            entries += now * d;
+            cold += behind * d;
+            cold_squares += behind * d * d;
+            at += now;
+            in_run -= now;
+            nodes -= now;
+            if (nodes <= 0.0 && ++run != degrees.end()) nodes = (double)run->second;
+        }
+        all_entries += entries;
+        const double used = regs_rows(g, entries / nnz / sh.spread), steps = sh.spread * std::max(1.0, used / tile) / 256.0;
+        const double run_work = 0.37e-6 * steps + b * entries / 256.0;
+        if (even) {
+            const double p = std::min(1.0, used / N), missed = (1.0 - std::pow(1.0 - p, 32.0)) / (32.0 * std::max(p, 1e-9));
+            seconds += std::max(run_work, rows_factor * (0.65e-6 + 2.5e-6 * missed) * steps);
+            if (cold > 0.0 && sh.run) seconds += 19e-6 * std::min(32.0, cold_squares / cold / sh.run) + 40e-6;  // sums that leave the registers
+        } else {
+            work += run_work;
+            copies += rows_factor * 1.5e-6 * steps;
+        }
+    }
+    seconds += std::max(work, copies) + 0.25 * std::min(work, copies);
+    const double tail = nnz - all_entries, lines = lines_touched(dim, k, val_bytes), miss = 1.0 - hot_share(g, 4e6 / ((double)dim * val_bytes));
+    if (shares > sh.head)
+        seconds += 6e-6 + tail * std::max(lines * (5.0 + 12.0 * miss), 12.0 + 0.55 * k) * 1e-12 + (double)(shares - sh.head) * 200e-12;
+    return seconds;
+}
+
+// The layout for a shape (n_sets = 0: the other kernels are taken).  Even: as many sets as CUs (or fewer, in ranges of the rows),
+// all sweeping the rows in step, so that an XCD brings a row into its L2 once.  By degree: as many sets as it takes.
+RegsShape regs_choice(maxk_graph* g, int dim, int val_bytes, int k)
+{
+    if (g->bwd_regs == 1) return RegsShape();
+    for (const auto& c : g->regs_choices)
+        if (c.dim == dim && c.val_bytes == val_bytes && c.k == k) return c.shape;
+    RegsShape best, base;
+    double seconds = HUGE_VAL, other = HUGE_VAL;
+    const int mode = auto_bwd_mode(g, dim, k, val_bytes, true, &other);
+    TiledShape tiled;
+    (void)tiled_shape(g->N, dim, k, tiled);
+    if (g->nnz > 0 && regs_fits(dim, val_bytes, k, base)) {
+        const int64_t D = (int64_t)regs_slots(base.kr) * base.groups * kRegsWaves;
+        // Even sets: a destination with many in-entries is several ones, or its wavefront's list holds up the others' at every
+        // step and its sum gets long.  By degree it is one: the sets that hold such ones are cut into units, and the entries
+        // of one share rows (8.0 against 6.7 ms on the graph of 2.4 M nodes, k = 64).
+        using Degrees = std::vector<std::pair<int32_t, int64_t>>;
+        const int64_t cap = std::max<int64_t>(64, std::min(8 * (g->nnz / g->N + 1), g->nnz / 16384));
+        Degrees capped;
+        for (const auto& [degree, n] : g->in_degrees) {
+            const int64_t m = degree > cap ? (degree + cap - 1) / cap : 1;
+            capped.emplace_back((int32_t)(degree / m), n * m);
+        }
+        std::stable_sort(capped.begin(), capped.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+        int64_t capped_shares = 0;
+        for (const auto& [degree, n] : capped) capped_shares += n;
+        const auto consider = [&](int64_t sets, int64_t spread, int32_t ranges) {
+            RegsShape sh = base;
+            const Degrees& degrees = ranges ? capped : g->in_degrees;
+            const int64_t shares = ranges ? capped_shares : g->N;
+            sh.cap = ranges ? cap : g->nnz;
+            sh.n_sets = (int32_t)sets;
+            sh.spread = (int32_t)spread;
+            sh.ranges = ranges;
+            // No kernel's sums get longer: the tiled one adds up a source range, slab pull eight rows at a time, the others short
+            // sums in several lane groups.
+            sh.run = mode != MAXK_BWD_TILED ? (mode == MAXK_BWD_SLAB_PULL ? 32 : 12) : ranges >= tiled.R ? 0 : 64;
+            sh.head = std::min<int64_t>(shares, sets * D);
+            // the tail is the end of the pull's item list: none of its destinations may be several or split there
+            int64_t above = 0;
+            for (const auto& [degree, n] : degrees) {
+                if (degree < std::min<int64_t>(g->chunk, sh.cap) / 2) break;
+                above += n;
+            }
+            if (sh.head < shares && sh.head < above && g->max_in_degree >= std::min<int64_t>(g->chunk, sh.cap) / 2) return;
+            const double t = regs_cost(g, degrees, sh, dim, val_bytes, k);
+            if (t < seconds) { seconds = t; best = sh; }
+        };
+        for (int R = 1; R <= 8 && g->bwd_regs != 3; R *= 2) consider(256 / R, 256 / R, R);
+        for (int64_t rounds = 2; rounds <= 8 && g->bwd_regs != 3 && (rounds - 1) * 256 * D < capped_shares; ++rounds) consider(256 * rounds, 256, 1);
+        int64_t nodes = 0;
+        int next = 128;
+        for (const auto& [degree, n] : g->in_degrees) {
+            while (nodes > 0 && degree < next && next >= 4) {
+                consider((nodes + D - 1) / D, 1, 0);
+                next /= 2;
+            }
+            nodes += n;
+        }
+        if (g->bwd_regs == 3) consider((nodes + D - 1) / D, 1, 0);
+    }
+    if (g->bwd_regs < 2 && !(seconds < (other < 600e-6 ? 0.7 : 0.9) * other)) best = RegsShape();
+    try {
+        g->regs_choices.push_back({dim, val_bytes, k, best});
+    } catch (const std::bad_alloc&) {  // then it is worked out again
+    }
+    return best;
 }
 
 // The backward kernel of a call and the tables it walks, which are built where they are missing.
@@ -1163,6 +1330,7 @@ struct BwdPlan {
     int mode = MAXK_BWD_PULL_CSC;
     bool sliced = false;  // the pull's column-sliced form
     TiledSet* T = nullptr;
+    RegsSet* M = nullptr;  // the register-tiled kernel stands in for `mode`
     SlabSet* S = nullptr;
 };
 
@@ -1174,6 +1342,13 @@ maxk_status plan_bwd(maxk_graph* g, int dim, int k, int vb, bool tiled_ok, const
     const bool automatic = g->bwd_mode == MAXK_BWD_AUTO;
     const auto captured = [&] { return stream && capturing(*stream); };
     const auto existing_only = [&] { return automatic && captured(); };
+    if (automatic && aligned(dY, 16)) {
+        const RegsShape sh = regs_choice(g, dim, vb, k);
+        if (sh.n_sets && !is_refused(g, regs_key(sh))) {
+            const maxk_status st = regs_for(g, sh, captured, &plan.M);
+            if (st == MAXK_OK || st == MAXK_HIP_ERROR) return st;
+        }
+    }
     int mode = automatic ? auto_bwd_mode(g, dim, k, vb, tiled_ok) : g->bwd_mode;
     for (;;) {
         maxk_status st = MAXK_OK;
@@ -1230,6 +1405,7 @@ maxk_status reserve_shape(maxk_graph* g, int dim, int k, int dy_value_type)
     forget_refused(g, sliced_key(g, dim, vb));
     TiledShape sh;
     if (tiled_shape(g->N, dim, k, sh)) forget_refused(g, tiled_key(sh, k));
+    if (const RegsShape rs = regs_choice(g, dim, vb, k); rs.n_sets) forget_refused(g, regs_key(rs));
     BwdPlan plan;
     return g->nnz ? plan_bwd(g, dim, k, vb, true, nullptr, nullptr, plan) : MAXK_OK;
 }
@@ -1270,6 +1446,7 @@ MAXK_API maxk_status maxk_graph_create(maxk_graph** out, int64_t N, int64_t nnz,
     g->fwd_pack_max = env_int("MAXK_FWD_PACK_MAX", 96, 0, 1 << 20);
     g->fwd_sweep = env_int("MAXK_FWD_SWEEP", 0, 0, 2);
     g->pull_form = env_int("MAXK_PULL_FORM", 0, 0, 2);
+    g->bwd_regs = env_int("MAXK_BWD_REGS", 0, 0, 3);
     (void)hipGetDevice(&g->device);
     {
         const maxk_status sst = noalloc_scratch_address(&g->d_noalloc_scratch);
@@ -1305,6 +1482,15 @@ MAXK_API maxk_status maxk_graph_create(maxk_graph** out, int64_t N, int64_t nnz,
         if (st != MAXK_OK) goto fail;
         build_items(h_csc_ptr, N, g->chunk, items, split, n_slots, max_len);
         g->max_in_degree = max_len;
+        {
+            std::vector<int32_t> degrees((size_t)N);
+            for (int64_t j = 0; j < N; ++j) degrees[(size_t)j] = h_csc_ptr[(size_t)j + 1] - h_csc_ptr[(size_t)j];
+            std::sort(degrees.begin(), degrees.end(), [](int32_t a, int32_t b) { return a > b; });
+            for (const int32_t d : degrees) {
+                if (g->in_degrees.empty() || g->in_degrees.back().first != d) g->in_degrees.emplace_back(d, 0);
+                ++g->in_degrees.back().second;
+            }
+        }
         st = upload_items(items, split, n_slots, g->csc_items, s);
         if (st != MAXK_OK) goto fail;
     } catch (const std::bad_alloc&) {
@@ -1336,6 +1522,7 @@ MAXK_API maxk_status maxk_graph_destroy(maxk_graph* g)
     for (char* p : g->sliced_before) (void)hipFree(p);
     for (SlabSet* S : g->slab_cache) { free_slabs(*S); delete S; }
     for (TiledSet* T : g->tiled_cache) { free_tiled(*T); delete T; }
+    for (RegsSet* T : g->regs_cache) { free_regs(*T); delete T; }
     for (SweepSet* W : g->sweep_cache) { free_sweep(*W); delete W; }
     (void)hipFree(g->d_partials);
     delete g;
@@ -1380,8 +1567,12 @@ MAXK_API maxk_status maxk_graph_info(const maxk_graph* g, int64_t* N, int64_t* n
     if (n_split_rows) *n_split_rows = g->csr_items.n_split;
     if (max_degree) *max_degree = g->max_degree;
     if (workspace_bytes)
-        *workspace_bytes = (g->partial_floats + g->expand_floats) * (int64_t)sizeof(float) + g->packed_bytes + g->sliced_bytes +
+    {
+        int64_t regs = 0;
+        for (const RegsSet* T : g->regs_cache) regs += (T->part_floats + T->extra_floats) * (int64_t)sizeof(float);
+        *workspace_bytes = regs + (g->partial_floats + g->expand_floats) * (int64_t)sizeof(float) + g->packed_bytes + g->sliced_bytes +
                            g->sliced_before_bytes;
+    }
     return MAXK_OK;
 }
 
@@ -1491,6 +1682,16 @@ MAXK_API maxk_status maxk_sspmm_bwd_narrow(maxk_graph* g, const void* d_dY, int3
     BwdPlan plan;
     st = plan_bwd(g, dim, k, vb, tiled_supports(d_dY, value_type, d_sp_index, index_bytes, dim, k), d_dY, &s, plan);
     if (st != MAXK_OK) return st;
+    if (plan.M) {
+        st = launch_bwd_regs(*plan.M, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs, s);
+        const int64_t tail = plan.M->n_tail;
+        if (st != MAXK_OK || tail <= 0) return st;
+        ItemList rest = g->csc_items;
+        rest.d_items += rest.n_items - tail;
+        rest.n_items = tail;
+        rest.n_split = rest.n_slots = 0;
+        return launch_bwd_pull(rest, g->d_csc_src, g->d_csc_val, d_dY, value_type, d_sp_index, index_bytes, dim, k, d_dXs, g->d_partials, s);
+    }
     if (plan.mode == MAXK_BWD_TILED)
         return launch_bwd_tiled(*plan.T, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs, s);
     if (plan.mode == MAXK_BWD_SLAB_PULL)
@@ -1572,6 +1773,8 @@ MAXK_API maxk_status maxk_graph_cached_tables(const maxk_graph* g, int32_t* n_sl
 }
 
 MAXK_API int32_t maxk_lone_visit_line(int32_t longest, int64_t entries) { return lone_visit_line(longest, entries); }
+
+MAXK_API int32_t maxk_graph_regs_tables(const maxk_graph* g) { return g ? (int32_t)g->regs_cache.size() : MAXK_INVALID_ARGUMENT; }
 
 MAXK_API int32_t maxk_graph_sweep_tables(const maxk_graph* g) { return g ? (int32_t)g->sweep_cache.size() : MAXK_INVALID_ARGUMENT; }
 
