@@ -1267,6 +1267,15 @@ RegsShape regs_choice(maxk_graph* g, int dim, int val_bytes, int k)
     const int mode = auto_bwd_mode(g, dim, k, val_bytes, true, &other);
     TiledShape tiled;
     (void)tiled_shape(g->N, dim, k, tiled);
+    if (mode == MAXK_BWD_SLAB_PULL) {
+        // Its line above was fitted where rows are long and degrees even.  Short rows cost their entries' instructions, few
+        // entries a visit the visits, and a hub's visits end their launches late: us, the line above / measured, 31 M entries on
+        // 96 k skewed nodes, width 128, bf16 539 / 3593; 39 M on 540 k, width 384 7515 / 11970; 27 M on 409 k, width 64, bf16 486 / 1456.
+        const double N = (double)g->N, nnz = (double)g->nnz, slabs = std::ceil(N / slab_rows_for(g, dim, val_bytes));
+        const double visits = N * slabs * -std::expm1(-nnz / (N * slabs));
+        other = std::max(0.85 * other, nnz * std::max((lines_touched(dim, k, val_bytes) + 0.35) * 4.3e-12, 27e-12) + visits * 45e-12 + slabs * 10e-6 +
+                                           15e-9 * (double)g->max_in_degree);
+    }
     if (g->nnz > 0 && regs_fits(dim, val_bytes, k, base)) {
         const int64_t D = (int64_t)regs_slots(base.kr) * base.groups * kRegsWaves;
         // Even sets: a destination with many in-entries is several ones, or its wavefront's list holds up the others' at every
