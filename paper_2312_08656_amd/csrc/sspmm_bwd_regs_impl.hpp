@@ -56,27 +56,27 @@ typedef float regs_v16 __attribute__((ext_vector_type(16)));
 #define ALL "s_mov_b64 exec, -1\n"
 
 // One batch in two halves.  ADDR: the accumulators' numbers, LDS addresses, the LDS reads under way.  FMA: what they brought,
-// times the weights, into the accumulators.  S0..S7: scalar registers of the batch, D0..D3: its data, M and X: the records,
+// times the weights, into the accumulators.  (All lanes add up a first address, the later lane groups then their own.)  S0..S7: scalar registers of the batch, D0..D3: its data, M and X: the records,
 // E0..E3: slots.
 // one destination a register (32 < k <= 64): four entries
 #define ADDR_1(LD, S0, S1, S2, S3, S4, S5, S6, S7, D0, D1, D2, D3, M, X, E0, E1, E2, E3)                                        \
     RL(S0, M, E0) RL(S1, M, E1) RL(S2, M, E2) RL(S3, M, E3)                                                                   \
-    ON_C(S0) AT(D0, M, E0) LD(D0) IDX(S1) AT(D1, M, E1) LD(D1) IDX(S2) AT(D2, M, E2) LD(D2) IDX(S3) AT(D3, M, E3) LD(D3) OFF
+    ON_C(S0) AT(D0, M, E0) LD(D0) IDX(S1) AT(D1, M, E1) LD(D1) IDX(S2) AT(D2, M, E2) LD(D2) IDX(S3) AT(D3, M, E3) LD(D3) LD##_END
 #define FMA_1(CV, S0, S1, S2, S3, S4, S5, S6, S7, D0, D1, D2, D3, M, X, E0, E1, E2, E3)                                         \
     CV(D0) CV(D1) CV(D2) CV(D3)                                                                                               \
     ON_A(S0) MAD(D0, X, E0) IDX(S1) MAD(D1, X, E1) IDX(S2) MAD(D2, X, E2) IDX(S3) MAD(D3, X, E3) OFF
 // two registers a destination (k > 64): two entries
 #define ADDR_W(LD, S0, S1, S2, S3, S4, S5, S6, S7, D0, D1, D2, D3, M, X, E0, E1)                                                \
     RL(S0, M, E0) RL(S1, M, E1)                                                                                               \
-    ON_C(S0) AT(D0, M, E0) LD(D0) AT2(D1, M, E0) LD(D1) IDX(S1) AT(D2, M, E1) LD(D2) AT2(D3, M, E1) LD(D3) OFF
+    ON_C(S0) AT(D0, M, E0) LD(D0) AT2(D1, M, E0) LD(D1) IDX(S1) AT(D2, M, E1) LD(D2) AT2(D3, M, E1) LD(D3) LD##_END
 #define FMA_W(CV, S0, S1, S2, S3, S4, S5, S6, S7, D0, D1, D2, D3, M, X, E0, E1)                                                 \
     CV(D0) CV(D1) CV(D2) CV(D3)                                                                                               \
     ON_A(S0) MAD(D0, X, E0) MAD2(D1, X, E0) IDX(S1) MAD(D2, X, E1) MAD2(D3, X, E1) OFF
 // two destinations a register (16 < k <= 32): four pairs
 #define ADDR_2(LD, S0, S1, S2, S3, S4, S5, S6, S7, D0, D1, D2, D3, M, X, E0, E1, E2, E3)                                        \
     RL(S0, M, E0) RL(S1, M, E1) RL(S2, M, E2) RL(S3, M, E3) RL(S4, M, "32+" E0) RL(S5, M, "32+" E1) RL(S6, M, "32+" E2) RL(S7, M, "32+" E3) \
-    LANES("32", "0") ON_C(S0) AT(D0, M, E0) IDX(S1) AT(D1, M, E1) IDX(S2) AT(D2, M, E2) IDX(S3) AT(D3, M, E3)                   \
-    LANES("32", "32") IDX(S4) AT(D0, M, E0) IDX(S5) AT(D1, M, E1) IDX(S6) AT(D2, M, E2) IDX(S7) AT(D3, M, E3) OFF               \
+    ON_C(S0) AT(D0, M, E0) IDX(S1) AT(D1, M, E1) IDX(S2) AT(D2, M, E2) IDX(S3) AT(D3, M, E3)                   \
+    LANES("32", "32") IDX(S4) AT(D0, M, E0) IDX(S5) AT(D1, M, E1) IDX(S6) AT(D2, M, E2) IDX(S7) AT(D3, M, E3) LD##_END          \
     ALL LD(D0) LD(D1) LD(D2) LD(D3)
 #define FMA_2(CV, S0, S1, S2, S3, S4, S5, S6, S7, D0, D1, D2, D3, M, X, E0, E1, E2, E3)                                         \
     CV(D0) CV(D1) CV(D2) CV(D3)                                                                                               \
@@ -85,8 +85,8 @@ typedef float regs_v16 __attribute__((ext_vector_type(16)));
 // four destinations a register (k <= 16): two quads
 #define ADDR_4(LD, S0, S1, S2, S3, S4, S5, S6, S7, D0, D1, D2, D3, M, X, E0, E1)                                                \
     RL(S0, M, E0) RL(S1, M, E1) RL(S2, M, "16+" E0) RL(S3, M, "16+" E1) RL(S4, M, "32+" E0) RL(S5, M, "32+" E1) RL(S6, M, "48+" E0) RL(S7, M, "48+" E1) \
-    LANES("16", "0") ON_C(S0) AT(D0, M, E0) IDX(S1) AT(D1, M, E1) LANES("16", "16") IDX(S2) AT(D0, M, E0) IDX(S3) AT(D1, M, E1)  \
-    LANES("16", "32") IDX(S4) AT(D0, M, E0) IDX(S5) AT(D1, M, E1) LANES("16", "48") IDX(S6) AT(D0, M, E0) IDX(S7) AT(D1, M, E1) OFF \
+    ON_C(S0) AT(D0, M, E0) IDX(S1) AT(D1, M, E1) LANES("16", "16") IDX(S2) AT(D0, M, E0) IDX(S3) AT(D1, M, E1)  \
+    LANES("16", "32") IDX(S4) AT(D0, M, E0) IDX(S5) AT(D1, M, E1) LANES("16", "48") IDX(S6) AT(D0, M, E0) IDX(S7) AT(D1, M, E1) LD##_END \
     ALL LD(D0) LD(D1)
 #define FMA_4(CV, S0, S1, S2, S3, S4, S5, S6, S7, D0, D1, D2, D3, M, X, E0, E1)                                                 \
     CV(D0) CV(D1)                                                                                                             \
@@ -95,6 +95,8 @@ typedef float regs_v16 __attribute__((ext_vector_type(16)));
 
 #define LD_F32(D) "ds_read_b32 " D ", " D "\n"
 #define LD_16(D) "ds_read_u16 " D ", " D "\n"
+#define LD_F32_END ""  // the next vector instruction sets its own mode
+#define LD_16_END OFF  // ... is a conversion
 #define CV_F32(D) ""
 #define CV_BF16(D) "v_lshlrev_b32 " D ", 16, " D "\n"
 #define CV_F16(D) "v_cvt_f32_f16 " D ", " D "\n"
