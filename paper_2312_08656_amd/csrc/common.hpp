@@ -142,9 +142,9 @@ constexpr RegsLayout regs_layout(int pitch)
 }
 constexpr int regs_batch_records(int groups, int kr) { return kr == 2 ? 1 : groups == 1 ? 2 : 4; }  // a list is whole batches
 struct RegsUnit { int32_t set, begin, end, part_begin, part_end; };  // steps [begin, end) of a set, and its parts (none: the set is one part)
-struct RegsSum { int32_t set, part_begin, part_end; };  // the parts of a set
+struct RegsSum { int32_t set, whole_begin, whole_end, hot_begin, hot_end; };  // the parts of a set in which all slots leave, and the others
 struct RegsSplit { int32_t node, row_begin, row_end; };  // a destination that is several ones: their rows of `extra`
-struct RegsPart { int32_t end, slots; };  // step behind its last; the sums of that many slots leave then, kRegsHotSlots or all
+struct RegsPart { int32_t end, slots; int64_t at; };  // step behind its last; the sums of that many slots leave then, kRegsHotSlots or all; where to
 // Destinations are dealt to slots most in-entries first: the sums of the first slots get long first.
 constexpr int kRegsHotSlots = 16;  // (a multiple of the four registers that leave at a time)
 struct RegsShape {
@@ -170,7 +170,7 @@ struct RegsSet {
     RegsUnit* d_unit = nullptr;
     RegsPart* d_part = nullptr;
     float* d_parts = nullptr;      // partial sums of sets in several parts (a call's workspace)
-    int64_t part_floats = 0;
+    int64_t part_floats = 0, hot_parts = 0;  // the parts in which only the first slots leave begin at hot_parts
     RegsSum* d_sum = nullptr;      // the sets in several parts
     int64_t n_sums = 0;
 };

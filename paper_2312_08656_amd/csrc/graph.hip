@@ -1242,7 +1242,7 @@ double regs_cost(const maxk_graph* g, const std::vector<std::pair<int32_t, int64
         if (even) {
             const double p = std::min(1.0, used / N), missed = (1.0 - std::pow(1.0 - p, 32.0)) / (32.0 * std::max(p, 1e-9));
             seconds += std::max(run_work, rows_factor * (0.65e-6 + 2.5e-6 * missed) * steps);
-            if (cold > 0.0 && sh.run) seconds += 19e-6 * std::min(32.0, cold_squares / cold / sh.run) + 40e-6;  // sums that leave the registers
+            if (cold > 0.0 && sh.run) seconds += 10e-6 * std::min(32.0, cold_squares / cold / sh.run) + 40e-6;  // sums that leave the registers
         } else {
             work += run_work;
             copies += rows_factor * 1.5e-6 * steps;

@@ -23,7 +23,7 @@ struct RegsArgs {
     int64_t N;
     const RegsUnit* unit;    // one per workgroup
     const RegsPart* part;
-    float* parts;            // [parts][8 wavefronts][accumulators][64 lanes] sums of a part
+    float* parts;            // sums that left: of a part [8 wavefronts][its accumulators][64 lanes]
     uint32_t row_bytes;
     int32_t k, index_bytes;
 };
@@ -496,9 +496,9 @@ __global__ __launch_bounds__(kRegsWaves* kWave) __attribute__((amdgpu_waves_per_
             else { MAXK_REGS_FORMAT(LD_16, CV_F16) }
 #undef MAXK_REGS_FORMAT
             if (u.begin + s + 1 == part_end) {  // the sums of a part leave, and the next one starts from zero
-                char* const out = reinterpret_cast<char*>(a.parts + ((int64_t)part * kRegsWaves + wave) * (SLOTS * KR * kWave));
-                const uint32_t at = lane4();
                 const int leaving = part_list[part].slots * KR;
+                char* const out = reinterpret_cast<char*>(a.parts + (part_list[part].at + (int64_t)wave * leaving * kWave));
+                const uint32_t at = lane4();
                 for (int r0 = 0; r0 < leaving; r0 += 4) {
                     float x[4];
 #pragma unroll
