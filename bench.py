@@ -188,7 +188,7 @@ def main() -> int:
     dom_name, dom_ms, dom_bytes = max((("maxk_spgemm_fwd", t_fwd, ab["fwd"]), ("maxk_sspmm_bwd", t_bwd, ab["bwd"])),
                                       key=lambda t: t[1])
     achieved = dom_bytes / (dom_ms * 1e-3) / 1e9
-    dom_kernel = gr.bwd_choice(dim, k0) if "bwd" in dom_name else "rmw"
+    dom_kernel = gr.bwd_kernel(dim, k0) if "bwd" in dom_name else "rmw"
     tr = measured_traffic(cfg.name, k0, dom_name, dom_kernel)
     roofline = {"bound": "hbm", "kernel": dom_name, "device_kernel": dom_kernel, "achieved": round(achieved, 1),
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
@@ -258,7 +258,7 @@ def main() -> int:
             row.update({"bwd_bf16_dY_ms": round(t16, 4)})
             del dY16
             tb, _ = timeit(lambda: maxk.maxk_sspmm_bwd(gr, dYd, si, dx), args.sweep_reps, warm=1)
-            row.update({"bwd_auto_kernel": gr.bwd_choice(dim, k),
+            row.update({"bwd_auto_kernel": gr.bwd_kernel(dim, k),
                         "bwd_ms": round(tb, 4), "bwd_edges_k_per_s": nnz * k / (tb * 1e-3),
                         "bwd_hbm_frac": round(b["bwd"] / (tb * 1e-3) / 8e12, 4),
                         "bwd_speedup_vs_spmm": round(spmm_ms / tb, 2),
@@ -313,7 +313,7 @@ def main() -> int:
         "config": {"workload": f"{cfg.name}: R-MAT graph N={N} nnz={nnz} (stands for: {cfg.stands_for}), "
                                f"dim={dim}, k={k0}, uint{8 * ib} sp_index, GCN weights, H,dY~N(0,1)",
                    "N": N, "nnz": nnz, "dim": dim, "k": k0, "max_degree": g.meta.get("max_degree"),
-                   "bwd_mode": args.bwd_mode, "bwd_kernel": gr.bwd_choice(dim, k0),
+                   "bwd_mode": args.bwd_mode, "bwd_kernel": gr.bwd_kernel(dim, k0),
                    "graph_handle": gr.info()},
         "step_breakdown_ms": {"topk_cbsr": round(t_topk, 4), "spgemm_fwd": round(t_fwd, 4),
                               "sspmm_bwd": round(t_bwd, 4)},

@@ -20,7 +20,7 @@ EXPORTS = (
     "maxk_topk_cbsr", "maxk_spgemm_fwd", "maxk_spgemm_fwd_noalloc", "maxk_topk_cbsr_narrow", "maxk_spgemm_fwd_narrow", "maxk_sspmm_bwd",
     "maxk_sspmm_bwd_narrow", "maxk_cbsr_scatter", "spmm_baseline", "maxk_status_string",
     "maxk_last_hip_error", "maxk_version", "maxk_fwd_private_copies", "maxk_graph_cached_tables", "maxk_graph_sweep_tables",
-    "maxk_graph_regs_tables",
+    "maxk_graph_regs_tables", "maxk_graph_regs_stands_in",
     "maxk_graph_limit_allocations", "maxk_expand_past_l2", "maxk_scatter_past_l2", "maxk_lone_visit_line",
 )
 
@@ -77,6 +77,8 @@ def load_library() -> ctypes.CDLL:
     lib.maxk_graph_sweep_tables.restype = i32
     lib.maxk_graph_regs_tables.argtypes = [vp]
     lib.maxk_graph_regs_tables.restype = i32
+    lib.maxk_graph_regs_stands_in.argtypes = [vp, i32, i32, i32]
+    lib.maxk_graph_regs_stands_in.restype = i32
     lib.maxk_graph_limit_allocations.argtypes = [vp, i64]
     lib.maxk_graph_limit_allocations.restype = i64
     lib.maxk_expand_past_l2.argtypes = [i64, i64, i32, i32, i32, i32]
@@ -173,6 +175,12 @@ class MaxKGraph:
     def sweep_tables(self) -> int:
         """Regroupings of A for the forward sweep that the handle holds -- a test hook."""
         return int(load_library().maxk_graph_sweep_tables(self.handle))
+
+    def bwd_kernel(self, dim: int, k: int, dy_dtype=torch.float32) -> str:
+        """bwd_choice, or "register_tiled" where that kernel stands in for it."""
+        if load_library().maxk_graph_regs_stands_in(self.handle, dim, k, _VALUE_TYPE[dy_dtype]) == 1:
+            return "register_tiled"
+        return self.bwd_choice(dim, k)
 
     def regs_tables(self) -> int:
         """Regroupings of A^T for the register-tiled backward kernel that the handle holds."""

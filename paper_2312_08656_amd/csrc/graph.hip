@@ -1783,6 +1783,18 @@ MAXK_API maxk_status maxk_graph_cached_tables(const maxk_graph* g, int32_t* n_sl
 
 MAXK_API int32_t maxk_lone_visit_line(int32_t longest, int64_t entries) { return lone_visit_line(longest, entries); }
 
+MAXK_API int32_t maxk_graph_regs_stands_in(maxk_graph* g, int32_t dim, int32_t k, int32_t dy_value_type)
+{
+    if (!g || dim < 1 || k < 1 || k > dim || dy_value_type < MAXK_VALUE_F32 || dy_value_type > MAXK_VALUE_F16) return MAXK_INVALID_ARGUMENT;
+    try {
+        if (g->bwd_mode != MAXK_BWD_AUTO || g->nnz == 0) return 0;
+        const RegsShape sh = regs_choice(g, dim, value_bytes(dy_value_type), k);
+        return sh.n_sets && !is_refused(g, regs_key(sh));
+    } catch (const std::bad_alloc&) {
+        return MAXK_OUT_OF_MEMORY;
+    }
+}
+
 MAXK_API int32_t maxk_graph_regs_tables(const maxk_graph* g) { return g ? (int32_t)g->regs_cache.size() : MAXK_INVALID_ARGUMENT; }
 
 MAXK_API int32_t maxk_graph_sweep_tables(const maxk_graph* g) { return g ? (int32_t)g->sweep_cache.size() : MAXK_INVALID_ARGUMENT; }

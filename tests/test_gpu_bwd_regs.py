@@ -132,8 +132,10 @@ def test_refused_memory_and_misaligned_rows_take_the_other_kernels(monkeypatch):
     N, dim, k = 2000, 256, 32
     rowptr, col, val, dY, index, want = _case(N, 50_000, dim, k, "f32", 7)
     gr = _graph(monkeypatch, "2", rowptr, col, val)
+    assert gr.bwd_kernel(dim, k) == "register_tiled"
     gr.limit_allocations(0)
     assert torch.equal(_run(gr, dY, index, 1), want)
+    assert gr.bwd_kernel(dim, k) == gr.bwd_choice(dim, k)
     gr.limit_allocations(-1)
     assert torch.equal(_run(gr, dY, index, 1), want) and gr.regs_tables() == 0  # asked for again by a reserve only
     gr.reserve(dim, k)
