@@ -8,9 +8,9 @@
 // added to the register numbers of an instruction (VGPR index mode).  Against accumulators in LDS (sspmm_bwd_tiled.hip) that
 // leaves one LDS access of three an entry, no read-add-write for the next entry to wait for, and twice the destinations a
 // workgroup, so half the rows to bring; against the pull kernels a row is brought once per set instead of once per entry.
-// us, before / now, width 256 unless said (115 M entries on 233 k nodes): k = 32 4790 / 2480 (tiled), k = 64 5370 / 3850 and bf16 dY
-// 3970 / 3060 (slab pull), k = 128 6280 / 5770; 126 M on 2.4 M nodes, k = 64 14600 / 6740 (pull); 14.7 M directed on 717 k, width 384,
-// k = 96 2390 / 1640 (pull); 43 M on 576 k, k = 32 2900 / 2450 (expand/reduce).
+// us, before / now, width 256 unless said (115 M entries on 233 k nodes): k = 32 4760 / 2405 (tiled), k = 64 5380 / 3570 and bf16 dY
+// 3970 / 2825 (slab pull), k = 128 6270 / 5355; 126 M on 2.4 M nodes, k = 64 14870 / 6560 (pull); 14.7 M directed on 717 k, width 384,
+// k = 96 2385 / 1593 (pull); 43 M on 576 k, k = 32 2770 / 2382 (expand/reduce).
 //
 // Sets.  Destinations are sorted by in-entries, so that a wavefront's lists are about equal.  With as many even sets as CUs, all
 // CUs sweep the rows in step and an XCD brings a row into its L2 once; where a set uses few of the rows (large sparse
