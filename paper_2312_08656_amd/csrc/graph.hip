@@ -1208,44 +1208,45 @@ double regs_rows(const maxk_graph* g, double x)
     return rows;
 }
 
-// Seconds of a call with the sets of `sh`, the destinations behind its head by plain pull.  A step costs its instructions
-// (0.37 us, and 3.9 to 6.5 ns an entry) or its rows: 0.65 us where they come from L2, 2.5 us more where each comes from
-// beyond (even sets: an XCD's 32 CUs bring what one of them uses; by degree: 1.5 us); rows of two copies 1.5 times.
+// Seconds of a call with the sets of `sh`, the destinations behind its head by plain pull.  A step costs its entries (3.6 to 6.8
+// ns each) and its rows: 0.63 us where they come from L2, 1.32 us more where each comes from beyond (even sets: an XCD's 32 CUs
+// bring what one of them uses; by degree: 1.5 us), and the one hides a fifth of the other.  Fitted to 190 shapes of 1 k to 2.4 M
+// nodes, degree 8 to 600: 8 % rms (even sets; 26 % before sums were added up with 16-byte loads), by degree 0.9 to 1.2 from 400 us up.
 double regs_cost(const maxk_graph* g, const std::vector<std::pair<int32_t, int64_t>>& degrees, const RegsShape& sh, int dim, int val_bytes, int k)
 {
     const double N = (double)g->N, nnz = (double)g->nnz, room = (double)regs_slots(sh.kr) * sh.groups * kRegsWaves * sh.spread;
-    const double tile = regs_layout(sh.pitch).rows * kRegsWaves, rows_factor = sh.pitch > 1024 ? 1.5 : 1.0;
-    const double b = sh.kr == 2 ? 6.5e-9 : sh.groups == 1 ? 4.4e-9 : sh.groups == 2 ? 3.9e-9 : 5e-9;
+    const double tile = regs_layout(sh.pitch).rows * kRegsWaves, rows_factor = sh.pitch > 1024 ? 1.15 : 1.0;
+    const double b = sh.kr == 2 ? 6.8e-9 : sh.groups == 1 ? 4.6e-9 : sh.groups == 2 ? 3.55e-9 : 4.2e-9;
     const double hot = room * kRegsHotSlots / regs_slots(sh.kr);
     const bool even = sh.ranges > 0;
     int64_t shares = 0;
     for (const auto& [degree, n] : degrees) shares += n;
-    double seconds = even ? 60e-6 : 180e-6, all_entries = 0.0, work = 0.0, copies = 0.0;
+    double seconds = even ? 44e-6 : 180e-6, all_entries = 0.0, work = 0.0, copies = 0.0;
     auto run = degrees.begin();
     double nodes = run == degrees.end() ? 0.0 : (double)run->second, left = (double)sh.head;
     while (left > 0.0 && run != degrees.end()) {  // a run of `spread` sets at a time
-        double in_run = std::min(room, left), at = 0.0, entries = 0.0, cold = 0.0, cold_squares = 0.0;
+        double in_run = std::min(room, left), at = 0.0, entries = 0.0;
         left -= in_run;
+        bool cold = false;
         while (in_run > 0.0 && run != degrees.end()) {
-            const double now = std::min(nodes, in_run), d = (double)run->first, behind = std::max(0.0, at + now - std::max(at, hot));
+            const double now = std::min(nodes, in_run), d = (double)run->first;
             entries += now * d;
-            cold += behind * d;
-            cold_squares += behind * d * d;
             at += now;
+            cold = cold || (at > hot && d > 0.0);
             in_run -= now;
             nodes -= now;
             if (nodes <= 0.0 && ++run != degrees.end()) nodes = (double)run->second;
         }
         all_entries += entries;
         const double used = regs_rows(g, entries / nnz / sh.spread), steps = sh.spread * std::max(1.0, used / tile) / 256.0;
-        const double run_work = 0.37e-6 * steps + b * entries / 256.0;
         if (even) {
             const double p = std::min(1.0, used / N), missed = (1.0 - std::pow(1.0 - p, 32.0)) / (32.0 * std::max(p, 1e-9));
-            seconds += std::max(run_work, rows_factor * (0.65e-6 + 2.5e-6 * missed) * steps);
-            if (cold > 0.0 && sh.run) seconds += 10e-6 * std::min(32.0, cold_squares / cold / sh.run) + 40e-6;  // sums that leave the registers
+            const double run_work = b * entries / 256.0, run_copies = rows_factor * (0.63e-6 + 1.32e-6 * missed) * steps;
+            seconds += std::max(run_work, run_copies) + 0.8 * std::min(run_work, run_copies);
+            if (cold && sh.run) seconds += 10e-6;  // the sums that leave the registers are added up
         } else {
-            work += run_work;
-            copies += rows_factor * 1.5e-6 * steps;
+            work += 0.37e-6 * steps + b * entries / 256.0;
+            copies += 1.5e-6 * steps * (sh.pitch > 1024 ? 1.5 : 1.0);
         }
     }
     seconds += std::max(work, copies) + 0.25 * std::min(work, copies);
@@ -1271,10 +1272,12 @@ RegsShape regs_choice(maxk_graph* g, int dim, int val_bytes, int k)
         // Its line above was fitted where rows are long and degrees even.  Short rows cost their entries' instructions, few
         // entries a visit the visits, and a hub's visits end their launches late: us, the line above / measured, 31 M entries on
         // 96 k skewed nodes, width 128, bf16 539 / 3593; 39 M on 540 k, width 384 7515 / 11970; 27 M on 409 k, width 64, bf16 486 / 1456.
+        // (The sampled form has fewer instructions an entry: 108 M on 371 k, width 128, k = 8, bf16 1954.)
+        const bool sampled = val_bytes == 4 ? 8 * k < dim : 16 * k <= dim;
         const double N = (double)g->N, nnz = (double)g->nnz, slabs = std::ceil(N / slab_rows_for(g, dim, val_bytes));
         const double visits = N * slabs * -std::expm1(-nnz / (N * slabs));
-        other = std::max(0.85 * other, nnz * std::max((lines_touched(dim, k, val_bytes) + 0.35) * 4.3e-12, 27e-12) + visits * 45e-12 + slabs * 10e-6 +
-                                           15e-9 * (double)g->max_in_degree);
+        const double entry = std::max((lines_touched(dim, k, val_bytes) + 0.35) * 4.3e-12, sampled ? 16e-12 : 27e-12);
+        other = std::max(0.85 * other, nnz * entry + visits * 45e-12 + slabs * 10e-6 + 15e-9 * (double)g->max_in_degree);
     }
     if (g->nnz > 0 && regs_fits(dim, val_bytes, k, base)) {
         const int64_t D = (int64_t)regs_slots(base.kr) * base.groups * kRegsWaves;
@@ -1326,7 +1329,12 @@ RegsShape regs_choice(maxk_graph* g, int dim, int val_bytes, int k)
         }
         if (g->bwd_regs == 3) consider((nodes + D - 1) / D, 1, 0);
     }
-    if (g->bwd_regs < 2 && !(seconds < (other < 600e-6 ? 0.7 : 0.9) * other)) best = RegsShape();
+    // The others' lines over what was measured on 190 shapes: slab pull 0.45 to 1.3, mostly below 1; pull and tiled 0.9 to 1.2;
+    // expand/reduce 1.0 to 1.2, but 1.2 to 1.6 where dY stays in the 256 MB Infinity Cache.  This kernel's: 0.75 to 1.25.
+    const bool small = other < 600e-6;
+    const double line = mode == MAXK_BWD_SLAB_PULL ? (small ? 0.9 : 1.0)
+                        : mode == MAXK_BWD_EXPAND_REDUCE ? ((double)g->N * dim * val_bytes > 256e6 ? 0.85 : 0.7) : (small ? 0.8 : 0.9);
+    if (g->bwd_regs < 2 && !(seconds < line * other)) best = RegsShape();
     try {
         g->regs_choices.push_back({dim, val_bytes, k, best});
     } catch (const std::bad_alloc&) {  // then it is worked out again
