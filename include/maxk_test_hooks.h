@@ -38,6 +38,13 @@ MAXK_API int32_t maxk_graph_regs_stands_in(maxk_graph* g, int32_t dim, int32_t k
 /* How many regroupings of A^T for the register-tiled backward kernel the handle holds (kept like the tables above). */
 MAXK_API int32_t maxk_graph_regs_tables(const maxk_graph* g);
 
+/* What a wavefront of that kernel copies of its list in step `step` of a tile: first record, records. */
+MAXK_API maxk_status maxk_regs_step_list(uint32_t record0, uint32_t records, uint32_t step, uint32_t* first, uint32_t* copied);
+
+/* Copies table `which` of the i-th of those regroupings to host memory (nothing where out is NULL) and returns its bytes, or a
+ * negative maxk_status: 0 sizes (int64 each), 1 records, 2 headers, 3 destinations, 4 rows, 5 units, 6 parts, 7 sums, 8 splits. */
+MAXK_API int64_t maxk_graph_regs_table(const maxk_graph* g, int32_t i, int32_t which, void* out, int64_t bytes);
+
 /* From here on the handle's tables, the slice-major copy and the expand/reduce buffer are refused, as if memory had run
  * out, when they take more than `bytes` (a table: 8 an entry); negative: no limit.  Returns how many were refused so far. */
 MAXK_API int64_t maxk_graph_limit_allocations(maxk_graph* g, int64_t bytes);

@@ -20,7 +20,7 @@ EXPORTS = (
     "maxk_topk_cbsr", "maxk_spgemm_fwd", "maxk_spgemm_fwd_noalloc", "maxk_topk_cbsr_narrow", "maxk_spgemm_fwd_narrow", "maxk_sspmm_bwd",
     "maxk_sspmm_bwd_narrow", "maxk_cbsr_scatter", "spmm_baseline", "maxk_status_string",
     "maxk_last_hip_error", "maxk_version", "maxk_fwd_private_copies", "maxk_graph_cached_tables", "maxk_graph_sweep_tables",
-    "maxk_graph_regs_tables", "maxk_graph_regs_stands_in",
+    "maxk_graph_regs_tables", "maxk_graph_regs_stands_in", "maxk_regs_step_list", "maxk_graph_regs_table",
     "maxk_graph_limit_allocations", "maxk_expand_past_l2", "maxk_scatter_past_l2", "maxk_lone_visit_line",
 )
 
@@ -79,6 +79,10 @@ def load_library() -> ctypes.CDLL:
     lib.maxk_graph_regs_tables.restype = i32
     lib.maxk_graph_regs_stands_in.argtypes = [vp, i32, i32, i32]
     lib.maxk_graph_regs_stands_in.restype = i32
+    lib.maxk_regs_step_list.argtypes = [ctypes.c_uint32] * 3 + [ctypes.POINTER(ctypes.c_uint32)] * 2
+    lib.maxk_regs_step_list.restype = i32
+    lib.maxk_graph_regs_table.argtypes = [vp, i32, i32, vp, i64]
+    lib.maxk_graph_regs_table.restype = i64
     lib.maxk_graph_limit_allocations.argtypes = [vp, i64]
     lib.maxk_graph_limit_allocations.restype = i64
     lib.maxk_expand_past_l2.argtypes = [i64, i64, i32, i32, i32, i32]

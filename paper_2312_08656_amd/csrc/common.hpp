@@ -134,6 +134,7 @@ struct TiledSet {
 constexpr int kRegsWaves = 8;            // wavefronts of a workgroup, one workgroup a CU
 constexpr int kRegsListRecords = 32;     // 16-byte records (two entries each) of a wavefront's list in one step
 constexpr int kRegsTileBuffers = 3;
+constexpr int kRegsSpareSteps = 4;       // headers behind the last step, which the kernel reads
 constexpr int regs_slots(int kr) { return kr == 2 ? 55 : 111; }  // destinations (per lane group) of a wavefront; one more takes the padding
 struct RegsLayout { int rows, head; };   // rows that a wavefront brings per step; 4-byte words of its header
 constexpr RegsLayout regs_layout(int pitch)
@@ -141,6 +142,16 @@ constexpr RegsLayout regs_layout(int pitch)
     return pitch == 256 ? RegsLayout{24, 32} : pitch == 512 ? RegsLayout{12, 16} : pitch == 1024 ? RegsLayout{6, 8} : pitch == 1536 ? RegsLayout{4, 8} : RegsLayout{3, 8};
 }
 constexpr int regs_batch_records(int groups, int kr) { return kr == 2 ? 1 : groups == 1 ? 2 : 4; }  // a list is whole batches
+// What a wavefront with `records` records from `record0` on in a tile works on in the tile's step i.  The kernel copies at least one
+// record a step: where the list has ended (another wavefront's is longer), record 0, which is always there.
+struct RegsStepList { uint32_t first, records; };
+__host__ __device__ constexpr RegsStepList regs_step_list(uint32_t record0, uint32_t records, uint32_t i)
+{
+    const uint32_t done = i * (uint32_t)kRegsListRecords;
+    if (done >= records) return {0u, 0u};
+    return {record0 + done, records - done < (uint32_t)kRegsListRecords ? records - done : (uint32_t)kRegsListRecords};
+}
+constexpr uint32_t regs_copied(uint32_t records) { return records > 1u ? records : 1u; }
 struct RegsUnit { int32_t set, begin, end, part_begin, part_end; };  // steps [begin, end) of a set, and its parts (none: the set is one part)
 struct RegsSum { int32_t set, whole_begin, whole_end, hot_begin, hot_end; };  // the parts of a set in which all slots leave, and the others
 struct RegsSplit { int32_t node, row_begin, row_end; };  // a destination that is several ones: their rows of `extra`
@@ -170,7 +181,7 @@ struct RegsSet {
     RegsUnit* d_unit = nullptr;
     RegsPart* d_part = nullptr;
     float* d_parts = nullptr;      // partial sums of sets in several parts (a call's workspace)
-    int64_t part_floats = 0, hot_parts = 0;  // the parts in which only the first slots leave begin at hot_parts
+    int64_t n_parts = 0, part_floats = 0, hot_parts = 0;  // the parts in which only the first slots leave begin at hot_parts
     RegsSum* d_sum = nullptr;      // the sets in several parts
     int64_t n_sums = 0;
 };

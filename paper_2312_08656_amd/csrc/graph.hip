@@ -1805,6 +1805,45 @@ MAXK_API int32_t maxk_graph_regs_stands_in(maxk_graph* g, int32_t dim, int32_t k
 
 MAXK_API int32_t maxk_graph_regs_tables(const maxk_graph* g) { return g ? (int32_t)g->regs_cache.size() : MAXK_INVALID_ARGUMENT; }
 
+MAXK_API maxk_status maxk_regs_step_list(uint32_t record0, uint32_t records, uint32_t step, uint32_t* first, uint32_t* copied)
+{
+    if (!first || !copied) return MAXK_INVALID_ARGUMENT;
+    const RegsStepList list = regs_step_list(record0, records, step);
+    *first = list.first;
+    *copied = regs_copied(list.records);
+    return MAXK_OK;
+}
+
+MAXK_API int64_t maxk_graph_regs_table(const maxk_graph* g, int32_t i, int32_t which, void* out, int64_t bytes)
+{
+    if (!g || i < 0 || (size_t)i >= g->regs_cache.size()) return MAXK_INVALID_ARGUMENT;
+    const RegsSet& T = *g->regs_cache[(size_t)i];
+    const RegsShape& sh = T.shape;
+    const RegsLayout layout = regs_layout(sh.pitch);
+    const int64_t slots = regs_slots(sh.kr), accumulators = (int64_t)sh.n_sets * kRegsWaves * slots * sh.groups;
+    const int64_t sizes[] = {sh.pitch, sh.groups, sh.kr, sh.n_sets, sh.spread, sh.ranges, sh.run, sh.cap, sh.head, slots, layout.rows, layout.head,
+                             T.n_steps, T.n_records, T.n_units, T.n_parts, T.n_sums, T.n_split, T.n_tail, T.part_floats, T.hot_parts,
+                             T.extra_floats};
+    const std::pair<const void*, int64_t> tables[] = {
+        {nullptr, (int64_t)sizeof(sizes)},
+        {T.d_rec, T.n_records * (int64_t)sizeof(uint4)},
+        {T.d_hdr, (T.n_steps + kRegsSpareSteps) * kRegsWaves * layout.head * (int64_t)sizeof(uint32_t)},
+        {T.d_node, accumulators * (int64_t)sizeof(int32_t)},
+        {T.d_row, accumulators * (int64_t)sizeof(int32_t)},
+        {T.d_unit, T.n_units * (int64_t)sizeof(RegsUnit)},
+        {T.d_part, T.n_parts * (int64_t)sizeof(RegsPart)},
+        {T.d_sum, T.n_sums * (int64_t)sizeof(RegsSum)},
+        {T.d_split, T.n_split * (int64_t)sizeof(RegsSplit)},
+    };
+    if (which < 0 || which >= (int32_t)std::size(tables)) return MAXK_INVALID_ARGUMENT;
+    const auto [at, n] = tables[which];
+    if (!out || n == 0) return n;
+    if (bytes < n) return MAXK_INVALID_ARGUMENT;
+    if (which == 0) std::memcpy(out, sizes, sizeof(sizes));
+    else MAXK_HIP_TRY(hipMemcpy(out, at, (size_t)n, hipMemcpyDeviceToHost));
+    return n;
+}
+
 MAXK_API int32_t maxk_graph_sweep_tables(const maxk_graph* g) { return g ? (int32_t)g->sweep_cache.size() : MAXK_INVALID_ARGUMENT; }
 
 MAXK_API int64_t maxk_graph_limit_allocations(maxk_graph* g, int64_t bytes)

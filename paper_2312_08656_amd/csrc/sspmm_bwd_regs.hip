@@ -31,7 +31,6 @@ namespace {
 
 constexpr double kRegsMaxParts[2] = {64.0, 32.0};  // of a set: for the first slots, and for all
 constexpr double kRegsUnitCost = 2000.0;  // a unit by cost: about 200 us, against some 25 to begin and end one
-constexpr int kRegsSpareSteps = 4;          // headers behind the last step, which the kernel reads
 constexpr uint32_t kNowhere = 0xFFFFFFFFu;  // place of a destination that is in no set
 
 // a destination's place: accumulator | lane group << 8 | wavefront << 10 | set << 13
@@ -251,23 +250,19 @@ __global__ __launch_bounds__(256) void regs_headers_kernel(const RegsTables t, c
     const uint32_t local = (uint32_t)(tile - t.tile0[lo]);
     const int64_t first = (int64_t)lo * t.words;
     const uint32_t row_begin = t.before[first], row_end = t.before[first + t.words];
-    uint32_t records = regs_list_records(t, start, tile, w);
+    const uint32_t records = regs_list_records(t, start, tile, w);
     for (uint32_t s = step0[tile], i = 0; s < step0[tile + 1]; ++s, ++i) {
-        const uint32_t here = min(records, (uint32_t)kRegsListRecords);
-        records -= here;
+        const RegsStepList list = regs_step_list(record0[tile * kRegsWaves + w], records, i);
         uint32_t* const h = hdr + ((int64_t)s * kRegsWaves + w) * head;
-        h[0] = record0[tile * kRegsWaves + w] + i * kRegsListRecords;
-        h[1] = here / (uint32_t)regs_batch_records(t.groups, t.kr) | (uint32_t)tile % kRegsTileBuffers << 8;
+        h[0] = list.first;
+        h[1] = list.records / (uint32_t)regs_batch_records(t.groups, t.kr) | (uint32_t)tile % kRegsTileBuffers << 8;
         for (int r = 0; r < rows_per_wave; ++r) {
             const uint32_t at = row_begin + local * (uint32_t)t.tile_rows + (uint32_t)(w * rows_per_wave + r);
             h[2 + r] = rows[min(at, row_end - 1)];
         }
         if (w == 0) {
             uint32_t longest = 0;
-            for (int v = 0; v < kRegsWaves; ++v) {
-                const uint32_t all = regs_list_records(t, start, tile, v), done = i * kRegsListRecords;
-                longest = max(longest, all > done ? min(all - done, (uint32_t)kRegsListRecords) : 0u);
-            }
+            for (int v = 0; v < kRegsWaves; ++v) longest = max(longest, regs_step_list(0u, regs_list_records(t, start, tile, v), i).records);
             cost[s] = (uint8_t)longest;
             pos[s] = (uint32_t)t.rank[rows[min(row_begin + local * (uint32_t)t.tile_rows, row_end - 1)]];
         }
@@ -529,8 +524,8 @@ maxk_status build_regs(RegsSet& T, const RegsShape& shape, int64_t N, int64_t nn
         free_regs(T);
         return MAXK_UNSUPPORTED;
     }
-    // the kernel reads two headers and their lists past its last step: empty ones, and a record's room behind the last
-    const int64_t all_steps = (int64_t)n_steps + kRegsSpareSteps, all_records = (int64_t)n_records + 64;
+    // the kernel reads headers past its last step, and their lists: empty ones, at record 0 like every empty list
+    const int64_t all_steps = (int64_t)n_steps + kRegsSpareSteps, all_records = std::max<int64_t>(n_records, 1);
     MAXK_TRY_CLEAN(hipMalloc((void**)&T.d_hdr, sizeof(uint32_t) * (size_t)(all_steps * kRegsWaves * layout.head)));
     MAXK_TRY_CLEAN(hipMalloc((void**)&T.d_rec, sizeof(uint4) * (size_t)all_records));
     MAXK_TRY_CLEAN(get(d_cost, n_steps));
@@ -641,6 +636,7 @@ maxk_status build_regs(RegsSet& T, const RegsShape& shape, int64_t N, int64_t nn
     T.n_sums = (int64_t)sums.size();
     T.n_steps = n_steps;
     T.n_records = n_records;
+    T.n_parts = (int64_t)part_end.size();
     return MAXK_OK;
 }
 

@@ -456,7 +456,7 @@ __global__ __launch_bounds__(kRegsWaves* kWave) __attribute__((amdgpu_waves_per_
                 if constexpr (PITCH == 2048) regs_copy(row1 + off, dst + i * PITCH + 1024);
                 if constexpr (PITCH == 1536) regs_copy_some(row1 + off, dst + i * PITCH + 1024, 32);
             }
-            regs_copy_list(rec0 + (uint64_t)first * 16u, lane16, list0 + slot * kListStride, max(nb * (uint32_t)regs_batch_records(G, KR), 1u));
+            regs_copy_list(rec0 + (uint64_t)first * 16u, lane16, list0 + slot * kListStride, regs_copied(nb * (uint32_t)regs_batch_records(G, KR)));
             slot = slot == 2 ? 0 : slot + 1;
             regs_copy_head(head_at, lane4(), head0 + (uint32_t)((s + 2) & 3) * kHeadStride, L.head);
             head_at += (uint64_t)kHeadStride;
