@@ -297,7 +297,9 @@ typedef float regs_v16 __attribute__((ext_vector_type(16)));
                  : "memory", "scc", "v24", "v25", "v26", "v27", "v28", "v29", "v30", "v31", "s48", "s49", "s50", "s51", "s52", "s53", \
                    "s54", "s55", "s56", "s57", "s58", "s59", "s60", "s61", "s62", "s63", "s64")
 
-// 16 bytes a lane from `from` to LDS at `to` + 16 * lane (4 bytes with _4), without a register in between
+// 16 bytes a lane from `from` to LDS at `to` + 16 * lane (4 bytes: regs_copy_head), without a register in between.  All are
+// called where every lane of the wavefront is on, which is what they leave.  (M0, which they and the index mode set, is a register that
+// the compiler reserves: it sets it right before each use of its own and holds nothing in it over a statement.)
 __device__ __forceinline__ void regs_copy(uint64_t from, uint32_t to)
 {
     asm volatile("s_mov_b32 m0, %1\n s_nop 0\n global_load_lds_dwordx4 %0, off" ::"v"(from), "s"(to) : "memory");
@@ -308,16 +310,17 @@ __device__ __forceinline__ void regs_copy_some(uint64_t from, uint32_t to, uint3
                  "s"(lanes)
                  : "memory");
 }
-// the same from a uniform address + `offset`
+// The same from a uniform address + `offset`.  A scalar register that a vector instruction wrote (a lane read, a spill) may be an
+// address five wait states later; the compiler counts none inside the statement, so they are all here.
 __device__ __forceinline__ void regs_copy_list(uint64_t from, uint32_t offset, uint32_t to, uint32_t lanes)
 {
-    asm volatile("s_mov_b32 m0, %2\n s_bfm_b64 exec, %3, 0\n global_load_lds_dwordx4 %1, %0\n s_mov_b64 exec, -1" ::"s"(from), "v"(offset), "s"(to),
+    asm volatile("s_mov_b32 m0, %2\n s_nop 2\n s_bfm_b64 exec, %3, 0\n global_load_lds_dwordx4 %1, %0\n s_mov_b64 exec, -1" ::"s"(from), "v"(offset), "s"(to),
                  "s"(lanes)
                  : "memory");
 }
 __device__ __forceinline__ void regs_copy_head(uint64_t from, uint32_t offset, uint32_t to, uint32_t lanes)
 {
-    asm volatile("s_mov_b32 m0, %2\n s_bfm_b64 exec, %3, 0\n global_load_lds_dword %1, %0\n s_mov_b64 exec, -1" ::"s"(from), "v"(offset), "s"(to),
+    asm volatile("s_mov_b32 m0, %2\n s_nop 2\n s_bfm_b64 exec, %3, 0\n global_load_lds_dword %1, %0\n s_mov_b64 exec, -1" ::"s"(from), "v"(offset), "s"(to),
                  "s"(lanes)
                  : "memory");
 }
