@@ -163,6 +163,7 @@ struct RegsShape {
     int32_t n_sets = 0, spread = 0;         // sets; sets that a run of destinations is dealt over (1: sets by falling degree)
     int32_t ranges = 0;                     // units a set (0: by cost)
     int32_t run = 0;                        // entries that a destination adds up before its sum leaves the registers, about (0: a unit's)
+    int32_t longest = 0;                    // entries that it may at most (0: as many as it has)
     int64_t cap = 0;                        // in-entries of a destination above which it is several ones, with every n-th entry each
     int64_t head = 0;                       // destinations in the sets; the others have the fewest in-entries
     bool operator==(const RegsShape&) const = default;

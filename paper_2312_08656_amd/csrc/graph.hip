@@ -1256,6 +1256,14 @@ double regs_cost(const maxk_graph* g, const std::vector<std::pair<int32_t, int64
     return seconds;
 }
 
+// What a running sum of the pull takes at most: a lane group's share of a piece of `chunk` entries, four at a time.  (Slab pull by rows
+// takes eight at a time and stores a sum per slab: up to 450 of either at 1 KB a row.)
+int pull_longest(const maxk_graph* g, int k)
+{
+    const int groups = k > 32 ? 1 : kWave / (int)std::bit_ceil((uint32_t)k);
+    return std::min(g->chunk, 2048) / (4 * groups);
+}
+
 // The layout for a shape (n_sets = 0: the other kernels are taken).  Even: as many sets as CUs (or fewer, in ranges of the rows),
 // all sweeping the rows in step, so that an XCD brings a row into its L2 once.  By degree: as many sets as it takes.
 RegsShape regs_choice(maxk_graph* g, int dim, int val_bytes, int k)
@@ -1268,12 +1276,13 @@ RegsShape regs_choice(maxk_graph* g, int dim, int val_bytes, int k)
     const int mode = auto_bwd_mode(g, dim, k, val_bytes, true, &other);
     TiledShape tiled;
     (void)tiled_shape(g->N, dim, k, tiled);
+    bool sampled = false;
     if (mode == MAXK_BWD_SLAB_PULL) {
         // Its line above was fitted where rows are long and degrees even.  Short rows cost their entries' instructions, few
         // entries a visit the visits, and a hub's visits end their launches late: us, the line above / measured, 31 M entries on
         // 96 k skewed nodes, width 128, bf16 539 / 3593; 39 M on 540 k, width 384 7515 / 11970; 27 M on 409 k, width 64, bf16 486 / 1456.
         // (The sampled form has fewer instructions an entry: 108 M on 371 k, width 128, k = 8, bf16 1954.)
-        const bool sampled = val_bytes == 4 ? 8 * k < dim : 16 * k <= dim;
+        sampled = val_bytes == 4 ? 8 * k < dim : 16 * k <= dim;
         const double N = (double)g->N, nnz = (double)g->nnz, slabs = std::ceil(N / slab_rows_for(g, dim, val_bytes));
         const double visits = N * slabs * -std::expm1(-nnz / (N * slabs));
         const double entry = std::max((lines_touched(dim, k, val_bytes) + 0.35) * 4.3e-12, sampled ? 16e-12 : 27e-12);
@@ -1281,29 +1290,35 @@ RegsShape regs_choice(maxk_graph* g, int dim, int val_bytes, int k)
     }
     if (g->nnz > 0 && regs_fits(dim, val_bytes, k, base)) {
         const int64_t D = (int64_t)regs_slots(base.kr) * base.groups * kRegsWaves;
+        // No kernel's sums get longer.  The tiled one adds up a source range, slab pull's sampled form a destination's entries one by
+        // one, whatever their number; the others keep to what a running sum of the pull takes (64 is a step's share of a list).
+        const int32_t longest = mode == MAXK_BWD_TILED || sampled ? 0 : std::max(64, pull_longest(g, k));
         // Even sets: a destination with many in-entries is several ones, or its wavefront's list holds up the others' at every
-        // step and its sum gets long.  By degree it is one: the sets that hold such ones are cut into units, and the entries
-        // of one share rows (8.0 against 6.7 ms on the graph of 2.4 M nodes, k = 64).
+        // step and its sum gets long.  By degree few are: the sets that hold such ones are cut into units, and the entries
+        // of one share rows (2.4 M nodes, k = 64: 8.0 ms with the even sets' line, 6.7 without one).
         using Degrees = std::vector<std::pair<int32_t, int64_t>>;
-        const int64_t cap = std::max<int64_t>(64, std::min(8 * (g->nnz / g->N + 1), g->nnz / 16384));
-        Degrees capped;
-        for (const auto& [degree, n] : g->in_degrees) {
-            const int64_t m = degree > cap ? (degree + cap - 1) / cap : 1;
-            capped.emplace_back((int32_t)(degree / m), n * m);
-        }
-        std::stable_sort(capped.begin(), capped.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
-        int64_t capped_shares = 0;
-        for (const auto& [degree, n] : capped) capped_shares += n;
+        const auto capped_at = [&](int64_t cap, Degrees& out) {
+            int64_t shares = 0;
+            for (const auto& [degree, n] : g->in_degrees) {
+                const int64_t m = degree > cap ? (degree + cap - 1) / cap : 1;
+                out.emplace_back((int32_t)(degree / m), n * m);
+                shares += n * m;
+            }
+            std::stable_sort(out.begin(), out.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+            return shares;
+        };
+        const int64_t cap = std::max<int64_t>(64, std::min(8 * (g->nnz / g->N + 1), g->nnz / 16384)), hub_cap = longest ? 64ll * longest : g->nnz;
+        Degrees capped, hubs_capped;
+        const int64_t capped_shares = capped_at(cap, capped), hubs_capped_shares = capped_at(hub_cap, hubs_capped);
         const auto consider = [&](int64_t sets, int64_t spread, int32_t ranges) {
             RegsShape sh = base;
-            const Degrees& degrees = ranges ? capped : g->in_degrees;
-            const int64_t shares = ranges ? capped_shares : g->N;
-            sh.cap = ranges ? cap : g->nnz;
+            const Degrees& degrees = ranges ? capped : hubs_capped;
+            const int64_t shares = ranges ? capped_shares : hubs_capped_shares;
+            sh.cap = ranges ? cap : hub_cap;
             sh.n_sets = (int32_t)sets;
             sh.spread = (int32_t)spread;
             sh.ranges = ranges;
-            // No kernel's sums get longer: the tiled one adds up a source range, slab pull eight rows at a time, the others short
-            // sums in several lane groups.
+            sh.longest = longest;
             sh.run = mode != MAXK_BWD_TILED ? (mode == MAXK_BWD_SLAB_PULL ? 32 : 12) : ranges >= tiled.R ? 0 : 64;
             sh.head = std::min<int64_t>(shares, sets * D);
             // the tail is the end of the pull's item list: none of its destinations may be several or split there
@@ -1320,7 +1335,7 @@ RegsShape regs_choice(maxk_graph* g, int dim, int val_bytes, int k)
         for (int64_t rounds = 2; rounds <= 8 && g->bwd_regs != 3 && (rounds - 1) * 256 * D < capped_shares; ++rounds) consider(256 * rounds, 256, 1);
         int64_t nodes = 0;
         int next = 128;
-        for (const auto& [degree, n] : g->in_degrees) {
+        for (const auto& [degree, n] : hubs_capped) {
             while (nodes > 0 && degree < next && next >= 4) {
                 consider((nodes + D - 1) / D, 1, 0);
                 next /= 2;
@@ -1821,7 +1836,7 @@ MAXK_API int64_t maxk_graph_regs_table(const maxk_graph* g, int32_t i, int32_t w
     const RegsShape& sh = T.shape;
     const RegsLayout layout = regs_layout(sh.pitch);
     const int64_t slots = regs_slots(sh.kr), accumulators = (int64_t)sh.n_sets * kRegsWaves * slots * sh.groups;
-    const int64_t sizes[] = {sh.pitch, sh.groups, sh.kr, sh.n_sets, sh.spread, sh.ranges, sh.run, sh.cap, sh.head, slots, layout.rows, layout.head,
+    const int64_t sizes[] = {sh.pitch, sh.groups, sh.kr, sh.n_sets, sh.spread, sh.ranges, sh.run, sh.longest, sh.cap, sh.head, slots, layout.rows, layout.head,
                              T.n_steps, T.n_records, T.n_units, T.n_parts, T.n_sums, T.n_split, T.n_tail, T.part_floats, T.hot_parts,
                              T.extra_floats};
     const std::pair<const void*, int64_t> tables[] = {

@@ -83,8 +83,9 @@ __global__ __launch_bounds__(256) void regs_share_kernel(const int32_t* __restri
 // Shares in falling order of in-entries are dealt to the lists (set, wavefront, lane group) of `spread` sets forth and
 // back, so that the lists of a run of sets have about the same number of entries.
 __global__ __launch_bounds__(256) void regs_place_kernel(const int32_t* __restrict__ order, const int2* __restrict__ goes, int64_t n_shares, int64_t head,
-                                                         int32_t spread, int32_t groups, int32_t slots, int32_t kr, uint32_t* __restrict__ place,
-                                                         int32_t* __restrict__ node, int32_t* __restrict__ row)
+                                                         int32_t spread, int32_t groups, int32_t slots, int32_t kr,
+                                                         const uint32_t* __restrict__ degree, uint32_t* __restrict__ place,
+                                                         int32_t* __restrict__ node, int32_t* __restrict__ row, uint32_t* __restrict__ entries)
 {
     const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (q >= n_shares) return;
@@ -102,6 +103,7 @@ __global__ __launch_bounds__(256) void regs_place_kernel(const int32_t* __restri
     const int64_t to = ((int64_t)set * kRegsWaves + w) * (slots * groups) + slot * groups + g;
     node[to] = goes[v].x;
     row[to] = goes[v].y;
+    entries[to] = degree[q];
 }
 
 // rank[] of order[]
@@ -287,6 +289,40 @@ __global__ __launch_bounds__(256) void regs_records_kernel(const RegsTables t, c
     }
 }
 
+// Counts, where each sum of a part will be stored, the entries that go into it - of the accumulators that have more than `longest` -
+// and notes for every set the largest count above that, of the first slots and of the others.
+__global__ __launch_bounds__(256) void regs_longest_kernel(const RegsTables t, const uint32_t* __restrict__ key, const uint2* __restrict__ entry, int64_t n,
+                                                           const uint32_t* __restrict__ start, const uint32_t* __restrict__ step0, int32_t n_sets,
+                                                           int32_t slots, const uint32_t* __restrict__ entries, const int2* __restrict__ part_range,
+                                                           const RegsPart* __restrict__ part, uint32_t longest, uint32_t* __restrict__ count,
+                                                           uint32_t* __restrict__ most)
+{
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < n; p += stride) {
+        const uint32_t l = key[p], g = l % (uint32_t)t.groups, w = l / (uint32_t)t.groups % kRegsWaves, tile = l / (uint32_t)t.groups / kRegsWaves;
+        int32_t set = 0, hi = n_sets;  // as in regs_headers_kernel
+        while (hi - set > 1) {
+            const int32_t mid = (set + hi) >> 1;
+            if (t.tile0[mid] <= tile) set = mid; else hi = mid;
+        }
+        const int32_t slot = (int32_t)((entry[p].x & 0xFFu) / (uint32_t)t.kr);
+        if (entries[(((int64_t)set * kRegsWaves + w) * slots + slot) * t.groups + g] <= longest) continue;
+        const uint32_t e = (uint32_t)p - start[l], record = (t.groups == 1 ? e : e * (uint32_t)t.groups + g) / 2;
+        const uint32_t step = step0[tile] + record / (uint32_t)kRegsListRecords;
+        int32_t at = part_range[set].x, last = part_range[set].y - 1;  // the first part that ends behind the step
+        if (at > last) continue;
+        while (at < last) {
+            const int32_t mid = (at + last) >> 1;
+            if ((uint32_t)part[mid].end > step) last = mid; else at = mid + 1;
+        }
+        const bool hot = slot < kRegsHotSlots;
+        while (!hot && part[at].slots != slots) ++at;  // (the last part of a unit has them all)
+        const int64_t to = part[at].at + (((int64_t)w * part[at].slots + slot) * t.kr * kWave + g);
+        const uint32_t now = atomicAdd(count + to, 1u) + 1u;
+        if (now > longest) atomicMax(most + 2 * set + (hot ? 0 : 1), now);
+    }
+}
+
 }  // namespace
 
 bool regs_fits(int dim, int val_bytes, int k, RegsShape& sh)
@@ -420,8 +456,10 @@ maxk_status build_regs(RegsSet& T, const RegsShape& shape, int64_t N, int64_t nn
     MAXK_TRY_CLEAN(hipMalloc((void**)&T.d_row, sizeof(int32_t) * (size_t)(per_set * S)));
     MAXK_TRY_CLEAN(hipMemsetAsync(T.d_node, 0xFF, sizeof(int32_t) * (size_t)(per_set * S), s));
     MAXK_TRY_CLEAN(hipMemsetAsync(T.d_row, 0xFF, sizeof(int32_t) * (size_t)(per_set * S), s));
+    uint32_t* d_entries;
+    MAXK_TRY_CLEAN(get(d_entries, per_set * S));
     hipLaunchKernelGGL(regs_place_kernel, blocks(n_shares), dim3(256), 0, s, d_order, d_goes, n_shares, shape.head, shape.spread, shape.groups, slots,
-                       shape.kr, d_place, T.d_node, T.d_row);
+                       shape.kr, d_degree_sorted, d_place, T.d_node, T.d_row, d_entries);
     MAXK_TRY_CLEAN(hipGetLastError());
 
     // The order that a set takes its rows in.  By degree: sources with most entries first, so that the sets that run at a time
@@ -547,49 +585,127 @@ maxk_status build_regs(RegsSet& T, const RegsShape& shape, int64_t N, int64_t nn
 
     // Units: a set's steps, cut by what they cost.  Parts: a unit's steps, cut where the sums of a destination get long: a
     // set's mean in-entries (seen from an entry) over `run` times, at most kRegsMaxParts; the first slots by themselves, oftener.
+    // That is a mean: a hub has more entries than its set's, and they may crowd into few of the steps.  So no sum may take more
+    // than `longest` either: the entries of every sum that could are counted, and a set where one does is cut more often.  (126 M
+    // entries on 2.4 M nodes, k = 64, the eight destinations of up to 156 k in-entries: error against 64 bits 8.5e-7 by the mean alone,
+    // some 1,900 entries a sum, 2.9e-7 so, pull 4.9e-7; 6.67 / 6.62 ms, 5 ms more to build.)
     std::vector<uint32_t> degree((size_t)shape.head);
     MAXK_TRY_CLEAN(hipMemcpy(degree.data(), d_degree_sorted, sizeof(uint32_t) * degree.size(), hipMemcpyDeviceToHost));
     std::vector<RegsUnit> units;
     std::vector<RegsSum> sums;
     std::vector<RegsPart> part_end;
+    std::vector<int2> part_range((size_t)S);
+    struct Parts { double least[2] = {}, have[2] = {}; };  // of the first slots and of the others: asked for by `longest`; cut
+    std::vector<Parts> parts_of((size_t)S);
     const auto step_cost = [&](uint32_t st) { return std::max(14.0, 8.0 + (double)cost[st]); };
     double total = 0.0;
     for (uint32_t st = 0; st < n_steps; ++st) total += step_cost(st);
     const double share = total / (256.0 * std::clamp(std::round(total / (256.0 * kRegsUnitCost)), 1.0, 4.0)) + 1.0;
-    for (int32_t set = 0; set < S; ++set) {
-        const uint32_t b = step0[tile0[(size_t)set]], e = step0[tile0[(size_t)set + 1]];
-        double all = 0.0, entries[2] = {}, squares[2] = {};  // of the first slots and of the others
-        for (uint32_t st = b; st < e; ++st) all += step_cost(st);
-        const int64_t run0 = set / shape.spread * (per_set * shape.spread), run1 = std::min<int64_t>(run0 + per_set * shape.spread, shape.head);
-        for (int64_t q = run0; q < run1; q += shape.spread) {
-            const int cold = (q - run0) / (per_set / slots * shape.spread) >= kRegsHotSlots;
-            entries[cold] += degree[(size_t)q];
-            squares[cold] += (double)degree[(size_t)q] * degree[(size_t)q];
-        }
-        const int pieces = shape.ranges ? shape.ranges : std::max(1, (int)(all / share + 0.5));
-        const auto wanted = [&](int cold) {
-            return shape.run && entries[cold] > 0.0 ? std::min(kRegsMaxParts[cold], squares[cold] / entries[cold] / shape.run) : 1.0;
-        };
-        const auto times = [](double a, int b) { return std::max(1, (int)std::ceil(a / b)); };
-        const int whole = times(wanted(1), pieces), per_unit = whole * times(wanted(0), pieces * whole), parts = pieces * per_unit;
-        const int32_t first_part = (int32_t)part_end.size();
-        uint32_t at = b;
-        double sum = 0.0;
-        for (int i = 0; i < pieces; ++i) {
-            RegsUnit u = {set, (int32_t)at, 0, (int32_t)part_end.size(), 0};
-            for (int j = 0; j < per_unit; ++j) {
-                const int cut = i * per_unit + j + 1;
-                const uint32_t from = at;
-                while (at < e && (cut == parts || sum < all * cut / parts)) sum += step_cost(at++);
-                const int leave = (j + 1) % (per_unit / whole) == 0 ? slots : kRegsHotSlots;
-                if (parts > 1 && at > from) part_end.push_back(RegsPart{(int32_t)at, leave, 0});
-                else if ((int32_t)part_end.size() > u.part_begin) part_end.back().slots = std::max(part_end.back().slots, leave);  // (fewer steps than parts)
+    const int64_t whole_floats = (int64_t)kRegsWaves * slots * shape.kr * kWave, hot_floats = (int64_t)kRegsWaves * kRegsHotSlots * shape.kr * kWave;
+    const int64_t per_run = per_set * shape.spread, hot_per_run = per_run / slots * kRegsHotSlots;
+    const auto cut = [&] {
+        units.clear();
+        sums.clear();
+        part_end.clear();
+        for (int32_t set = 0; set < S; ++set) {
+            const uint32_t b = step0[tile0[(size_t)set]], e = step0[tile0[(size_t)set + 1]];
+            Parts& of = parts_of[(size_t)set];
+            double all = 0.0, entries[2] = {}, squares[2] = {};  // of the first slots and of the others
+            for (uint32_t st = b; st < e; ++st) all += step_cost(st);
+            const int64_t run0 = set / shape.spread * per_run, run1 = std::min<int64_t>(run0 + per_run, shape.head);
+            for (int64_t q = run0; q < run1; q += shape.spread) {
+                const int cold = q - run0 >= hot_per_run;
+                entries[cold] += degree[(size_t)q];
+                squares[cold] += (double)degree[(size_t)q] * degree[(size_t)q];
             }
-            u.end = (int32_t)at;
-            u.part_end = (int32_t)part_end.size();
-            if (u.begin < u.end || parts == 1) units.push_back(u);
+            const int pieces = shape.ranges ? shape.ranges : std::max(1, (int)(all / share + 0.5));
+            const auto wanted = [&](int cold) {
+                const double mean = shape.run && entries[cold] > 0.0 ? std::min(kRegsMaxParts[cold], squares[cold] / entries[cold] / shape.run) : 1.0;
+                const int64_t first = run0 + (cold ? hot_per_run : 0);
+                if (shape.longest && first < run1) of.least[cold] = std::max(of.least[cold], (double)degree[(size_t)first] / shape.longest);
+                return std::max(mean, std::min(of.least[cold], 4.0 * (e - b)));
+            };
+            const auto times = [](double a, int b) { return std::max(1, (int)std::ceil(a / b)); };
+            const int whole = times(wanted(1), pieces), per_unit = whole * times(wanted(0), pieces * whole), parts = pieces * per_unit;
+            of.have[0] = parts;
+            of.have[1] = pieces * whole;
+            const int32_t first_part = (int32_t)part_end.size();
+            uint32_t at = b;
+            double sum = 0.0;
+            for (int i = 0; i < pieces; ++i) {
+                RegsUnit u = {set, (int32_t)at, 0, (int32_t)part_end.size(), 0};
+                for (int j = 0; j < per_unit; ++j) {
+                    const int cut = i * per_unit + j + 1;
+                    const uint32_t from = at;
+                    while (at < e && (cut == parts || sum < all * cut / parts)) sum += step_cost(at++);
+                    const int leave = (j + 1) % (per_unit / whole) == 0 ? slots : kRegsHotSlots;
+                    if (parts > 1 && at > from) part_end.push_back(RegsPart{(int32_t)at, leave, 0});
+                    else if ((int32_t)part_end.size() > u.part_begin) part_end.back().slots = std::max(part_end.back().slots, leave);  // (fewer steps than parts)
+                }
+                u.end = (int32_t)at;
+                u.part_end = (int32_t)part_end.size();
+                if (u.begin < u.end || parts == 1) units.push_back(u);
+            }
+            part_range[(size_t)set] = make_int2(first_part, (int32_t)part_end.size());
+            if (parts > 1) sums.push_back(RegsSum{set, first_part, (int32_t)part_end.size(), 0, 0});
         }
-        if (parts > 1) sums.push_back(RegsSum{set, first_part, (int32_t)part_end.size(), 0, 0});
+        // parts in which all slots leave first, set after set, then the others
+        int64_t n_whole = 0, n_hot = 0;
+        for (const RegsPart& x : part_end) (x.slots == slots ? n_whole : n_hot) += 1;
+        T.hot_parts = n_whole * whole_floats;
+        T.part_floats = T.hot_parts + n_hot * hot_floats;
+        int32_t whole = 0, hot = 0;
+        for (RegsSum& x : sums) {
+            const int32_t b = x.whole_begin, e = x.whole_end;
+            x.whole_begin = whole;
+            x.hot_begin = hot;
+            for (int32_t i = b; i < e; ++i) {
+                RegsPart& q = part_end[(size_t)i];
+                q.at = q.slots == slots ? whole++ * whole_floats : T.hot_parts + hot++ * hot_floats;
+            }
+            x.whole_end = whole;
+            x.hot_end = hot;
+        }
+    };
+    const bool limited = shape.longest && !degree.empty() && degree[0] > (uint32_t)shape.longest;
+    int2* d_part_range;
+    uint32_t* d_most;
+    MAXK_TRY_CLEAN(get(d_part_range, S));
+    MAXK_TRY_CLEAN(get(d_most, 2 * S));
+    for (int tries = 0;; ++tries) {
+        cut();
+        if (!sums.empty()) {
+            (void)hipFree(T.d_part);
+            (void)hipFree(T.d_parts);
+            T.d_part = nullptr;
+            T.d_parts = nullptr;
+            MAXK_TRY_CLEAN(hipMalloc((void**)&T.d_part, sizeof(RegsPart) * std::max<size_t>(part_end.size(), 1)));
+            MAXK_TRY_CLEAN(hipMalloc((void**)&T.d_parts, sizeof(float) * (size_t)std::max<int64_t>(T.part_floats, 1)));
+            MAXK_TRY_CLEAN(hipMemcpy(T.d_part, part_end.data(), sizeof(RegsPart) * part_end.size(), hipMemcpyHostToDevice));
+        }
+        if (!limited || part_end.empty()) break;
+        uint32_t* const count = reinterpret_cast<uint32_t*>(T.d_parts);
+        std::vector<uint32_t> most(2 * (size_t)S);
+        MAXK_TRY_CLEAN(hipMemcpy(d_part_range, part_range.data(), sizeof(int2) * part_range.size(), hipMemcpyHostToDevice));
+        MAXK_TRY_CLEAN(hipMemsetAsync(count, 0, sizeof(uint32_t) * (size_t)T.part_floats, s));
+        MAXK_TRY_CLEAN(hipMemsetAsync(d_most, 0, sizeof(uint32_t) * most.size(), s));
+        hipLaunchKernelGGL(regs_longest_kernel, wide, dim3(256), 0, s, t, d_key_sorted, d_entry_sorted, (int64_t)n_entries, d_start, d_step0, S, slots,
+                           d_entries, d_part_range, T.d_part, (uint32_t)shape.longest, count, d_most);
+        MAXK_TRY_CLEAN(hipGetLastError());
+        MAXK_TRY_CLEAN(hipMemcpy(most.data(), d_most, sizeof(uint32_t) * most.size(), hipMemcpyDeviceToHost));
+        bool good = true;
+        for (int32_t set = 0; set < S; ++set)
+            for (int c = 0; c < 2; ++c)
+                if (const uint32_t n = most[2 * (size_t)set + (size_t)c]; n) {
+                    parts_of[(size_t)set].least[c] = parts_of[(size_t)set].have[c] * std::max(1.25, 1.1 * n / shape.longest);
+                    good = false;
+                }
+        if (good) break;
+        // a graph whose order needs this many parts is for the other kernels
+        if (tries == 8 || (double)T.part_floats * sizeof(float) > 16.0 * (double)nnz + 256e6) {
+            free_regs(T);
+            return MAXK_UNSUPPORTED;
+        }
     }
     // 256 units run at a time, unit u on XCD u % 8: an XCD gets units that begin with about the same rows
     std::vector<RegsUnit> placed(units.size());
@@ -602,31 +718,10 @@ maxk_status build_regs(RegsSet& T, const RegsShape& shape, int64_t N, int64_t nn
             for (size_t m = x; m < n; m += 8) placed[c + m] = units[c + from++];
     }
     units.swap(placed);
-    // parts in which all slots leave first, set after set, then the others
-    const int64_t whole_floats = (int64_t)kRegsWaves * slots * shape.kr * kWave, hot_floats = (int64_t)kRegsWaves * kRegsHotSlots * shape.kr * kWave;
-    int64_t n_whole = 0, n_hot = 0;
-    for (const RegsPart& x : part_end) (x.slots == slots ? n_whole : n_hot) += 1;
-    T.hot_parts = n_whole * whole_floats;
-    T.part_floats = T.hot_parts + n_hot * hot_floats;
-    int32_t whole = 0, hot = 0;
-    for (RegsSum& x : sums) {
-        const int32_t b = x.whole_begin, e = x.whole_end;
-        x.whole_begin = whole;
-        x.hot_begin = hot;
-        for (int32_t i = b; i < e; ++i) {
-            RegsPart& q = part_end[(size_t)i];
-            q.at = q.slots == slots ? whole++ * whole_floats : T.hot_parts + hot++ * hot_floats;
-        }
-        x.whole_end = whole;
-        x.hot_end = hot;
-    }
     MAXK_TRY_CLEAN(hipMalloc((void**)&T.d_unit, sizeof(RegsUnit) * units.size()));
     MAXK_TRY_CLEAN(hipMemcpy(T.d_unit, units.data(), sizeof(RegsUnit) * units.size(), hipMemcpyHostToDevice));
     if (!sums.empty()) {
-        MAXK_TRY_CLEAN(hipMalloc((void**)&T.d_part, sizeof(RegsPart) * std::max<size_t>(part_end.size(), 1)));
-        MAXK_TRY_CLEAN(hipMalloc((void**)&T.d_parts, sizeof(float) * (size_t)std::max<int64_t>(T.part_floats, 1)));
         MAXK_TRY_CLEAN(hipMalloc((void**)&T.d_sum, sizeof(RegsSum) * sums.size()));
-        MAXK_TRY_CLEAN(hipMemcpy(T.d_part, part_end.data(), sizeof(RegsPart) * part_end.size(), hipMemcpyHostToDevice));
         MAXK_TRY_CLEAN(hipMemcpy(T.d_sum, sums.data(), sizeof(RegsSum) * sums.size(), hipMemcpyHostToDevice));
     }
 #undef MAXK_TRY_CLEAN

@@ -13,7 +13,7 @@ if torch.cuda.is_available():
     import paper_2312_08656_amd as maxk
 
 WAVES, RECORDS, BUFFERS, SPARE_STEPS, HOT = 8, 32, 3, 4, 16
-_SIZES = ("pitch", "groups", "kr", "n_sets", "spread", "ranges", "run", "cap", "head", "slots", "rows", "words", "n_steps", "n_records", "n_units",
+_SIZES = ("pitch", "groups", "kr", "n_sets", "spread", "ranges", "run", "longest", "cap", "head", "slots", "rows", "words", "n_steps", "n_records", "n_units",
           "n_parts", "n_sums", "n_split", "n_tail", "part_floats", "hot_parts", "extra_floats")
 
 
@@ -35,6 +35,36 @@ def table(gr, which, dtype, i=0):
 
 def sizes(gr, i=0):
     return dict(zip(_SIZES, table(gr, 0, np.int64, i).tolist(), strict=True))
+
+
+def longest_sum(gr):
+    """Most entries that an accumulator adds up before it is stored, from the records of every step."""
+    t = sizes(gr)
+    groups, kr, slots, steps = t["groups"], t["kr"], t["slots"], t["n_steps"]
+    head = table(gr, 2, np.uint32).reshape(-1, WAVES, t["words"])[:steps].astype(np.int64)
+    records = (head[..., 1] & 0xFF) * (1 if kr == 2 else 2 if groups == 1 else 4)
+    which = np.repeat(np.arange(steps * WAVES), records.ravel())
+    inside = np.arange(len(which)) - np.repeat(np.cumsum(records.ravel()) - records.ravel(), records.ravel())
+    acc = (table(gr, 1, np.uint32).reshape(-1, 2, 2)[:, :, 0] & 0xFF)[head[..., 0].ravel()[which] + inside].astype(np.int64)
+    group = np.zeros_like(acc) if groups == 1 else (2 * inside[:, None] + np.arange(2)) % groups
+    step, wave = np.repeat(which // WAVES, 2), np.repeat(which % WAVES, 2)
+    acc, group = acc.ravel(), group.ravel()
+    real = acc < slots * kr
+    step, wave, acc, group = step[real], wave[real], acc[real], group[real]
+    unit, part = table(gr, 5, np.int32).reshape(-1, 5), table(gr, 6, np.int32).reshape(-1, 4)
+    worst = 0
+    for hot in (False, True):
+        ends = np.unique(np.concatenate([unit[:, 2], part[part[:, 1] == slots, 0], part[:, 0] if hot else unit[:, 2]]))
+        mine = (acc < HOT * kr) == hot
+        sums = np.stack([np.searchsorted(ends, step[mine], side="right"), wave[mine], acc[mine], group[mine]])
+        if sums.size:
+            worst = max(worst, np.unique(sums, axis=1, return_counts=True)[1].max())
+    return worst
+
+
+def check_sums(gr):
+    longest = sizes(gr)["longest"]
+    assert longest == 0 or longest_sum(gr) <= longest
 
 
 def check_ranges(gr, N, k):
@@ -69,6 +99,8 @@ def check_ranges(gr, N, k):
     split = table(gr, 8, np.int32).reshape(-1, 3)
     assert (split[:, 0] < N).all() and (split[:, 1:] * k <= t["extra_floats"]).all() and (split[:, 1] < split[:, 2]).all()
     assert (np.sort(row[row >= N] - N) == np.arange(split[:, 2].max(initial=0))).all()
+
+    check_sums(gr)
 
     unit, part = table(gr, 5, np.int32).reshape(-1, 5), table(gr, 6, np.int32).reshape(-1, 4)
     at = part.view(np.int64)[:, 1] if len(part) else np.zeros(0, np.int64)
@@ -112,4 +144,38 @@ def test_uneven_lists(monkeypatch, how, N, nnz, dim, k, hubs):
     gr.reserve(dim, k)
     assert gr.regs_tables() == 1
     check_ranges(gr, N, k)
+    gr.destroy()
+
+
+def _hub(N, d, n):
+    """A hub of d in-entries beside n others; its sources crowd into the first tenth of the nodes."""
+    gen = torch.Generator(device="cuda").manual_seed(N + d)
+    src = torch.cat([torch.randint(N // 10, (d,), generator=gen, device="cuda"), torch.randint(N, (n,), generator=gen, device="cuda")])
+    dst = torch.cat([torch.full((d,), 7, device="cuda"), torch.randint(N, (n,), generator=gen, device="cuda")])
+    order = torch.argsort(src, stable=True)
+    rowptr = torch.zeros(N + 1, dtype=torch.int32, device="cuda")
+    rowptr[1:] = torch.cumsum(torch.bincount(src, minlength=N), 0)
+    return rowptr, dst[order].to(torch.int32)
+
+
+# Terms of 1.1 each: what an addition rounds off has the same sign over a whole binade of the sum, so errors add up instead of cancelling
+# (3000 of them: 2.7e-5).
+# A sum of n equal terms is off by at most (n + 1)/2 units of 2^-24 (half a unit of the running sum an addition); the stored sums are added up in
+# 64 bits, and a share and the result are rounded once each.
+@pytest.mark.parametrize("how,k", [("2", 64), ("3", 64), ("3", 100), ("3", 24), ("2", 24)])
+@pytest.mark.parametrize("N,d,n", [(20_000, 200_000, 200_000), (3000, 40_000, 30_000)])
+def test_hub_sums_are_short(monkeypatch, how, k, N, d, n):
+    dim = 256
+    rowptr, col = _hub(N, d, n)
+    gr = _graph(monkeypatch, how, rowptr, col, torch.ones(d + n, device="cuda"))
+    dY = torch.full((N, dim), 1.1, device="cuda")
+    index = torch.arange(k, device="cuda", dtype=torch.uint8).repeat(N, 1)
+    out = torch.empty((N, k), device="cuda")
+    maxk.maxk_sspmm_bwd(gr, dY, index, out)
+    assert gr.regs_tables() == 1
+    exact = torch.bincount(col.long(), minlength=N).double() * float(np.float32(1.1))
+    error = ((out.double() - exact[:, None]).abs().amax(1) / exact.clamp_min(1.0)).max().item()
+    longest = 64  # of the pull on graphs of up to a million entries, a quarter of its pieces' 128 to 256
+    assert error <= (longest / 2 + 3) * 2.0 ** -24
+    check_sums(gr)
     gr.destroy()
