@@ -49,6 +49,7 @@ struct maxk_graph {
     std::vector<maxk::RegsSet*> regs_cache;    // A^T regrouped for the register-tiled kernel, one per shape
     struct RegsChoice { int32_t dim, val_bytes, k; maxk::RegsShape shape; };
     std::vector<RegsChoice> regs_choices;      // what regs_choice found, per shape
+    std::vector<maxk::RegsShape> regs_refused; // tables that could not be built (see is_refused)
     int32_t bwd_regs = 0;
     std::vector<std::pair<int32_t, int64_t>> in_degrees;  // in-entries of a node, how many such nodes; most first
     std::vector<maxk::SweepSet*> sweep_cache;  // A regrouped for the forward sweep, one per (lane groups, rows of a bin)
@@ -309,7 +310,7 @@ bool denied(maxk_graph* g, int64_t bytes)
 // A table or buffer that could not be built is not asked for again by compute calls: each try synchronises the device
 // and may allocate most of what it needs before it fails, and one that succeeds later would change the kernel mid-run.
 using RefusedKey = std::array<int64_t, 4>;
-enum : int64_t { kRefusedSweep, kRefusedSlab, kRefusedTiled, kRefusedRegs, kRefusedExpand, kRefusedSliced };
+enum : int64_t { kRefusedSweep, kRefusedSlab, kRefusedTiled, kRefusedExpand, kRefusedSliced };
 
 bool is_refused(const maxk_graph* g, const RefusedKey& key)
 {
@@ -677,7 +678,10 @@ maxk_status tiled_for(maxk_graph* g, int dim, int k, const F& existing_only, Til
     return MAXK_OK;
 }
 
-RefusedKey regs_key(const RegsShape& sh) { return {kRefusedRegs, sh.pitch, sh.groups + 16 * sh.kr, sh.head}; }
+bool regs_refused(const maxk_graph* g, const RegsShape& sh)
+{
+    return std::find(g->regs_refused.begin(), g->regs_refused.end(), sh) != g->regs_refused.end();
+}
 
 template <class F>
 maxk_status regs_for(maxk_graph* g, const RegsShape& sh, const F& existing_only, RegsSet** out)
@@ -698,7 +702,12 @@ maxk_status regs_for(maxk_graph* g, const RegsShape& sh, const F& existing_only,
     if (st != MAXK_OK) {
         if (T) free_regs(*T);
         delete T;
-        note_refused(g, regs_key(sh));
+        if (st != MAXK_HIP_ERROR && !regs_refused(g, sh)) {  // lack of memory, or a graph that the lists do not hold
+            try {
+                g->regs_refused.push_back(sh);
+            } catch (const std::bad_alloc&) {  // then the next call tries again
+            }
+        }
         return st;
     }
     *out = T;
@@ -1394,7 +1403,7 @@ maxk_status plan_bwd(maxk_graph* g, int dim, int k, int vb, bool tiled_ok, const
     const auto existing_only = [&] { return automatic && captured(); };
     if (automatic && aligned(dY, 16)) {
         const RegsShape sh = regs_choice(g, dim, vb, k);
-        if (sh.n_sets && !is_refused(g, regs_key(sh))) {
+        if (sh.n_sets && !regs_refused(g, sh)) {
             const maxk_status st = regs_for(g, sh, captured, &plan.M);
             if (st == MAXK_OK || st == MAXK_HIP_ERROR) return st;
         }
@@ -1455,7 +1464,7 @@ maxk_status reserve_shape(maxk_graph* g, int dim, int k, int dy_value_type)
     forget_refused(g, sliced_key(g, dim, vb));
     TiledShape sh;
     if (tiled_shape(g->N, dim, k, sh)) forget_refused(g, tiled_key(sh, k));
-    if (const RegsShape rs = regs_choice(g, dim, vb, k); rs.n_sets) forget_refused(g, regs_key(rs));
+    if (const RegsShape rs = regs_choice(g, dim, vb, k); rs.n_sets) std::erase(g->regs_refused, rs);
     BwdPlan plan;
     return g->nnz ? plan_bwd(g, dim, k, vb, true, nullptr, nullptr, plan) : MAXK_OK;
 }
@@ -1822,7 +1831,7 @@ MAXK_API int32_t maxk_graph_regs_stands_in(maxk_graph* g, int32_t dim, int32_t k
     try {
         if (g->bwd_mode != MAXK_BWD_AUTO || g->nnz == 0) return 0;
         const RegsShape sh = regs_choice(g, dim, value_bytes(dy_value_type), k);
-        return sh.n_sets && !is_refused(g, regs_key(sh));
+        return sh.n_sets && !regs_refused(g, sh);
     } catch (const std::bad_alloc&) {
         return MAXK_OUT_OF_MEMORY;
     }
