@@ -1141,7 +1141,7 @@ double lines_touched(int dim, int k, int val_bytes)
 // thousand fills it) and 25 ps from beyond; 60 + 0.5 k ps per (item, slice) to sample the sums; the copy, where one is
 // needed, at 4.5 TB/s.
 struct PullCost { double plain, sliced; };
-PullCost pull_cost(const maxk_graph* g, int dim, int k, int val_bytes, const void* dY)
+PullCost pull_cost(const maxk_graph* g, int dim, int k, int val_bytes, const void* dY, bool even_refused = false)
 {
     const double N = (double)g->N, nnz = (double)g->nnz, row_bytes = (double)dim * val_bytes;
     const double miss = 1.0 - hot_share(g, 4e6 / row_bytes);
@@ -1154,7 +1154,7 @@ PullCost pull_cost(const maxk_graph* g, int dim, int k, int val_bytes, const voi
     const double slices = sliced_slices(dim, val_bytes), hit = hot_share(g, 24000.0);
     const bool in_place = sliced_in_place(dim, val_bytes);
     c.sliced = !sliced_supports(dY, g->N, dim, val_bytes) ||
-                       (!in_place && is_refused(g, sliced_key(g, dim, val_bytes)) && sliced_copy_bytes(g->N, dim, val_bytes) > g->sliced_bytes)
+                       (!in_place && !even_refused && is_refused(g, sliced_key(g, dim, val_bytes)) && sliced_copy_bytes(g->N, dim, val_bytes) > g->sliced_bytes)
                    ? HUGE_VAL
                    : 6e-6 + nnz * slices * (7e-12 * hit + 25e-12 * (1.0 - hit)) + N * slices * (60e-12 + 0.5e-12 * k) +
                          (in_place ? 0.0 : N * (row_bytes + slices * 128.0) / 4.5e12);
@@ -1170,18 +1170,19 @@ PullCost pull_cost(const maxk_graph* g, int dim, int k, int val_bytes, const voi
 // taken on 42 k nodes, 3.3 M entries, k = 32 (243 us, expand/reduce 191), 40 k, 1.6 M, k = 32 (136 / 100), 118 k, 1.7 M, k = 64
 // (241 / 208), 282 k, 3.4 M, k = 16 (247 / 214) and 169 k, 2.5 M, k = 32 (230 / 216; a whole pass 424 / 414).
 // Times in seconds; `lines` = 128-byte lines of a dY row that an entry's k columns touch.
-int auto_bwd_mode(const maxk_graph* g, int dim, int k, int val_bytes = 4, bool tiled_ok = true, double* seconds = nullptr)
+int auto_bwd_mode(const maxk_graph* g, int dim, int k, int val_bytes = 4, bool tiled_ok = true, bool even_refused = false, double* seconds = nullptr)
 {
     const double N = (double)g->N, nnz = (double)g->nnz, row_bytes = (double)dim * val_bytes;
     const double lines = lines_touched(dim, k, val_bytes);
 
-    const PullCost p = pull_cost(g, dim, k, val_bytes, nullptr);
+    const PullCost p = pull_cost(g, dim, k, val_bytes, nullptr, even_refused);
     const double pull = std::min(p.plain, p.sliced);
 
-    // what was refused memory is out of the race until a reserve gets it
+    // what was refused memory is out of the race until a reserve gets it (unless asked for the choice apart from that)
+    const auto refused = [&](const RefusedKey& key) { return !even_refused && is_refused(g, key); };
     // expand/reduce: 8k bytes an entry through HBM, whatever the graph looks like (scalar stores when
     // k % 4 != 0, two-byte columns above dim 256)
-    const double expand = nnz * k * 4.0 > 96e9 || (is_refused(g, {kRefusedExpand, k}) && g->nnz * (int64_t)k > g->expand_floats) ? HUGE_VAL
+    const double expand = nnz * k * 4.0 > 96e9 || (refused({kRefusedExpand, k}) && g->nnz * (int64_t)k > g->expand_floats) ? HUGE_VAL
                           : 8e-6 + nnz * (18e-12 + (dim > 256 ? 1.75e-12 : 1.5e-12) * k) * (k % 4 ? 1.7 : 1.0) +
                                 N * (400e-12 + 0.22e-12 * row_bytes);
 
@@ -1189,13 +1190,13 @@ int auto_bwd_mode(const maxk_graph* g, int dim, int k, int val_bytes = 4, bool t
     // with its ramp and tail
     const int32_t slab_rows = slab_rows_for(g, dim, val_bytes);
     const double n_slabs = std::ceil(N / slab_rows);
-    const double slab = n_slabs * N >= 1.8e19 || is_refused(g, {kRefusedSlab, slab_rows}) ? HUGE_VAL : 5e-6 + nnz * (lines + 0.35) * 5.2e-12 + n_slabs * 22e-6;
+    const double slab = n_slabs * N >= 1.8e19 || refused({kRefusedSlab, slab_rows}) ? HUGE_VAL : 5e-6 + nnz * (lines + 0.35) * 5.2e-12 + n_slabs * 22e-6;
 
     // LDS-tiled: a (destination set, tile) step on each CU (the dim = 256 specialization is 3-5 times cheaper than the
     // general one), the entries, and fp32 atomics when the source rows are cut into ranges
     double tiled = HUGE_VAL;
     TiledShape sh;
-    if (tiled_ok && val_bytes == 4 && tiled_shape(g->N, dim, k, sh) && !is_refused(g, tiled_key(sh, k))) {
+    if (tiled_ok && val_bytes == 4 && tiled_shape(g->N, dim, k, sh) && !refused(tiled_key(sh, k))) {
         const double n_tiles = std::ceil(N / sh.TR);
         if (sh.n_dsets * n_tiles < 2.6e8)
             tiled = 15e-6 + (dim == 256 ? 0.2e-6 : 0.5e-6 + 1.2e-9 * dim) * sh.n_dsets * n_tiles / 256.0 +
@@ -1292,7 +1293,8 @@ int pull_longest(const maxk_graph* g, int k)
 }
 
 // The layout for a shape (n_sets = 0: the other kernels are taken).  Even: as many sets as CUs (or fewer, in ranges of the rows),
-// all sweeping the rows in step, so that an XCD brings a row into its L2 once.  By degree: as many sets as it takes.
+// all sweeping the rows in step, so that an XCD brings a row into its L2 once.  By degree: as many sets as it takes.  Of the graph and
+// the shape alone, whatever memory was refused: it is kept for the handle's life.
 RegsShape regs_choice(maxk_graph* g, int dim, int val_bytes, int k)
 {
     if (g->bwd_regs == 1) return RegsShape();
@@ -1300,7 +1302,7 @@ RegsShape regs_choice(maxk_graph* g, int dim, int val_bytes, int k)
         if (c.dim == dim && c.val_bytes == val_bytes && c.k == k) return c.shape;
     RegsShape best, base;
     double seconds = HUGE_VAL, other = HUGE_VAL;
-    const int mode = auto_bwd_mode(g, dim, k, val_bytes, true, &other);
+    const int mode = auto_bwd_mode(g, dim, k, val_bytes, true, true, &other);
     TiledShape tiled;
     (void)tiled_shape(g->N, dim, k, tiled);
     bool sampled = false;

@@ -62,3 +62,26 @@ def test_a_refused_layout_denies_no_other(monkeypatch):
     assert gr.regs_tables() == 1 and gr.bwd_kernel(dim_b, k_b, _DTYPE[fmt_b]) != "register_tiled"
     assert torch.equal(_run(gr, b[3], b[4], 2), b[5]) and gr.regs_tables() == 1
     gr.destroy()
+
+
+def test_a_refusal_leaves_no_mark_on_the_layout(monkeypatch):
+    # a slab table refused at one k must not change what another k of that width is compared with once there is memory again
+    N, nnz, fmt = 30_000, 6_000_000, "bf16"
+    for dim, k in ((256, 64), (512, 64), (512, 128), (1024, 128)):
+        case = _case(N, nnz, dim, k, fmt, 12)
+        gr = _graph(monkeypatch, "2", *case[:3])
+        gr.reserve(dim, k, _DTYPE[fmt])
+        fresh = sizes(gr)
+        gr.destroy()
+        if fresh["run"] == 32:  # it stands in for slab pull
+            break
+    assert fresh["run"] == 32
+    gr = _graph(monkeypatch, "2", *case[:3])
+    gr.limit_allocations(0)
+    _run(gr, case[3], case[4][:, :k - 8].contiguous(), 2)
+    assert torch.equal(_run(gr, case[3], case[4], 2), case[5]) and gr.regs_tables() == 0
+    gr.limit_allocations(-1)
+    gr.reserve(dim, k, _DTYPE[fmt])
+    assert gr.regs_tables() == 1 and sizes(gr) == fresh
+    assert torch.equal(_run(gr, case[3], case[4], 2), case[5])
+    gr.destroy()
