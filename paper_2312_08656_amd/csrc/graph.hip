@@ -1295,11 +1295,8 @@ int pull_longest(const maxk_graph* g, int k)
 // The layout for a shape (n_sets = 0: the other kernels are taken).  Even: as many sets as CUs (or fewer, in ranges of the rows),
 // all sweeping the rows in step, so that an XCD brings a row into its L2 once.  By degree: as many sets as it takes.  Of the graph and
 // the shape alone, whatever memory was refused: it is kept for the handle's life.
-RegsShape regs_choice(maxk_graph* g, int dim, int val_bytes, int k)
+RegsShape best_regs_shape(const maxk_graph* g, int dim, int val_bytes, int k)
 {
-    if (g->bwd_regs == 1) return RegsShape();
-    for (const auto& c : g->regs_choices)
-        if (c.dim == dim && c.val_bytes == val_bytes && c.k == k) return c.shape;
     RegsShape best, base;
     double seconds = HUGE_VAL, other = HUGE_VAL;
     const int mode = auto_bwd_mode(g, dim, k, val_bytes, true, true, &other);
@@ -1379,11 +1376,21 @@ RegsShape regs_choice(maxk_graph* g, int dim, int val_bytes, int k)
     const double line = mode == MAXK_BWD_SLAB_PULL ? (small ? 0.9 : 1.0)
                         : mode == MAXK_BWD_EXPAND_REDUCE ? ((double)g->N * dim * val_bytes > 256e6 ? 0.85 : 0.7) : (small ? 0.8 : 0.9);
     if (g->bwd_regs < 2 && !(seconds < line * other)) best = RegsShape();
-    try {
-        g->regs_choices.push_back({dim, val_bytes, k, best});
-    } catch (const std::bad_alloc&) {  // then it is worked out again
-    }
     return best;
+}
+
+RegsShape regs_choice(maxk_graph* g, int dim, int val_bytes, int k)
+{
+    if (g->bwd_regs == 1) return RegsShape();
+    for (const auto& c : g->regs_choices)
+        if (c.dim == dim && c.val_bytes == val_bytes && c.k == k) return c.shape;
+    try {
+        const RegsShape best = best_regs_shape(g, dim, val_bytes, k);
+        g->regs_choices.push_back({dim, val_bytes, k, best});
+        return best;
+    } catch (const std::bad_alloc&) {  // the other kernels, and it is worked out again
+        return RegsShape();
+    }
 }
 
 // The backward kernel of a call and the tables it walks, which are built where they are missing.
@@ -1830,13 +1837,9 @@ MAXK_API int32_t maxk_lone_visit_line(int32_t longest, int64_t entries) { return
 MAXK_API int32_t maxk_graph_regs_stands_in(maxk_graph* g, int32_t dim, int32_t k, int32_t dy_value_type)
 {
     if (!g || dim < 1 || k < 1 || k > dim || dy_value_type < MAXK_VALUE_F32 || dy_value_type > MAXK_VALUE_F16) return MAXK_INVALID_ARGUMENT;
-    try {
-        if (g->bwd_mode != MAXK_BWD_AUTO || g->nnz == 0) return 0;
-        const RegsShape sh = regs_choice(g, dim, value_bytes(dy_value_type), k);
-        return sh.n_sets && !regs_refused(g, sh);
-    } catch (const std::bad_alloc&) {
-        return MAXK_OUT_OF_MEMORY;
-    }
+    if (g->bwd_mode != MAXK_BWD_AUTO || g->nnz == 0) return 0;
+    const RegsShape sh = regs_choice(g, dim, value_bytes(dy_value_type), k);
+    return sh.n_sets && !regs_refused(g, sh);
 }
 
 MAXK_API int32_t maxk_graph_regs_tables(const maxk_graph* g) { return g ? (int32_t)g->regs_cache.size() : MAXK_INVALID_ARGUMENT; }
