@@ -1284,12 +1284,21 @@ double regs_cost(const maxk_graph* g, const std::vector<std::pair<int32_t, int64
     return seconds;
 }
 
-// What a running sum of the pull takes at most: a lane group's share of a piece of `chunk` entries, four at a time.  (Slab pull by rows
-// takes eight at a time and stores a sum per slab: up to 450 of either at 1 KB a row.)
-int pull_longest(const maxk_graph* g, int k)
+// Entries that a sum of the register-tiled kernel may take, so that it is no further off than the kernel `mode` that it stands in for
+// (0: as many as it likes).  Plain pull of k > 32 adds up pieces of `chunk` entries four at a time; the others and the column slices
+// a lane group's share of them; slab pull by rows takes eight at a time and then a sum per slab, which for the hubs that sets by
+// degree hold is little.  The LDS-tiled kernel adds up a source range, slab pull's sampled form a destination, one by one
+// whatever their number.  Errors go with the root of the length, and the mean length is a quarter to a half of the limit.  Error of
+// the 12 largest destinations against 64 bits, k = 64, so / of the kernel before: 126 M entries on 2.4 M nodes 2.1e-7 / 4.3e-7 (plain pull);
+// 41 M on 411 k, directed, mean weights 1.1e-7 / 1.5e-7 (column slices; 2.0e-7 with a limit of 512 here too).
+int32_t regs_longest(const maxk_graph* g, int dim, int k, int val_bytes, int mode, bool sampled, bool even)
 {
-    const int groups = k > 32 ? 1 : kWave / (int)std::bit_ceil((uint32_t)k);
-    return std::min(g->chunk, 2048) / (4 * groups);
+    if (mode == MAXK_BWD_TILED || sampled) return 0;
+    const PullCost p = pull_cost(g, dim, k, val_bytes, nullptr, true);
+    const bool sliced = g->pull_form == 0 ? p.sliced < p.plain : g->pull_form == 2 && p.sliced < HUGE_VAL;
+    const int piece = std::min(g->chunk, 2048);
+    if (mode == MAXK_BWD_SLAB_PULL && even) return std::max(128, piece / 8);
+    return mode == MAXK_BWD_PULL_CSC && k > 32 && !sliced ? std::max(128, piece / 4) : 128;
 }
 
 // The layout for a shape (n_sets = 0: the other kernels are taken).  Even: as many sets as CUs (or fewer, in ranges of the rows),
@@ -1303,6 +1312,7 @@ RegsShape best_regs_shape(const maxk_graph* g, int dim, int val_bytes, int k)
     TiledShape tiled;
     (void)tiled_shape(g->N, dim, k, tiled);
     bool sampled = false;
+    int32_t slab_run = 32;
     if (mode == MAXK_BWD_SLAB_PULL) {
         // Its line above was fitted where rows are long and degrees even.  Short rows cost their entries' instructions, few
         // entries a visit the visits, and a hub's visits end their launches late: us, the line above / measured, 31 M entries on
@@ -1312,13 +1322,13 @@ RegsShape best_regs_shape(const maxk_graph* g, int dim, int val_bytes, int k)
         const double N = (double)g->N, nnz = (double)g->nnz, slabs = std::ceil(N / slab_rows_for(g, dim, val_bytes));
         const double visits = N * slabs * -std::expm1(-nnz / (N * slabs));
         const double entry = std::max((lines_touched(dim, k, val_bytes) + 0.35) * 4.3e-12, sampled ? 16e-12 : 27e-12);
+// its sums: eight rows at a time, then one a slab; a little less than for a destination with three times the mean
+        slab_run = (int32_t)std::clamp(0.875 * (slabs + 3.0 * nnz / (8.0 * N * slabs)), 16.0, 32.0);
         other = std::max(0.85 * other, nnz * entry + visits * 45e-12 + slabs * 10e-6 + 15e-9 * (double)g->max_in_degree);
     }
     if (g->nnz > 0 && regs_fits(dim, val_bytes, k, base)) {
         const int64_t D = (int64_t)regs_slots(base.kr) * base.groups * kRegsWaves;
-        // No kernel's sums get longer.  The tiled one adds up a source range, slab pull's sampled form a destination's entries one by
-        // one, whatever their number; the others keep to what a running sum of the pull takes (64 is a step's share of a list).
-        const int32_t longest = mode == MAXK_BWD_TILED || sampled ? 0 : std::max(64, pull_longest(g, k));
+        const int32_t longest = regs_longest(g, dim, k, val_bytes, mode, sampled, true), hub_longest = regs_longest(g, dim, k, val_bytes, mode, sampled, false);
         // Even sets: a destination with many in-entries is several ones, or its wavefront's list holds up the others' at every
         // step and its sum gets long.  By degree few are: the sets that hold such ones are cut into units, and the entries
         // of one share rows (2.4 M nodes, k = 64: 8.0 ms with the even sets' line, 6.7 without one).
@@ -1333,7 +1343,7 @@ RegsShape best_regs_shape(const maxk_graph* g, int dim, int val_bytes, int k)
             std::stable_sort(out.begin(), out.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
             return shares;
         };
-        const int64_t cap = std::max<int64_t>(64, std::min(8 * (g->nnz / g->N + 1), g->nnz / 16384)), hub_cap = longest ? 64ll * longest : g->nnz;
+        const int64_t cap = std::max<int64_t>(64, std::min(8 * (g->nnz / g->N + 1), g->nnz / 16384)), hub_cap = hub_longest ? 64ll * hub_longest : g->nnz;
         Degrees capped, hubs_capped;
         const int64_t capped_shares = capped_at(cap, capped), hubs_capped_shares = capped_at(hub_cap, hubs_capped);
         const auto consider = [&](int64_t sets, int64_t spread, int32_t ranges) {
@@ -1344,9 +1354,12 @@ RegsShape best_regs_shape(const maxk_graph* g, int dim, int val_bytes, int k)
             sh.n_sets = (int32_t)sets;
             sh.spread = (int32_t)spread;
             sh.ranges = ranges;
-            sh.longest = longest;
-            sh.run = mode != MAXK_BWD_TILED ? (mode == MAXK_BWD_SLAB_PULL ? 32 : 12) : ranges >= tiled.R ? 0 : 64;
+            sh.longest = ranges ? longest : hub_longest;
             sh.head = std::min<int64_t>(shares, sets * D);
+            // Pull and expand/reduce: 12, or 8 where a sum of 12 is most of many results, because most destinations have few entries and
+            // sets of one range hold them (15 M entries on 989 k nodes, k = 32: error 4.35e-8 before, 4.59e-8 with 12, 4.29e-8 with 8).
+            const bool few = g->nnz < 24 * g->N && ranges <= 1 && 2 * sh.head > shares;
+            sh.run = mode == MAXK_BWD_SLAB_PULL ? slab_run : mode != MAXK_BWD_TILED ? (few ? 8 : 12) : ranges >= tiled.R ? 0 : 64;
             // the tail is the end of the pull's item list: none of its destinations may be several or split there
             int64_t above = 0;
             for (const auto& [degree, n] : degrees) {

@@ -672,8 +672,10 @@ maxk_status build_regs(RegsSet& T, const RegsShape& shape, int64_t N, int64_t nn
     uint32_t* d_most;
     MAXK_TRY_CLEAN(get(d_part_range, S));
     MAXK_TRY_CLEAN(get(d_most, 2 * S));
+    int64_t first_floats = 0;
     for (int tries = 0;; ++tries) {
         cut();
+        if (tries == 0) first_floats = T.part_floats;
         if (!sums.empty()) {
             (void)hipFree(T.d_part);
             (void)hipFree(T.d_parts);
@@ -701,8 +703,8 @@ maxk_status build_regs(RegsSet& T, const RegsShape& shape, int64_t N, int64_t nn
                     good = false;
                 }
         if (good) break;
-        // a graph whose order needs this many parts is for the other kernels
-        if (tries == 8 || (double)T.part_floats * sizeof(float) > 16.0 * (double)nnz + 256e6) {
+        // a graph whose order needs far more parts than were reckoned with is for the other kernels
+        if (tries == 8 || T.part_floats > 2 * first_floats + 64000000) {
             free_regs(T);
             return MAXK_UNSUPPORTED;
         }

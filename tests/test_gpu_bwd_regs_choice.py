@@ -73,9 +73,9 @@ def test_a_refusal_leaves_no_mark_on_the_layout(monkeypatch):
         gr.reserve(dim, k, _DTYPE[fmt])
         fresh = sizes(gr)
         gr.destroy()
-        if fresh["run"] == 32:  # it stands in for slab pull
+        if 16 <= fresh["run"] <= 32:  # it stands in for slab pull
             break
-    assert fresh["run"] == 32
+    assert 16 <= fresh["run"] <= 32
     gr = _graph(monkeypatch, "2", *case[:3])
     gr.limit_allocations(0)
     _run(gr, case[3], case[4][:, :k - 8].contiguous(), 2)
@@ -85,3 +85,33 @@ def test_a_refusal_leaves_no_mark_on_the_layout(monkeypatch):
     assert gr.regs_tables() == 1 and sizes(gr) == fresh
     assert torch.equal(_run(gr, case[3], case[4], 2), case[5])
     gr.destroy()
+
+
+# (graph: a power of a uniform number makes some sources and destinations frequent, 1: none.)  Real numbers; a call gives the same bits every time.
+@pytest.mark.parametrize("how", ["2", "3"])
+@pytest.mark.parametrize("fmt,dim,k", [("f32", 128, 64), ("f32", 256, 32), ("bf16", 256, 96)])
+@pytest.mark.parametrize("N,nnz,power", [(60_000, 6_000_000, 3), (200_000, 3_000_000, 1), (30_000, 4_000_000, 1)])
+def test_errors_are_no_larger_than_those_of_the_kernel_before(monkeypatch, how, fmt, dim, k, N, nnz, power):
+    gen = torch.Generator(device="cuda").manual_seed(N + k)
+    src, dst = ((torch.rand(nnz, generator=gen, device="cuda", dtype=torch.float64) ** power * N).long() for _ in range(2))
+    order = torch.argsort(src, stable=True)
+    src, dst = src[order], dst[order]
+    degree = torch.bincount(src, minlength=N)
+    rowptr = torch.zeros(N + 1, dtype=torch.int32, device="cuda")
+    rowptr[1:] = torch.cumsum(degree, 0)
+    val = (1.0 / degree.double())[src].float()  # mean weights
+    dY = torch.randn(N, dim, generator=gen, device="cuda").to(_DTYPE[fmt])
+    index = torch.rand(N, dim, generator=gen, device="cuda").topk(k, dim=1).indices.sort(dim=1).values
+    exact = torch.zeros((N, k), dtype=torch.float64, device="cuda")
+    for at in range(0, nnz, 1 << 18):
+        s, d = src[at: at + (1 << 18)], dst[at: at + (1 << 18)]
+        exact.index_add_(0, d, dY[s].double().gather(1, index[d]) * val[at: at + (1 << 18), None].double())
+    error = {}
+    for form in ("1", how):
+        gr = _graph(monkeypatch, form, rowptr, dst.to(torch.int32), val)
+        out = _run(gr, dY, index, 4)
+        assert gr.regs_tables() == (form != "1")
+        error[form] = (torch.linalg.vector_norm(out.double() - exact) / torch.linalg.vector_norm(exact)).item()
+        gr.destroy()
+    # (sums of a few terms are rounded alike by both: a few per cent either way)
+    assert error[how] <= 1.05 * error["1"], error
