@@ -1385,9 +1385,14 @@ RegsShape best_regs_shape(const maxk_graph* g, int dim, int val_bytes, int k)
     }
     // The others' lines over what was measured on 190 shapes: slab pull 0.45 to 1.3, mostly below 1; pull and tiled 0.9 to 1.2;
     // expand/reduce 1.0 to 1.2, but 1.2 to 1.6 where dY stays in the 256 MB Infinity Cache.  This kernel's: 0.75 to 1.25.
+    // Against pull, this kernel's runs low where rows are short (256 bytes and k > 32: 1.2 to 1.45; k > 16: 1.2 to 1.3 where a
+    // graph's frequent sources, which pull finds in L2, hold much of its entries; 512 and k > 64: 1.2 to 1.45).
+    const double pull_line = base.pitch == 256 && k > 32 ? 0.7 : base.pitch == 256 && k > 16 && hot_share(g, 16384.0) > 0.4 ? 0.72
+                             : k <= 64 ? 1.0 : best.run == 8 ? 0.8 : base.pitch > 512 ? 0.87 : best.ranges ? 0.83 : 0.7;
     const bool small = other < 600e-6;
     const double line = mode == MAXK_BWD_SLAB_PULL ? (small ? 0.9 : 1.0)
-                        : mode == MAXK_BWD_EXPAND_REDUCE ? ((double)g->N * dim * val_bytes > 256e6 ? 0.85 : 0.7) : (small ? 0.8 : 0.9);
+                        : mode == MAXK_BWD_EXPAND_REDUCE ? ((double)g->N * dim * val_bytes > 256e6 ? 0.85 : 0.7)
+                        : mode == MAXK_BWD_PULL_CSC ? std::min(small ? 0.8 : 0.9, pull_line) : (small ? 0.8 : 0.9);
     if (g->bwd_regs < 2 && !(seconds < line * other)) best = RegsShape();
     return best;
 }
