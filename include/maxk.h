@@ -63,10 +63,11 @@ enum {
 
 /* Which kernel maxk_sspmm_bwd runs (see maxk_graph_set_bwd_mode). */
 enum {
-    MAXK_BWD_AUTO = 0,    /* library's choice (the faster one on MI355X).  Where it is faster than the kernel that this would
-                             take, and its sums are no longer, the register-tiled kernel stands in for it: a workgroup keeps
+    MAXK_BWD_AUTO = 0,    /* library's choice (the faster one on MI355X).  Where it is reckoned to be faster than the kernel
+                             that this would take, the register-tiled kernel stands in for it: a workgroup keeps
                              the dXs rows of a set of destination nodes in registers and takes the dY rows that they need
-                             through LDS; deterministic, no atomics.  k <= 128, rows of dY of at most 2048 bytes and whole
+                             through LDS; deterministic, no atomics, its running sums cut short so that rounding is no
+                             larger than that kernel's.  k <= 128, rows of dY of at most 2048 bytes and whole
                              16-byte units, 16-byte aligned dY */
     MAXK_BWD_PULL_CSC = 1,/* owner-computes over A^T stored as CSC: deterministic, no atomics */
     MAXK_BWD_PUSH_CSR = 2,/* Alg. 2's dataflow: stage dY[i,:] on chip, push along row i of A with fp32 atomics */
@@ -138,6 +139,9 @@ MAXK_API maxk_status maxk_graph_set_bwd_mode(maxk_graph* g, int32_t mode);
 /* The MAXK_BWD_* kernel maxk_sspmm_bwd would run for (dim, k) with the handle's current mode
  * (resolves MAXK_BWD_AUTO; the register-tiled kernel may stand in for what this names); negative maxk_status on bad arguments. */
 MAXK_API int32_t maxk_graph_bwd_choice(const maxk_graph* g, int32_t dim, int32_t k);
+
+/* Whether it does (0 or 1), for a 16-byte aligned dY stored as `dy_value_type` (MAXK_VALUE_*); negative maxk_status on bad arguments. */
+MAXK_API int32_t maxk_graph_regs_stands_in(maxk_graph* g, int32_t dim, int32_t k, int32_t dy_value_type);
 
 /* Reads back sizes: any out pointer may be NULL. */
 MAXK_API maxk_status maxk_graph_info(const maxk_graph* g, int64_t* N, int64_t* nnz, int64_t* n_fwd_items,

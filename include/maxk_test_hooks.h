@@ -32,9 +32,6 @@ MAXK_API int32_t maxk_lone_visit_line(int32_t longest, int64_t entries);
 /* How many regroupings of A for the forward sweep the handle holds (kept like the tables above). */
 MAXK_API int32_t maxk_graph_sweep_tables(const maxk_graph* g);
 
-/* Whether the register-tiled backward kernel stands in for what MAXK_BWD_AUTO takes at this shape (0 or 1; 16-byte aligned dY). */
-MAXK_API int32_t maxk_graph_regs_stands_in(maxk_graph* g, int32_t dim, int32_t k, int32_t dy_value_type);
-
 /* How many regroupings of A^T for the register-tiled backward kernel the handle holds (kept like the tables above). */
 MAXK_API int32_t maxk_graph_regs_tables(const maxk_graph* g);
 

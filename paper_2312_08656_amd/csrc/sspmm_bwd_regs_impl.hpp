@@ -560,6 +560,18 @@ maxk_status launch_regs_t(const RegsArgs& a, int64_t n_units, hipStream_t s)
     return MAXK_OK;
 }
 
+template <int VT, int G, int KR>
+maxk_status launch_regs_p(int pitch, const RegsArgs& a, int64_t n_units, hipStream_t s)
+{
+    if constexpr (VT != MAXK_VALUE_F32 || KR == 1) {  // (256 bytes of fp32 are at most 64 columns, one register a destination)
+        if (pitch == 256) return launch_regs_t<VT, G, KR, 256>(a, n_units, s);
+    }
+    return pitch == 512    ? launch_regs_t<VT, G, KR, 512>(a, n_units, s)
+           : pitch == 1024 ? launch_regs_t<VT, G, KR, 1024>(a, n_units, s)
+           : pitch == 1536 ? launch_regs_t<VT, G, KR, 1536>(a, n_units, s)
+           : pitch == 2048 ? launch_regs_t<VT, G, KR, 2048>(a, n_units, s) : MAXK_UNSUPPORTED;
+}
+
 }  // namespace
 
 template <int VT>
@@ -567,14 +579,11 @@ maxk_status launch_regs_format(const RegsSet& T, const void* dY, const void* sp_
                                hipStream_t s)
 {
     const RegsArgs a = {dY, sp_index, dXs, T.d_rec, T.d_hdr, T.d_node, T.d_row, T.d_extra, N, T.d_unit, T.d_part, T.d_parts, (uint32_t)dim * (VT == MAXK_VALUE_F32 ? 4u : 2u), k, index_bytes};
-#define MAXK_REGS_P(G, KR)                                                         \
-    (T.shape.pitch == 256    ? launch_regs_t<VT, G, KR, 256>(a, T.n_units, s)      \
-     : T.shape.pitch == 512  ? launch_regs_t<VT, G, KR, 512>(a, T.n_units, s)      \
-     : T.shape.pitch == 1024 ? launch_regs_t<VT, G, KR, 1024>(a, T.n_units, s)     \
-     : T.shape.pitch == 1536 ? launch_regs_t<VT, G, KR, 1536>(a, T.n_units, s)     \
-                             : launch_regs_t<VT, G, KR, 2048>(a, T.n_units, s))
-    return T.shape.kr == 2 ? MAXK_REGS_P(1, 2) : T.shape.groups == 1 ? MAXK_REGS_P(1, 1) : T.shape.groups == 2 ? MAXK_REGS_P(2, 1) : MAXK_REGS_P(4, 1);
-#undef MAXK_REGS_P
+    const int pitch = T.shape.pitch;
+    return T.shape.kr == 2       ? launch_regs_p<VT, 1, 2>(pitch, a, T.n_units, s)
+           : T.shape.groups == 1 ? launch_regs_p<VT, 1, 1>(pitch, a, T.n_units, s)
+           : T.shape.groups == 2 ? launch_regs_p<VT, 2, 1>(pitch, a, T.n_units, s)
+                                 : launch_regs_p<VT, 4, 1>(pitch, a, T.n_units, s);
 }
 
 }  // namespace maxk
