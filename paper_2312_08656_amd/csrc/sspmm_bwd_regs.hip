@@ -16,7 +16,8 @@
 // CUs sweep the rows in step and an XCD brings a row into its L2 once; where a set uses few of the rows (large sparse
 // graphs) sets by falling degree use fewer of them: 0.35 a stored entry on the graph of 2.4 M nodes, 0.24 to 0.45 on the others.
 // Rounding.  A sum in a register is one running sum, so it leaves the register several times a sweep ("parts", kept as they
-// are and added up in 64 bits by a second kernel).  Nothing is added with atomics: a call gives the same bits every time.
+// are and added up in 64 bits by a second kernel): after `run` entries by a set's mean, and in no case after more than `longest`,
+// which is counted when the tables are built.  Nothing is added with atomics: a call gives the same bits every time.
 #include <algorithm>
 #include <cstring>
 #include <new>
