@@ -27,7 +27,7 @@
  *     them): MAXK_CHUNK (entries per work item; default nnz / 4096,
  *     at least 128 and at most 2048), MAXK_SLAB_KB (KiB of dY per slab of the slab-pull
  *     backward kernel, default 3584), MAXK_FWD_PACK_MAX (largest CBSR row in bytes that the forward pass
- *     repacks into one record per node, default 96), MAXK_PULL_FORM (form of the CSC pull: 0 = by cost, 1 = whole
+ *     repacks into one record per node; default 96, and none of a CBSR of up to 3 MiB), MAXK_PULL_FORM (form of the CSC pull: 0 = by cost, 1 = whole
  *     rows, 2 = column slices wherever the shape allows them; default 0), MAXK_FWD_SWEEP (forward kernel: 0 = by
  *     size, 1 = row by row, 2 = the sweep wherever the shape allows it; default 0), MAXK_BWD_REGS (register-tiled
  *     backward kernel in MAXK_BWD_AUTO: 0 = by cost, 1 = never, 2 = wherever the shape allows it, 3 = the same, its
@@ -110,7 +110,7 @@ MAXK_API maxk_status maxk_graph_destroy(maxk_graph* g);
 /*
  * Builds everything the handle's compute calls need for hidden width `dim`, MaxK `k` and (for the backward pass)
  * dY stored as `dy_value_type`: the partial-sum workspace of split rows, the forward pass's repack buffer, the regrouped
- * copy of A that the forward sweep walks (k = 8, 16, 32, 64, 128 on large graphs; 8 bytes an entry), and
+ * copy of A that the forward sweep walks (k = 8, 16 and 22 to 128 on large graphs; 8 bytes an entry), and
  * what the backward kernel that would run needs (the nnz*k float buffer of expand/reduce, the slab regrouping
  * of A^T for the slab height of (dim, dy_value_type), the visit lists of the LDS-tiled kernel for (dim, k), the
  * regrouping of A^T and the partial sums of the register-tiled kernel, the

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "../../include/maxk.h"
 
 namespace maxk {
@@ -198,9 +200,51 @@ struct SweepSet {
     uint32_t* d_batch = nullptr;   // [n_bins + 1] first batch of every bin
     int2* d_rows = nullptr;        // [n_bins * per_bin] {output row or -1, partial-sum slot or -1}
 };
-constexpr int kSweepRowShift = 26;  // source nodes below 2^26, at most 31 rows a bin
-__host__ __device__ constexpr int sweep_groups(int k) { return k < kWave ? kWave / k : 1; }  // k a power of two
-__host__ __device__ constexpr int sweep_batch(int k) { return k < 16 ? 8 : 16; }
+constexpr int kSweepRowShift = 26, kSweepMaxRows = 31;  // source nodes below 2^26, at most 31 rows a bin
+
+// Where a wavefront finds a node's values and columns: in the two arrays, or in the node's record - columns behind values; 16-bit
+// values each with its column, which one load of 4 bytes brings; 8 fp32 values and, as words, 4 x their columns.
+enum : int { kFwdArrays = 0, kFwdRecord = 1, kFwdPairs = 2, kFwdHalves = 3 };
+
+// Lanes of an entry and wave instructions an entry in the kernels that work by lane groups (lanes = 0: the others run).  As many
+// groups as there were private copies, so that a row has no fewer partial sums, and of those the fewest idle lanes.
+struct FwdGroups { int lanes, passes; };
+constexpr FwdGroups fwd_groups(int k)
+{
+    if (k == 64 || k == 128 || k == 192) return {64, k / 64};
+    if (k == 8 || k == 16 || k == 32) return {k, 1};
+    if (k < 10 || k > 128) return {0, 0};
+    if (k <= 21) return {8, (k + 7) / 8};
+    if (k <= 63) return {16, (k + 15) / 16};
+    return {32, (k + 31) / 32};
+}
+
+// Whether byte offsets into the CBSR need more than 32 bits (record: bytes of a packed one, 0: two arrays)
+inline int fwd_wide(int64_t N, int k, int val_bytes, int index_bytes, int record)
+{
+    return N * (record ? (int64_t)record : (int64_t)k * std::max(val_bytes, index_bytes)) > 0xFFFFFFFFll;
+}
+int fwd_layout(int k, int index_bytes, int val_bytes);  // of a repacked CBSR
+
+constexpr int sweep_groups(int k) { return kWave / fwd_groups(k).lanes; }
+constexpr int sweep_batch(int k) { return fwd_groups(k).lanes < 16 ? 8 : 16; }
+
+// LDS of a workgroup of the sweep, two on a CU, its wavefronts, and the rows of a bin.  The rows follow k, and the width only below
+// 129 columns, so that most widths walk one regrouped A; more rows where they are short, fewer wavefronts where they are long: us,
+// rows 2 / 5 / 10: k = 32, 30 M entries on 300 k nodes, dim 128 708 / 670 / 609; 60 M on 300 k, dim 64 5 / 10 / 20 rows 1184 / 860 / 860; 45 M
+// on 150 k, dim 512 842 / 853 / -; k = 96, dim 384 2832 / 2263 (row by row 2960); k = 128, dim 512 5 / 10 rows 3274 / 2385 (4645).
+constexpr int64_t kSweepLds = 80 * 1024;
+constexpr int sweep_bin_rows(int k, int dim)
+{
+    const int groups = sweep_groups(k), base = groups == 8 ? 1 : groups == 4 ? 2 : groups == 2 || k == kWave ? 5 : 10;
+    const int rows = base * (dim <= 64 ? 4 : dim <= 128 ? 2 : 1);
+    return rows < kSweepMaxRows ? rows : kSweepMaxRows;
+}
+constexpr int sweep_waves(int k, int per_bin, int dim)  // 0: a bin does not fit
+{
+    const int64_t room = kSweepLds / ((int64_t)sweep_groups(k) * per_bin * dim * 4), most = k == kWave ? 16 : 8;
+    return (int)(room < most ? room : most);
+}
 
 extern thread_local int32_t g_last_hip_error;
 
@@ -273,7 +317,7 @@ maxk_status launch_cbsr_scatter(const float* values, const void* sp_index, int i
 maxk_status launch_spgemm_fwd(const ItemList& items, const int32_t* col, const float* val, const void* sp_data,
                               int value_type, const void* sp_index, int index_bytes, int64_t N, char* packed, int dim,
                               int k, float* Y, float* partials, hipStream_t s);
-// the same on a regrouped A (k = 8, 16, 32, 64 or 128, sweep_groups(k) == sweep.groups)
+// the same on a regrouped A (fwd_groups(k).lanes > 0, sweep_groups(k) == sweep.groups)
 maxk_status launch_spgemm_fwd_sweep(const ItemList& items, const SweepSet& sweep, const void* sp_data, int value_type,
                                     const void* sp_index, int index_bytes, int64_t N, char* packed, int dim, int k, float* Y,
                                     float* partials, hipStream_t s);

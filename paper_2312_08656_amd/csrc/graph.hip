@@ -968,11 +968,16 @@ maxk_status note_reserved(maxk_graph* g, int dim, int k)
     return MAXK_OK;
 }
 
-// existing_only: nothing is built, and a refusal is not remembered (the call is being captured, or was reserved)
-maxk_status sweep_for(maxk_graph* g, int groups, int batch_len, int per_bin, bool existing_only, SweepSet** out)
+// existing_only: nothing is built, and a refusal is not remembered (the call is being captured, or was reserved); bins of other
+// numbers of rows do then, as long as a workgroup has a few wavefronts
+maxk_status sweep_for(maxk_graph* g, int k, int dim, int per_bin, bool existing_only, SweepSet** out)
 {
+    const int groups = sweep_groups(k), batch_len = sweep_batch(k);
     for (SweepSet* W : g->sweep_cache)
         if (W->groups == groups && W->batch_len == batch_len && W->per_bin == per_bin) { *out = W; return MAXK_OK; }
+    if (existing_only)
+        for (SweepSet* W : g->sweep_cache)
+            if (W->groups == groups && W->batch_len == batch_len && sweep_waves(k, W->per_bin, dim) >= 4) { *out = W; return MAXK_OK; }
     const RefusedKey key = {kRefusedSweep, groups, batch_len, per_bin};
     if (existing_only || is_refused(g, key)) return MAXK_UNSUPPORTED;
     SweepSet* W = new (std::nothrow) SweepSet();
@@ -995,42 +1000,45 @@ maxk_status sweep_for(maxk_graph* g, int groups, int batch_len, int per_bin, boo
     return MAXK_OK;
 }
 
-// The forward kernel repacks the CBSR when a row of it is well below a cache line.
+// The forward kernel repacks the CBSR when a row of it is well below a cache line - but for one that an L2 has room for beside the
+// entries: there a launch more costs what the requests gain.  us, repacked / not: 1 k nodes, k = 8 7.4 / 3.9; 4 k, 2.1 M entries,
+// k = 16 24.4 / 21.6; 40 k, 1.2 M, k = 13 (2.6 MB) 31.7 / 25.8; 60 k, 3.6 M, k = 8 (2.4 MB) 47.7 / 49.0; 60 k, 18 M, k = 16 (4.8
+// MB) 128 / 172; 132 k, 79 M, k = 8 (5.3 MB) 700 / 979.
+constexpr int64_t kFwdPackFrom = 3 << 20;  // bytes of the CBSR
 bool fwd_uses_packed(const maxk_graph* g, int k, int index_bytes, int val_bytes)
 {
-    return k * (val_bytes + index_bytes) <= g->fwd_pack_max;
+    const int row = k * (val_bytes + index_bytes);
+    return g->fwd_pack_max >= 0 ? row <= g->fwd_pack_max : row <= 96 && g->N * (int64_t)row > kFwdPackFrom;
 }
 
 // Rows of a bin of the forward sweep for MaxK k, 0 where the row-by-row kernel is taken.  The sweep pays when the CBSR is
-// several times an L2, the bins fill the chip (256 CUs x 32 wavefronts), the rows in LDS leave enough wavefronts a CU, and
-// a bin has enough entries for its padding to whole batches and its copies of the rows.  The lines are drawn by k where both
-// sides were measured, over 16 graphs (profiles/forward_sweep_rule_over_graphs.txt: the kernel taken is 0.4 % above the
-// better one on average, 15 % at most, row by row 3.2 %); us, row by row / sweep:
-//   CBSR size: k = 32, 100 k nodes (16 MB) 191 / 197 and 531 / 500, 40 k (6 MB) 57 / 66; k = 64, 100 k (32 MB) 357 / 342, 40 k
-//     (13 MB) 259 / 291, bf16 values 100 k (19 MB) 756 / 825 and 303 / 315; k = 128, 40 k (26 MB) 524 / 441 and 171 / 163
-//   entries a lane group: k = 16, 123 1549 / 1245, 75 306 / 311, 19 795 / 842; k = 8, 62 1264 / 1126, 38 218 / 268; k = 32,
-//     101 597 / 555, 31 188 / 217; k = 64, 124 291 / 332 (250 k nodes, skewed, the largest miss) and 132 / 134
-//   width: k = 16, dim 400 271 / 332; k = 32, dim 400 441 / 429, dim 512 215 / 269; k = 64, dim 400 705 / 650, dim 512
-//     382 / 439; k = 128, dim 512 845 / 713
-// Rows of a bin, us, when the lines were drawn (the sweep was 2 to 13 % slower then): k = 64, 3 / 4 / 5 rows 3541 / 3175 / 4010 (dense workload); k = 32, 1 / 2 / 3 rows 2211 / 2085 / 1922
-// there, 1312 / 1282 / 1326 on 79 M entries and 132 k nodes, 1 / 2 / 4 rows 1425 / 1336 / 1264 on 43 M and 576 k: two are ahead of
-// one on each, three and four are faster where the rows are long resp. the nodes many; k = 16, 1 / 2 1303 / 1369 (dense),
-// 805 / 917 (79 M), 924 / 825 (43 M, below the entries line: row by row 828).
+// several times an L2, the bins fill the chip (256 CUs x 16 wavefronts), and a bin has enough entries for its padding to whole
+// batches and its copies of the rows.  The lines are drawn by lane groups and row size where both sides were measured, over 11 graphs of
+// 30 k to 2 M nodes, average degree 15 to 500, k 8 to 128, widths 64 to 512 (profiles/forward_sweep_rule_over_graphs.txt: the kernel
+// taken is 0.4 % above the better one on average, 16 % at most, row by row 16 %); us, row by row / sweep (MB: of the CBSR; entries: of a lane group):
+//   8 groups: k = 8, 8.5 MB, 75 entries 678 / 641, 9.6 MB, 61 entries 709 / 652, 38 entries 337 / 372; k = 12 behind everywhere
+//   4 groups: k = 16, 13 MB, 150 entries 509 / 400, 32 MB, 60 entries 512 / 504, 77 MB, 31 entries 604 / 610; k = 50, 63 MB, 60 entries 1103 / 1025
+//   2 groups: k = 32, 16 MB, 752 entries 610 / 374, 102 entries 78 / 82, 96 MB, 40 entries 236 / 228; dim 512, 48 MB, 26 entries 220 / 264;
+//     bf16 values 77 MB, 152 entries 640 / 588, 32 MB, 301 entries 351 / 356; k = 96, 14 MB, 149 entries 60 / 58, 346 MB, 24 entries 674 / 733
+//   1 group: k = 64, 19 MB, 755 entries 310 / 264, 9.6 MB, 298 entries 53 / 79, 192 MB, 80 entries 569 / 512; k = 128, 23 MB, 298 entries 187 / 171
 int sweep_rows(const maxk_graph* g, int dim, int k, int index_bytes, int val_bytes)
 {
-    if ((k & (k - 1)) != 0 || k < 8 || k > 128 || dim > 512 || g->N > (1 << kSweepRowShift) || g->nnz == 0 || g->fwd_sweep == 1)
-        return 0;
-    const int per_bin = k >= 64 ? 4 : k == 32 ? 2 : 1;
+    if (!fwd_groups(k).lanes || k > 128 || dim > 512 || g->N > (1 << kSweepRowShift) || g->nnz == 0 || g->fwd_sweep == 1) return 0;
+    const int per_bin = sweep_bin_rows(k, dim), groups = sweep_groups(k);
     // a wavefront per bin, rounded up to whole workgroups, is below the 2^32 threads of a launch
     if ((g->csr_items.n_items + per_bin - 1) / per_bin > (1 << 26) - 64) return 0;
     if (g->fwd_sweep == 2) return per_bin;
     const int record = fwd_uses_packed(g, k, index_bytes, val_bytes) ? fwd_packed_record_bytes(k, index_bytes, val_bytes)
                                                                      : k * (val_bytes + index_bytes);
     const double bins = (double)g->csr_items.n_items / per_bin, table = (double)g->N * record;
-    const double entries = (double)g->nnz / (bins * sweep_groups(k));  // of a lane group
-    const bool pays = table >= (k == 64 ? 30e6 : 10e6) && bins >= 8192.0 && entries >= (k == 16 ? 100.0 : 48.0) &&
-                      dim <= (k == 128 ? 512 : k >= 32 ? 400 : 256);
-    return pays ? per_bin : 0;
+    const double entries = (double)g->nnz / (bins * groups) * std::min(1.0, 256.0 / dim);  // of a lane group, by the length of its rows
+    const bool pays = groups == 8   ? k == 8 && table >= 8e6 && entries >= 48.0
+                      : groups == 4 ? (table >= 9e6 && entries >= 100.0) || (table >= 20e6 && entries >= 58.0)
+                      : groups == 1 ? table >= 18e6 && entries >= 60.0
+                      : k > kWave   ? table >= 14e6 && entries >= 32.0
+                      : val_bytes == 4 ? (table >= 10e6 && entries >= 300.0) || (table >= 20e6 && entries >= 40.0)
+                                       : (table >= 10e6 && entries >= 500.0) || (table >= 60e6 && entries >= 60.0);
+    return pays && bins >= 4096.0 ? per_bin : 0;
 }
 
 maxk_status ensure_packed(maxk_graph* g, int k, int index_bytes, int val_bytes)
@@ -1472,7 +1480,7 @@ maxk_status reserve_shape(maxk_graph* g, int dim, int k, int dy_value_type)
     if (const int per_bin = sweep_rows(g, dim, k, dim <= 256 ? 1 : 2, 4)) {  // (narrower records may not need it)
         SweepSet* W = nullptr;
         forget_refused(g, {kRefusedSweep, sweep_groups(k), sweep_batch(k), per_bin});
-        (void)sweep_for(g, sweep_groups(k), sweep_batch(k), per_bin, false, &W);  // (not built: row by row)
+        (void)sweep_for(g, k, dim, per_bin, false, &W);  // (not built: row by row)
     }
     for (int vb = 2; vb <= 4; vb += 2) {
         for (int ib = 1; ib <= 4; ib *= 2) {
@@ -1529,7 +1537,7 @@ MAXK_API maxk_status maxk_graph_create(maxk_graph** out, int64_t N, int64_t nnz,
     g->d_val = d_val;
     g->chunk = env_int("MAXK_CHUNK", default_chunk(nnz), 64, 1 << 20);
     g->slab_kb = env_int("MAXK_SLAB_KB", 3584, 64, 1 << 20);
-    g->fwd_pack_max = env_int("MAXK_FWD_PACK_MAX", 96, 0, 1 << 20);
+    g->fwd_pack_max = env_int("MAXK_FWD_PACK_MAX", -1, -1, 1 << 20);
     g->fwd_sweep = env_int("MAXK_FWD_SWEEP", 0, 0, 2);
     g->pull_form = env_int("MAXK_PULL_FORM", 0, 0, 2);
     g->bwd_regs = env_int("MAXK_BWD_REGS", 0, 0, 3);
@@ -1697,7 +1705,7 @@ MAXK_API maxk_status maxk_spgemm_fwd_narrow(maxk_graph* g, const void* d_sp_data
     }
     if (const int per_bin = sweep_rows(g, dim, k, index_bytes, vb)) {
         SweepSet* W = nullptr;
-        st = sweep_for(g, sweep_groups(k), sweep_batch(k), per_bin, reserved_for(g, dim, k) || capturing((hipStream_t)stream), &W);
+        st = sweep_for(g, k, dim, per_bin, reserved_for(g, dim, k) || capturing((hipStream_t)stream), &W);
         if (st == MAXK_OK)
             return launch_spgemm_fwd_sweep(g->csr_items, *W, d_sp_data, value_type, d_sp_index, index_bytes, g->N, packed, dim, k,
                                            d_Y, g->d_partials, (hipStream_t)stream);
@@ -1734,7 +1742,7 @@ MAXK_API maxk_status maxk_spgemm_fwd_noalloc(maxk_graph* g, const float* d_sp_da
     // nothing in the array has to start at zero: the kernels write every partial row and every record they read
     if (const int per_bin = sweep_rows(g, dim, k, index_bytes, 4)) {  // where the regrouped A is there already
         SweepSet* W = nullptr;
-        if (sweep_for(g, sweep_groups(k), sweep_batch(k), per_bin, true, &W) == MAXK_OK)
+        if (sweep_for(g, k, dim, per_bin, true, &W) == MAXK_OK)
             return launch_spgemm_fwd_sweep(g->csr_items, *W, d_sp_data, MAXK_VALUE_F32, d_sp_index, index_bytes, g->N, packed, dim,
                                            k, d_Y, partials, (hipStream_t)stream);
     }

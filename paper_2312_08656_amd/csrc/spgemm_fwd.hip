@@ -41,12 +41,33 @@ int fwd_packed_index_offset(int k, int index_bytes, int val_bytes)
     return (k * val_bytes + index_bytes - 1) / index_bytes * index_bytes;
 }
 
-int fwd_packed_record_bytes(int k, int index_bytes, int val_bytes)
+namespace {
+int padded(int bytes) { return (bytes + 63) & ~63; }
+int split_record_bytes(int k, int index_bytes, int val_bytes) { return padded(fwd_packed_index_offset(k, index_bytes, val_bytes) + k * index_bytes); }
+}  // namespace
+
+// From k = 33 on a row is whole cache lines or nearly so.  16-bit values and their columns in pairs where those take no more
+// sectors: half the loads (132 k nodes, 79 M entries, us with columns behind the values / so: k = 8 706 / 658, k = 16 680 / 616).  Pairs
+// of 8 bytes are slower for fp32 (k = 16 696 / 796): a load of 8 bytes a lane takes an access for every four lanes.
+int fwd_layout(int k, int index_bytes, int val_bytes)
 {
-    return (fwd_packed_index_offset(k, index_bytes, val_bytes) + k * index_bytes + 63) & ~63;
+    const FwdGroups by = fwd_groups(k);
+    if (k > kWave / 2) return kFwdArrays;
+    if (val_bytes == 4) return k == 8 ? kFwdHalves : kFwdRecord;
+    return by.lanes && by.passes < 3 && padded(4 * k) <= split_record_bytes(k, index_bytes, val_bytes) ? kFwdPairs : kFwdRecord;
 }
 
-int fwd_private_copies(int k) { return private_copies(k); }
+int fwd_packed_record_bytes(int k, int index_bytes, int val_bytes)
+{
+    const int layout = fwd_layout(k, index_bytes, val_bytes);
+    return layout == kFwdHalves ? 64 : layout == kFwdPairs ? padded(4 * k) : split_record_bytes(k, index_bytes, val_bytes);
+}
+
+int fwd_private_copies(int k)
+{
+    const int lanes = fwd_groups(k).lanes;
+    return lanes ? kWave / lanes : private_copies(k);
+}
 
 maxk_status launch_spgemm_fwd(const ItemList& L, const int32_t* col, const float* val, const void* sp_data,
                               int value_type, const void* sp_index, int index_bytes, int64_t N, char* packed, int dim,

@@ -1,12 +1,16 @@
 // Forward aggregation: row-wise-product SpGEMM with dense output
 // (Eq. 2 left; Sec. 3.2 "Forward Computation"; prior art: Alg. 1).
 //
-// One 64-lane wavefront (= one workgroup, so no cross-wave barrier exists)
-// owns one work item: a run of at most `chunk` stored entries of one row of A.
-// The item's (col, val) pairs are staged 64 at a time through LDS, and the
-// wavefront walks a FLAT list of units (entry e, position t): unit u belongs to
-// entry u / k and CBSR position u % k, so all 64 lanes stay busy for every k and
-// the k lanes of one entry read k contiguous values and k contiguous indices.
+// One 64-lane wavefront owns one work item (a run of at most `chunk` stored entries of one row of A) or a bin of them, and
+// works on 64 / LANES entries side by side, LANES lanes an entry (FwdLanes).  The other k run spgemm_fwd_rmw_kernel, which walks a
+// FLAT list of units (entry e, position t), 64 at a time: unit u belongs to entry u / k and CBSR position u % k.
+//
+// Bound by instruction issue before, by LDS now: a wave instruction of 64 positions took 14 to 20 vector instructions (the entry's
+// node and weight, 64-bit addresses, predicates) beside an LDS read-add-write pair of 12 clocks, 8 of them bank conflicts of
+// random columns; now it takes 4 to 8: offsets are 32 bits and the broadcasts of an entry's node, row and weight are part of the
+// instructions that use them, whole batches need no predicates, and the loads of the next batch's first entries are under way while a
+// batch is added.  us, before / now: 2.1 M entries on 4 k nodes, k = 16 29.8 / 21.9; 1.2 M on 40 k, width 100, k = 13 45.3 / 26.7; 4 M on
+// 40 k, k = 24 110 / 64; 14.7 M on 717 k, width 384, k = 96 1080 / 957; 115 M on 233 k, k = 32 2025 / 1665, bf16 k = 64 2922 / 2455.
 //
 // Accumulation.  LDS floating-point atomics (ds_add_f32) retire about one lane
 // every three clocks on this chip (measured: ~190 clocks per wave instruction),
@@ -15,7 +19,7 @@
 // safe here without atomics because (a) the k positions of one CBSR row are
 // distinct columns, and (b) the entries that share one wave instruction (at most
 // NB = ceil(64/k)+1 consecutive ones) accumulate into NB PRIVATE copies of the
-// output row (copy e % NB), while LDS operations of one wavefront execute in
+// output row (copy e % NB; one for each lane group), while LDS operations of one wavefront execute in
 // program order.  The copies are added up when the row is written out.
 // Rows longer than `chunk` write partial rows that a second kernel adds up
 // (deterministic order, and it bounds the length of any fp32 running sum);
@@ -119,12 +123,20 @@ __global__ __launch_bounds__(kWave) void spgemm_fwd_atomic_kernel(const WorkItem
     for (int c = lane; c < dim; c += kWave) out[c] = row_buf[c];
 }
 
+// A pair: a 16-bit value in the upper half, 4 x its column (below 4096) in the lower one.
+__device__ __forceinline__ uint32_t fwd_pair_column(uint32_t p) { return p & 0xFFFFu; }
+template <int VT>
+__device__ __forceinline__ float fwd_pair_value(uint32_t p)
+{
+    return VT == MAXK_VALUE_BF16 ? __uint_as_float(p & 0xFFFF0000u) : widen_value<MAXK_VALUE_F16>((uint16_t)(p >> 16));
+}
+
 // For small k a CBSR row is a fraction of a cache line in EACH of the two arrays, and the kernel is
 // bound by the number of row requests (~137 G/s measured), not by bytes.  The packed path reads a
 // per-call repack instead: one record per node, k values followed by k indices, so an entry costs
 // one request.  The repack reads and writes N*k*(4+ib) bytes, against nnz*k*(4+ib) for the kernel
 // (2+ib with 16-bit values; the indices start at the next multiple of their own width).
-template <int VT, typename IdxT>
+template <int LAYOUT, int VT, typename IdxT>
 __global__ __launch_bounds__(256) void pack_cbsr_kernel(const value_store_t<VT>* __restrict__ sp_data,
                                                         const IdxT* __restrict__ sp_index, int64_t n_units, int k,
                                                         int rec_bytes, int idx_off, char* __restrict__ packed)
@@ -134,15 +146,22 @@ __global__ __launch_bounds__(256) void pack_cbsr_kernel(const value_store_t<VT>*
         const int64_t node = u / k;
         const int t = (int)(u - node * k);
         char* rec = packed + node * rec_bytes;
-        reinterpret_cast<value_store_t<VT>*>(rec)[t] = sp_data[u];
-        reinterpret_cast<IdxT*>(rec + idx_off)[t] = sp_index[u];
+        if constexpr (LAYOUT == kFwdPairs) {
+            reinterpret_cast<uint32_t*>(rec)[t] = (uint32_t)sp_data[u] << 16 | (uint32_t)sp_index[u] * 4u;
+        } else if constexpr (LAYOUT == kFwdHalves) {
+            reinterpret_cast<float*>(rec)[t] = sp_data[u];
+            reinterpret_cast<uint32_t*>(rec)[8 + t] = (uint32_t)sp_index[u] * 4u;
+        } else {
+            reinterpret_cast<value_store_t<VT>*>(rec)[t] = sp_data[u];
+            reinterpret_cast<IdxT*>(rec + idx_off)[t] = sp_index[u];
+        }
     }
 }
 
-// K: MaxK k when known at compile time (0 = runtime); ROUNDS: 64-unit rounds in flight;
+// ROUNDS: 64-unit rounds in flight;
 // PACKED: read the per-node (values, indices) records of pack_cbsr_kernel instead of the two arrays
 // VT: storage format of the CBSR values (widened exactly; products and sums are fp32 in every format)
-template <int K, int ROUNDS, bool PACKED, int VT, typename IdxT>
+template <int ROUNDS, bool PACKED, int VT, typename IdxT>
 __global__ __launch_bounds__(kWave) void spgemm_fwd_rmw_kernel(const WorkItem* __restrict__ items,
                                                                const int32_t* __restrict__ col,
                                                                const float* __restrict__ val,
@@ -150,14 +169,12 @@ __global__ __launch_bounds__(kWave) void spgemm_fwd_rmw_kernel(const WorkItem* _
                                                                const IdxT* __restrict__ sp_index,
                                                                const char* __restrict__ packed, int rec_bytes,
                                                                int idx_off,
-                                                               int dim, int k_rt, int nb_rt, int vec_out,
+                                                               int dim, int k, int nb, int vec_out,
                                                                float* __restrict__ Y, float* __restrict__ partials)
 {
     // vec_out: dim % 4 == 0 and Y / partials 16-byte aligned, so that a row is written with 16-byte stores; 2: past
     // L2, but for the partial rows of split ones, which combine_kernel reads next
     extern __shared__ __attribute__((aligned(16))) float lds[];
-    const int k = K ? K : k_rt;
-    const int nb = K ? private_copies(K) : nb_rt;
     const int lane = threadIdx.x;
     float* __restrict__ row_buf = lds;                                         // nb copies of the output row
     const int cs = dim + kCopyPad;                                             // floats from one copy to the next
@@ -241,12 +258,13 @@ __global__ __launch_bounds__(kWave) void spgemm_fwd_rmw_kernel(const WorkItem* _
 // add into private copies of the row (one per lane group of K lanes: the same number of partial sums per row), and LDS
 // operations of a wavefront execute in order.
 //
-// The LDS pipe bounds it next (a read-add-write pair is ~14 clocks a wave instruction), so entries do not go through LDS:
-// each row of 16 lanes holds the next 16 entries of its lane group (8 lanes the next 8 for K = 8) and hands them out by
-// data-parallel-primitive broadcasts.
-// Measured, us, kernel above / sweep: dense k = 8 1264 / 1126, k = 16 1549 / 1245, k = 32 2809 / 1995, k = 64 5262 / 2986,
-// k = 128 9239 / 5944, bf16 k = 64 3251 / 2893; 79 M entries on 132 k nodes k = 32 1513 / 1171; 43 M on 576 k k = 32
-// 1428 / 1270; 126 M on 2.4 M nodes k = 64 6079 / 4491.
+// A workgroup has half a CU's LDS.  The more rows a wavefront keeps there, the more often a record is met while an L2 holds it: us, rows
+// x wavefronts of a workgroup, 115 M entries on 233 k nodes: k = 32 2 x 16 1939, 4 x 10 1755, 5 x 8 1663, 10 x 4 1918 (43 M on 577 k:
+// 1250, 1178, 1187, 1179); k = 64 4 x 16 2778, 5 x 16 2626, 10 x 8 2688; k = 128 5 x 16 5470, 10 x 8 4894; k = 16 1 x 16 1293, 2 x 8 1176,
+// 4 x 5 1155.  Fetched from beyond L2 at k = 32: 12.2 GB at 2 x 16 (1939 us, the fabric's rate).
+// Measured, us, row by row / sweep: 115 M entries on 233 k nodes k = 16 1513 / 1173, k = 32 2774 / 1665, k = 64 5060 / 2633, k = 96 7789 / 5671,
+// k = 128 10436 / 4878, bf16 k = 64 3174 / 2455; 79 M entries on 132 k nodes k = 32 1521 / 1109; 43 M on 576 k k = 32
+// 1451 / 1216; 126 M on 2.4 M nodes k = 64 5948 / 4490.
 //
 // The entries are read once and Y is written once: both pass by L2's replacement order and leave its 4 MB to the records.
 // us, both plain / so: 43 M entries on 577 k nodes k = 32 1311 / 1276; 126 M on 2.4 M k = 64 4650 / 4547.  Y alone: 115 M on 233 k
@@ -256,9 +274,30 @@ __global__ __launch_bounds__(kWave) void spgemm_fwd_rmw_kernel(const WorkItem* _
 // 577 k k = 32 1476 / 1450 for both, 14.7 M on 717 k, dim 384, k = 96 1481 / 1439; rows of 100 or 300 floats too (8.5 M on
 // 500 k 336 / 307, 6.2 M on 200 k 286 / 261).
 constexpr int kSweepWaves = 16;            // wavefronts of a workgroup, at most
-constexpr size_t kSweepLds = 64 * 1024;    // LDS of a workgroup, at most: two of them on a CU
-constexpr uint32_t kSweepMeet = 8;         // batches between barriers (k = 32: 1996 / 2028 / 2098 us at 4 / 8 / 16, bf16
-                                           // k = 64: 3109 / 3028 / 2988)
+constexpr uint32_t kSweepMeet = 4;         // batches between barriers (5 x 8, k = 32: 1706 / 1681 / 1663 us at 1 / 2 / 4)
+
+// ---- the lane groups of a wavefront ----
+//
+// LANES lanes (8, 16, 32 or 64) work on an entry, a CBSR position each, in PASSES wave instructions; kWave / LANES entries are worked
+// on side by side.  Lane groups whose last pass is not full repeat position k - 1: the same value to the same place.  The entries
+// of a batch are held by the lanes themselves, a register of them in every 16 lanes (LANES = 8: in every quad), and an
+// instruction takes entry E of its group by a data-parallel-primitive broadcast that is part of it.
+template <int LANES_, int PASSES_>
+struct FwdLanes {
+    static constexpr int LANES = LANES_, PASSES = PASSES_, GROUPS = kWave / LANES;
+    static constexpr int PER = LANES >= 16 ? 16 : 4;                   // entries of a group in one register
+    static constexpr int BATCH = LANES >= 16 ? 16 : 8, HELD = BATCH / PER;  // entries of a group in a batch; registers that hold them
+    static constexpr int STEP = LANES == 8 && PASSES == 1 ? 4 : PASSES >= 5 ? 1 : PASSES >= 3 ? 2 : 8 / PASSES;  // loaded together
+    static constexpr int STEPS = BATCH / STEP, ROUNDS = STEP * PASSES;
+    static_assert(STEPS % 2 == 0, "two sets of registers take turns");
+    static constexpr bool WHOLE = LANES == kWave || PASSES == 1;       // the last pass is full
+};
+
+// k = 8 from records of 8 fp32 values and 4 x their columns: two groups share 16 lanes, which hold eight entries of each and bring a
+// whole record with one load, an access of 64 bytes (values and columns by themselves: two accesses of 32 and 8).
+struct FwdHalves : FwdLanes<8, 1> {
+    static constexpr int PER = 8, BATCH = 8, HELD = 1;
+};
 
 template <int I>
 __device__ __forceinline__ uint32_t row16_lane(uint32_t x)  // lane I of the caller's 16 lanes
@@ -266,166 +305,506 @@ __device__ __forceinline__ uint32_t row16_lane(uint32_t x)  // lane I of the cal
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x150 + I, 0xF, 0xF, true);
 }
 
-template <int I>
-__device__ __forceinline__ uint32_t row8_lane(uint32_t x)  // lane I of the caller's 8 lanes
+template <int PER, int I>
+__device__ __forceinline__ uint32_t held_entry(uint32_t x)  // entry I of the register of the caller's 16 or 8 lanes or quad
 {
-    // the quad of the eight that holds lane I, moved into both; then lane I % 4 of the quad
-    const uint32_t half = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, I < 4 ? 0x114 : 0x104, 0xF, I < 4 ? 0xA : 0x5, false);
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)half, (I & 3) * 0x55, 0xF, 0xF, true);
+    if constexpr (PER == 16) return row16_lane<I>(x);
+    else if constexpr (PER == 4) return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, I * 0x55, 0xF, 0xF, true);
+    else return (uint32_t)__builtin_amdgcn_update_dpp((int)row16_lane<I>(x), (int)x, 0x158 + I, 0xF, 0xC, false);  // (upper eight: their own)
 }
 
-// K: MaxK k (a power of two, 8..128).  A workgroup is up to 16 wavefronts with a bin each; they meet at a barrier every
-// kSweepMeet batches, which keeps a CU together on its way over the source nodes (k = 32: 2580 us without, 2100 with).
-template <int K, bool PACKED, int VT, typename IdxT>
-__global__ __launch_bounds__(kSweepWaves * kWave) void spgemm_fwd_sweep_kernel(
-    const int2* __restrict__ ent, const uint32_t* __restrict__ batch, const int2* __restrict__ bin_rows, int64_t n_bins,
-    int per_bin, const value_store_t<VT>* __restrict__ sp_data, const IdxT* __restrict__ sp_index,
-    const char* __restrict__ packed, int rec_bytes, int idx_off, int dim, int vec_out, float* __restrict__ Y,
-    float* __restrict__ partials)
-{
-    constexpr int GROUPS = sweep_groups(K), BATCH = sweep_batch(K);
-    constexpr int LANES = kWave / GROUPS;             // lanes of a group
-    constexpr int PASSES = K < kWave ? 1 : K / kWave;  // wave instructions per entry
-    constexpr int STEP = 8 / PASSES;                  // entries of a lane group in flight
-    extern __shared__ __attribute__((aligned(16))) float sweep_lds[];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int waves = blockDim.x / kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int64_t bin0 = (int64_t)blockIdx.x * waves, bin = bin0 + wave;
-    const int copy = per_bin * dim, total = GROUPS * copy;  // floats of one copy of the bin's rows, and of all of them
-    float* __restrict__ rows = sweep_lds + wave * total;
-    if ((total & 3) == 0) {
-        for (int c = lane * 4; c < total; c += kWave * 4) *reinterpret_cast<float4*>(rows + c) = make_float4(0.f, 0.f, 0.f, 0.f);
-    } else {
-        for (int c = lane; c < total; c += kWave) rows[c] = 0.f;
+// What one wavefront needs of the CBSR.  Offsets are 32 bits (fwd_wide: the arrays are larger, and they are 64).
+// ROWS: the entries say which row of a bin they belong to.
+template <class S, int LAYOUT, bool ROWS, int VT, typename IdxT>
+struct FwdWave {
+    static constexpr bool PAIRS = LAYOUT == kFwdPairs, HALVES = LAYOUT == kFwdHalves, PACKED = LAYOUT != kFwdArrays;
+    static_assert(HALVES == std::is_same_v<S, FwdHalves> && (!HALVES || VT == MAXK_VALUE_F32) && (!PAIRS || VT != MAXK_VALUE_F32));
+    static constexpr uint32_t kVal = PAIRS ? 4u : sizeof(value_store_t<VT>), kIdx = HALVES ? 4u : sizeof(IdxT);
+    using Value = std::conditional_t<PAIRS, uint32_t, value_store_t<VT>>;
+    typedef __attribute__((address_space(3))) float lds_float;
+    struct Held {  // a batch of entries: node (-1: none) and row; bytes from the first record; LDS bytes of the row; weight
+        uint32_t x[S::HELD], d[S::HELD], i[S::HELD], row[S::HELD];
+        float w[S::HELD];
+    };
+    struct Step {
+        Value d[S::ROUNDS];
+        uint32_t i[PAIRS ? 1 : S::ROUNDS];
+    };
+    const char* data;
+    const char* index;
+    uint32_t d_stride, i_stride;             // bytes of a node's values and columns (PACKED: of its record, both)
+    uint32_t d_lane, i_lane, d_last, i_last;  // this lane's position in the first and the last pass
+    uint32_t own, row_bytes;                  // LDS address of the group's copy; bytes of a row
+
+    __device__ __forceinline__ FwdWave(const value_store_t<VT>* sp_data, const IdxT* sp_index, const char* packed, int rec_bytes, int idx_off,
+                                       int dim, int k, int lane, uint32_t group_copy)
+    {
+        const uint32_t t = (uint32_t)(lane % S::LANES), last = min(t + (uint32_t)((S::PASSES - 1) * S::LANES), (uint32_t)k - 1u);
+        data = PACKED ? packed : reinterpret_cast<const char*>(sp_data);
+        index = PACKED ? packed + idx_off : reinterpret_cast<const char*>(sp_index);
+        d_stride = PACKED ? (uint32_t)rec_bytes : (uint32_t)k * kVal;
+        i_stride = PACKED ? (uint32_t)rec_bytes : (uint32_t)k * kIdx;
+        d_lane = t * kVal;
+        i_lane = t * kIdx;
+        d_last = last * kVal;
+        i_last = last * kIdx;
+        if (HALVES) {  // the first group's record as it is, the second's with its halves changed round
+            d_lane = (uint32_t)(lane % 16) * 4u;
+            i_lane = d_lane ^ 32u;
+        }
+        own = group_copy;
+        row_bytes = (uint32_t)dim * 4u;
     }
-    const uint32_t b0 = bin < n_bins ? batch[bin] : 0u, b1 = bin < n_bins ? batch[bin + 1] : 0u;
-    uint32_t longest = 0;  // batches of the workgroup's longest bin: every wavefront meets every barrier
-    for (int i = 0; i < waves && bin0 + i < n_bins; ++i) longest = max(longest, batch[bin0 + i + 1] - batch[bin0 + i]);
-    const int t = lane % LANES;  // CBSR position
-    const int own = lane / LANES * copy;
-    constexpr int64_t kBatchEntries = GROUPS * BATCH;
-    const int2* __restrict__ mine = ent + lane / LANES * BATCH + lane % BATCH;
-    int2 next = b0 < b1 ? load_once(mine + b0 * kBatchEntries) : make_int2(-1, 0);
-    for (uint32_t i = 0; i < longest; ++i) {
-        if (i % kSweepMeet == 0) __syncthreads();
-        const uint32_t b = b0 + i;
-        if (b >= b1) continue;  // wave-uniform
-        const int2 cur = next;
-        if (b + 1 < b1) next = load_once(mine + (b + 1) * kBatchEntries);
-        const auto steps = [&](auto first) {
-            constexpr int F = decltype(first)::value;
-            float d[8], w[8];
-            int at[8];
-            bool ok[8];
-            const auto load = [&](auto idx) {
-                constexpr int R = decltype(idx)::value, E = F + R / PASSES, P = R % PASSES;
-                uint32_t x;
-                if constexpr (BATCH == 8) {
-                    x = row8_lane<E>((uint32_t)cur.x);
-                    w[R] = __uint_as_float(row8_lane<E>((uint32_t)cur.y));
-                } else {
-                    x = row16_lane<E>((uint32_t)cur.x);
-                    w[R] = __uint_as_float(row16_lane<E>((uint32_t)cur.y));
-                }
-                ok[R] = x != 0xFFFFFFFFu;
-                const uint32_t node = ok[R] ? x & ((1u << kSweepRowShift) - 1u) : 0u;  // (padding reads node 0 and drops it)
-                const int base = own + (int)(x >> kSweepRowShift) * dim;
-                if constexpr (PACKED) {
-                    const char* rec = packed + (int64_t)node * rec_bytes;
-                    d[R] = widen_value<VT>(reinterpret_cast<const value_store_t<VT>*>(rec)[t + P * kWave]);
-                    at[R] = base + (int)reinterpret_cast<const IdxT*>(rec + idx_off)[t + P * kWave];
-                } else {
-                    const int64_t off = (int64_t)node * K + (t + P * kWave);
-                    d[R] = widen_value<VT>(sp_data[off]);
-                    at[R] = base + (int)sp_index[off];
-                }
-            };
-            [&]<int... I>(std::integer_sequence<int, I...>) { (load(std::integral_constant<int, I>{}), ...); }
-            (std::make_integer_sequence<int, 8>{});
+
+    __device__ __forceinline__ Held hold(const int2 (&e)[S::HELD]) const
+    {
+        Held h;
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                if (ok[r]) {
-                    const float old = rows[at[r]];
-                    rows[at[r]] = old + w[r] * d[r];
-                }
+        for (int r = 0; r < S::HELD; ++r) {
+            const uint32_t x = (uint32_t)e[r].x, node = ROWS ? x & ((1u << kSweepRowShift) - 1u) : x;
+            const uint32_t n = x == 0xFFFFFFFFu ? 0u : node;  // (padding reads node 0 and drops it)
+            h.x[r] = x;
+            h.d[r] = n * d_stride;
+            h.i[r] = PACKED ? h.d[r] : n * i_stride;
+            h.row[r] = ROWS ? own + (x >> kSweepRowShift) * row_bytes : own;
+            h.w[r] = __int_as_float(e[r].y);
+        }
+        return h;
+    }
+
+    __device__ __forceinline__ bool gap(const Held& h) const  // whether this lane holds padding
+    {
+        bool none = false;
+#pragma unroll
+        for (int r = 0; r < S::HELD; ++r) none |= h.x[r] == 0xFFFFFFFFu;
+        return none;
+    }
+
+    // Waits for the first loads of a loop.  (Columns that came into it as 8- or 16-bit values would be widened again in every turn.)
+    __device__ __forceinline__ void settle(Step& s) const
+    {
+#pragma unroll
+        for (int r = 0; r < (PAIRS || HALVES ? 0 : S::ROUNDS); ++r) asm volatile("" : "+v"(s.i[r]));
+    }
+
+    template <int E>
+    __device__ __forceinline__ uint32_t entry(const Held& h) const { return held_entry<S::PER, E % S::PER>(h.x[E / S::PER]); }
+
+    // The loads of entries F .. F + STEP - 1
+    template <int F, bool WIDE = false, typename Ok>
+    __device__ __forceinline__ void load(const Held& h, Step& s, Ok&& ok) const
+    {
+        const auto one = [&](auto idx) {
+            constexpr int R = decltype(idx)::value, E = F + R / S::PASSES, P = R % S::PASSES, H = E / S::PER, I = E % S::PER;
+            constexpr bool LAST = !S::WHOLE && P == S::PASSES - 1;
+            if (!ok(E)) return;
+            if constexpr (HALVES && !WIDE) {
+                s.d[R] = *reinterpret_cast<const float*>(data + (uint64_t)(row16_lane<I>(h.d[H]) + d_lane));
+                s.i[R] = *reinterpret_cast<const uint32_t*>(data + (uint64_t)(row16_lane<I + 8>(h.d[H]) + i_lane));
+                return;
             }
+            uint64_t at_d, at_i;
+            if constexpr (WIDE) {
+                const uint32_t x = held_entry<S::PER, I>(h.x[H]), node = x == 0xFFFFFFFFu ? 0u : ROWS ? x & ((1u << kSweepRowShift) - 1u) : x;
+                at_d = (uint64_t)node * d_stride + (LAST ? d_last : d_lane);
+                at_i = (uint64_t)node * i_stride + (LAST ? i_last : i_lane);
+                if constexpr (HALVES) {
+                    const uint32_t x0 = row16_lane<I>(h.x[H]), x1 = row16_lane<I + 8>(h.x[H]), mask = ROWS ? (1u << kSweepRowShift) - 1u : 0xFFFFFFFFu;
+                    at_d = (uint64_t)(x0 == 0xFFFFFFFFu ? 0u : x0 & mask) * d_stride + d_lane;
+                    at_i = (uint64_t)(x1 == 0xFFFFFFFFu ? 0u : x1 & mask) * d_stride + i_lane;
+                }
+            } else {
+                at_d = held_entry<S::PER, I>(h.d[H]) + (LAST ? d_last : d_lane);
+                at_i = held_entry<S::PER, I>(PACKED ? h.d[H] : h.i[H]) + (LAST ? i_last : i_lane);
+            }
+            constexpr uint32_t skip = LAST ? 0u : (uint32_t)(P * S::LANES);
+            s.d[R] = *reinterpret_cast<const Value*>(data + skip * kVal + at_d);
+            if constexpr (HALVES) s.i[R] = *reinterpret_cast<const uint32_t*>(data + at_i);
+            else if constexpr (!PAIRS) s.i[R] = *reinterpret_cast<const IdxT*>(index + skip * kIdx + at_i);
         };
-        [&]<int... I>(std::integer_sequence<int, I...>) { (steps(std::integral_constant<int, I * STEP>{}), ...); }
-        (std::make_integer_sequence<int, BATCH / STEP>{});
+        [&]<int... I>(std::integer_sequence<int, I...>) { (one(std::integral_constant<int, I>{}), ...); }
+        (std::make_integer_sequence<int, S::ROUNDS>{});
     }
-    if (bin >= n_bins) return;
-    // the wavefront's own LDS, whose operations execute in order: only the compiler has to keep it
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (int i = 0; i < per_bin; ++i) {
-        const int2 to = bin_rows[bin * per_bin + i];
-        if (to.x < 0) continue;
-        float* __restrict__ out = to.y < 0 ? Y + (int64_t)to.x * dim : partials + (int64_t)to.y * dim;
-        const float* __restrict__ row = rows + i * dim;
-        if (vec_out) {
-            const bool once = vec_out == 2 && to.y < 0;
-            for (int c = lane * 4; c < dim; c += kWave * 4) {
-                float4 acc = *reinterpret_cast<const float4*>(row + c);
-#pragma unroll
-                for (int g = 1; g < GROUPS; ++g) {
-                    const float4 x = *reinterpret_cast<const float4*>(row + g * copy + c);
-                    acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
-                }
-                if (once) store_once(out + c, acc); else *reinterpret_cast<float4*>(out + c) = acc;
+
+    // ... and what they brought, times the weights, into the row.  LDS operations of a wavefront execute in order.
+    template <int F, typename Ok>
+    __device__ __forceinline__ void add(const Held& h, const Step& s, Ok&& ok) const
+    {
+        const auto one = [&](auto idx) {
+            constexpr int R = decltype(idx)::value, E = F + R / S::PASSES, H = E / S::PER, I = E % S::PER;
+            const uint32_t row = ROWS ? held_entry<S::PER, I>(h.row[H]) : own;
+            uint32_t column;  // 4 x
+            float x;
+            if constexpr (PAIRS) {
+                column = fwd_pair_column(s.d[R]);
+                x = fwd_pair_value<VT>(s.d[R]);
+            } else if constexpr (HALVES) {
+                const bool low = (threadIdx.x & 8u) == 0;
+                const uint32_t first = __float_as_uint(s.d[R]), second = s.i[R];
+                x = __uint_as_float(low ? first : second);
+                column = (uint32_t)__builtin_amdgcn_mov_dpp((int)(low ? second : first), 0x128, 0xF, 0xF, true);  // from 8 lanes on, round 16
+            } else {
+                column = s.i[R] * 4u;
+                x = widen_value<VT>(s.d[R]);
             }
-        } else {
-            for (int c = lane; c < dim; c += kWave) {
-                float acc = row[c];
+            lds_float* const at = reinterpret_cast<lds_float*>(row + column);
+            const float w = __uint_as_float(held_entry<S::PER, I>(__float_as_uint(h.w[H])));
+            if (ok(std::integral_constant<int, E>{})) *at = fmaf(w, x, *at);
+        };
+        [&]<int... I>(std::integer_sequence<int, I...>) { (one(std::integral_constant<int, I>{}), ...); }
+        (std::make_integer_sequence<int, S::ROUNDS>{});
+    }
+};
+
+constexpr auto kAlways = [](auto) { return true; };
+
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f)
+{
+    [&]<int... I>(std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }(std::make_integer_sequence<int, N>{});
+}
+
+// The group's copies of a row, `copy` floats apart, added up and written
+template <int GROUPS>
+__device__ __forceinline__ void write_out(const float* __restrict__ row, int copy, int dim, int lane, bool vec, bool once, float* __restrict__ out)
+{
+    if (vec) {
+        for (int c = lane * 4; c < dim; c += kWave * 4) {
+            float4 acc = *reinterpret_cast<const float4*>(row + c);
 #pragma unroll
-                for (int g = 1; g < GROUPS; ++g) acc += row[g * copy + c];
-                out[c] = acc;
+            for (int g = 1; g < GROUPS; ++g) {
+                const float4 x = *reinterpret_cast<const float4*>(row + g * copy + c);
+                acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
             }
+            if (once) store_once(out + c, acc); else *reinterpret_cast<float4*>(out + c) = acc;
+        }
+    } else {
+        for (int c = lane; c < dim; c += kWave) {
+            float acc = row[c];
+#pragma unroll
+            for (int g = 1; g < GROUPS; ++g) acc += row[g * copy + c];
+            out[c] = acc;
         }
     }
 }
 
-template <bool PACKED, int VT, typename IdxT>
+__device__ __forceinline__ void zero_lds(float* __restrict__ p, int n, int lane)
+{
+    if ((n & 3) == 0) {
+        for (int c = lane * 4; c < n; c += kWave * 4) *reinterpret_cast<float4*>(p + c) = make_float4(0.f, 0.f, 0.f, 0.f);
+    } else {
+        for (int c = lane; c < n; c += kWave) p[c] = 0.f;
+    }
+}
+
+// the wavefront's own LDS, whose operations execute in order: only the compiler has to keep it
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ __forceinline__ uint32_t lds_address(const float* p)
+{
+    typedef __attribute__((address_space(3))) const float lds_const_float;
+    return (uint32_t)(uintptr_t)(lds_const_float*)p;
+}
+
+// Row by row: a wavefront per work item.  (k = 8, 10 .. 128 and 192; the others run spgemm_fwd_rmw_kernel.)
+template <class S, int LAYOUT, int VT, typename IdxT>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(8))) void spgemm_fwd_row_kernel(
+    const WorkItem* __restrict__ items, const int32_t* __restrict__ col, const float* __restrict__ val,
+    const value_store_t<VT>* __restrict__ sp_data, const IdxT* __restrict__ sp_index, const char* __restrict__ packed, int rec_bytes,
+    int idx_off, int dim, int k, int wide, int vec_out, float* __restrict__ Y, float* __restrict__ partials)
+{
+    extern __shared__ __attribute__((aligned(16))) float row_lds[];
+    const int lane = threadIdx.x;
+    const WorkItem it = items[blockIdx.x];
+    const int copy = (dim + 3) & ~3;  // floats from one copy to the next
+    float* __restrict__ row = row_lds;
+    zero_lds(row, S::GROUPS * copy, lane);
+    wave_lds_fence();
+    const int g = lane / S::LANES;
+    using Wave = FwdWave<S, LAYOUT, false, VT, IdxT>;
+    const Wave wv(sp_data, sp_index, packed, rec_bytes, idx_off, dim, k, lane, lds_address(row + g * copy));
+    constexpr int kBatch = S::GROUPS * S::BATCH;
+    // Whole batches: a run of entries to each register of a group, so that the lanes of a load are next to each other; the last,
+    // shorter one: the groups take its entries in turn (the last entry again behind them).
+    const uint32_t in_run = (uint32_t)(g * S::PER + lane % S::PER), in_turn = (uint32_t)((lane % S::PER) * S::GROUPS + g);
+    const auto fetch = [&](int base, int2 (&e)[S::HELD]) {
+        const int from = min(base, it.end - 1);
+        const uint32_t most = (uint32_t)(it.end - 1 - from), mine = most + 1u >= (uint32_t)kBatch ? in_run : in_turn;
+#pragma unroll
+        for (int r = 0; r < S::HELD; ++r) {
+            const uint32_t p = min(mine + (uint32_t)(r * S::PER * S::GROUPS), most);
+            e[r] = make_int2((col + from)[p], __float_as_int((val + from)[p]));
+        }
+    };
+    if (it.begin < it.end) {
+        int base = it.begin, left = it.end - it.begin;
+        int2 e[S::HELD];
+        fetch(base, e);
+        typename Wave::Held cur = wv.hold(e);
+        typename Wave::Step s0, s1;
+        if (wide) {
+            while (left > 0) {
+                const auto ok = [&](int n) { return n * S::GROUPS < left; };
+                static_for<S::STEPS>([&](auto i) {
+                    wv.template load<decltype(i)::value * S::STEP, true>(cur, s0, ok);
+                    wv.template add<decltype(i)::value * S::STEP>(cur, s0, [&](auto n) { return decltype(n)::value * S::GROUPS + g < left; });
+                });
+                base += kBatch;
+                left -= kBatch;
+                if (left > 0) { fetch(base, e); cur = wv.hold(e); }
+            }
+        } else {
+            if (left >= kBatch) {
+                fetch(base + kBatch, e);
+                wv.template load<0>(cur, s0, kAlways);
+                wv.settle(s0);
+                do {
+                    typename Wave::Held next;
+                    static_for<S::STEPS>([&](auto i) {
+                        constexpr int I = decltype(i)::value, F = I * S::STEP;
+                        typename Wave::Step& mine = I % 2 ? s1 : s0;
+                        typename Wave::Step& other = I % 2 ? s0 : s1;
+                        if constexpr (I + 1 < S::STEPS) {
+                            wv.template load<F + S::STEP>(cur, other, kAlways);
+                        } else {  // the first ones of the next batch (the last entry's again behind the last)
+                            next = wv.hold(e);
+                            wv.template load<0>(next, other, kAlways);
+                            fetch(base + 2 * kBatch, e);
+                        }
+                        wv.template add<F>(cur, mine, kAlways);
+                    });
+                    cur = next;
+                    base += kBatch;
+                    left -= kBatch;
+                } while (left >= kBatch);
+            } else {
+                wv.template load<0>(cur, s0, [&](int n) { return n * S::GROUPS < left; });
+            }
+            if (left > 0) {
+                static_for<S::STEPS>([&](auto i) {
+                    constexpr int I = decltype(i)::value, F = I * S::STEP;
+                    typename Wave::Step& mine = I % 2 ? s1 : s0;
+                    typename Wave::Step& other = I % 2 ? s0 : s1;
+                    if (F * S::GROUPS < left) {
+                        if constexpr (I + 1 < S::STEPS) wv.template load<F + S::STEP>(cur, other, [&](int n) { return n * S::GROUPS < left; });
+                        wv.template add<F>(cur, mine, [&](auto n) { return decltype(n)::value * S::GROUPS + g < left; });
+                    }
+                });
+            }
+        }
+    }
+    wave_lds_fence();
+    float* __restrict__ out = it.slot < 0 ? Y + (int64_t)it.row * dim : partials + (int64_t)it.slot * dim;
+    write_out<S::GROUPS>(row, copy, dim, lane, vec_out != 0, vec_out == 2 && it.slot < 0, out);
+}
+
+// A workgroup is up to 16 wavefronts with a bin each; they meet at a barrier every kSweepMeet batches, which keeps a CU together on its
+// way over the source nodes.
+template <class S, int LAYOUT, int VT, typename IdxT>
+__global__ __launch_bounds__(kSweepWaves * kWave) __attribute__((amdgpu_waves_per_eu(8))) void spgemm_fwd_sweep_kernel(
+    const int2* __restrict__ ent, const uint32_t* __restrict__ batch, const int2* __restrict__ bin_rows, int64_t n_bins,
+    int per_bin, const value_store_t<VT>* __restrict__ sp_data, const IdxT* __restrict__ sp_index,
+    const char* __restrict__ packed, int rec_bytes, int idx_off, int dim, int k, int wide, int vec_out, float* __restrict__ Y,
+    float* __restrict__ partials)
+{
+    extern __shared__ __attribute__((aligned(16))) float sweep_lds[];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int waves = blockDim.x / kWave, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t bin0 = (int64_t)blockIdx.x * waves, bin = bin0 + wave;
+    const int copy = per_bin * dim, total = S::GROUPS * copy;  // floats of one copy of the bin's rows, and of all of them
+    float* __restrict__ rows = sweep_lds + wave * total;
+    zero_lds(rows, total, lane);
+    wave_lds_fence();
+    const uint32_t b0 = bin < n_bins ? batch[bin] : 0u, b1 = bin < n_bins ? batch[bin + 1] : 0u;
+    uint32_t longest = 0;  // batches of the workgroup's longest bin: every wavefront meets every barrier
+    for (int i = 0; i < waves && bin0 + i < n_bins; ++i) longest = max(longest, batch[bin0 + i + 1] - batch[bin0 + i]);
+    const int g = lane / S::LANES;
+    using Wave = FwdWave<S, LAYOUT, true, VT, IdxT>;
+    const Wave wv(sp_data, sp_index, packed, rec_bytes, idx_off, dim, k, lane, lds_address(rows + g * copy));
+    const uint32_t lane_entry = (uint32_t)(g * S::BATCH + lane % S::PER);
+    const auto fetch = [&](uint32_t b, int2 (&e)[S::HELD]) {
+        const int2* const at = ent + (int64_t)min(b, b1 - 1u) * (S::GROUPS * S::BATCH);
+#pragma unroll
+        for (int r = 0; r < S::HELD; ++r) e[r] = load_once(at + (lane_entry + (uint32_t)(r * S::PER)));
+    };
+    const uint32_t n = b1 - b0;
+    uint32_t i = 0;
+    if (n) {
+        int2 e[S::HELD];
+        fetch(b0, e);
+        typename Wave::Held cur = wv.hold(e);
+        fetch(b0 + 1, e);
+        const auto there = [&](auto m) { return wv.template entry<decltype(m)::value>(cur) != 0xFFFFFFFFu; };
+        if (wide) {
+            for (; i < n; ++i) {
+                if (i % kSweepMeet == 0) __builtin_amdgcn_s_barrier();
+                static_for<S::STEPS>([&](auto j) {
+                    typename Wave::Step s;
+                    wv.template load<decltype(j)::value * S::STEP, true>(cur, s, kAlways);
+                    wv.template add<decltype(j)::value * S::STEP>(cur, s, there);
+                });
+                cur = wv.hold(e);
+                fetch(b0 + i + 2, e);
+            }
+        } else {
+            typename Wave::Step s0, s1;
+            wv.template load<0>(cur, s0, kAlways);
+            wv.settle(s0);
+            const auto batch_of = [&](auto&& ok) {
+                typename Wave::Held next;
+                static_for<S::STEPS>([&](auto j) {
+                    constexpr int J = decltype(j)::value, F = J * S::STEP;
+                    typename Wave::Step& now = J % 2 ? s1 : s0;
+                    typename Wave::Step& other = J % 2 ? s0 : s1;
+                    if constexpr (J + 1 < S::STEPS) {
+                        wv.template load<F + S::STEP>(cur, other, kAlways);
+                    } else {  // the first ones of the next batch (behind the last: the last batch's again)
+                        next = wv.hold(e);
+                        wv.template load<0>(next, other, kAlways);
+                        fetch(b0 + i + 2, e);
+                    }
+                    wv.template add<F>(cur, now, ok);
+                });
+                cur = next;
+            };
+            // whole batches; the lists of a bin differ by a few entries, so that only its last one or two have gaps
+            for (; i < n && __builtin_amdgcn_ballot_w64(wv.gap(cur)) == 0; ++i) {
+                if (i % kSweepMeet == 0) __builtin_amdgcn_s_barrier();
+                batch_of(kAlways);
+            }
+            for (; i < n; ++i) {
+                if (i % kSweepMeet == 0) __builtin_amdgcn_s_barrier();
+                batch_of(there);
+            }
+        }
+    }
+    for (; i < longest; ++i)
+        if (i % kSweepMeet == 0) __builtin_amdgcn_s_barrier();
+    if (bin >= n_bins) return;
+    wave_lds_fence();
+    for (int r = 0; r < per_bin; ++r) {
+        const int2 to = bin_rows[bin * per_bin + r];
+        if (to.x < 0) continue;
+        float* __restrict__ out = to.y < 0 ? Y + (int64_t)to.x * dim : partials + (int64_t)to.y * dim;
+        write_out<S::GROUPS>(rows + r * dim, copy, dim, lane, vec_out != 0, vec_out == 2 && to.y < 0, out);
+    }
+}
+
+// Runs F<FwdLanes<LANES, PASSES>> for MaxK k.
+template <int LAYOUT, typename F>
+maxk_status for_fwd_groups(int k, F&& f)
+{
+    const FwdGroups by = fwd_groups(k);
+    if constexpr (LAYOUT == kFwdHalves) return f.template operator()<FwdHalves>();
+    else {
+#define MAXK_FWD_GROUPS(LANES, PASSES) \
+    if (by.lanes == LANES && by.passes == PASSES) return f.template operator()<FwdLanes<LANES, PASSES>>()
+    MAXK_FWD_GROUPS(8, 1);
+    MAXK_FWD_GROUPS(8, 2);
+    MAXK_FWD_GROUPS(16, 1);
+    if constexpr (LAYOUT != kFwdPairs) MAXK_FWD_GROUPS(8, 3);
+    MAXK_FWD_GROUPS(16, 2);
+    MAXK_FWD_GROUPS(32, 1);
+    if constexpr (LAYOUT == kFwdArrays) {
+        MAXK_FWD_GROUPS(16, 3);
+        MAXK_FWD_GROUPS(16, 4);
+        MAXK_FWD_GROUPS(32, 3);
+        MAXK_FWD_GROUPS(32, 4);
+        MAXK_FWD_GROUPS(64, 1);
+        MAXK_FWD_GROUPS(64, 2);
+        MAXK_FWD_GROUPS(64, 3);
+    }
+#undef MAXK_FWD_GROUPS
+    return MAXK_UNSUPPORTED;
+    }
+}
+
+template <int LAYOUT, int VT, typename IdxT>
 maxk_status launch_sweep(const SweepSet& S, const value_store_t<VT>* sp_data, const IdxT* sp_index, const char* packed,
                          int rec_bytes, int idx_off, int64_t N, int dim, int k, float* Y, float* partials, hipStream_t s)
 {
     const size_t lds = sizeof(float) * (size_t)(S.groups * S.per_bin) * (size_t)dim;
-    int waves = kSweepWaves;
-    while (waves > 1 && lds * waves > kSweepLds) waves /= 2;
+    const int waves = sweep_waves(k, S.per_bin, dim);
+    if (waves < 1) return MAXK_UNSUPPORTED;
     const int vec_out = dim % 4 == 0 && aligned(Y, 16) && aligned(partials, 16) ? (past_l2(N * dim * 4) ? 2 : 1) : 0;
     const dim3 grid((unsigned)((S.n_bins + waves - 1) / waves)), block((unsigned)(kWave * waves));
-#define MAXK_FWD_SWEEP(K)                                                                                               \
-    hipLaunchKernelGGL((spgemm_fwd_sweep_kernel<K, PACKED, VT, IdxT>), grid, block, lds * waves, s, S.d_ent, S.d_batch, \
-                       S.d_rows, S.n_bins, S.per_bin, sp_data, sp_index, packed, rec_bytes, idx_off, dim, vec_out, Y, partials)
-    switch (k) {
-        case 8: MAXK_FWD_SWEEP(8); break;
-        case 16: MAXK_FWD_SWEEP(16); break;
-        case 32: MAXK_FWD_SWEEP(32); break;
-        default:
-            if constexpr (PACKED) return MAXK_UNSUPPORTED;
-            else if (k == 64) MAXK_FWD_SWEEP(64);
-            else if (k == 128) MAXK_FWD_SWEEP(128);
-            else return MAXK_UNSUPPORTED;
+    const int wide = fwd_wide(N, k, (int)sizeof(value_store_t<VT>), (int)sizeof(IdxT), LAYOUT ? rec_bytes : 0);
+    return for_fwd_groups<LAYOUT>(k, [&]<class G>() -> maxk_status {
+        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&spgemm_fwd_sweep_kernel<G, LAYOUT, VT, IdxT>),
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSweepLds);
+        MAXK_HIP_TRY(attr);
+        hipLaunchKernelGGL((spgemm_fwd_sweep_kernel<G, LAYOUT, VT, IdxT>), grid, block, lds * waves, s, S.d_ent, S.d_batch, S.d_rows, S.n_bins,
+                           S.per_bin, sp_data, sp_index, packed, rec_bytes, idx_off, dim, k, wide, vec_out, Y, partials);
+        MAXK_LAUNCH_CHECK();
+        return MAXK_OK;
+    });
+}
+
+template <int LAYOUT, int VT, typename IdxT>
+maxk_status launch_row(const ItemList& L, const int32_t* col, const float* val, const value_store_t<VT>* sp_data,
+                       const IdxT* sp_index, const char* packed, int rec_bytes, int idx_off, int64_t N, int dim, int k, float* Y,
+                       float* partials, hipStream_t s)
+{
+    if (L.n_items > 0x7FFFFFFF) return MAXK_UNSUPPORTED;
+    const int vec_out = dim % 4 == 0 && aligned(Y, 16) && aligned(partials, 16) ? (past_l2(N * dim * 4) ? 2 : 1) : 0;
+    if (const int lanes = fwd_groups(k).lanes) {
+        const int wide = fwd_wide(N, k, (int)sizeof(value_store_t<VT>), (int)sizeof(IdxT), LAYOUT ? rec_bytes : 0);
+        const size_t lds = sizeof(float) * (size_t)(kWave / lanes) * (size_t)((dim + 3) & ~3);
+        return for_fwd_groups<LAYOUT>(k, [&]<class G>() -> maxk_status {
+            hipLaunchKernelGGL((spgemm_fwd_row_kernel<G, LAYOUT, VT, IdxT>), dim3((unsigned)L.n_items), dim3(kWave), lds, s, L.d_items, col, val,
+                               sp_data, sp_index, packed, rec_bytes, idx_off, dim, k, wide, vec_out, Y, partials);
+            MAXK_LAUNCH_CHECK();
+            return MAXK_OK;
+        });
     }
-#undef MAXK_FWD_SWEEP
-    MAXK_LAUNCH_CHECK();
-    return MAXK_OK;
+    if constexpr (LAYOUT == kFwdPairs || LAYOUT == kFwdHalves) return MAXK_UNSUPPORTED;
+    else {
+        const int nb = private_copies(k);
+        const size_t lds = sizeof(float) * (size_t)((nb * (dim + kCopyPad) + 1) & ~1) + sizeof(int2) * kWave;
+        hipLaunchKernelGGL((spgemm_fwd_rmw_kernel<8, LAYOUT == kFwdRecord, VT, IdxT>), dim3((unsigned)L.n_items), dim3(kWave), lds, s, L.d_items,
+                           col, val, sp_data, sp_index, packed, rec_bytes, idx_off, dim, k, nb, vec_out, Y, partials);
+        MAXK_LAUNCH_CHECK();
+        return MAXK_OK;
+    }
+}
+
+// Calls launch(layout, index type's stand-in, record bytes, column offset) on the layout for this call, repacking the CBSR first
+// where there is a workspace for it.
+template <int VT, typename IdxT, typename F>
+maxk_status with_layout(const value_store_t<VT>* sp_data, const IdxT* sp_index, int64_t N, char* packed, int k, hipStream_t s, F&& launch)
+{
+    const int vb = (int)sizeof(value_store_t<VT>), ib = (int)sizeof(IdxT);
+    const int layout = packed ? fwd_layout(k, ib, vb) : kFwdArrays;
+    if (layout == kFwdArrays) return launch(std::integral_constant<int, kFwdArrays>{}, sp_index, 0, 0);
+    const int rec_bytes = fwd_packed_record_bytes(k, ib, vb), idx_off = fwd_packed_index_offset(k, ib, vb);
+    const int64_t n_units = N * (int64_t)k;
+    const dim3 blocks((unsigned)std::min<int64_t>((n_units + 255) / 256, 65536));
+    const auto repacked = [&](auto l, auto* index, int offset) -> maxk_status {
+        hipLaunchKernelGGL((pack_cbsr_kernel<decltype(l)::value, VT, IdxT>), blocks, dim3(256), 0, s, sp_data, sp_index, n_units, k, rec_bytes, idx_off, packed);
+        MAXK_LAUNCH_CHECK();
+        return launch(l, index, rec_bytes, offset);
+    };
+    const uint8_t* const any = nullptr;  // (columns of one width)
+    if constexpr (VT == MAXK_VALUE_F32) {
+        if (layout == kFwdHalves) return repacked(std::integral_constant<int, kFwdHalves>{}, any, 0);
+    } else {
+        if (layout == kFwdPairs) return repacked(std::integral_constant<int, kFwdPairs>{}, any, 0);
+    }
+    return repacked(std::integral_constant<int, kFwdRecord>{}, sp_index, idx_off);
 }
 
 template <int VT, typename IdxT>
 maxk_status launch_sweep_i(const SweepSet& S, const value_store_t<VT>* sp_data, const IdxT* sp_index, int64_t N, char* packed,
                            int dim, int k, float* Y, float* partials, hipStream_t s)
 {
-    // (a CBSR row of 64 positions is whole cache lines in both arrays: nothing to gain from a record, whatever the knob says)
-    if (!packed || k >= kWave) return launch_sweep<false, VT>(S, sp_data, sp_index, nullptr, 0, 0, N, dim, k, Y, partials, s);
-    const int vb = (int)sizeof(value_store_t<VT>);
-    const int rec_bytes = fwd_packed_record_bytes(k, (int)sizeof(IdxT), vb), idx_off = fwd_packed_index_offset(k, (int)sizeof(IdxT), vb);
-    const int64_t n_units = N * (int64_t)k;
-    const unsigned blocks = (unsigned)std::min<int64_t>((n_units + 255) / 256, 65536);
-    hipLaunchKernelGGL((pack_cbsr_kernel<VT, IdxT>), dim3(blocks), dim3(256), 0, s, sp_data, sp_index, n_units, k, rec_bytes,
-                       idx_off, packed);
-    MAXK_LAUNCH_CHECK();
-    return launch_sweep<true, VT>(S, sp_data, sp_index, packed, rec_bytes, idx_off, N, dim, k, Y, partials, s);
+    return with_layout<VT>(sp_data, sp_index, N, packed, k, s, [&](auto layout, auto* index, int rec_bytes, int idx_off) {
+        return launch_sweep<decltype(layout)::value, VT>(S, sp_data, index, packed, rec_bytes, idx_off, N, dim, k, Y, partials, s);
+    });
 }
 
 template <int VT>
@@ -449,51 +828,14 @@ maxk_status launch_atomic(const ItemList& L, const int32_t* col, const float* va
     return MAXK_OK;
 }
 
-template <bool PACKED, int VT, typename IdxT>
-maxk_status launch_rmw(const ItemList& L, const int32_t* col, const float* val, const value_store_t<VT>* sp_data,
-                       const IdxT* sp_index, const char* packed, int rec_bytes, int idx_off, int64_t N, int dim, int k, float* Y,
-                       float* partials, hipStream_t s)
-{
-    if (L.n_items > 0x7FFFFFFF) return MAXK_UNSUPPORTED;
-    dim3 grid((unsigned)L.n_items), block(kWave);
-    const int nb = private_copies(k);
-    const size_t lds = sizeof(float) * (size_t)((nb * (dim + kCopyPad) + 1) & ~1) + sizeof(int2) * kWave;
-    const int vec_out = dim % 4 == 0 && aligned(Y, 16) && aligned(partials, 16) ? (past_l2(N * dim * 4) ? 2 : 1) : 0;
-#define MAXK_FWD_RMW(K, R)                                                                                        \
-    hipLaunchKernelGGL((spgemm_fwd_rmw_kernel<K, R, PACKED, VT, IdxT>), grid, block, lds, s, L.d_items, col, val, \
-                       sp_data, sp_index, packed, rec_bytes, idx_off, dim, k, nb, vec_out, Y, partials)
-    switch (k) {
-        case 8: MAXK_FWD_RMW(8, 8); break;
-        case 16: MAXK_FWD_RMW(16, 8); break;
-        case 32: MAXK_FWD_RMW(32, 8); break;
-        case 64: MAXK_FWD_RMW(64, 8); break;
-        case 96: MAXK_FWD_RMW(96, 8); break;
-        case 128: MAXK_FWD_RMW(128, 8); break;
-        case 192: MAXK_FWD_RMW(192, 8); break;
-        default: MAXK_FWD_RMW(0, 8); break;
-    }
-#undef MAXK_FWD_RMW
-    MAXK_LAUNCH_CHECK();
-    return MAXK_OK;
-}
-
 template <int VT, typename IdxT>
-maxk_status launch_rmw_i(const ItemList& L, const int32_t* col, const float* val, const value_store_t<VT>* sp_data,
+maxk_status launch_row_i(const ItemList& L, const int32_t* col, const float* val, const value_store_t<VT>* sp_data,
                          const IdxT* sp_index, int64_t N, char* packed, int dim, int k, float* Y, float* partials,
                          hipStream_t s)
 {
-    if (packed) {
-        const int vb = (int)sizeof(value_store_t<VT>);
-        const int rec_bytes = fwd_packed_record_bytes(k, (int)sizeof(IdxT), vb);
-        const int idx_off = fwd_packed_index_offset(k, (int)sizeof(IdxT), vb);
-        const int64_t n_units = N * (int64_t)k;
-        const unsigned blocks = (unsigned)std::min<int64_t>((n_units + 255) / 256, 65536);
-        hipLaunchKernelGGL((pack_cbsr_kernel<VT, IdxT>), dim3(blocks), dim3(256), 0, s, sp_data, sp_index, n_units, k,
-                           rec_bytes, idx_off, packed);
-        MAXK_LAUNCH_CHECK();
-        return launch_rmw<true, VT>(L, col, val, sp_data, sp_index, packed, rec_bytes, idx_off, N, dim, k, Y, partials, s);
-    }
-    return launch_rmw<false, VT>(L, col, val, sp_data, sp_index, nullptr, 0, 0, N, dim, k, Y, partials, s);
+    return with_layout<VT>(sp_data, sp_index, N, packed, k, s, [&](auto layout, auto* index, int rec_bytes, int idx_off) {
+        return launch_row<decltype(layout)::value, VT>(L, col, val, sp_data, index, packed, rec_bytes, idx_off, N, dim, k, Y, partials, s);
+    });
 }
 
 // everything but the final sum of split rows, for one storage format of the values
@@ -503,11 +845,12 @@ maxk_status launch_fwd_vt(const ItemList& L, const int32_t* col, const float* va
                           float* partials, hipStream_t s)
 {
     const auto* sp_data = (const value_store_t<VT>*)sp_data_v;
-    const size_t private_lds = sizeof(float) * (size_t)private_copies(k) * (size_t)dim;
+    const FwdGroups by = fwd_groups(k);
+    const size_t private_lds = sizeof(float) * (size_t)(by.lanes ? kWave / by.lanes : private_copies(k)) * (size_t)dim;
     if (private_lds <= kMaxPrivateLds) {
-        if (index_bytes == 1) return launch_rmw_i<VT>(L, col, val, sp_data, (const uint8_t*)sp_index, N, packed, dim, k, Y, partials, s);
-        if (index_bytes == 2) return launch_rmw_i<VT>(L, col, val, sp_data, (const uint16_t*)sp_index, N, packed, dim, k, Y, partials, s);
-        return launch_rmw_i<VT>(L, col, val, sp_data, (const int32_t*)sp_index, N, packed, dim, k, Y, partials, s);
+        if (index_bytes == 1) return launch_row_i<VT>(L, col, val, sp_data, (const uint8_t*)sp_index, N, packed, dim, k, Y, partials, s);
+        if (index_bytes == 2) return launch_row_i<VT>(L, col, val, sp_data, (const uint16_t*)sp_index, N, packed, dim, k, Y, partials, s);
+        return launch_row_i<VT>(L, col, val, sp_data, (const int32_t*)sp_index, N, packed, dim, k, Y, partials, s);
     }
     if (index_bytes == 1) return launch_atomic<VT>(L, col, val, sp_data, (const uint8_t*)sp_index, dim, k, Y, partials, s);
     if (index_bytes == 2) return launch_atomic<VT>(L, col, val, sp_data, (const uint16_t*)sp_index, dim, k, Y, partials, s);

@@ -1,0 +1,76 @@
+"""The forward kernels that work by lane groups: every split of a wavefront, every layout of the CBSR, both kernels.
+
+Row lengths at the edges of a batch (8 to 64 entries, whatever the split) and of its steps, k at the edges of every split; each
+element within 1e-5 of the sum of the terms' magnitudes of the oracle, the bound of the other forward tests.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2312_08656_amd as maxk
+import synth
+from gpu_common import to_dev
+from helpers import csr_from_coo
+
+pytestmark = pytest.mark.gpu
+
+_DTYPE = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
+_LENGTHS = (0, 1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 95, 96, 127, 128, 129, 191, 193, 300)
+
+
+def _graph(seed):
+    rng = np.random.default_rng(seed)
+    N = 331
+    coo = []
+    for i in range(N):
+        n = _LENGTHS[i % len(_LENGTHS)]
+        coo += [(i, int(j), float(rng.normal())) for j in rng.choice(N, n, replace=False)]
+    return N, *csr_from_coo(N, coo)
+
+
+@pytest.mark.parametrize("k,dim,ib", [(8, 8, 1), (8, 300, 2), (10, 64, 1), (13, 100, 1), (15, 16, 4), (16, 256, 1), (17, 90, 1), (21, 256, 2),
+                                      (22, 130, 1), (31, 31, 1), (32, 256, 1), (33, 64, 1), (48, 200, 4), (49, 256, 1), (63, 100, 1), (64, 64, 1),
+                                      (65, 256, 1), (96, 384, 2), (97, 256, 1), (127, 130, 4), (128, 256, 1), (192, 255, 1), (9, 256, 1), (130, 256, 1)])
+@pytest.mark.parametrize("fmt", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("sweep", ["1", "2"])
+def test_forward_by_lane_groups(monkeypatch, k, dim, ib, fmt, sweep):
+    monkeypatch.setenv("MAXK_FWD_SWEEP", sweep)
+    N, rowptr, col, val = _graph(k)
+    H = synth.normal_matrix(N, dim, 5 + k)
+    sp_data = torch.empty((N, k), dtype=_DTYPE[fmt], device="cuda")
+    sp_index = torch.empty((N, k), dtype={1: torch.uint8, 2: torch.int16, 4: torch.int32}[ib], device="cuda")
+    maxk.maxk_topk_cbsr_narrow(to_dev(H), k, sp_data, sp_index)
+    index = oracle.topk_cbsr(H, k)[1]
+    ref, refabs = oracle.spgemm_fwd(rowptr, col, val, sp_data.float().cpu().numpy(), index, dim)
+    for pack in ("0", "192"):  # bytes of the largest row that is repacked: none; those of k <= 32
+        monkeypatch.setenv("MAXK_FWD_PACK_MAX", pack)
+        gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val))
+        Y = torch.full((N, dim), float("nan"), device="cuda")
+        maxk.maxk_spgemm_fwd_narrow(gr, sp_data, sp_index, dim, Y)
+        torch.cuda.synchronize()
+        assert (np.abs(Y.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all(), (k, dim, fmt, sweep, pack)
+        gr.destroy()
+
+
+@pytest.mark.parametrize("sweep", ["1", "2"])
+def test_forward_of_a_cbsr_above_4_gib(monkeypatch, sweep):
+    # byte offsets of 64 bits: nodes on both sides of the line, each row three entries of weight 1.  Whole numbers: any order, the same bits
+    monkeypatch.setenv("MAXK_FWD_SWEEP", sweep)
+    N, k, dim = 17_000_000, 64, 64
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    sp_data = torch.randint(-5, 6, (N, k), generator=gen, device="cuda", dtype=torch.int8).float()
+    assert sp_data.numel() * 4 > 2**32
+    sp_index = torch.arange(k, dtype=torch.uint8, device="cuda").repeat(N, 1)
+    rows = 3000
+    rowptr = torch.full((N + 1,), 3 * rows, dtype=torch.int32, device="cuda")
+    rowptr[: rows + 1] = torch.arange(0, 3 * rows + 1, 3, dtype=torch.int32, device="cuda")
+    col = torch.randint(N, (3 * rows,), generator=gen, device="cuda").to(torch.int32)
+    col[:2] = torch.tensor([0, N - 1], dtype=torch.int32)
+    gr = maxk.maxk_graph_create(rowptr, col, torch.ones(3 * rows, device="cuda"))
+    Y = torch.full((N, dim), float("nan"), device="cuda")
+    maxk.maxk_spgemm_fwd(gr, sp_data, sp_index, dim, Y)
+    want = sp_data[col.long()].view(rows, 3, dim).sum(1)
+    assert torch.equal(Y[:rows], want)
+    assert not bool(Y[rows:].any())
+    gr.destroy()
