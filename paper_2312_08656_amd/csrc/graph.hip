@@ -1776,7 +1776,7 @@ MAXK_API maxk_status maxk_sspmm_bwd_narrow(maxk_graph* g, const void* d_dY, int3
         rest.d_items += rest.n_items - tail;
         rest.n_items = tail;
         rest.n_split = rest.n_slots = 0;
-        return launch_bwd_pull(rest, g->d_csc_src, g->d_csc_val, d_dY, value_type, d_sp_index, index_bytes, dim, k, d_dXs, g->d_partials, s);
+        return launch_bwd_pull(rest, g->d_csc_src, g->d_csc_val, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs, g->d_partials, s);
     }
     if (plan.mode == MAXK_BWD_TILED)
         return launch_bwd_tiled(*plan.T, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs, s);
@@ -1792,7 +1792,7 @@ MAXK_API maxk_status maxk_sspmm_bwd_narrow(maxk_graph* g, const void* d_dY, int3
                                    sliced_in_place(dim, vb) ? nullptr : g->d_sliced, d_dXs, g->d_partials, s);
             if (st != MAXK_UNSUPPORTED) return st;
         }
-        return launch_bwd_pull(g->csc_items, g->d_csc_src, g->d_csc_val, d_dY, value_type, d_sp_index, index_bytes, dim, k,
+        return launch_bwd_pull(g->csc_items, g->d_csc_src, g->d_csc_val, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k,
                                d_dXs, g->d_partials, s);
     }
     return launch_bwd_push(g->csr_items, g->d_col, g->d_val, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs, s);

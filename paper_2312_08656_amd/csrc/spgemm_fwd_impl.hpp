@@ -36,6 +36,7 @@
 #include <utility>
 
 #include "common.hpp"
+#include "lanes.hpp"
 
 namespace maxk {
 
@@ -276,42 +277,11 @@ __global__ __launch_bounds__(kWave) void spgemm_fwd_rmw_kernel(const WorkItem* _
 constexpr int kSweepWaves = 16;            // wavefronts of a workgroup, at most
 constexpr uint32_t kSweepMeet = 4;         // batches between barriers (5 x 8, k = 32: 1706 / 1681 / 1663 us at 1 / 2 / 4)
 
-// ---- the lane groups of a wavefront ----
-//
-// LANES lanes (8, 16, 32 or 64) work on an entry, a CBSR position each, in PASSES wave instructions; kWave / LANES entries are worked
-// on side by side.  Lane groups whose last pass is not full repeat position k - 1: the same value to the same place.  The entries
-// of a batch are held by the lanes themselves, a register of them in every 16 lanes (LANES = 8: in every quad), and an
-// instruction takes entry E of its group by a data-parallel-primitive broadcast that is part of it.
-template <int LANES_, int PASSES_>
-struct FwdLanes {
-    static constexpr int LANES = LANES_, PASSES = PASSES_, GROUPS = kWave / LANES;
-    static constexpr int PER = LANES >= 16 ? 16 : 4;                   // entries of a group in one register
-    static constexpr int BATCH = LANES >= 16 ? 16 : 8, HELD = BATCH / PER;  // entries of a group in a batch; registers that hold them
-    static constexpr int STEP = LANES == 8 && PASSES == 1 ? 4 : PASSES >= 5 ? 1 : PASSES >= 3 ? 2 : 8 / PASSES;  // loaded together
-    static constexpr int STEPS = BATCH / STEP, ROUNDS = STEP * PASSES;
-    static_assert(STEPS % 2 == 0, "two sets of registers take turns");
-    static constexpr bool WHOLE = LANES == kWave || PASSES == 1;       // the last pass is full
-};
-
 // k = 8 from records of 8 fp32 values and 4 x their columns: two groups share 16 lanes, which hold eight entries of each and bring a
 // whole record with one load, an access of 64 bytes (values and columns by themselves: two accesses of 32 and 8).
 struct FwdHalves : FwdLanes<8, 1> {
     static constexpr int PER = 8, BATCH = 8, HELD = 1;
 };
-
-template <int I>
-__device__ __forceinline__ uint32_t row16_lane(uint32_t x)  // lane I of the caller's 16 lanes
-{
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x150 + I, 0xF, 0xF, true);
-}
-
-template <int PER, int I>
-__device__ __forceinline__ uint32_t held_entry(uint32_t x)  // entry I of the register of the caller's 16 or 8 lanes or quad
-{
-    if constexpr (PER == 16) return row16_lane<I>(x);
-    else if constexpr (PER == 4) return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, I * 0x55, 0xF, 0xF, true);
-    else return (uint32_t)__builtin_amdgcn_update_dpp((int)row16_lane<I>(x), (int)x, 0x158 + I, 0xF, 0xC, false);  // (upper eight: their own)
-}
 
 // What one wavefront needs of the CBSR.  Offsets are 32 bits (fwd_wide: the arrays are larger, and they are 64).
 // ROWS: the entries say which row of a bin they belong to.
@@ -456,14 +426,6 @@ struct FwdWave {
     }
 };
 
-constexpr auto kAlways = [](auto) { return true; };
-
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f)
-{
-    [&]<int... I>(std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }(std::make_integer_sequence<int, N>{});
-}
-
 // The group's copies of a row, `copy` floats apart, added up and written
 template <int GROUPS>
 __device__ __forceinline__ void write_out(const float* __restrict__ row, int copy, int dim, int lane, bool vec, bool once, float* __restrict__ out)
@@ -528,76 +490,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(8))) void
     const int g = lane / S::LANES;
     using Wave = FwdWave<S, LAYOUT, false, VT, IdxT>;
     const Wave wv(sp_data, sp_index, packed, rec_bytes, idx_off, dim, k, lane, lds_address(row + g * copy));
-    constexpr int kBatch = S::GROUPS * S::BATCH;
-    // Whole batches: a run of entries to each register of a group, so that the lanes of a load are next to each other; the last,
-    // shorter one: the groups take its entries in turn (the last entry again behind them).
-    const uint32_t in_run = (uint32_t)(g * S::PER + lane % S::PER), in_turn = (uint32_t)((lane % S::PER) * S::GROUPS + g);
-    const auto fetch = [&](int base, int2 (&e)[S::HELD]) {
-        const int from = min(base, it.end - 1);
-        const uint32_t most = (uint32_t)(it.end - 1 - from), mine = most + 1u >= (uint32_t)kBatch ? in_run : in_turn;
-#pragma unroll
-        for (int r = 0; r < S::HELD; ++r) {
-            const uint32_t p = min(mine + (uint32_t)(r * S::PER * S::GROUPS), most);
-            e[r] = make_int2((col + from)[p], __float_as_int((val + from)[p]));
-        }
-    };
-    if (it.begin < it.end) {
-        int base = it.begin, left = it.end - it.begin;
-        int2 e[S::HELD];
-        fetch(base, e);
-        typename Wave::Held cur = wv.hold(e);
-        typename Wave::Step s0, s1;
-        if (wide) {
-            while (left > 0) {
-                const auto ok = [&](int n) { return n * S::GROUPS < left; };
-                static_for<S::STEPS>([&](auto i) {
-                    wv.template load<decltype(i)::value * S::STEP, true>(cur, s0, ok);
-                    wv.template add<decltype(i)::value * S::STEP>(cur, s0, [&](auto n) { return decltype(n)::value * S::GROUPS + g < left; });
-                });
-                base += kBatch;
-                left -= kBatch;
-                if (left > 0) { fetch(base, e); cur = wv.hold(e); }
-            }
-        } else {
-            if (left >= kBatch) {
-                fetch(base + kBatch, e);
-                wv.template load<0>(cur, s0, kAlways);
-                wv.settle(s0);
-                do {
-                    typename Wave::Held next;
-                    static_for<S::STEPS>([&](auto i) {
-                        constexpr int I = decltype(i)::value, F = I * S::STEP;
-                        typename Wave::Step& mine = I % 2 ? s1 : s0;
-                        typename Wave::Step& other = I % 2 ? s0 : s1;
-                        if constexpr (I + 1 < S::STEPS) {
-                            wv.template load<F + S::STEP>(cur, other, kAlways);
-                        } else {  // the first ones of the next batch (the last entry's again behind the last)
-                            next = wv.hold(e);
-                            wv.template load<0>(next, other, kAlways);
-                            fetch(base + 2 * kBatch, e);
-                        }
-                        wv.template add<F>(cur, mine, kAlways);
-                    });
-                    cur = next;
-                    base += kBatch;
-                    left -= kBatch;
-                } while (left >= kBatch);
-            } else {
-                wv.template load<0>(cur, s0, [&](int n) { return n * S::GROUPS < left; });
-            }
-            if (left > 0) {
-                static_for<S::STEPS>([&](auto i) {
-                    constexpr int I = decltype(i)::value, F = I * S::STEP;
-                    typename Wave::Step& mine = I % 2 ? s1 : s0;
-                    typename Wave::Step& other = I % 2 ? s0 : s1;
-                    if (F * S::GROUPS < left) {
-                        if constexpr (I + 1 < S::STEPS) wv.template load<F + S::STEP>(cur, other, [&](int n) { return n * S::GROUPS < left; });
-                        wv.template add<F>(cur, mine, [&](auto n) { return decltype(n)::value * S::GROUPS + g < left; });
-                    }
-                });
-            }
-        }
-    }
+    run_item(wv, EntryBatches<S>(col, val, it.end, lane), it.begin, it.end, g, wide != 0);
     wave_lds_fence();
     float* __restrict__ out = it.slot < 0 ? Y + (int64_t)it.row * dim : partials + (int64_t)it.slot * dim;
     write_out<S::GROUPS>(row, copy, dim, lane, vec_out != 0, vec_out == 2 && it.slot < 0, out);

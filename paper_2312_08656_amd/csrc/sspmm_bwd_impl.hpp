@@ -46,13 +46,14 @@
 #include <algorithm>
 
 #include "common.hpp"
+#include "lanes.hpp"
 
 namespace maxk {
 
 // implemented once per storage format of dY (sspmm_bwd_f32.hip, _bf16.hip, _f16.hip)
 template <int VT>
 maxk_status bwd_pull_format(const ItemList& L, const int32_t* csc_src, const float* csc_val, const void* dY,
-                            const void* sp_index, int index_bytes, int dim, int k, float* dXs, float* partials,
+                            const void* sp_index, int index_bytes, int64_t N, int dim, int k, float* dXs, float* partials,
                             hipStream_t s);
 template <int VT>
 maxk_status bwd_push_format(const ItemList& L, const int32_t* col, const float* val, const void* dY,
@@ -111,7 +112,7 @@ __device__ __forceinline__ float pull_sum(const float (&a)[kPullUnroll], const f
 
 // ---------------------------------------------------------------- pull ----
 
-// k <= 64: KP = power of two >= k lanes per in-entry, 64/KP entries per step
+// k <= 8, and up to 32 (see launch_pull_t): KP = power of two >= k lanes per in-entry, 64/KP entries per step
 template <int KP, int VT, typename IdxT>
 __global__ __launch_bounds__(kWave) void bwd_pull_small_kernel(const WorkItem* __restrict__ items,
                                                                const int32_t* __restrict__ csc_src,
@@ -148,7 +149,98 @@ __global__ __launch_bounds__(kWave) void bwd_pull_small_kernel(const WorkItem* _
     }
 }
 
-// any k: lane handles positions t = lane, lane + 64, ...; one pass over the in-entries per 64 positions
+// k = 9 .. 128: 64 / LANES entries side by side, LANES lanes an entry (lanes.hpp).  Four products are added up before they reach the
+// running sum, as in pull_sum.  Bound by the L2-to-L1 path where dY stays in an L2, by the fabric beyond; what it takes off is the rest: a
+// position took some 12 vector instructions (now 3: an offset with the entry's row as a DPP operand, the multiply-add with its weight
+// as one), and a step's gathers waited for its sources and then for themselves before the next began.  us, before / now: 2 k nodes, degree 100,
+// k = 48 25.6 / 11.6; 5 k, 50, k = 64 fp16 dY 27.0 / 14.0; 10 k, 300, width 200, k = 24 153 / 107; 40 k, 60, width 100, k = 13 89.8 / 76.7;
+// 60 k, 60, k = 64 446 / 373; 100 k, 40, k = 64 bf16 dY 340 / 208; 300 k, 30, width 384, k = 128 2066 / 1896.  Eight entries under way
+// instead of four gain nothing; k = 8 stays with the kernel above (20 k nodes, degree 200 157 / 186).
+template <int LANES, int PASSES>
+struct PullLanes : FwdLanes<LANES, PASSES> {
+    static constexpr int STEP = kPullUnroll, STEPS = FwdLanes<LANES, PASSES>::BATCH / STEP, ROUNDS = STEP * PASSES;
+};
+
+template <class S, int VT>
+struct PullWave {
+    static constexpr uint32_t kVal = sizeof(value_store_t<VT>);
+    static_assert(S::STEP == kPullUnroll);
+    struct Held {  // a batch of entries: source row (WIDE) and its first byte; weight
+        uint32_t x[S::HELD], d[S::HELD];
+        float w[S::HELD];
+    };
+    struct Step { value_store_t<VT> d[S::ROUNDS]; };
+    const char* dY;
+    uint32_t row_bytes;
+    uint32_t at[S::PASSES];  // bytes of this lane's columns in a row
+    float acc[S::PASSES];
+
+    __device__ __forceinline__ Held hold(const int2 (&e)[S::HELD]) const
+    {
+        Held h;
+#pragma unroll
+        for (int r = 0; r < S::HELD; ++r) {
+            h.x[r] = (uint32_t)e[r].x;
+            h.d[r] = h.x[r] * row_bytes;
+            h.w[r] = __int_as_float(e[r].y);
+        }
+        return h;
+    }
+    __device__ __forceinline__ void settle(Step&) const {}
+
+    template <int F, bool WIDE = false, typename Ok>
+    __device__ __forceinline__ void load(const Held& h, Step& s, Ok&& ok) const
+    {
+        static_for<S::ROUNDS>([&](auto idx) {
+            constexpr int R = decltype(idx)::value, E = F + R / S::PASSES, P = R % S::PASSES, H = E / S::PER, I = E % S::PER;
+            if (!ok(E)) return;
+            const uint64_t from = WIDE ? (uint64_t)held_entry<S::PER, I>(h.x[H]) * row_bytes + at[P] : held_entry<S::PER, I>(h.d[H]) + at[P];
+            s.d[R] = *reinterpret_cast<const value_store_t<VT>*>(dY + from);
+        });
+    }
+
+    template <int F, typename Ok>
+    __device__ __forceinline__ void add(const Held& h, const Step& s, Ok&& ok)
+    {
+        float sum[S::PASSES] = {};
+        static_for<S::ROUNDS>([&](auto idx) {
+            constexpr int R = decltype(idx)::value, E = F + R / S::PASSES, P = R % S::PASSES;
+            const float w = __uint_as_float(held_entry<S::PER, E % S::PER>(__float_as_uint(h.w[E / S::PER])));
+            const float more = fmaf(w, widen_value<VT>(s.d[R]), sum[P]);
+            sum[P] = ok(std::integral_constant<int, E>{}) ? more : sum[P];
+        });
+#pragma unroll
+        for (int p = 0; p < S::PASSES; ++p) acc[p] += sum[p];
+    }
+};
+
+template <class S, int VT, typename IdxT>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(8))) void bwd_pull_lanes_kernel(
+    const WorkItem* __restrict__ items, const int32_t* __restrict__ csc_src, const float* __restrict__ csc_val,
+    const value_store_t<VT>* __restrict__ dY, const IdxT* __restrict__ sp_index, int dim, int k, int wide, float* __restrict__ dXs,
+    float* __restrict__ partials)
+{
+    const int lane = threadIdx.x, t = lane % S::LANES, g = lane / S::LANES;
+    const WorkItem it = items[blockIdx.x];
+    PullWave<S, VT> w;
+    w.dY = reinterpret_cast<const char*>(dY);
+    w.row_bytes = (uint32_t)dim * (uint32_t)sizeof(value_store_t<VT>);
+#pragma unroll
+    for (int p = 0; p < S::PASSES; ++p) {
+        w.at[p] = (uint32_t)sp_index[(int64_t)it.row * k + min(t + p * S::LANES, k - 1)] * (uint32_t)sizeof(value_store_t<VT>);
+        w.acc[p] = 0.f;
+    }
+    run_item(w, EntryBatches<S>(csc_src, csc_val, it.end, lane), it.begin, it.end, g, wide != 0);
+    float* __restrict__ out = (it.slot < 0) ? dXs + (int64_t)it.row * k : partials + (int64_t)it.slot * k;
+#pragma unroll
+    for (int p = 0; p < S::PASSES; ++p) {
+#pragma unroll
+        for (int off = S::LANES; off < kWave; off <<= 1) w.acc[p] += __shfl_xor(w.acc[p], off);
+        if (g == 0 && t + p * S::LANES < k) out[t + p * S::LANES] = w.acc[p];
+    }
+}
+
+// k > 128: lane handles positions t = lane, lane + 64, ...; one pass over the in-entries per 64 positions
 template <int VT, typename IdxT>
 __global__ __launch_bounds__(kWave) void bwd_pull_wide_kernel(const WorkItem* __restrict__ items,
                                                               const int32_t* __restrict__ csc_src,
@@ -826,7 +918,7 @@ maxk_status launch_slab_i(const SlabSet& S, const value_store_t<VT>* dY, const I
 
 template <int VT, typename IdxT>
 maxk_status launch_pull_t(const ItemList& L, const int32_t* csc_src, const float* csc_val, const value_store_t<VT>* dY,
-                          const IdxT* sp_index, int dim, int k, float* dXs, float* partials, hipStream_t s)
+                          const IdxT* sp_index, int64_t N, int dim, int k, float* dXs, float* partials, hipStream_t s)
 {
     dim3 grid((unsigned)L.n_items), block(kWave);
 #define MAXK_PULL(KERNEL) \
@@ -835,11 +927,22 @@ maxk_status launch_pull_t(const ItemList& L, const int32_t* csc_src, const float
     else if (k <= 2) MAXK_PULL((bwd_pull_small_kernel<2, VT, IdxT>));
     else if (k <= 4) MAXK_PULL((bwd_pull_small_kernel<4, VT, IdxT>));
     else if (k <= 8) MAXK_PULL((bwd_pull_small_kernel<8, VT, IdxT>));
-    else if (k <= 16) MAXK_PULL((bwd_pull_small_kernel<16, VT, IdxT>));
-    else if (k <= 32) MAXK_PULL((bwd_pull_small_kernel<32, VT, IdxT>));
-    else if (k <= 64) MAXK_PULL((bwd_pull_small_kernel<64, VT, IdxT>));
-    else MAXK_PULL((bwd_pull_wide_kernel<VT, IdxT>));
+    // (16 < k <= 32 and a dY of several L2s together: fewer rows under way are the better ones, us, this / by lane groups: 100 k nodes, degree
+    // 100 1043 / 1094, 169 k, 14 343 / 353, 1 M, 15 2361 / 2410; 60 k nodes of 512 bytes 204 / 152; k = 16 on 300 k nodes 1160 / 1125)
+    else if (k > 16 && k <= 32 && N * dim * (int64_t)sizeof(value_store_t<VT>) > (64 << 20)) MAXK_PULL((bwd_pull_small_kernel<32, VT, IdxT>));
+    else if (k > 128) MAXK_PULL((bwd_pull_wide_kernel<VT, IdxT>));
 #undef MAXK_PULL
+    else {
+        const int wide = N * dim * (int64_t)sizeof(value_store_t<VT>) > 0xFFFFFFFFll;  // byte offsets into dY need more than 32 bits
+#define MAXK_PULL(LANES, PASSES)                                                                                                            \
+    hipLaunchKernelGGL((bwd_pull_lanes_kernel<PullLanes<LANES, PASSES>, VT, IdxT>), grid, block, 0, s, L.d_items, csc_src, csc_val, dY, sp_index, \
+                       dim, k, wide, dXs, partials)
+        if (k <= 16) MAXK_PULL(16, 1);
+        else if (k <= 32) MAXK_PULL(32, 1);
+        else if (k <= 64) MAXK_PULL(64, 1);
+        else MAXK_PULL(64, 2);
+#undef MAXK_PULL
+    }
     MAXK_LAUNCH_CHECK();
     return MAXK_OK;
 }
@@ -872,13 +975,13 @@ maxk_status launch_push_t(const ItemList& L, const int32_t* col, const float* va
 
 template <int VT>
 maxk_status pull_format(const ItemList& L, const int32_t* csc_src, const float* csc_val, const void* dY_v,
-                        const void* sp_index, int index_bytes, int dim, int k, float* dXs, float* partials,
+                        const void* sp_index, int index_bytes, int64_t N, int dim, int k, float* dXs, float* partials,
                         hipStream_t s)
 {
     const auto* dY = (const value_store_t<VT>*)dY_v;
-    if (index_bytes == 1) return launch_pull_t<VT>(L, csc_src, csc_val, dY, (const uint8_t*)sp_index, dim, k, dXs, partials, s);
-    if (index_bytes == 2) return launch_pull_t<VT>(L, csc_src, csc_val, dY, (const uint16_t*)sp_index, dim, k, dXs, partials, s);
-    return launch_pull_t<VT>(L, csc_src, csc_val, dY, (const int32_t*)sp_index, dim, k, dXs, partials, s);
+    if (index_bytes == 1) return launch_pull_t<VT>(L, csc_src, csc_val, dY, (const uint8_t*)sp_index, N, dim, k, dXs, partials, s);
+    if (index_bytes == 2) return launch_pull_t<VT>(L, csc_src, csc_val, dY, (const uint16_t*)sp_index, N, dim, k, dXs, partials, s);
+    return launch_pull_t<VT>(L, csc_src, csc_val, dY, (const int32_t*)sp_index, N, dim, k, dXs, partials, s);
 }
 
 template <int VT>

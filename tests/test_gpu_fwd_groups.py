@@ -1,7 +1,7 @@
-"""The forward kernels that work by lane groups: every split of a wavefront, every layout of the CBSR, both kernels.
+"""The kernels that work by lane groups: every split of a wavefront; forward every layout of the CBSR and both kernels, backward the pull.
 
 Row lengths at the edges of a batch (8 to 64 entries, whatever the split) and of its steps, k at the edges of every split; each
-element within 1e-5 of the sum of the terms' magnitudes of the oracle, the bound of the other forward tests.
+element within 1e-5 of the sum of the terms' magnitudes of the oracle, the bound of the other parity tests.
 """
 import numpy as np
 import pytest
@@ -73,4 +73,49 @@ def test_forward_of_a_cbsr_above_4_gib(monkeypatch, sweep):
     want = sp_data[col.long()].view(rows, 3, dim).sum(1)
     assert torch.equal(Y[:rows], want)
     assert not bool(Y[rows:].any())
+    gr.destroy()
+
+
+@pytest.mark.parametrize("k,dim,ib", [(8, 64, 1), (9, 100, 1), (16, 256, 1), (17, 33, 4), (32, 256, 2), (33, 90, 1), (64, 64, 1), (65, 256, 1),
+                                      (128, 130, 1), (129, 256, 1)])
+@pytest.mark.parametrize("fmt", ["f32", "bf16", "f16"])
+def test_pull_by_lane_groups(monkeypatch, k, dim, ib, fmt):
+    monkeypatch.setenv("MAXK_PULL_FORM", "1")  # whole rows
+    N, rowptr, col, val = _graph(k + 1)
+    order = np.argsort(col, kind="stable")  # the transpose: in-entries of those lengths
+    rows = np.repeat(np.arange(N), np.diff(rowptr))
+    rowptr, col, val = csr_from_coo(N, list(zip(col[order].tolist(), rows[order].tolist(), val[order].tolist())))
+    H = synth.normal_matrix(N, dim, 7 + k)
+    index = oracle.topk_cbsr(H, k)[1]
+    sp_index = torch.from_numpy(index.astype({1: np.uint8, 2: np.int16, 4: np.int32}[ib])).cuda()
+    dY = to_dev(synth.normal_matrix(N, dim, 9)).to(_DTYPE[fmt])
+    ref, refabs = oracle.sspmm_bwd(rowptr, col, val, dY.float().cpu().numpy(), index)
+    gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val))
+    gr.set_bwd_mode(maxk.BWD_PULL_CSC)
+    dXs = torch.full((N, k), float("nan"), device="cuda")
+    maxk.maxk_sspmm_bwd_narrow(gr, dY, sp_index, dXs)
+    torch.cuda.synchronize()
+    assert (np.abs(dXs.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all(), (k, dim, fmt)
+    gr.destroy()
+
+
+def test_pull_from_a_gradient_above_4_gib(monkeypatch):
+    # byte offsets of 64 bits: sources on both sides of the line.  Whole numbers: any order, the same bits
+    monkeypatch.setenv("MAXK_PULL_FORM", "1")
+    N, k, dim = 4_300_000, 32, 256
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    dY = torch.randint(-5, 6, (N, dim), generator=gen, device="cuda", dtype=torch.int8).float()
+    assert dY.numel() * 4 > 2**32
+    rows = torch.cat([torch.randint(N, (4000,), generator=gen, device="cuda"), torch.tensor([0, N - 1], device="cuda")]).unique()
+    rowptr = torch.zeros(N + 1, dtype=torch.int32, device="cuda")
+    rowptr[1:] = torch.cumsum(torch.bincount(rows, minlength=N) * 3, 0)
+    col = torch.randint(50, (3 * rows.numel(),), generator=gen, device="cuda").to(torch.int32)
+    sp_index = torch.arange(200, 200 + k, device="cuda").to(torch.uint8).repeat(N, 1)
+    gr = maxk.maxk_graph_create(rowptr, col, torch.ones(col.numel(), device="cuda"))
+    gr.set_bwd_mode(maxk.BWD_PULL_CSC)
+    dXs = torch.full((N, k), float("nan"), device="cuda")
+    maxk.maxk_sspmm_bwd(gr, dY, sp_index, dXs)
+    want = torch.zeros(50, k, device="cuda").index_add_(0, col.long(), dY[rows.repeat_interleave(3), 200 : 200 + k])
+    assert torch.equal(dXs[:50], want)
+    assert not bool(dXs[50:].any())
     gr.destroy()
