@@ -9,6 +9,9 @@ import torch
 
 _HERE = Path(__file__).resolve().parent
 _LIB: Optional[ctypes.CDLL] = None
+# The same calls marshalled in C++ (csrc/torch_calls.cpp): each says whether it was made; what it leaves is made here, checks and errors
+# included.  None: not built for this torch, and every call is made here.
+_FAST = None
 
 BWD_AUTO, BWD_PULL_CSC, BWD_PUSH_CSR, BWD_EXPAND_REDUCE, BWD_SLAB_PULL, BWD_TILED = 0, 1, 2, 3, 4, 5
 VALUE_F32, VALUE_BF16, VALUE_F16 = 0, 1, 2
@@ -94,7 +97,20 @@ def load_library() -> ctypes.CDLL:
     lib.maxk_last_hip_error.argtypes = []
     lib.maxk_version.argtypes = []
     _LIB = lib
+    _load_fast(lib)
     return lib
+
+
+def _load_fast(lib: ctypes.CDLL) -> None:
+    global _FAST
+    try:
+        from . import _torch_calls
+    except ImportError:
+        return
+    _torch_calls.bind([ctypes.cast(f, ctypes.c_void_p).value for f in (
+        lib.maxk_topk_cbsr_narrow, lib.maxk_spgemm_fwd_narrow, lib.maxk_spgemm_fwd_noalloc, lib.maxk_sspmm_bwd_narrow,
+        lib.maxk_cbsr_scatter)])
+    _FAST = _torch_calls
 
 
 def _check(status: int, what: str) -> None:
@@ -135,10 +151,12 @@ class MaxKGraph:
         self.nnz = int(colidx.shape[0])
         self._keep = (rowptr, colidx, val)
         self._h = ctypes.c_void_p()
+        self._at = 0  # the handle's address, 0 where there is none
         _check(lib.maxk_graph_create(ctypes.byref(self._h), self.N, self.nnz, _dev(rowptr, torch.int32, "rowptr"),
                                      _dev(colidx, torch.int32, "colidx") if self.nnz else None,
                                      _dev(val, torch.float32, "val") if self.nnz else None, _stream()),
                "maxk_graph_create")
+        self._at = self._h.value or 0
 
     @property
     def handle(self):
@@ -195,6 +213,7 @@ class MaxKGraph:
         return int(load_library().maxk_graph_limit_allocations(self.handle, limit))
 
     def destroy(self) -> None:
+        self._at = 0
         if self._h:
             load_library().maxk_graph_destroy(self._h)
             self._h = ctypes.c_void_p()
@@ -217,6 +236,8 @@ def maxk_graph_destroy(g: MaxKGraph) -> None:
 
 def maxk_topk_cbsr(H: torch.Tensor, k: int, sp_data: torch.Tensor, sp_index: torch.Tensor) -> None:
     """sp_data [N,k] fp32 and sp_index [N,k] (uint8 / uint16 / int32) are overwritten."""
+    if _FAST is not None and _FAST.topk(H, k, sp_data, sp_index, False):
+        return
     N, dim = H.shape
     ib = _INDEX_BYTES[sp_index.dtype]
     if sp_data.shape != (N, k) or sp_index.shape != (N, k):
@@ -227,6 +248,8 @@ def maxk_topk_cbsr(H: torch.Tensor, k: int, sp_data: torch.Tensor, sp_index: tor
 
 def maxk_spgemm_fwd(g: MaxKGraph, sp_data: torch.Tensor, sp_index: torch.Tensor, dim: int, Y: torch.Tensor) -> None:
     """Y [N,dim] fp32 is overwritten with A * X, X given as CBSR."""
+    if _FAST is not None and _FAST.forward(g._at, g.N, sp_data, sp_index, dim, Y, False):
+        return
     N, k = sp_data.shape
     if N != g.N or sp_index.shape != (N, k) or Y.shape != (N, dim):
         raise MaxKError("maxk_spgemm_fwd: shape mismatch")
@@ -239,6 +262,8 @@ def maxk_spgemm_fwd(g: MaxKGraph, sp_data: torch.Tensor, sp_index: torch.Tensor,
 def maxk_spgemm_fwd_noalloc(g: MaxKGraph, sp_data: torch.Tensor, sp_index: torch.Tensor, dim: int,
                             Y: torch.Tensor) -> None:
     """maxk_spgemm_fwd with its scratch memory in the library's fixed device array: allocates nothing."""
+    if _FAST is not None and _FAST.forward_noalloc(g._at, g.N, sp_data, sp_index, dim, Y):
+        return
     N, k = sp_data.shape
     if N != g.N or sp_index.shape != (N, k) or Y.shape != (N, dim):
         raise MaxKError("maxk_spgemm_fwd_noalloc: shape mismatch")
@@ -250,6 +275,8 @@ def maxk_spgemm_fwd_noalloc(g: MaxKGraph, sp_data: torch.Tensor, sp_index: torch
 
 def maxk_topk_cbsr_narrow(H: torch.Tensor, k: int, sp_data: torch.Tensor, sp_index: torch.Tensor) -> None:
     """As maxk_topk_cbsr, the values stored in sp_data's own dtype (bfloat16, float16 or float32)."""
+    if _FAST is not None and _FAST.topk(H, k, sp_data, sp_index, True):
+        return
     N, dim = H.shape
     ib = _INDEX_BYTES[sp_index.dtype]
     if sp_data.dtype not in _VALUE_TYPE:
@@ -265,6 +292,8 @@ def maxk_topk_cbsr_narrow(H: torch.Tensor, k: int, sp_data: torch.Tensor, sp_ind
 def maxk_spgemm_fwd_narrow(g: MaxKGraph, sp_data: torch.Tensor, sp_index: torch.Tensor, dim: int,
                            Y: torch.Tensor) -> None:
     """As maxk_spgemm_fwd with the CBSR values in sp_data's own dtype (bfloat16, float16 or float32)."""
+    if _FAST is not None and _FAST.forward(g._at, g.N, sp_data, sp_index, dim, Y, True):
+        return
     N, k = sp_data.shape
     if sp_data.dtype not in _VALUE_TYPE:
         raise MaxKError("maxk_spgemm_fwd_narrow: sp_data must be float32, bfloat16 or float16")
@@ -279,6 +308,8 @@ def maxk_spgemm_fwd_narrow(g: MaxKGraph, sp_data: torch.Tensor, sp_index: torch.
 
 def maxk_sspmm_bwd(g: MaxKGraph, dY: torch.Tensor, sp_index: torch.Tensor, dXs: torch.Tensor) -> None:
     """dXs [N,k] fp32 is overwritten with (A^T dY) sampled at sp_index."""
+    if _FAST is not None and _FAST.backward(g._at, g.N, dY, sp_index, dXs, False):
+        return
     N, dim = dY.shape
     k = sp_index.shape[1]
     if N != g.N or sp_index.shape != (N, k) or dXs.shape != (N, k):
@@ -291,6 +322,8 @@ def maxk_sspmm_bwd(g: MaxKGraph, dY: torch.Tensor, sp_index: torch.Tensor, dXs: 
 
 def maxk_sspmm_bwd_narrow(g: MaxKGraph, dY: torch.Tensor, sp_index: torch.Tensor, dXs: torch.Tensor) -> None:
     """As maxk_sspmm_bwd with dY in its own dtype (bfloat16, float16 or float32); dXs stays fp32."""
+    if _FAST is not None and _FAST.backward(g._at, g.N, dY, sp_index, dXs, True):
+        return
     N, dim = dY.shape
     k = sp_index.shape[1]
     if dY.dtype not in _VALUE_TYPE:
@@ -305,6 +338,8 @@ def maxk_sspmm_bwd_narrow(g: MaxKGraph, dY: torch.Tensor, sp_index: torch.Tensor
 
 def maxk_cbsr_scatter(values: torch.Tensor, sp_index: torch.Tensor, dense: torch.Tensor) -> None:
     """dense [N,dim] fp32 is overwritten: values [N,k] placed at the CBSR columns, zeros elsewhere."""
+    if _FAST is not None and _FAST.scatter(values, sp_index, dense):
+        return
     N, k = values.shape
     dim = dense.shape[1]
     if sp_index.shape != (N, k) or dense.shape[0] != N:
@@ -313,6 +348,33 @@ def maxk_cbsr_scatter(values: torch.Tensor, sp_index: torch.Tensor, dense: torch
     _check(load_library().maxk_cbsr_scatter(_dev(values, torch.float32, "values"),
                                             _dev(sp_index, sp_index.dtype, "sp_index"), ib, N, dim, k,
                                             _dev(dense, torch.float32, "dense"), _stream()), "maxk_cbsr_scatter")
+
+
+def aggregate_forward(g: MaxKGraph, H: torch.Tensor, k: int, index_bytes: int):
+    """(Y, sp_index) = A * MaxK_k(H) and the columns kept, for contiguous H."""
+    made = None if _FAST is None else _FAST.aggregate_forward(g._at, g.N, H, k, index_bytes)
+    if made is not None:
+        return made
+    N, dim = H.shape
+    sp_data = torch.empty((N, k), dtype=torch.float32, device=H.device)
+    sp_index = torch.empty((N, k), dtype=index_dtype(index_bytes), device=H.device)
+    Y = torch.empty((N, dim), dtype=torch.float32, device=H.device)
+    maxk_topk_cbsr(H, k, sp_data, sp_index)
+    maxk_spgemm_fwd(g, sp_data, sp_index, dim, Y)
+    return Y, sp_index
+
+
+def aggregate_backward(g: MaxKGraph, dY: torch.Tensor, sp_index: torch.Tensor, dim: int, k: int) -> torch.Tensor:
+    """dH of aggregate_forward for contiguous dY."""
+    dH = None if _FAST is None else _FAST.aggregate_backward(g._at, g.N, dY, sp_index, dim, k)
+    if dH is not None:
+        return dH
+    N = sp_index.shape[0]
+    dXs = torch.empty((N, k), dtype=torch.float32, device=dY.device)
+    dH = torch.empty((N, dim), dtype=torch.float32, device=dY.device)
+    maxk_sspmm_bwd(g, dY, sp_index, dXs)
+    maxk_cbsr_scatter(dXs, sp_index, dH)
+    return dH
 
 
 def spmm_baseline(g: MaxKGraph, H: torch.Tensor, Y: torch.Tensor) -> None:
