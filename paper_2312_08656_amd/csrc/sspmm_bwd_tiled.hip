@@ -644,26 +644,38 @@ __global__ __launch_bounds__(kTiledThreads) void bwd_tiled_kernel(const TiledArg
             // Mode 1 (many overflow entries, spread evenly: small dense graphs): every lane group adds its own bucket.
             const uint32_t b0 = a.ovf_dir[bucket0 + (wave * E + g)], b1 = a.ovf_dir[bucket0 + (wave * E + g) + 1];
             if (b0 < b1) {
-                // two stages ahead of the adds: the next record, and the next destination's columns (reads past the
-                // end are clamped to the last entry and dropped)
+                // A step's records, columns and samples are under way together (2900 clocks a step of eight; one entry after the
+                // other, records and columns ahead, took 1500 an entry: the samples' round trip).  Then its entries are added in
+                // order.  Reads past the end are clamped to the last entry and dropped.
+                constexpr int AHEAD = 8;
                 const uint32_t last = b1 - 1;
-                uint4 r0 = a.ovf[b0], r1 = a.ovf[min(b0 + 1, last)];
-                IdxVec<IdxT, PPL> i0;
-                i0.load(ib + (int64_t)r0.z * k);
-                for (uint32_t e = b0; e < b1; ++e) {
-                    const uint4 r2 = a.ovf[min(e + 2, last)];
-                    IdxVec<IdxT, PPL> i1;
-                    i1.load(ib + (int64_t)r1.z * k);
-                    const float w = __uint_as_float(r0.x);
-                    const float* __restrict__ row = a.dY + (int64_t)r0.y * dim;
-                    float x[PPL];
+                uint4 r[AHEAD];
 #pragma unroll
-                    for (int c = 0; c < PPL; ++c) x[c] = row[i0.get(c)];
-                    float4* const ap = reinterpret_cast<float4*>(acc + (r0.z * k + q * PPL));
-                    float4 av = *ap;
-                    av.x += w * x[0]; av.y += w * x[1]; av.z += w * x[2]; av.w += w * x[3];
-                    *ap = av;
-                    r0 = r1; r1 = r2; i0 = i1;
+                for (int u = 0; u < AHEAD; ++u) r[u] = a.ovf[min(b0 + u, last)];
+                for (uint32_t e = b0; e < b1; e += AHEAD) {
+                    IdxVec<IdxT, PPL> columns[AHEAD];
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) columns[u].load(ib + (int64_t)r[u].z * k);
+                    float w[AHEAD], x[AHEAD][PPL];
+                    uint32_t j[AHEAD];
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) {
+                        const float* __restrict__ row = a.dY + (int64_t)r[u].y * dim;
+                        w[u] = __uint_as_float(r[u].x);
+                        j[u] = r[u].z;
+#pragma unroll
+                        for (int c = 0; c < PPL; ++c) x[u][c] = row[columns[u].get(c)];
+                    }
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) r[u] = a.ovf[min(e + AHEAD + u, last)];
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) {
+                        if (e + u >= b1) break;
+                        float4* const ap = reinterpret_cast<float4*>(acc + (j[u] * k + q * PPL));
+                        float4 av = *ap;
+                        av.x += w[u] * x[u][0]; av.y += w[u] * x[u][1]; av.z += w[u] * x[u][2]; av.w += w[u] * x[u][3];
+                        *ap = av;
+                    }
                 }
             }
         } else if (g < E) {
@@ -911,14 +923,14 @@ maxk_status build_tiled(TiledSet& T, int64_t N, int64_t nnz, const int32_t* d_cs
     MAXK_TRY_CLEAN(hipStreamSynchronize(s));
     int ovf_by_bucket = 0;
     if (n_chain > 0 && n_buckets <= ((int64_t)1 << 24)) {
-        // bucket by bucket costs about one memory round trip (~1500 clocks) per entry of the longest bucket, the
-        // atomics about 3 clocks per element of a workgroup's share
+        // bucket by bucket costs about 2900 clocks for every eight entries of the longest bucket, the atomics about 3
+        // clocks per element of a workgroup's share
         try {
             std::vector<uint32_t> h_dir((size_t)n_buckets + 1);
             MAXK_TRY_CLEAN(hipMemcpy(h_dir.data(), T.d_ovf_dir, sizeof(uint32_t) * h_dir.size(), hipMemcpyDeviceToHost));
             uint32_t longest = 0;
             for (int64_t b2 = 0; b2 < n_buckets; ++b2) longest = std::max(longest, h_dir[(size_t)b2 + 1] - h_dir[(size_t)b2]);
-            const double by_bucket = 1500.0 * longest, by_atomics = 3.0 * k * (double)n_chain / (double)(n_dsets * R);
+            const double by_bucket = 2900.0 * ((longest + 7) / 8), by_atomics = 3.0 * k * (double)n_chain / (double)(n_dsets * R);
             ovf_by_bucket = by_bucket < by_atomics ? 1 : 0;
         } catch (const std::bad_alloc&) {
             ovf_by_bucket = 0;  // the atomics need no look at the buckets
@@ -982,7 +994,8 @@ maxk_status launch_bwd_tiled(const TiledSet& T, const void* dY, int value_type, 
     // k = 8, 16, 32: 3-5 % faster than without pacing, with a quarter of the L2 fills.  Calls that run at the same
     // time on one handle share the marks; that can only make them nap at the wrong moments.
     // Only when every workgroup has a CU from the start (256 CUs): otherwise the running ones are not one pack.
-    a.window = (int64_t)8 * a.G * a.R <= 256 ? kPaceWindow : 0;
+    // And only where a workgroup has more tiles than it may lead by.
+    a.window = (int64_t)8 * a.G * a.R <= 256 && a.tiles_per_range > kPaceWindow ? kPaceWindow : 0;
     if (!T.d_progress || (int64_t)8 * a.G * a.R > kMaxUnits(T.n_dsets)) a.window = 0;
     if (a.window > 0) {
         const maxk_status st = launch_fill_zero(reinterpret_cast<float*>(T.d_progress), (int64_t)8 * a.G * a.R * kMarkStride, s);
