@@ -1482,16 +1482,19 @@ maxk_status reserve_shape(maxk_graph* g, int dim, int k, int dy_value_type)
         forget_refused(g, {kRefusedSweep, sweep_groups(k), sweep_batch(k), per_bin});
         (void)sweep_for(g, k, dim, per_bin, false, &W);  // (not built: row by row)
     }
+    int largest[3] = {0, 0, 0}, bytes = 0;  // k', index and value bytes of the largest repacked record among k' <= k
     for (int vb = 2; vb <= 4; vb += 2) {
         for (int ib = 1; ib <= 4; ib *= 2) {
-            for (int kk = 1; kk <= k; ++kk) {  // the largest repacked record among k' <= k
-                if (!fwd_uses_packed(g, kk, ib, vb)) break;
-                if (kk == k || !fwd_uses_packed(g, kk + 1, ib, vb)) {
-                    st = ensure_packed(g, kk, ib, vb);
-                    if (st != MAXK_OK) return st;
-                }
+            for (int kk = 1; kk <= k && kk * (vb + ib) <= std::max(96, g->fwd_pack_max); ++kk) {
+                if (!fwd_uses_packed(g, kk, ib, vb) || fwd_packed_record_bytes(kk, ib, vb) <= bytes) continue;
+                bytes = fwd_packed_record_bytes(kk, ib, vb);
+                largest[0] = kk, largest[1] = ib, largest[2] = vb;
             }
         }
+    }
+    if (bytes) {
+        st = ensure_packed(g, largest[0], largest[1], largest[2]);
+        if (st != MAXK_OK) return st;
     }
     const int vb = value_bytes(dy_value_type);
     forget_refused(g, {kRefusedExpand, k});

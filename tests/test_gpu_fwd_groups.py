@@ -119,3 +119,22 @@ def test_pull_from_a_gradient_above_4_gib(monkeypatch):
     assert torch.equal(dXs[:50], want)
     assert not bool(dXs[50:].any())
     gr.destroy()
+
+
+@pytest.mark.parametrize("N,k", [(5000, 16), (90_000, 8), (90_000, 16), (300_000, 32)])
+def test_reserve_holds_the_repacked_records(N, k):
+    # a CBSR above 3 MiB is repacked, a smaller one (here that of the smaller k') is not: no forward call at k' <= k allocates
+    dim = 64
+    rowptr = torch.arange(N + 1, dtype=torch.int32, device="cuda")
+    gr = maxk.maxk_graph_create(rowptr, torch.arange(N, dtype=torch.int32, device="cuda"), torch.ones(N, device="cuda"))
+    gr.reserve(dim, k)
+    held = gr.info()["workspace_bytes"]
+    Y = torch.empty((N, dim), device="cuda")
+    for kk in range(1, k + 1):
+        for fmt in _DTYPE.values():
+            for index in (torch.uint8, torch.int16, torch.int32):
+                sp_index = torch.arange(kk, device="cuda").to(index).repeat(N, 1)
+                maxk.maxk_spgemm_fwd_narrow(gr, torch.ones((N, kk), dtype=fmt, device="cuda"), sp_index, dim, Y)
+                assert gr.info()["workspace_bytes"] == held, (N, k, kk, fmt, index)
+    torch.cuda.synchronize()
+    gr.destroy()
