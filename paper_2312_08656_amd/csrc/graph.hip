@@ -653,7 +653,7 @@ template <class F>
 maxk_status tiled_for(maxk_graph* g, int dim, int k, const F& existing_only, TiledSet** out)
 {
     TiledShape sh;
-    if (!tiled_shape(g->N, dim, k, sh)) return MAXK_UNSUPPORTED;
+    if (!tiled_shape(g->N, g->nnz, dim, k, sh)) return MAXK_UNSUPPORTED;
     for (TiledSet* T : g->tiled_cache)
         if (T->D == sh.D && T->TR == sh.TR && T->LPV == k / tiled_positions_per_lane(k)) { *out = T; return MAXK_OK; }
     if (existing_only()) return MAXK_OUT_OF_MEMORY;
@@ -1203,8 +1203,8 @@ int auto_bwd_mode(const maxk_graph* g, int dim, int k, int val_bytes = 4, bool t
     // general one), the entries, and fp32 atomics when the source rows are cut into ranges
     double tiled = HUGE_VAL;
     TiledShape sh;
-    if (tiled_ok && val_bytes == 4 && tiled_shape(g->N, dim, k, sh) && !refused(tiled_key(sh, k))) {
-        const double n_tiles = std::ceil(N / sh.TR);
+    if (tiled_ok && val_bytes == 4 && tiled_shape(g->N, g->nnz, dim, k, sh) && !refused(tiled_key(sh, k))) {
+        const double n_tiles = std::ceil(N / 16.0);  // (tiles of 8 where they are faster)
         if (sh.n_dsets * n_tiles < 2.6e8)
             tiled = 15e-6 + (dim == 256 ? 0.2e-6 : 0.5e-6 + 1.2e-9 * dim) * sh.n_dsets * n_tiles / 256.0 +
                     nnz * (3e-12 + 0.6e-12 * k) + (sh.R > 1 ? sh.R * N * k / 330e9 : 0.0);
@@ -1317,7 +1317,7 @@ RegsShape best_regs_shape(const maxk_graph* g, int dim, int val_bytes, int k)
     double seconds = HUGE_VAL, other = HUGE_VAL;
     const int mode = auto_bwd_mode(g, dim, k, val_bytes, true, true, &other);
     TiledShape tiled;
-    (void)tiled_shape(g->N, dim, k, tiled);
+    (void)tiled_shape(g->N, g->nnz, dim, k, tiled);
     bool sampled = false;
     int32_t slab_run = 32;
     if (mode == MAXK_BWD_SLAB_PULL) {
@@ -1501,7 +1501,7 @@ maxk_status reserve_shape(maxk_graph* g, int dim, int k, int dy_value_type)
     forget_refused(g, {kRefusedSlab, slab_rows_for(g, dim, vb)});
     forget_refused(g, sliced_key(g, dim, vb));
     TiledShape sh;
-    if (tiled_shape(g->N, dim, k, sh)) forget_refused(g, tiled_key(sh, k));
+    if (tiled_shape(g->N, g->nnz, dim, k, sh)) forget_refused(g, tiled_key(sh, k));
     if (const RegsShape rs = regs_choice(g, dim, vb, k); rs.n_sets) std::erase(g->regs_refused, rs);
     BwdPlan plan;
     return g->nnz ? plan_bwd(g, dim, k, vb, true, nullptr, nullptr, plan) : MAXK_OK;

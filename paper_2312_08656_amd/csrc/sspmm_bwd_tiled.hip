@@ -257,7 +257,7 @@ struct IdxVec<int32_t, 4> {
     __device__ __forceinline__ uint32_t get(int i) const { return i == 0 ? w.x : i == 1 ? w.y : i == 2 ? w.z : w.w; }
 };
 
-// TR: source rows per tile (16 is what the launcher uses: 32 and 48 were measured slower);
+// TR: source rows per tile (16 or 8: tiled_shape);
 // DIMC: hidden width when known at compile time (LDS and row offsets become immediates), 0 = a.dim;
 // RC: 256-column chunks that cover a dY row (dim <= RC * 256); PPL: CBSR positions per lane (4; 8 was measured slower)
 //
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(kTiledThreads) void bwd_tiled_kernel(const TiledArg
     } else if (wave >= kAccWaves) {
         // ---- loading wavefronts: tile t -> row buffer t & 1 ----
         constexpr int RP = TR / kLoadWaves;                    // rows per wavefront and tile
-        constexpr int Q = (TR == 16 && RC == 1) ? 4 : 2;        // tiles this wavefront keeps in flight
+        constexpr int Q = (TR <= 16 && RC == 1) ? 4 : 2;        // tiles this wavefront keeps in flight
         static_assert(TR % kLoadWaves == 0 && Q * RP * RC * 4 <= 96, "the row queue must fit the register budget");
         const int lw = wave - kAccWaves;
         float4 q0[RP][RC], q1[RP][RC], q2[RP][RC], q3[RP][RC];  // named, not indexed: they must stay in registers
@@ -767,12 +767,15 @@ void tiled_ranges(int n_dsets, int n_tiles, int& G, int& R, int& tiles_per_range
 
 // Destination-set size for (N, dim, k): as many nodes as LDS holds accumulators for beside two row buffers, rounded
 // so that the number of sets is a power of two (the 32 CUs of an XCD then hold whole groups of sets).  Tiles of 16
-// rows: taller ones (32, 48 rows, with correspondingly smaller sets) were measured slower at every k.
-bool tiled_shape(int64_t N, int dim, int k, TiledShape& sh)
+// rows: taller ones (32, 48 rows, with correspondingly smaller sets) were measured slower at every k.  Tiles of 8, up to k = 32, where 16
+// rows have 1.6 entries a destination on average: few visits then have more than the three entries that the sweep takes.  us, 16 rows / 8,
+// width 256, by entries a destination and 16 rows: 0.6 k = 16 46.4 / 50.3, 0.96 k = 32 116 / 125; 1.9 k = 8 30.0 / 23.2, k = 16 38.7 / 35.3
+// and 22.8 / 19.0, k = 32 57.2 / 55.3, k = 64 82.9 / 84.9; 3.0 k = 16 181 / 114; 4.8 25.7 / 13.7; 5.6 135 / 73.
+bool tiled_shape(int64_t N, int64_t nnz, int dim, int k, TiledShape& sh)
 {
     if (N < 1 || k % 4 != 0 || k < 4 || k > 256 || dim % 4 != 0 || dim > 512) return false;
-    const int tr = 16;
-    const int64_t row_bytes = 2ll * tr * dim * 4;
+    const int tr = dim <= 256 && k <= 32 && (double)nnz * 16.0 >= 1.6 * (double)N * (double)N ? 8 : 16;
+    const int64_t row_bytes = 2ll * 16 * dim * 4;  // (the same sets either way)
     const int64_t dmax = std::min<int64_t>((kLdsBytes - row_bytes - 256) / (4ll * k), 4096);
     if (dmax < 64) return false;
     int64_t S = 8;
@@ -963,7 +966,8 @@ bool tiled_supports(const void* dY, int value_type, const void* sp_index, int in
 maxk_status launch_bwd_tiled(const TiledSet& T, const void* dY, int value_type, const void* sp_index, int index_bytes,
                              int64_t N, int dim, int k, float* dXs, hipStream_t s)
 {
-    if (!tiled_supports(dY, value_type, sp_index, index_bytes, dim, k) || T.LPV != k / tiled_positions_per_lane(k) || T.TR != 16) return MAXK_UNSUPPORTED;
+    if (!tiled_supports(dY, value_type, sp_index, index_bytes, dim, k) || T.LPV != k / tiled_positions_per_lane(k) ||
+        (T.TR != 16 && (T.TR != 8 || dim > 256))) return MAXK_UNSUPPORTED;
     TiledArgs a;
     a.dY = (const float*)dY;
     a.sp_index = sp_index;
@@ -1007,7 +1011,8 @@ maxk_status launch_bwd_tiled(const TiledSet& T, const void* dY, int value_type, 
     (index_bytes == 1 ? launch_tiled_t<TR, DIMC, RC, PPL, uint8_t>(a, lds_bytes, s)                               \
      : index_bytes == 2 ? launch_tiled_t<TR, DIMC, RC, PPL, uint16_t>(a, lds_bytes, s)                            \
                         : launch_tiled_t<TR, DIMC, RC, PPL, int32_t>(a, lds_bytes, s))
-    const maxk_status st = dim == 256 ? MAXK_TILED_I(16, 256, 1, 4) : dim < 256 ? MAXK_TILED_I(16, 0, 1, 4) : MAXK_TILED_I(16, 0, 2, 4);
+    const maxk_status st = T.TR == 8 ? (dim == 256 ? MAXK_TILED_I(8, 256, 1, 4) : MAXK_TILED_I(8, 0, 1, 4))
+                           : dim == 256 ? MAXK_TILED_I(16, 256, 1, 4) : dim < 256 ? MAXK_TILED_I(16, 0, 1, 4) : MAXK_TILED_I(16, 0, 2, 4);
 #undef MAXK_TILED_I
     return st;
 }
