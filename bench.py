@@ -188,7 +188,7 @@ def main() -> int:
     dom_name, dom_ms, dom_bytes = max((("maxk_spgemm_fwd", t_fwd, ab["fwd"]), ("maxk_sspmm_bwd", t_bwd, ab["bwd"])),
                                       key=lambda t: t[1])
     achieved = dom_bytes / (dom_ms * 1e-3) / 1e9
-    dom_kernel = gr.bwd_kernel(dim, k0) if "bwd" in dom_name else "rmw"
+    dom_kernel = gr.bwd_kernel(dim, k0) if "bwd" in dom_name else "lane_groups" if 10 <= k0 <= 128 or k0 in (8, 192) else "rmw"
     tr = measured_traffic(cfg.name, k0, dom_name, dom_kernel)
     roofline = {"bound": "hbm", "kernel": dom_name, "device_kernel": dom_kernel, "achieved": round(achieved, 1),
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),

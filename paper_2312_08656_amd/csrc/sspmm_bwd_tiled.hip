@@ -644,9 +644,9 @@ __global__ __launch_bounds__(kTiledThreads) void bwd_tiled_kernel(const TiledArg
             // Mode 1 (many overflow entries, spread evenly: small dense graphs): every lane group adds its own bucket.
             const uint32_t b0 = a.ovf_dir[bucket0 + (wave * E + g)], b1 = a.ovf_dir[bucket0 + (wave * E + g) + 1];
             if (b0 < b1) {
-                // A step's records, columns and samples are under way together (2900 clocks a step of eight; one entry after the
-                // other, records and columns ahead, took 1500 an entry: the samples' round trip).  Then its entries are added in
-                // order.  Reads past the end are clamped to the last entry and dropped.
+                // A step's records, columns and samples are under way together, then its entries are added in order (one entry after
+                // the other, with records and columns ahead, each took the samples' round trip of some 1500 clocks).  Reads past
+                // the end are clamped to the last entry and dropped.
                 constexpr int AHEAD = 8;
                 const uint32_t last = b1 - 1;
                 uint4 r[AHEAD];
@@ -927,7 +927,8 @@ maxk_status build_tiled(TiledSet& T, int64_t N, int64_t nnz, const int32_t* d_cs
     int ovf_by_bucket = 0;
     if (n_chain > 0 && n_buckets <= ((int64_t)1 << 24)) {
         // bucket by bucket costs about 2900 clocks for every eight entries of the longest bucket, the atomics about 3
-        // clocks per element of a workgroup's share
+        // clocks per element of a workgroup's share.  us, atomics / buckets (tiles of 16 rows): 4 k nodes, 2.1 M entries, k = 8 30.7 / 29.7,
+        // k = 16 49.3 / 38.6, k = 32 88 / 58; 8 k, 2.4 M, k = 16 46.0 / 46.8; 133 k, 79 M, k = 8 1039 / 2571 (hubs in one bucket)
         try {
             std::vector<uint32_t> h_dir((size_t)n_buckets + 1);
             MAXK_TRY_CLEAN(hipMemcpy(h_dir.data(), T.d_ovf_dir, sizeof(uint32_t) * h_dir.size(), hipMemcpyDeviceToHost));
