@@ -29,6 +29,10 @@ MAXK_API maxk_status maxk_graph_cached_tables(const maxk_graph* g, int32_t* n_sl
 /* From how many entries on a visit gets a wavefront of its own (32: above 32) in a slab of `entries` whose longest has `longest`. */
 MAXK_API int32_t maxk_lone_visit_line(int32_t longest, int64_t entries);
 
+/* First entry of the batch that a kernel fetches `ahead` entries behind `base`, of a work item that ends at `end` (the last entry where
+   the batch lies behind it). */
+MAXK_API int64_t maxk_entry_batch(uint32_t base, uint32_t ahead, uint32_t end);
+
 /* How many regroupings of A for the forward sweep the handle holds (kept like the tables above). */
 MAXK_API int32_t maxk_graph_sweep_tables(const maxk_graph* g);
 

@@ -67,6 +67,10 @@ struct WorkItem {
     int32_t slot;   // -1: this item owns the whole row and writes the result; else partial-sum slot
 };
 
+// First entry of the batch at position `base` of the entries of a work item that ends at `end`: the item's last entry where the batch lies
+// behind it.  Positions are unsigned: batches are fetched two ahead, and an item may end at 2^31 - 16.
+__host__ __device__ constexpr uint32_t batch_begin(uint32_t base, uint32_t end) { return base < end ? base : end - 1u; }
+
 // A row whose entries were split over several items; its partial sums live in
 // slots [slot_begin, slot_begin + slot_count) and are added up by a second kernel.
 struct SplitRow {

@@ -1882,6 +1882,8 @@ MAXK_API maxk_status maxk_regs_step_list(uint32_t record0, uint32_t records, uin
     return MAXK_OK;
 }
 
+MAXK_API int64_t maxk_entry_batch(uint32_t base, uint32_t ahead, uint32_t end) { return batch_begin(base + ahead, end); }
+
 MAXK_API int64_t maxk_graph_regs_table(const maxk_graph* g, int32_t i, int32_t which, void* out, int64_t bytes)
 {
     if (!g || i < 0 || (size_t)i >= g->regs_cache.size()) return MAXK_INVALID_ARGUMENT;

@@ -53,19 +53,19 @@ struct EntryBatches {
     static constexpr int kBatch = S::GROUPS * S::BATCH;
     const int32_t* node;
     const float* weight;
-    int end;
+    uint32_t end;
     uint32_t in_run, in_turn;
 
-    __device__ __forceinline__ EntryBatches(const int32_t* n, const float* w, int e, int lane) : node(n), weight(w), end(e)
+    __device__ __forceinline__ EntryBatches(const int32_t* n, const float* w, uint32_t e, int lane) : node(n), weight(w), end(e)
     {
         const int g = lane / S::LANES;
         in_run = (uint32_t)(g * S::PER + lane % S::PER);
         in_turn = (uint32_t)((lane % S::PER) * S::GROUPS + g);
     }
-    __device__ __forceinline__ void fetch(int base, int2 (&e)[S::HELD]) const
+    __device__ __forceinline__ void fetch(uint32_t base, int2 (&e)[S::HELD]) const
     {
-        const int from = min(base, end - 1);
-        const uint32_t most = (uint32_t)(end - 1 - from), mine = most + 1u >= (uint32_t)kBatch ? in_run : in_turn;
+        const uint32_t from = batch_begin(base, end), most = end - 1u - from,
+                       mine = most + 1u >= (uint32_t)kBatch ? in_run : in_turn;
 #pragma unroll
         for (int r = 0; r < S::HELD; ++r) {
             const uint32_t p = min(mine + (uint32_t)(r * S::PER * S::GROUPS), most);
@@ -81,7 +81,8 @@ __device__ __forceinline__ void run_item(Wave& w, const EntryBatches<S>& entries
 {
     constexpr int kBatch = EntryBatches<S>::kBatch;
     if (begin >= end) return;
-    int base = begin, left = end - begin;
+    uint32_t base = begin;
+    int left = end - begin;
     int2 e[S::HELD];
     entries.fetch(base, e);
     typename Wave::Held cur = w.hold(e);

@@ -87,8 +87,9 @@ __global__ __launch_bounds__(kWave) void spgemm_fwd_atomic_kernel(const WorkItem
     for (int c = lane; c < dim; c += kWave) row_buf[c] = 0.f;
     __syncthreads();
 
-    for (int base = it.begin; base < it.end; base += kWave) {
-        const int n = min(kWave, it.end - base);
+    const uint32_t end = it.end;
+    for (uint32_t base = it.begin; base < end; base += kWave) {  // (unsigned: the position behind the last entry may pass 2^31)
+        const int n = (int)min((uint32_t)kWave, end - base);
         int my_col = 0;
         float my_val = 0.f;
         if (lane < n) {
@@ -188,8 +189,9 @@ __global__ __launch_bounds__(kWave) void spgemm_fwd_rmw_kernel(const WorkItem* _
         for (int c = lane; c < nb * cs; c += kWave) row_buf[c] = 0.f;
     }
 
-    for (int base = it.begin; base < it.end; base += kWave) {
-        const int n = min(kWave, it.end - base);
+    const uint32_t end = it.end;
+    for (uint32_t base = it.begin; base < end; base += kWave) {  // (unsigned: the position behind the last entry may pass 2^31)
+        const int n = (int)min((uint32_t)kWave, end - base);
         __syncthreads();  // previous batch fully consumed (and the zero fill done)
         if (lane < n) entry_buf[lane] = make_int2(col[base + lane], __float_as_int(val[base + lane]));
         __syncthreads();

@@ -25,13 +25,14 @@ __global__ __launch_bounds__(kWave) void spmm_vec_kernel(const WorkItem* __restr
 #pragma unroll
     for (int r = 0; r < R; ++r) acc[r] = make_float4(0.f, 0.f, 0.f, 0.f);
 
-    for (int p = it.begin; p < it.end; p += kUnroll) {
+    const uint32_t end = it.end;
+    for (uint32_t p = it.begin; p < end; p += kUnroll) {  // (unsigned: positions behind the last entry may pass 2^31)
         float4 h[kUnroll][R];
         float a[kUnroll];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
-            const bool ok = p + u < it.end;
-            const int q = ok ? p + u : it.begin;
+            const bool ok = p + u < end;
+            const uint32_t q = ok ? p + u : (uint32_t)it.begin;
             a[u] = ok ? val[q] : 0.f;
             const float* __restrict__ hr = H + (int64_t)col[q] * dim;
 #pragma unroll

@@ -36,13 +36,14 @@ __global__ __launch_bounds__(kWave) void bwd_reduce_kernel(const WorkItem* __res
         float acc[VEC];
 #pragma unroll
         for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
-        for (int p0 = it.begin; p0 < it.end; p0 += G * kReduceUnroll) {
+        const uint32_t end = it.end;
+        for (uint32_t p0 = it.begin; p0 < end; p0 += G * kReduceUnroll) {  // (unsigned: positions behind the last entry may pass 2^31)
             float v[kReduceUnroll][VEC];
 #pragma unroll
             for (int u = 0; u < kReduceUnroll; ++u) {
-                const int p = p0 + u * G + g;
-                const bool ok = active && p < it.end;
-                const float* __restrict__ src = expand + (int64_t)csc_entry[ok ? p : it.begin] * k + (ok ? qq : 0) * VEC;
+                const uint32_t p = p0 + u * G + g;
+                const bool ok = active && p < end;
+                const float* __restrict__ src = expand + (int64_t)csc_entry[ok ? p : (uint32_t)it.begin] * k + (ok ? qq : 0) * VEC;
                 if constexpr (VEC == 4) {
                     const float4* __restrict__ row = reinterpret_cast<const float4*>(src);
                     const float4 x = !ok ? make_float4(0.f, 0.f, 0.f, 0.f) : ONCE ? load_once(row) : *row;

@@ -128,13 +128,14 @@ __global__ __launch_bounds__(kWave) void bwd_pull_small_kernel(const WorkItem* _
     const bool active = t < k;
     const int my_idx = active ? (int)sp_index[(int64_t)it.row * k + t] : 0;
     float acc = 0.f;
-    for (int p0 = it.begin; p0 < it.end; p0 += G * kPullUnroll) {
+    const uint32_t end = it.end;
+    for (uint32_t p0 = it.begin; p0 < end; p0 += G * kPullUnroll) {  // (unsigned: positions behind the last entry may pass 2^31)
         float gv[kPullUnroll], a[kPullUnroll];
 #pragma unroll
         for (int u = 0; u < kPullUnroll; ++u) {
-            const int p = p0 + u * G + g;
-            const bool ok = p < it.end;
-            const int q = ok ? p : it.begin;
+            const uint32_t p = p0 + u * G + g;
+            const bool ok = p < end;
+            const uint32_t q = ok ? p : (uint32_t)it.begin;
             a[u] = ok ? csc_val[q] : 0.f;
             const float x = widen_value<VT>(dY[(int64_t)csc_src[q] * dim + my_idx]);
             gv[u] = ok ? x : 0.f;
@@ -255,12 +256,13 @@ __global__ __launch_bounds__(kWave) void bwd_pull_wide_kernel(const WorkItem* __
     for (int t = lane; t < k; t += kWave) {
         const int my_idx = (int)sp_index[(int64_t)it.row * k + t];
         float acc = 0.f;
-        for (int p0 = it.begin; p0 < it.end; p0 += kPullUnroll) {
+        const uint32_t end = it.end;
+        for (uint32_t p0 = it.begin; p0 < end; p0 += kPullUnroll) {
             float gv[kPullUnroll], a[kPullUnroll];
 #pragma unroll
             for (int u = 0; u < kPullUnroll; ++u) {
-                const bool ok = p0 + u < it.end;
-                const int q = ok ? p0 + u : it.begin;
+                const bool ok = p0 + u < end;
+                const uint32_t q = ok ? p0 + u : (uint32_t)it.begin;
                 a[u] = ok ? csc_val[q] : 0.f;
                 const float x = widen_value<VT>(dY[(int64_t)csc_src[q] * dim + my_idx]);
                 gv[u] = ok ? x : 0.f;
@@ -292,8 +294,9 @@ __global__ __launch_bounds__(kWave) void bwd_push_kernel(const WorkItem* __restr
     for (int c = lane; c < dim; c += kWave) g_row[c] = widen_value<VT>(src[c]);
     __syncthreads();
 
-    for (int base = it.begin; base < it.end; base += kWave) {
-        const int n = min(kWave, it.end - base);
+    const uint32_t end = it.end;
+    for (uint32_t base = it.begin; base < end; base += kWave) {  // (unsigned: the position behind the last entry may pass 2^31)
+        const int n = (int)min((uint32_t)kWave, end - base);
         int my_col = 0;
         float my_val = 0.f;
         if (lane < n) {
@@ -352,8 +355,9 @@ __global__ __launch_bounds__(kWave) void bwd_expand_kernel(const WorkItem* __res
     const value_store_t<VT>* __restrict__ src = dY + (int64_t)it.row * dim;
     for (int c = lane; c < dim; c += kWave) g_row[c] = widen_value<VT>(src[c]);
 
-    for (int base = it.begin; base < it.end; base += kWave) {
-        const int n = min(kWave, it.end - base);
+    const uint32_t end = it.end;
+    for (uint32_t base = it.begin; base < end; base += kWave) {  // (unsigned: the position behind the last entry may pass 2^31)
+        const int n = (int)min((uint32_t)kWave, end - base);
         __syncthreads();
         if (lane < n) entry_buf[lane] = make_int2(col[base + lane], __float_as_int(val[base + lane]));
         __syncthreads();
@@ -482,7 +486,7 @@ __global__ __launch_bounds__(kWave) void bwd_slab_kernel(const int32_t* __restri
         for (int64_t l = l_begin + blockIdx.x; l < l_end; l += n_long_blocks) {
             const int64_t v = long_visit[l];
             const int64_t j = visit_node[v];
-            const int b = visit_begin[v], e = visit_begin[v + 1];
+            const uint32_t b = visit_begin[v], e = visit_begin[v + 1];  // (unsigned: positions behind the last entry may pass 2^31)
             for (int qb = 0; qb < kq; qb += LPD) {  // one pass unless k / VEC > 64
                 const int q = qb + q0;
                 const bool active = q < kq;
@@ -494,13 +498,13 @@ __global__ __launch_bounds__(kWave) void bwd_slab_kernel(const int32_t* __restri
                     my[c] = (int32_t)sp_index[o + c * kq];
                     acc[c] = 0.f;
                 }
-                for (int p0 = b; p0 < e; p0 += G * 4) {
+                for (uint32_t p0 = b; p0 < e; p0 += G * 4) {
                     float gv[4][VEC], a[4];
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
-                        const int p = p0 + u * G + g;
+                        const uint32_t p = p0 + u * G + g;
                         const bool ok = p < e;
-                        const int pc = ok ? p : b;
+                        const uint32_t pc = ok ? p : b;
                         const int32_t row = slab_src[pc];
                         a[u] = ok ? slab_val[pc] : 0.f;
 #pragma unroll
