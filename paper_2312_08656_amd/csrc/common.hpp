@@ -230,6 +230,9 @@ inline int fwd_wide(int64_t N, int k, int val_bytes, int index_bytes, int record
 }
 int fwd_layout(int k, int index_bytes, int val_bytes);  // of a repacked CBSR
 
+// k that the sweep takes.  Eight groups in two or three passes lost to the row-by-row kernel on every graph measured (k = 12: eight copies of a
+// row leave a bin one row).
+constexpr bool sweep_takes(int k) { return fwd_groups(k).lanes && k <= 128 && (fwd_groups(k).lanes > 8 || k == 8); }
 constexpr int sweep_groups(int k) { return kWave / fwd_groups(k).lanes; }
 constexpr int sweep_batch(int k) { return fwd_groups(k).lanes < 16 ? 8 : 16; }
 

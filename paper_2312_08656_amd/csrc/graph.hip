@@ -1023,7 +1023,7 @@ bool fwd_uses_packed(const maxk_graph* g, int k, int index_bytes, int val_bytes)
 //   1 group: k = 64, 19 MB, 755 entries 310 / 264, 9.6 MB, 298 entries 53 / 79, 192 MB, 80 entries 569 / 512; k = 128, 23 MB, 298 entries 187 / 171
 int sweep_rows(const maxk_graph* g, int dim, int k, int index_bytes, int val_bytes)
 {
-    if (!fwd_groups(k).lanes || k > 128 || dim > 512 || g->N > (1 << kSweepRowShift) || g->nnz == 0 || g->fwd_sweep == 1) return 0;
+    if (!sweep_takes(k) || dim > 512 || g->N > (1 << kSweepRowShift) || g->nnz == 0 || g->fwd_sweep == 1) return 0;
     const int per_bin = sweep_bin_rows(k, dim), groups = sweep_groups(k);
     // a wavefront per bin, rounded up to whole workgroups, is below the 2^32 threads of a launch
     if ((g->csr_items.n_items + per_bin - 1) / per_bin > (1 << 26) - 64) return 0;
@@ -1032,7 +1032,7 @@ int sweep_rows(const maxk_graph* g, int dim, int k, int index_bytes, int val_byt
                                                                      : k * (val_bytes + index_bytes);
     const double bins = (double)g->csr_items.n_items / per_bin, table = (double)g->N * record;
     const double entries = (double)g->nnz / (bins * groups) * std::min(1.0, 256.0 / dim);  // of a lane group, by the length of its rows
-    const bool pays = groups == 8   ? k == 8 && table >= 8e6 && entries >= 48.0
+    const bool pays = groups == 8   ? table >= 8e6 && entries >= 48.0
                       : groups == 4 ? (table >= 9e6 && entries >= 100.0) || (table >= 20e6 && entries >= 58.0)
                       : groups == 1 ? table >= 18e6 && entries >= 60.0
                       : k > kWave   ? table >= 14e6 && entries >= 32.0

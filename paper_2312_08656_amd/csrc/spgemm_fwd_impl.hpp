@@ -590,8 +590,8 @@ __global__ __launch_bounds__(kSweepWaves * kWave) __attribute__((amdgpu_waves_pe
     }
 }
 
-// Runs F<FwdLanes<LANES, PASSES>> for MaxK k.
-template <int LAYOUT, typename F>
+// Runs F<FwdLanes<LANES, PASSES>> for MaxK k.  SWEEP: the sweep takes eight lane groups at k = 8 alone (sweep_takes).
+template <int LAYOUT, bool SWEEP, typename F>
 maxk_status for_fwd_groups(int k, F&& f)
 {
     const FwdGroups by = fwd_groups(k);
@@ -600,9 +600,9 @@ maxk_status for_fwd_groups(int k, F&& f)
 #define MAXK_FWD_GROUPS(LANES, PASSES) \
     if (by.lanes == LANES && by.passes == PASSES) return f.template operator()<FwdLanes<LANES, PASSES>>()
     MAXK_FWD_GROUPS(8, 1);
-    MAXK_FWD_GROUPS(8, 2);
     MAXK_FWD_GROUPS(16, 1);
-    if constexpr (LAYOUT != kFwdPairs) MAXK_FWD_GROUPS(8, 3);
+    if constexpr (!SWEEP) MAXK_FWD_GROUPS(8, 2);
+    if constexpr (!SWEEP && LAYOUT != kFwdPairs) MAXK_FWD_GROUPS(8, 3);
     MAXK_FWD_GROUPS(16, 2);
     MAXK_FWD_GROUPS(32, 1);
     if constexpr (LAYOUT == kFwdArrays) {
@@ -612,7 +612,7 @@ maxk_status for_fwd_groups(int k, F&& f)
         MAXK_FWD_GROUPS(32, 4);
         MAXK_FWD_GROUPS(64, 1);
         MAXK_FWD_GROUPS(64, 2);
-        MAXK_FWD_GROUPS(64, 3);
+        if constexpr (!SWEEP) MAXK_FWD_GROUPS(64, 3);
     }
 #undef MAXK_FWD_GROUPS
     return MAXK_UNSUPPORTED;
@@ -629,7 +629,7 @@ maxk_status launch_sweep(const SweepSet& S, const value_store_t<VT>* sp_data, co
     const int vec_out = dim % 4 == 0 && aligned(Y, 16) && aligned(partials, 16) ? (past_l2(N * dim * 4) ? 2 : 1) : 0;
     const dim3 grid((unsigned)((S.n_bins + waves - 1) / waves)), block((unsigned)(kWave * waves));
     const int wide = fwd_wide(N, k, (int)sizeof(value_store_t<VT>), (int)sizeof(IdxT), LAYOUT ? rec_bytes : 0);
-    return for_fwd_groups<LAYOUT>(k, [&]<class G>() -> maxk_status {
+    return for_fwd_groups<LAYOUT, true>(k, [&]<class G>() -> maxk_status {
         static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&spgemm_fwd_sweep_kernel<G, LAYOUT, VT, IdxT>),
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSweepLds);
         MAXK_HIP_TRY(attr);
@@ -650,7 +650,7 @@ maxk_status launch_row(const ItemList& L, const int32_t* col, const float* val, 
     if (const int lanes = fwd_groups(k).lanes) {
         const int wide = fwd_wide(N, k, (int)sizeof(value_store_t<VT>), (int)sizeof(IdxT), LAYOUT ? rec_bytes : 0);
         const size_t lds = sizeof(float) * (size_t)(kWave / lanes) * (size_t)((dim + 3) & ~3);
-        return for_fwd_groups<LAYOUT>(k, [&]<class G>() -> maxk_status {
+        return for_fwd_groups<LAYOUT, false>(k, [&]<class G>() -> maxk_status {
             hipLaunchKernelGGL((spgemm_fwd_row_kernel<G, LAYOUT, VT, IdxT>), dim3((unsigned)L.n_items), dim3(kWave), lds, s, L.d_items, col, val,
                                sp_data, sp_index, packed, rec_bytes, idx_off, dim, k, wide, vec_out, Y, partials);
             MAXK_LAUNCH_CHECK();

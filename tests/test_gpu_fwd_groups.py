@@ -138,3 +138,14 @@ def test_reserve_holds_the_repacked_records(N, k):
                 assert gr.info()["workspace_bytes"] == held, (N, k, kk, fmt, index)
     torch.cuda.synchronize()
     gr.destroy()
+
+
+@pytest.mark.parametrize("k,tables", [(8, 1), (9, 0), (10, 0), (13, 0), (16, 1), (17, 0), (21, 0), (22, 1), (128, 1), (129, 0), (192, 0)])
+def test_widths_that_the_sweep_takes(monkeypatch, k, tables):
+    # asked for wherever the shape allows it, it takes k = 8, 16 and 22 to 128, as the header says
+    monkeypatch.setenv("MAXK_FWD_SWEEP", "2")
+    N, rowptr, col, val = _graph(k)
+    gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val))
+    gr.reserve(256, k)
+    assert gr.sweep_tables() == tables
+    gr.destroy()
