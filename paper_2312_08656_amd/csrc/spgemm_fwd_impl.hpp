@@ -476,8 +476,24 @@ __device__ __forceinline__ uint32_t lds_address(const float* p)
 }
 
 // Row by row: a wavefront per work item.  (k = 8, 10 .. 128 and 192; the others run spgemm_fwd_rmw_kernel.)
+// Wavefronts a SIMD that the registers leave room for: nothing of a pass may spill, and from two passes on 64 registers do not hold two
+// sets of loads.  us, by units / lane groups with spills for 8 wavefronts / with 6: 60 k nodes, degree 16, k = 50 with 4-byte columns
+// 82 / 102 / 80, width 512, k = 128 bf16 84 / 108 / 82; 100 k, 61, k = 50 bf16, 2-byte columns 359 / 284 / 231; 300 k, 31, k = 128 786 / 952 / 786.
+// Half as many loads under way leave room for more wavefronts, which is better where one group works on an entry (1 M nodes, degree 9,
+// k = 128 863 us by units, 1092 with spills, 928 / 854 with all loads / half) and in two passes of 16 lanes (717 k, 11, k = 24 462, 313, 345 / 309),
+// but not from column pairs (100 k, 61, k = 24 bf16 89 / 92).
+template <class S>
+struct HalfStep : S {
+    static constexpr int STEP = S::STEP / 2, STEPS = S::BATCH / STEP, ROUNDS = STEP * S::PASSES;
+};
+template <class S, int LAYOUT>
+constexpr bool kRowHalf = (S::LANES == kWave && S::PASSES <= 2) || (S::LANES == 16 && S::PASSES == 2 && LAYOUT != kFwdPairs);
+template <class S, int LAYOUT>
+using RowSplit = std::conditional_t<kRowHalf<S, LAYOUT>, HalfStep<S>, S>;
+template <class S, int LAYOUT, int VT>
+constexpr int kRowWaves = S::PASSES == 1 ? 8 : S::LANES == 16 && kRowHalf<S, LAYOUT> ? (VT == MAXK_VALUE_F32 ? 8 : 7) : 6;
 template <class S, int LAYOUT, int VT, typename IdxT>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(8))) void spgemm_fwd_row_kernel(
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(kRowWaves<S, LAYOUT, VT>))) void spgemm_fwd_row_kernel(
     const WorkItem* __restrict__ items, const int32_t* __restrict__ col, const float* __restrict__ val,
     const value_store_t<VT>* __restrict__ sp_data, const IdxT* __restrict__ sp_index, const char* __restrict__ packed, int rec_bytes,
     int idx_off, int dim, int k, int wide, int vec_out, float* __restrict__ Y, float* __restrict__ partials)
@@ -651,7 +667,7 @@ maxk_status launch_row(const ItemList& L, const int32_t* col, const float* val, 
         const int wide = fwd_wide(N, k, (int)sizeof(value_store_t<VT>), (int)sizeof(IdxT), LAYOUT ? rec_bytes : 0);
         const size_t lds = sizeof(float) * (size_t)(kWave / lanes) * (size_t)((dim + 3) & ~3);
         return for_fwd_groups<LAYOUT, false>(k, [&]<class G>() -> maxk_status {
-            hipLaunchKernelGGL((spgemm_fwd_row_kernel<G, LAYOUT, VT, IdxT>), dim3((unsigned)L.n_items), dim3(kWave), lds, s, L.d_items, col, val,
+            hipLaunchKernelGGL((spgemm_fwd_row_kernel<RowSplit<G, LAYOUT>, LAYOUT, VT, IdxT>), dim3((unsigned)L.n_items), dim3(kWave), lds, s, L.d_items, col, val,
                                sp_data, sp_index, packed, rec_bytes, idx_off, dim, k, wide, vec_out, Y, partials);
             MAXK_LAUNCH_CHECK();
             return MAXK_OK;

@@ -216,7 +216,7 @@ struct PullWave {
 };
 
 template <class S, int VT, typename IdxT>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(8))) void bwd_pull_lanes_kernel(
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(S::PASSES == 1 ? 8 : 6))) void bwd_pull_lanes_kernel(
     const WorkItem* __restrict__ items, const int32_t* __restrict__ csc_src, const float* __restrict__ csc_val,
     const value_store_t<VT>* __restrict__ dY, const IdxT* __restrict__ sp_index, int dim, int k, int wide, float* __restrict__ dXs,
     float* __restrict__ partials)
