@@ -171,6 +171,8 @@ maxk_status upload_items(const std::vector<WorkItem>& items, const std::vector<S
     L.n_items = (int64_t)items.size();
     L.n_split = (int64_t)split.size();
     L.n_slots = n_slots;
+    L.n_entries = 0;
+    for (const WorkItem& w : items) L.n_entries += w.end - w.begin;
     L.n_long = std::partition_point(items.begin(), items.end(),
                                     [](const WorkItem& w) { return w.end - w.begin > kSlicedLongItem; }) - items.begin();
     if (L.n_items) {
@@ -1880,6 +1882,11 @@ MAXK_API maxk_status maxk_regs_step_list(uint32_t record0, uint32_t records, uin
     *first = list.first;
     *copied = regs_copied(list.records);
     return MAXK_OK;
+}
+
+MAXK_API int32_t maxk_fwd_by_units(int32_t k, int32_t dim, int32_t value_type, int64_t items, int64_t entries)
+{
+    return k < 1 ? MAXK_INVALID_ARGUMENT : fwd_by_units(k, dim, value_bytes(value_type), items, entries);
 }
 
 MAXK_API int64_t maxk_entry_batch(uint32_t base, uint32_t ahead, uint32_t end) { return batch_begin(base + ahead, end); }

@@ -475,7 +475,7 @@ __device__ __forceinline__ uint32_t lds_address(const float* p)
     return (uint32_t)(uintptr_t)(lds_const_float*)p;
 }
 
-// Row by row: a wavefront per work item.  (k = 8, 10 .. 128 and 192; the others run spgemm_fwd_rmw_kernel.)
+// Row by row: a wavefront per work item.  (k = 8, 10 .. 128 and 192; the others, and some calls at k = 17 .. 21, run spgemm_fwd_rmw_kernel.)
 // Wavefronts a SIMD that the registers leave room for: nothing of a pass may spill, and from two passes on 64 registers do not hold two
 // sets of loads.  us, by units / lane groups with spills for 8 wavefronts / with 6: 60 k nodes, degree 16, k = 50 with 4-byte columns
 // 82 / 102 / 80, width 512, k = 128 bf16 84 / 108 / 82; 100 k, 61, k = 50 bf16, 2-byte columns 359 / 284 / 231; 300 k, 31, k = 128 786 / 952 / 786.
@@ -663,7 +663,7 @@ maxk_status launch_row(const ItemList& L, const int32_t* col, const float* val, 
 {
     if (L.n_items > 0x7FFFFFFF) return MAXK_UNSUPPORTED;
     const int vec_out = dim % 4 == 0 && aligned(Y, 16) && aligned(partials, 16) ? (past_l2(N * dim * 4) ? 2 : 1) : 0;
-    if (const int lanes = fwd_groups(k).lanes) {
+    if (const int lanes = fwd_groups(k).lanes; !fwd_by_units(k, dim, (int)sizeof(value_store_t<VT>), L.n_items, L.n_entries)) {
         const int wide = fwd_wide(N, k, (int)sizeof(value_store_t<VT>), (int)sizeof(IdxT), LAYOUT ? rec_bytes : 0);
         const size_t lds = sizeof(float) * (size_t)(kWave / lanes) * (size_t)((dim + 3) & ~3);
         return for_fwd_groups<LAYOUT, false>(k, [&]<class G>() -> maxk_status {
@@ -756,8 +756,8 @@ maxk_status launch_fwd_vt(const ItemList& L, const int32_t* col, const float* va
                           float* partials, hipStream_t s)
 {
     const auto* sp_data = (const value_store_t<VT>*)sp_data_v;
-    const FwdGroups by = fwd_groups(k);
-    const size_t private_lds = sizeof(float) * (size_t)(by.lanes ? kWave / by.lanes : private_copies(k)) * (size_t)dim;
+    const bool units = fwd_by_units(k, dim, (int)sizeof(value_store_t<VT>), L.n_items, L.n_entries);
+    const size_t private_lds = sizeof(float) * (size_t)(units ? private_copies(k) : kWave / fwd_groups(k).lanes) * (size_t)dim;
     if (private_lds <= kMaxPrivateLds) {
         if (index_bytes == 1) return launch_row_i<VT>(L, col, val, sp_data, (const uint8_t*)sp_index, N, packed, dim, k, Y, partials, s);
         if (index_bytes == 2) return launch_row_i<VT>(L, col, val, sp_data, (const uint16_t*)sp_index, N, packed, dim, k, Y, partials, s);

@@ -149,3 +149,28 @@ def test_widths_that_the_sweep_takes(monkeypatch, k, tables):
     gr.reserve(256, k)
     assert gr.sweep_tables() == tables
     gr.destroy()
+
+
+# k = 17 to 21 on wide rows: by units where the work items are short, by lane groups where they are long
+@pytest.mark.parametrize("k,dim,ib,units", [(17, 256, 1, 0), (17, 257, 2, 0), (17, 1024, 2, 1), (19, 640, 4, 1), (21, 600, 2, 1), (20, 300, 2, 0)])
+@pytest.mark.parametrize("fmt", ["f32", "bf16", "f16"])
+def test_forward_of_wide_rows(monkeypatch, k, dim, ib, units, fmt):
+    monkeypatch.setenv("MAXK_FWD_SWEEP", "1")
+    N, rowptr, col, val = _graph(k)
+    gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val))
+    value_type = {"f32": maxk.VALUE_F32, "bf16": maxk.VALUE_BF16, "f16": maxk.VALUE_F16}[fmt]
+    assert maxk.load_library().maxk_fwd_by_units(k, dim, value_type, gr.info()["n_fwd_items"], len(col)) == units
+    H = synth.normal_matrix(N, dim, 5 + k)
+    sp_data = torch.empty((N, k), dtype=_DTYPE[fmt], device="cuda")
+    sp_index = torch.empty((N, k), dtype={1: torch.uint8, 2: torch.int16, 4: torch.int32}[ib], device="cuda")
+    maxk.maxk_topk_cbsr_narrow(to_dev(H), k, sp_data, sp_index)
+    ref, refabs = oracle.spgemm_fwd(rowptr, col, val, sp_data.float().cpu().numpy(), oracle.topk_cbsr(H, k)[1], dim)
+    gr.destroy()
+    for pack in ("0", "192"):
+        monkeypatch.setenv("MAXK_FWD_PACK_MAX", pack)
+        gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val))
+        Y = torch.full((N, dim), float("nan"), device="cuda")
+        maxk.maxk_spgemm_fwd_narrow(gr, sp_data, sp_index, dim, Y)
+        torch.cuda.synchronize()
+        assert (np.abs(Y.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all(), (k, dim, fmt, pack)
+        gr.destroy()
