@@ -18,6 +18,10 @@ MAXK_API int32_t maxk_fwd_private_copies(int32_t k);
 /* Whether the row-by-row forward kernel works by units, not by lane groups, on `items` work items of `entries` entries (0 or 1). */
 MAXK_API int32_t maxk_fwd_by_units(int32_t k, int32_t dim, int32_t value_type, int64_t items, int64_t entries);
 
+/* Whether the pull of whole rows works by units, not by lane groups, on a graph where `beyond` of the entries have a row that is not among the most
+   frequent 4 MB (0 or 1). */
+MAXK_API int32_t maxk_pull_by_units(int32_t dim, int32_t k, int32_t value_type, int64_t N, int64_t nnz, double beyond);
+
 /* Whether the expand/reduce backward kernels write and read their products past L2 at this shape (0 or 1). */
 MAXK_API int32_t maxk_expand_past_l2(int64_t N, int64_t nnz, int32_t dim, int32_t k, int32_t index_bytes, int32_t dy_value_type);
 

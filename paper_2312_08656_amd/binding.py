@@ -25,7 +25,7 @@ EXPORTS = (
     "maxk_last_hip_error", "maxk_version", "maxk_fwd_private_copies", "maxk_graph_cached_tables", "maxk_graph_sweep_tables",
     "maxk_graph_regs_tables", "maxk_graph_regs_stands_in", "maxk_regs_step_list", "maxk_graph_regs_table",
     "maxk_graph_limit_allocations", "maxk_expand_past_l2", "maxk_scatter_past_l2", "maxk_lone_visit_line",
-    "maxk_entry_batch", "maxk_fwd_by_units",
+    "maxk_entry_batch", "maxk_fwd_by_units", "maxk_pull_by_units",
 )
 
 
@@ -99,6 +99,8 @@ def load_library() -> ctypes.CDLL:
     lib.maxk_entry_batch.restype = i64
     lib.maxk_fwd_by_units.argtypes = [i32, i32, i32, i64, i64]
     lib.maxk_fwd_by_units.restype = i32
+    lib.maxk_pull_by_units.argtypes = [i32, i32, i32, i64, i64, ctypes.c_double]
+    lib.maxk_pull_by_units.restype = i32
     lib.maxk_last_hip_error.argtypes = []
     lib.maxk_version.argtypes = []
     _LIB = lib

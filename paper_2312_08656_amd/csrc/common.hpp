@@ -347,7 +347,7 @@ maxk_status launch_spmm(const ItemList& items, const int32_t* col, const float* 
 
 // backward launchers: `dY` holds value_store_t<value_type> elements (fp32, or bf16 / fp16 patterns)
 maxk_status launch_bwd_pull(const ItemList& csc_items, const int32_t* csc_src, const float* csc_val, const void* dY,
-                            int value_type, const void* sp_index, int index_bytes, int64_t N, int dim, int k, float* dXs,
+                            int value_type, const void* sp_index, int index_bytes, int64_t N, int dim, int k, bool units, float* dXs,
                             float* partials, hipStream_t s);
 
 // Column-sliced pull: slices of one 128-byte line of a dY row.  It gathers from dY itself when rows are whole lines and

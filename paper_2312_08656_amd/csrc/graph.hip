@@ -1142,6 +1142,31 @@ double lines_touched(int dim, int k, int val_bytes)
     return dim <= per_line ? 1.0 : (dim / per_line) * (1.0 - std::pow(1.0 - per_line / dim, (double)k));
 }
 
+// Whether the pull of whole rows works by units (bwd_pull_small_kernel, _wide_kernel), not by lane groups; `beyond`: share of the entries whose row is
+// not among the most frequent 4 MB of them.  By lane groups an entry takes a third of the instructions; but the faster a wavefront walks its entries,
+// the less the wavefronts keep together on their way over the sources, and rows that they shared in an L2 come from beyond it instead (8 k nodes, 0.8 M
+// entries, rows of 2 KB, k = 32: 219 / 463 MB fetched, 8.8 / 4.1 M hits, 80 / 130 us).  So units are taken where an entry's lines, most of them from
+// beyond L2, weigh more than its instructions.  us, units / lane groups, rows of 4-byte elements but *: k = 16, 8 k nodes, degree 101, 1 KB 37 / 49; 20 k, 61, 1 KB
+// 73 / 82; 100 k, 61, 512 bytes* 289 / 319; 40 k, 31, 400 bytes (k = 13) 51 / 49; 300 k, 61, 256 bytes* (k = 12) 475 / 544; 300 k, 17, 256 bytes 167 / 132; k = 24, 8 k,
+// 501, 2 KB 301 / 516; 60 k, 201, 768 bytes* 663 / 793; k = 64, 14 k, 29, 1 KB 35 / 46; 150 k, 121, 1 KB 1704 / 2157; 20 k, 61, 1 KB 125 / 90; k = 100, 12 k, 101,
+// 2 KB 187 / 252; k = 128, 100 k, 61, 2 KB 1623 / 1437.  Over 966 such calls the kernel taken is 0.5 % above the better one on average, lane groups everywhere 4.2 %.
+// (16 < k <= 32 and a dY of several L2s together: 100 k nodes, degree 100 1043 / 1094, 169 k, 14 343 / 353, 1 M, 15 2361 / 2410.)
+bool pull_by_units(int dim, int k, int val_bytes, int64_t N, int64_t nnz, double beyond)
+{
+    if (k < 9 || k > 128) return true;
+    const double bytes = (double)N * dim * val_bytes, degree = (double)nnz / (double)std::max<int64_t>(N, 1);
+    const double lines = lines_touched(dim, k, val_bytes) * (5.0 + 12.0 * beyond);  // ps an entry
+    if (k <= 16) return beyond >= 0.25 && (lines > 40.0 || (degree >= 60.0 && beyond >= 0.33));
+    if (k <= 32) return bytes > (64 << 20) || (beyond >= 0.25 && lines > 60.0) || (degree >= 100.0 && beyond >= 0.5);
+    if (k <= 64) return beyond >= 0.52 && lines > 70.0 && (degree >= 40.0 || bytes < 64e6);
+    return beyond >= 0.5 && lines > 140.0 && bytes < 35e6;
+}
+
+bool pull_by_units(const maxk_graph* g, int dim, int k, int val_bytes)
+{
+    return pull_by_units(dim, k, val_bytes, g->N, g->nnz, 1.0 - hot_share(g, 4e6 / ((double)dim * val_bytes)));
+}
+
 // The two forms of the pull over CSC, in seconds (see auto_bwd_mode for where the figures come from).
 // Plain: a line costs 5 ps when its row sits in L2 (4 MB of the most frequent rows), 17 ps when it does not; below that
 // the gather's own instructions (12 + 0.55 k ps an entry).  One wavefront walks an item of at most `chunk` entries, 4 loads
@@ -1781,7 +1806,8 @@ MAXK_API maxk_status maxk_sspmm_bwd_narrow(maxk_graph* g, const void* d_dY, int3
         rest.d_items += rest.n_items - tail;
         rest.n_items = tail;
         rest.n_split = rest.n_slots = 0;
-        return launch_bwd_pull(rest, g->d_csc_src, g->d_csc_val, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs, g->d_partials, s);
+        return launch_bwd_pull(rest, g->d_csc_src, g->d_csc_val, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, pull_by_units(g, dim, k, vb), d_dXs,
+                               g->d_partials, s);
     }
     if (plan.mode == MAXK_BWD_TILED)
         return launch_bwd_tiled(*plan.T, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs, s);
@@ -1798,7 +1824,7 @@ MAXK_API maxk_status maxk_sspmm_bwd_narrow(maxk_graph* g, const void* d_dY, int3
             if (st != MAXK_UNSUPPORTED) return st;
         }
         return launch_bwd_pull(g->csc_items, g->d_csc_src, g->d_csc_val, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k,
-                               d_dXs, g->d_partials, s);
+                               pull_by_units(g, dim, k, vb), d_dXs, g->d_partials, s);
     }
     return launch_bwd_push(g->csr_items, g->d_col, g->d_val, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, d_dXs, s);
 }
@@ -1887,6 +1913,11 @@ MAXK_API maxk_status maxk_regs_step_list(uint32_t record0, uint32_t records, uin
 MAXK_API int32_t maxk_fwd_by_units(int32_t k, int32_t dim, int32_t value_type, int64_t items, int64_t entries)
 {
     return k < 1 ? MAXK_INVALID_ARGUMENT : fwd_by_units(k, dim, value_bytes(value_type), items, entries);
+}
+
+MAXK_API int32_t maxk_pull_by_units(int32_t dim, int32_t k, int32_t value_type, int64_t N, int64_t nnz, double beyond)
+{
+    return k < 1 || dim < k ? MAXK_INVALID_ARGUMENT : pull_by_units(dim, k, value_bytes(value_type), N, nnz, beyond);
 }
 
 MAXK_API int64_t maxk_entry_batch(uint32_t base, uint32_t ahead, uint32_t end) { return batch_begin(base + ahead, end); }

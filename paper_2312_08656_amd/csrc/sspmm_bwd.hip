@@ -93,12 +93,12 @@ maxk_status launch_reduce_v(const ItemList& L, const uint32_t* csc_entry, const 
 }  // namespace
 
 maxk_status launch_bwd_pull(const ItemList& L, const int32_t* csc_src, const float* csc_val, const void* dY,
-                            int value_type, const void* sp_index, int index_bytes, int64_t N, int dim, int k, float* dXs,
+                            int value_type, const void* sp_index, int index_bytes, int64_t N, int dim, int k, bool units, float* dXs,
                             float* partials, hipStream_t s)
 {
     if (L.n_items == 0) return MAXK_OK;
     if (L.n_items > 0x7FFFFFFF) return MAXK_UNSUPPORTED;
-    const maxk_status st = MAXK_BY_FORMAT(bwd_pull_format, L, csc_src, csc_val, dY, sp_index, index_bytes, N, dim, k, dXs, partials, s);
+    const maxk_status st = MAXK_BY_FORMAT(bwd_pull_format, L, csc_src, csc_val, dY, sp_index, index_bytes, N, dim, k, units, dXs, partials, s);
     if (st != MAXK_OK) return st;
     return launch_combine(L, partials, k, dXs, s);
 }

@@ -6,10 +6,10 @@ namespace maxk {
 
 template <>
 maxk_status bwd_pull_format<MAXK_VALUE_F32>(const ItemList& L, const int32_t* csc_src, const float* csc_val, const void* dY,
-                                  const void* sp_index, int index_bytes, int64_t N, int dim, int k, float* dXs, float* partials,
+                                  const void* sp_index, int index_bytes, int64_t N, int dim, int k, bool units, float* dXs, float* partials,
                                   hipStream_t s)
 {
-    return pull_format<MAXK_VALUE_F32>(L, csc_src, csc_val, dY, sp_index, index_bytes, N, dim, k, dXs, partials, s);
+    return pull_format<MAXK_VALUE_F32>(L, csc_src, csc_val, dY, sp_index, index_bytes, N, dim, k, units, dXs, partials, s);
 }
 
 template <>

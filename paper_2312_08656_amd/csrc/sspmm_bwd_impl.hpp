@@ -53,7 +53,7 @@ namespace maxk {
 // implemented once per storage format of dY (sspmm_bwd_f32.hip, _bf16.hip, _f16.hip)
 template <int VT>
 maxk_status bwd_pull_format(const ItemList& L, const int32_t* csc_src, const float* csc_val, const void* dY,
-                            const void* sp_index, int index_bytes, int64_t N, int dim, int k, float* dXs, float* partials,
+                            const void* sp_index, int index_bytes, int64_t N, int dim, int k, bool units, float* dXs, float* partials,
                             hipStream_t s);
 template <int VT>
 maxk_status bwd_push_format(const ItemList& L, const int32_t* col, const float* val, const void* dY,
@@ -112,7 +112,7 @@ __device__ __forceinline__ float pull_sum(const float (&a)[kPullUnroll], const f
 
 // ---------------------------------------------------------------- pull ----
 
-// k <= 8, and up to 32 (see launch_pull_t): KP = power of two >= k lanes per in-entry, 64/KP entries per step
+// k <= 64 by units (pull_by_units): KP = power of two >= k lanes per in-entry, 64/KP entries per step
 template <int KP, int VT, typename IdxT>
 __global__ __launch_bounds__(kWave) void bwd_pull_small_kernel(const WorkItem* __restrict__ items,
                                                                const int32_t* __restrict__ csc_src,
@@ -155,7 +155,8 @@ __global__ __launch_bounds__(kWave) void bwd_pull_small_kernel(const WorkItem* _
 // position took some 12 vector instructions (now 3: an offset with the entry's row as a DPP operand, the multiply-add with its weight
 // as one), and a step's gathers waited for its sources and then for themselves before the next began.  us, before / now: 2 k nodes, degree 100,
 // k = 48 25.6 / 11.6; 5 k, 50, k = 64 fp16 dY 27.0 / 14.0; 10 k, 300, width 200, k = 24 153 / 107; 40 k, 60, width 100, k = 13 89.8 / 76.7;
-// 60 k, 60, k = 64 446 / 373; 100 k, 40, k = 64 bf16 dY 340 / 208; 300 k, 30, width 384, k = 128 2066 / 1896.  Eight entries under way
+// 60 k, 60, k = 64 446 / 373; 100 k, 40, k = 64 bf16 dY 340 / 208; 300 k, 30, width 384, k = 128 2066 / 1896 (and where it is
+// slower: pull_by_units).  Eight entries under way
 // instead of four gain nothing; k = 8 stays with the kernel above (20 k nodes, degree 200 157 / 186).
 template <int LANES, int PASSES>
 struct PullLanes : FwdLanes<LANES, PASSES> {
@@ -241,7 +242,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(S::PASSES
     }
 }
 
-// k > 128: lane handles positions t = lane, lane + 64, ...; one pass over the in-entries per 64 positions
+// k > 64 by units: lane handles positions t = lane, lane + 64, ...; one pass over the in-entries per 64 positions
 template <int VT, typename IdxT>
 __global__ __launch_bounds__(kWave) void bwd_pull_wide_kernel(const WorkItem* __restrict__ items,
                                                               const int32_t* __restrict__ csc_src,
@@ -922,7 +923,7 @@ maxk_status launch_slab_i(const SlabSet& S, const value_store_t<VT>* dY, const I
 
 template <int VT, typename IdxT>
 maxk_status launch_pull_t(const ItemList& L, const int32_t* csc_src, const float* csc_val, const value_store_t<VT>* dY,
-                          const IdxT* sp_index, int64_t N, int dim, int k, float* dXs, float* partials, hipStream_t s)
+                          const IdxT* sp_index, int64_t N, int dim, int k, bool units, float* dXs, float* partials, hipStream_t s)
 {
     dim3 grid((unsigned)L.n_items), block(kWave);
 #define MAXK_PULL(KERNEL) \
@@ -931,10 +932,10 @@ maxk_status launch_pull_t(const ItemList& L, const int32_t* csc_src, const float
     else if (k <= 2) MAXK_PULL((bwd_pull_small_kernel<2, VT, IdxT>));
     else if (k <= 4) MAXK_PULL((bwd_pull_small_kernel<4, VT, IdxT>));
     else if (k <= 8) MAXK_PULL((bwd_pull_small_kernel<8, VT, IdxT>));
-    // (16 < k <= 32 and a dY of several L2s together: fewer rows under way are the better ones, us, this / by lane groups: 100 k nodes, degree
-    // 100 1043 / 1094, 169 k, 14 343 / 353, 1 M, 15 2361 / 2410; 60 k nodes of 512 bytes 204 / 152; k = 16 on 300 k nodes 1160 / 1125)
-    else if (k > 16 && k <= 32 && N * dim * (int64_t)sizeof(value_store_t<VT>) > (64 << 20)) MAXK_PULL((bwd_pull_small_kernel<32, VT, IdxT>));
-    else if (k > 128) MAXK_PULL((bwd_pull_wide_kernel<VT, IdxT>));
+    else if (units && k <= 16) MAXK_PULL((bwd_pull_small_kernel<16, VT, IdxT>));
+    else if (units && k <= 32) MAXK_PULL((bwd_pull_small_kernel<32, VT, IdxT>));
+    else if (units && k <= 64) MAXK_PULL((bwd_pull_small_kernel<64, VT, IdxT>));
+    else if (units || k > 128) MAXK_PULL((bwd_pull_wide_kernel<VT, IdxT>));
 #undef MAXK_PULL
     else {
         const int wide = N * dim * (int64_t)sizeof(value_store_t<VT>) > 0xFFFFFFFFll;  // byte offsets into dY need more than 32 bits
@@ -979,13 +980,13 @@ maxk_status launch_push_t(const ItemList& L, const int32_t* col, const float* va
 
 template <int VT>
 maxk_status pull_format(const ItemList& L, const int32_t* csc_src, const float* csc_val, const void* dY_v,
-                        const void* sp_index, int index_bytes, int64_t N, int dim, int k, float* dXs, float* partials,
+                        const void* sp_index, int index_bytes, int64_t N, int dim, int k, bool units, float* dXs, float* partials,
                         hipStream_t s)
 {
     const auto* dY = (const value_store_t<VT>*)dY_v;
-    if (index_bytes == 1) return launch_pull_t<VT>(L, csc_src, csc_val, dY, (const uint8_t*)sp_index, N, dim, k, dXs, partials, s);
-    if (index_bytes == 2) return launch_pull_t<VT>(L, csc_src, csc_val, dY, (const uint16_t*)sp_index, N, dim, k, dXs, partials, s);
-    return launch_pull_t<VT>(L, csc_src, csc_val, dY, (const int32_t*)sp_index, N, dim, k, dXs, partials, s);
+    if (index_bytes == 1) return launch_pull_t<VT>(L, csc_src, csc_val, dY, (const uint8_t*)sp_index, N, dim, k, units, dXs, partials, s);
+    if (index_bytes == 2) return launch_pull_t<VT>(L, csc_src, csc_val, dY, (const uint16_t*)sp_index, N, dim, k, units, dXs, partials, s);
+    return launch_pull_t<VT>(L, csc_src, csc_val, dY, (const int32_t*)sp_index, N, dim, k, units, dXs, partials, s);
 }
 
 template <int VT>

@@ -174,3 +174,26 @@ def test_forward_of_wide_rows(monkeypatch, k, dim, ib, units, fmt):
         torch.cuda.synchronize()
         assert (np.abs(Y.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all(), (k, dim, fmt, pack)
         gr.destroy()
+
+
+# whole rows from beyond L2: by units, every width of a unit and its last k
+@pytest.mark.parametrize("k,dim,ib", [(9, 512, 2), (16, 512, 4), (17, 512, 2), (32, 512, 2), (33, 512, 2), (64, 512, 2), (65, 512, 2), (128, 512, 4)])
+@pytest.mark.parametrize("fmt", ["f32", "bf16", "f16"])
+def test_pull_by_units(monkeypatch, k, dim, ib, fmt):
+    monkeypatch.setenv("MAXK_PULL_FORM", "1")
+    N, dim, value_type = 14_000, dim if fmt == "f32" else 2 * dim, {"f32": maxk.VALUE_F32, "bf16": maxk.VALUE_BF16, "f16": maxk.VALUE_F16}[fmt]
+    g = synth.make_graph(N, 30 * N, 0, directed=True, self_loops=True, seed=k, weights="normal")
+    gr = maxk.maxk_graph_create(to_dev(g.rowptr), to_dev(g.col), to_dev(g.val))
+    gr.set_bwd_mode(maxk.BWD_PULL_CSC)
+    hot = 4_000_000 // (dim * (4 if fmt == "f32" else 2))
+    beyond = 1.0 - np.sort(np.diff(g.rowptr))[::-1][:hot].sum() / len(g.col)
+    assert maxk.load_library().maxk_pull_by_units(dim, k, value_type, N, len(g.col), beyond) == 1
+    index = np.sort(np.random.default_rng(k).permuted(np.tile(np.arange(dim, dtype=np.int32), (N, 1)), axis=1)[:, :k], axis=1)
+    sp_index = torch.from_numpy(index.astype({2: np.int16, 4: np.int32}[ib])).cuda()
+    dY = to_dev(synth.normal_matrix(N, dim, 9)).to(_DTYPE[fmt])
+    ref, refabs = oracle.sspmm_bwd(g.rowptr, g.col, g.val, dY.float().cpu().numpy(), index)
+    dXs = torch.full((N, k), float("nan"), device="cuda")
+    maxk.maxk_sspmm_bwd_narrow(gr, dY, sp_index, dXs)
+    torch.cuda.synchronize()
+    assert (np.abs(dXs.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all(), (k, dim, fmt)
+    gr.destroy()

@@ -19,3 +19,15 @@ def lib():
     (16, 1024, 0, 60_000, 960_000, 0), (22, 1024, 0, 60_000, 960_000, 0), (9, 64, 0, 60_000, 960_000, 1), (193, 256, 0, 60_000, 960_000, 1)])
 def test_forward_row_by_row(lib, k, dim, value_type, items, entries, units):
     assert lib.maxk_fwd_by_units(k, dim, value_type, items, entries) == units
+
+
+# beyond: share of the entries whose row is not among the most frequent 4 MB
+@pytest.mark.parametrize("dim,k,value_type,N,nnz,beyond,units", [
+    (512, 16, 0, 2_000, 202_000, 0.0, 0), (512, 16, 0, 4_267, 2_140_089, 0.43, 1), (256, 16, 0, 8_000, 808_000, 0.39, 1), (512, 12, 1, 8_000, 4_008_000, 0.39, 1),
+    (100, 13, 0, 40_013, 1_240_013, 0.28, 0), (256, 16, 1, 20_000, 8_020_000, 0.16, 0), (64, 16, 0, 300_000, 5_100_000, 0.4, 0),
+    (128, 12, 1, 300_000, 18_300_000, 0.6, 1), (512, 32, 0, 8_000, 808_000, 0.63, 1), (256, 24, 0, 2_000, 202_000, 0.0, 0), (100, 24, 0, 100_000, 6_100_000, 0.45, 0),
+    (384, 24, 1, 60_000, 12_060_000, 0.52, 1), (256, 32, 0, 169_343, 2_501_829, 0.5, 1), (256, 64, 0, 14_000, 414_000, 0.71, 1),
+    (256, 64, 0, 20_000, 1_220_000, 0.35, 0), (256, 64, 0, 300_000, 5_100_000, 0.6, 0), (512, 100, 0, 12_000, 1_212_000, 0.74, 1),
+    (512, 128, 0, 100_000, 6_100_000, 0.75, 0), (256, 128, 0, 8_000, 808_000, 0.4, 0), (256, 8, 0, 2_000, 202_000, 0.0, 1), (512, 129, 0, 2_000, 202_000, 0.0, 1)])
+def test_pull_of_whole_rows(lib, dim, k, value_type, N, nnz, beyond, units):
+    assert lib.maxk_pull_by_units(dim, k, value_type, N, nnz, beyond) == units
