@@ -27,7 +27,7 @@
  *     them): MAXK_CHUNK (entries per work item; default nnz / 4096,
  *     at least 128 and at most 2048), MAXK_SLAB_KB (KiB of dY per slab of the slab-pull
  *     backward kernel, default 3584), MAXK_FWD_PACK_MAX (largest CBSR row in bytes that the forward pass
- *     repacks into one record per node; default 96, and none of a CBSR of up to 3 MiB), MAXK_PULL_FORM (form of the CSC pull: 0 = by cost, 1 = whole
+ *     repacks into one record per node, for k up to 32; -1, the default: 96, and none of a CBSR of up to 3 MiB), MAXK_PULL_FORM (form of the CSC pull: 0 = by cost, 1 = whole
  *     rows, 2 = column slices wherever the shape allows them; default 0), MAXK_FWD_SWEEP (forward kernel: 0 = by
  *     size, 1 = row by row, 2 = the sweep wherever the shape allows it; default 0), MAXK_BWD_REGS (register-tiled
  *     backward kernel in MAXK_BWD_AUTO: 0 = by cost, 1 = never, 2 = wherever the shape allows it, 3 = the same, its

@@ -1009,6 +1009,7 @@ maxk_status sweep_for(maxk_graph* g, int k, int dim, int per_bin, bool existing_
 constexpr int64_t kFwdPackFrom = 3 << 20;  // bytes of the CBSR
 bool fwd_uses_packed(const maxk_graph* g, int k, int index_bytes, int val_bytes)
 {
+    if (fwd_layout(k, index_bytes, val_bytes) == kFwdArrays) return false;  // no kernel reads such records
     const int row = k * (val_bytes + index_bytes);
     return g->fwd_pack_max >= 0 ? row <= g->fwd_pack_max : row <= 96 && g->N * (int64_t)row > kFwdPackFrom;
 }

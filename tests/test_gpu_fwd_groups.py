@@ -140,6 +140,20 @@ def test_reserve_holds_the_repacked_records(N, k):
     gr.destroy()
 
 
+@pytest.mark.parametrize("k,fmt,grows", [(32, "f32", True), (32, "bf16", True), (33, "f32", False), (64, "f32", False), (64, "bf16", False)])
+def test_no_buffer_for_records_that_no_kernel_reads(monkeypatch, k, fmt, grows):
+    monkeypatch.setenv("MAXK_FWD_PACK_MAX", "1024")
+    N, dim = 5000, 64
+    rowptr = torch.arange(N + 1, dtype=torch.int32, device="cuda")
+    gr = maxk.maxk_graph_create(rowptr, torch.arange(N, dtype=torch.int32, device="cuda"), torch.ones(N, device="cuda"))
+    held, Y = gr.info()["workspace_bytes"], torch.empty((N, dim), device="cuda")
+    sp_index = torch.arange(k, device="cuda").to(torch.uint8).repeat(N, 1)
+    maxk.maxk_spgemm_fwd_narrow(gr, torch.ones((N, k), dtype=_DTYPE[fmt], device="cuda"), sp_index, dim, Y)
+    assert (gr.info()["workspace_bytes"] > held) == grows
+    assert bool((Y[:, :k] == 1).all()) and not bool(Y[:, k:].any())
+    gr.destroy()
+
+
 @pytest.mark.parametrize("k,tables", [(8, 1), (9, 0), (10, 0), (13, 0), (16, 1), (17, 0), (21, 0), (22, 1), (128, 1), (129, 0), (192, 0)])
 def test_widths_that_the_sweep_takes(monkeypatch, k, tables):
     # asked for wherever the shape allows it, it takes k = 8, 16 and 22 to 128, as the header says
