@@ -121,6 +121,9 @@ MAXK_API maxk_status maxk_graph_destroy(maxk_graph* g);
  * that needs a table or a larger workspace builds it (synchronous allocations; the tables also sort A or A^T), later ones
  * reuse it; the same holds for a backward call whose pointers turn out too misaligned for the reserved kernel.  (Within
  * a reserved (dim, k), a forward call with a k' < k whose own regrouped copy nobody built runs row by row.)
+ * A handle keeps about one regrouped copy for each of the four splits of a wavefront into lane groups (by k; more where widths differ much, eight
+ * at most); other widths walk the copy that is there, or run row by row.  Copies differ in the order in which a row's partial sums are added up, so the last bits
+ * of Y may depend on the widths and k that the handle was used with before.
  * When memory runs out, MAXK_BWD_AUTO moves on to the next best backward kernel that fits (the last one, pull, needs no
  * buffer), and a forward call whose regrouped copy could not be built runs row by row, in the compute call and in
  * the reserve alike; what was refused is asked for again by a reserve of its shape only.

@@ -971,17 +971,20 @@ maxk_status note_reserved(maxk_graph* g, int dim, int k)
 }
 
 // existing_only: nothing is built, and a refusal is not remembered (the call is being captured, or was reserved); bins of other
-// numbers of rows do then, as long as a workgroup has a few wavefronts
+// numbers of rows do then, as long as a workgroup has a few wavefronts.  They do as well once the handle holds as many regroupings as there are
+// splits into lane groups, 8 bytes an entry each: one split at three widths would be three of them, all splits fourteen.  (Bins that are too long for a
+// width, built for narrower rows, are joined by others, up to twice as many; then such calls run row by row.)
+constexpr size_t kSweepTables = 4;
 maxk_status sweep_for(maxk_graph* g, int k, int dim, int per_bin, bool existing_only, SweepSet** out)
 {
     const int groups = sweep_groups(k), batch_len = sweep_batch(k);
     for (SweepSet* W : g->sweep_cache)
         if (W->groups == groups && W->batch_len == batch_len && W->per_bin == per_bin) { *out = W; return MAXK_OK; }
-    if (existing_only)
+    if (existing_only || g->sweep_cache.size() >= kSweepTables)
         for (SweepSet* W : g->sweep_cache)
             if (W->groups == groups && W->batch_len == batch_len && sweep_waves(k, W->per_bin, dim) >= 4) { *out = W; return MAXK_OK; }
     const RefusedKey key = {kRefusedSweep, groups, batch_len, per_bin};
-    if (existing_only || is_refused(g, key)) return MAXK_UNSUPPORTED;
+    if (existing_only || g->sweep_cache.size() >= 2 * kSweepTables || is_refused(g, key)) return MAXK_UNSUPPORTED;
     SweepSet* W = new (std::nothrow) SweepSet();
     maxk_status st = MAXK_OUT_OF_MEMORY;
     if (W && !denied(g, g->nnz * 8)) {

@@ -211,3 +211,23 @@ def test_pull_by_units(monkeypatch, k, dim, ib, fmt):
     torch.cuda.synchronize()
     assert (np.abs(dXs.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all(), (k, dim, fmt)
     gr.destroy()
+
+
+# the widest rows a bin is built for are those of the first call; orders in which later widths can share it, and cannot
+@pytest.mark.parametrize("widths,most", [((256, 128, 64), 4), ((512, 200, 100, 50), 4), ((64, 128, 256, 512), 8)])
+def test_a_handle_holds_few_regrouped_copies(monkeypatch, widths, most):
+    monkeypatch.setenv("MAXK_FWD_SWEEP", "2")
+    N, rowptr, col, val = _graph(3)
+    gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val))
+    for dim in widths:
+        for k in (8, 16, 24, 32, 33, 64, 96, 128):
+            if k > dim:
+                continue
+            H = synth.normal_matrix(N, dim, k)
+            data, index = oracle.topk_cbsr(H, k)
+            Y = torch.full((N, dim), float("nan"), device="cuda")
+            maxk.maxk_spgemm_fwd(gr, to_dev(data), torch.from_numpy(index.astype(np.int16)).cuda(), dim, Y)
+            ref, refabs = oracle.spgemm_fwd(rowptr, col, val, data, index, dim)
+            assert (np.abs(Y.cpu().numpy() - ref) <= 1e-5 * refabs + 1e-6).all(), (dim, k)
+    assert 4 <= gr.sweep_tables() <= most
+    gr.destroy()
