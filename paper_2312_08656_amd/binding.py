@@ -9,7 +9,7 @@ import torch
 
 _HERE = Path(__file__).resolve().parent
 _LIB: Optional[ctypes.CDLL] = None
-# The same calls marshalled in C++ (csrc/torch_calls.cpp): each says whether it was made; what it leaves is made here, checks and errors
+# The same calls marshalled in C++ (csrc/torch_calls.cpp): each says whether it was made, or raises; what it leaves is made here, checks and errors
 # included.  None: not built for this torch, and every call is made here.
 _FAST = None
 
@@ -116,7 +116,7 @@ def _load_fast(lib: ctypes.CDLL) -> None:
         return
     _torch_calls.bind([ctypes.cast(f, ctypes.c_void_p).value for f in (
         lib.maxk_topk_cbsr_narrow, lib.maxk_spgemm_fwd_narrow, lib.maxk_spgemm_fwd_noalloc, lib.maxk_sspmm_bwd_narrow,
-        lib.maxk_cbsr_scatter)])
+        lib.maxk_cbsr_scatter)], _check)
     _FAST = _torch_calls
 
 

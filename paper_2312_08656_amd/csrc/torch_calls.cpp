@@ -4,10 +4,12 @@
 // Bound by the host on small graphs: a call took 4.8 to 5.1 us from Python, 1.2 of them checks and 0.8 ctypes, an empty tensor 1.5, and
 // the backward half of a pass runs in a thread of its own, where the same Python is slower still.
 //
-// Every function returns false (None) on anything but plain device tensors of the shapes and types that the call takes, and on a status
-// other than MAXK_OK; binding.py then makes the call itself, which raises what is to be raised.
+// Every function returns false (None) on anything but plain device tensors of the shapes and types that the call takes; binding.py then makes
+// the call itself, which raises what is to be raised.  A call that was made and failed is not made again: its status goes to binding.py's check.
 #include <c10/hip/HIPStream.h>
 #include <torch/extension.h>
+
+#include <utility>
 
 #include "../../include/maxk.h"
 
@@ -19,7 +21,9 @@ decltype(&maxk_spgemm_fwd_noalloc) forward_noalloc_call;
 decltype(&maxk_sspmm_bwd_narrow) backward_call;
 decltype(&maxk_cbsr_scatter) scatter_call;
 
-void bind(const std::vector<uintptr_t>& at)
+PyObject* check;  // (status, name of the call): raises; held for good
+
+void bind(const std::vector<uintptr_t>& at, const py::function& raise)
 {
     TORCH_CHECK(at.size() == 5, "five addresses");
     topk_call = reinterpret_cast<decltype(topk_call)>(at[0]);
@@ -27,6 +31,7 @@ void bind(const std::vector<uintptr_t>& at)
     forward_noalloc_call = reinterpret_cast<decltype(forward_noalloc_call)>(at[2]);
     backward_call = reinterpret_cast<decltype(backward_call)>(at[3]);
     scatter_call = reinterpret_cast<decltype(scatter_call)>(at[4]);
+    Py_XDECREF(std::exchange(check, py::function(raise).release().ptr()));
 }
 
 // The tensor in `x`, where it is a plain one in device memory: no subclass with a dispatch of its own, no functorch wrapper
@@ -72,10 +77,15 @@ void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
 maxk_graph* graph(uintptr_t g) { return reinterpret_cast<maxk_graph*>(g); }
 
 template <typename F>
-bool ok(F&& call)
+bool made(const char* what, F&& call)  // call() may change `what` to the call that failed
 {
-    py::gil_scoped_release released;  // a first call may build tables
-    return call() == MAXK_OK;
+    maxk_status st;
+    {
+        py::gil_scoped_release released;  // a first call may build tables
+        st = call(what);
+    }
+    if (st != MAXK_OK) py::reinterpret_borrow<py::function>(check)(st, what);
+    return true;
 }
 
 bool topk(const py::handle& H_, int64_t k, const py::handle& data_, const py::handle& index_, bool narrow)
@@ -85,7 +95,7 @@ bool topk(const py::handle& H_, int64_t k, const py::handle& data_, const py::ha
     const int64_t N = H->size(0), dim = H->size(1);
     const at::Tensor *data = matrix(data_, N, k), *index = matrix(index_, N, k);
     if (!data || !index || !takes(*data, narrow) || !index_bytes(*index)) return false;
-    return ok([&, s = stream()] {
+    return made(narrow ? "maxk_topk_cbsr_narrow" : "maxk_topk_cbsr", [&, s = stream()](const char*) {
         return topk_call(static_cast<const float*>(H->data_ptr()), N, (int32_t)dim, (int32_t)k, data->data_ptr(), value_type(*data), index->data_ptr(),
                          index_bytes(*index), s);
     });
@@ -98,7 +108,7 @@ bool forward(uintptr_t g, int64_t N, const py::handle& data_, const py::handle& 
     const int64_t k = data->size(1);
     const at::Tensor* index = matrix(index_, N, k);
     if (!index || !index_bytes(*index)) return false;
-    return ok([&, s = stream()] {
+    return made(narrow ? "maxk_spgemm_fwd_narrow" : "maxk_spgemm_fwd", [&, s = stream()](const char*) {
         return forward_call(graph(g), data->data_ptr(), value_type(*data), index->data_ptr(), index_bytes(*index), (int32_t)dim, (int32_t)k,
                             static_cast<float*>(Y->data_ptr()), s);
     });
@@ -111,7 +121,7 @@ bool forward_noalloc(uintptr_t g, int64_t N, const py::handle& data_, const py::
     const int64_t k = data->size(1);
     const at::Tensor* index = matrix(index_, N, k);
     if (!index || !index_bytes(*index)) return false;
-    return ok([&, s = stream()] {
+    return made("maxk_spgemm_fwd_noalloc", [&, s = stream()](const char*) {
         return forward_noalloc_call(graph(g), static_cast<const float*>(data->data_ptr()), index->data_ptr(), index_bytes(*index), (int32_t)dim,
                                     (int32_t)k, static_cast<float*>(Y->data_ptr()), s);
     });
@@ -124,7 +134,7 @@ bool backward(uintptr_t g, int64_t N, const py::handle& dY_, const py::handle& i
     const int64_t k = index->size(1);
     const at::Tensor* dXs = matrix(dXs_, N, k);
     if (!dXs || dXs->scalar_type() != at::kFloat) return false;
-    return ok([&, s = stream()] {
+    return made(narrow ? "maxk_sspmm_bwd_narrow" : "maxk_sspmm_bwd", [&, s = stream()](const char*) {
         return backward_call(graph(g), dY->data_ptr(), value_type(*dY), index->data_ptr(), index_bytes(*index), (int32_t)dY->size(1), (int32_t)k,
                              static_cast<float*>(dXs->data_ptr()), s);
     });
@@ -137,7 +147,7 @@ bool scatter(const py::handle& values_, const py::handle& index_, const py::hand
     const int64_t N = values->size(0), k = values->size(1);
     const at::Tensor *index = matrix(index_, N, k), *dense = matrix(dense_, N, -1);
     if (!index || !dense || !index_bytes(*index) || dense->scalar_type() != at::kFloat) return false;
-    return ok([&, s = stream()] {
+    return made("maxk_cbsr_scatter", [&, s = stream()](const char*) {
         return scatter_call(static_cast<const float*>(values->data_ptr()), index->data_ptr(), index_bytes(*index), N, (int32_t)dense->size(1), (int32_t)k,
                             static_cast<float*>(dense->data_ptr()), s);
     });
@@ -160,14 +170,13 @@ py::object aggregate_forward(uintptr_t g, int64_t N, const py::handle& H_, int64
     } catch (const c10::Error&) {  // no memory: said by the calls from Python
         return py::none();
     }
-    const bool done = ok([&, s = stream()] {
+    made("maxk_topk_cbsr", [&, s = stream()](const char*& what) {
         const maxk_status st = topk_call(static_cast<const float*>(H->data_ptr()), N, (int32_t)dim, (int32_t)k, data.data_ptr(), MAXK_VALUE_F32,
                                          index.data_ptr(), ib, s);
-        return st != MAXK_OK ? st
-                             : forward_call(graph(g), data.data_ptr(), MAXK_VALUE_F32, index.data_ptr(), ib, (int32_t)dim, (int32_t)k,
-                                            static_cast<float*>(Y.data_ptr()), s);
+        if (st != MAXK_OK) return st;
+        what = "maxk_spgemm_fwd";
+        return forward_call(graph(g), data.data_ptr(), MAXK_VALUE_F32, index.data_ptr(), ib, (int32_t)dim, (int32_t)k, static_cast<float*>(Y.data_ptr()), s);
     });
-    if (!done) return py::none();
     return py::make_tuple(Y, index);
 }
 
@@ -184,14 +193,13 @@ py::object aggregate_backward(uintptr_t g, int64_t N, const py::handle& dY_, con
     } catch (const c10::Error&) {
         return py::none();
     }
-    const bool done = ok([&, s = stream()] {
+    made("maxk_sspmm_bwd", [&, s = stream()](const char*& what) {
         const maxk_status st = backward_call(graph(g), dY->data_ptr(), MAXK_VALUE_F32, index->data_ptr(), ib, (int32_t)dim, (int32_t)k,
                                              static_cast<float*>(dXs.data_ptr()), s);
-        return st != MAXK_OK ? st
-                             : scatter_call(static_cast<const float*>(dXs.data_ptr()), index->data_ptr(), ib, N, (int32_t)dim, (int32_t)k,
-                                            static_cast<float*>(dH.data_ptr()), s);
+        if (st != MAXK_OK) return st;
+        what = "maxk_cbsr_scatter";
+        return scatter_call(static_cast<const float*>(dXs.data_ptr()), index->data_ptr(), ib, N, (int32_t)dim, (int32_t)k, static_cast<float*>(dH.data_ptr()), s);
     });
-    if (!done) return py::none();
     return py::cast(dH);
 }
 

@@ -9,6 +9,7 @@ from paper_2312_08656_amd import binding
 def _both(monkeypatch, call):
     """What `call` gives with either marshalling: a value, or the text of its MaxKError."""
     got = []
+    assert binding._FAST is not None, "built with the library"
     for fast in (binding._FAST, None):
         monkeypatch.setattr(binding, "_FAST", fast)
         try:
@@ -28,6 +29,33 @@ def test_host_tensors_are_refused_alike(monkeypatch):
         assert isinstance(fast, str) and fast == slow
 
 
+class _Counted:
+    """The module, and which of its calls were made (True, or a value) and which were left to Python (False or None)."""
+
+    def __init__(self, module):
+        self.module, self.made, self.left = module, [], []
+
+    def __getattr__(self, name):
+        def call(*args):
+            got = getattr(self.module, name)(*args)
+            (self.left if got is None or got is False else self.made).append(name)
+            return got
+
+        return call
+
+
+def _counted(monkeypatch, call):
+    counted = _Counted(binding._FAST)
+    monkeypatch.setattr(binding, "_FAST", counted)
+    try:
+        call()
+    except maxk.MaxKError:
+        pass
+    finally:
+        monkeypatch.undo()
+    return counted.made, counted.left
+
+
 def _case(N=300, dim=40, k=8, seed=1):
     gen = torch.Generator(device="cuda").manual_seed(seed)
     degree = torch.randint(0, 40, (N,), generator=gen, device="cuda")
@@ -45,7 +73,6 @@ def _case(N=300, dim=40, k=8, seed=1):
 def test_calls_give_the_same_bits(monkeypatch, dtype, index):
     g, H, dY = _case()
     N, dim, k = 300, 40, 8
-    assert binding._FAST is not None, "built with the library"
 
     def chain():
         data, cols = torch.empty(N, k, dtype=dtype, device="cuda"), torch.empty(N, k, dtype=index, device="cuda")
@@ -67,6 +94,65 @@ def test_calls_give_the_same_bits(monkeypatch, dtype, index):
 
     fast, slow = _both(monkeypatch, chain)
     assert all(torch.equal(a, b) for a, b in zip(fast, slow))
+    noalloc = ["forward_noalloc"] if dtype == torch.float32 else []
+    assert _counted(monkeypatch, chain) == (["topk", "forward", *noalloc, "backward", "scatter"], [])
+    g.destroy()
+
+
+@pytest.mark.gpu
+def test_calls_go_to_the_current_stream():
+    # some 10 ms of work, then H, on a side stream; nothing waits before the calls
+    N, dim, k = 20_000, 256, 16
+    g, H, dY = _case(N=N, dim=dim)
+    data, cols = torch.empty(N, k, device="cuda"), torch.empty(N, k, dtype=torch.uint8, device="cuda")
+    Y, late = torch.empty(N, dim, device="cuda"), torch.zeros(N, dim, device="cuda")
+    dXs, dH = torch.empty(N, k, device="cuda"), torch.empty(N, dim, device="cuda")
+    busy = torch.randn(8192, 8192, device="cuda")
+    side = torch.cuda.Stream()
+
+    def chain():
+        maxk.maxk_topk_cbsr(late, k, data, cols)
+        maxk.maxk_spgemm_fwd(g, data, cols, dim, Y)
+        maxk.maxk_sspmm_bwd(g, late, cols, dXs)
+        maxk.maxk_cbsr_scatter(dXs, cols, dH)
+        return Y.clone(), dH.clone(), binding.aggregate_forward(g, late, k, 1)[0], binding.aggregate_backward(g, late, cols, dim, k)
+
+    late.copy_(H)
+    want = chain()
+    torch.cuda.synchronize()
+    late.zero_()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        for _ in range(2):
+            torch.mm(busy, busy)
+        late.copy_(H)
+        got = chain()
+    side.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+    g.destroy()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fast", [True, False])
+def test_a_call_that_fails_is_made_once(monkeypatch, fast):
+    # a width above the largest is refused by the library itself, and by it alone
+    N, dim, k = 30, 1025, 8
+    g, _, _ = _case(N=N, dim=40)
+    H = torch.zeros(N, dim, device="cuda")
+    data, cols = torch.zeros(N, k, device="cuda"), torch.zeros(N, k, dtype=torch.int16, device="cuda")
+    dXs, dH = torch.zeros(N, k, device="cuda"), torch.zeros(N, dim, device="cuda")
+    calls = [("maxk_topk_cbsr", lambda: maxk.maxk_topk_cbsr(H, k, data, cols)), ("maxk_spgemm_fwd", lambda: maxk.maxk_spgemm_fwd(g, data, cols, dim, H)),
+             ("maxk_spgemm_fwd_narrow", lambda: maxk.maxk_spgemm_fwd_narrow(g, data.bfloat16(), cols, dim, H)),
+             ("maxk_sspmm_bwd", lambda: maxk.maxk_sspmm_bwd(g, H, cols, dXs)), ("maxk_topk_cbsr", lambda: binding.aggregate_forward(g, H, k, 2)),
+             ("maxk_sspmm_bwd", lambda: binding.aggregate_backward(g, H, cols, dim, k))]
+    if not fast:
+        monkeypatch.setattr(binding, "_FAST", None)
+    else:
+        monkeypatch.setattr(binding, "_dev", lambda *_: pytest.fail("made again from Python"))
+    for name, call in calls:
+        with pytest.raises(maxk.MaxKError, match=rf"^{name}: .* \(status -2, hipError -?\d+\)$"):
+            call()
+    monkeypatch.undo()
     g.destroy()
 
 
@@ -82,6 +168,7 @@ def test_aggregation_gives_the_same_bits_and_refusals(monkeypatch):
     for h, grad in ((H, dY), (H.t().contiguous().t(), dY), (H, dY.t().contiguous().t())):  # copies where rows are not together
         fast, slow = _both(monkeypatch, lambda: step(h, 16, grad))
         assert all(torch.equal(a, b) for a, b in zip(fast, slow))
+        assert _counted(monkeypatch, lambda: step(h, 16, grad)) == (["aggregate_forward", "aggregate_backward"], [])
     for call in (lambda: step(H, 301, dY), lambda: step(H.double(), 16, dY.double()), lambda: step(H[:299], 16, dY[:299])):
         fast, slow = _both(monkeypatch, call)
         assert isinstance(fast, str) and fast == slow
@@ -105,4 +192,6 @@ def test_calls_refuse_alike(monkeypatch):
     for call in calls:
         fast, slow = _both(monkeypatch, call)
         assert isinstance(fast, str) and fast == slow
+        made, left = _counted(monkeypatch, call)
+        assert not made and len(left) == 1
     g.destroy()
