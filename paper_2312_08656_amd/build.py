@@ -38,8 +38,22 @@ def build_torch_calls(verbose: bool = False) -> None:
            str(CSRC / "torch_calls.cpp"), f"-L{home}/lib", "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", "-ltorch_hip", "-o", str(tmp)]
     if verbose:
         print(" ".join(cmd), flush=True)
-    subprocess.check_call(cmd)
-    os.replace(tmp, TORCH_CALLS)
+    try:
+        subprocess.check_call(cmd)
+        os.replace(tmp, TORCH_CALLS)
+    finally:
+        tmp.unlink(missing_ok=True)
+
+
+def try_torch_calls(verbose: bool = False) -> bool:
+    """build_torch_calls where the host has a compiler and torch's headers; without the module every call is marshalled in Python."""
+    try:
+        build_torch_calls(verbose)
+        return True
+    except (OSError, subprocess.CalledProcessError) as e:
+        TORCH_CALLS.unlink(missing_ok=True)  # (one of another build may not fit this library)
+        print(f"{TORCH_CALLS.name} not built, calls are marshalled in Python: {e}", file=sys.stderr, flush=True)
+        return False
 
 
 def build(verbose: bool = False) -> Path:
@@ -58,7 +72,7 @@ def build(verbose: bool = False) -> Path:
         return obj
 
     with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 4)) as ex:
-        calls = ex.submit(build_torch_calls, verbose)
+        calls = ex.submit(try_torch_calls, verbose)
         objs = list(ex.map(compile_one, SOURCES))
         calls.result()
     tmp = LIB.with_suffix(".so.tmp%d" % os.getpid())

@@ -3,7 +3,7 @@ import pytest
 import torch
 
 import paper_2312_08656_amd as maxk
-from paper_2312_08656_amd import binding
+from paper_2312_08656_amd import binding, build
 
 
 def _both(monkeypatch, call):
@@ -18,6 +18,17 @@ def _both(monkeypatch, call):
             got.append(str(e))
         monkeypatch.undo()
     return got
+
+
+def test_the_library_builds_without_a_host_compiler(monkeypatch, tmp_path, capfd):
+    # (the module is optional; one of an earlier build does not stay behind)
+    old = tmp_path / "_torch_calls.so"
+    old.write_bytes(b"of an earlier build")
+    monkeypatch.setattr(build, "TORCH_CALLS", old)
+    for compiler in ("/nowhere/c++", "false"):
+        monkeypatch.setenv("CXX", compiler)
+        assert not build.try_torch_calls()
+        assert list(tmp_path.iterdir()) == [] and "_torch_calls.so not built" in capfd.readouterr().err
 
 
 def test_host_tensors_are_refused_alike(monkeypatch):
