@@ -67,6 +67,34 @@ def check_sums(gr):
     assert longest == 0 or longest_sum(gr) <= longest
 
 
+def check_steps(gr):
+    """The step loop played back: what is copied into a buffer while it may still be read, and where a step's entries look for their rows.
+
+    In step s the rows of step s + 2 are on their way, those of s + 1 may have landed, and other wavefronts still read those of s: each of the
+    three has a buffer of its own, or the same rows (a tile with long lists).  Past the end of a unit the steps of the next one follow."""
+    t = sizes(gr)
+    tile, steps = t["rows"] * WAVES, t["n_steps"]
+    head = table(gr, 2, np.uint32).reshape(steps + SPARE_STEPS, WAVES, t["words"])
+    buffer, rows = head[..., 1] >> 8, head[..., 2: 2 + t["rows"]]
+    assert (buffer == buffer[:, :1]).all()
+    for ahead in (1, 2):
+        same = buffer[:-ahead, 0] == buffer[ahead:, 0]
+        same[max(0, steps - ahead):] = False  # (a buffer that is no longer read)
+        at = np.flatnonzero(same)
+        assert (rows[at] == rows[at + ahead]).all()
+    # the records of a list, in the order of the steps: inside the rows of the step's own buffer
+    batch = 1 if t["kr"] == 2 else 2 if t["groups"] == 1 else 4
+    first, n = head[:steps, :, 0].astype(np.int64), (head[:steps, :, 1] & 0xFF).astype(np.int64) * batch
+    start = first[n > 0]  # (lists do not overlap: check_ranges)
+    which = np.broadcast_to(buffer[:steps], n.shape)[n > 0]
+    order = np.argsort(start)
+    edge = np.repeat(which[order].astype(np.int8), n[n > 0][order])
+    record = table(gr, 1, np.uint32).reshape(-1, 4)
+    for half in (0, 2):
+        real = (record[:, half] & 0xFF) < t["slots"] * t["kr"]  # (padding reads any row, for an accumulator that nobody stores)
+        assert (((record[:, half] >> 8) // (t["pitch"] // 256) // tile == edge) | ~real).all()
+
+
 def check_ranges(gr, N, k):
     t = sizes(gr)
     groups, kr, slots = t["groups"], t["kr"], t["slots"]
@@ -101,6 +129,7 @@ def check_ranges(gr, N, k):
     assert (np.sort(row[row >= N] - N) == np.arange(split[:, 2].max(initial=0))).all()
 
     check_sums(gr)
+    check_steps(gr)
 
     unit, part = table(gr, 5, np.int32).reshape(-1, 5), table(gr, 6, np.int32).reshape(-1, 4)
     at = part.view(np.int64)[:, 1] if len(part) else np.zeros(0, np.int64)
