@@ -1021,7 +1021,7 @@ bool fwd_uses_packed(const maxk_graph* g, int k, int index_bytes, int val_bytes)
 // several times an L2, the bins fill the chip (256 CUs x 16 wavefronts), and a bin has enough entries for its padding to whole
 // batches and its copies of the rows.  The lines are drawn by lane groups and row size where both sides were measured, over 11 graphs of
 // 30 k to 2 M nodes, average degree 15 to 500, k 8 to 128, widths 64 to 512 (profiles/forward_sweep_rule_over_graphs.txt: the kernel
-// taken is 0.4 % above the better one on average, 16 % at most, row by row 16 %); us, row by row / sweep (MB: of the CBSR; entries: of a lane group):
+// taken is 0.2 % above the better one on average, 13 % at most, row by row 16 % on average); us, row by row / sweep (MB: of the CBSR; entries: of a lane group):
 //   8 groups: k = 8, 8.5 MB, 75 entries 678 / 641, 9.6 MB, 61 entries 709 / 652, 38 entries 337 / 372; k = 12 behind everywhere
 //   4 groups: k = 16, 13 MB, 150 entries 509 / 400, 32 MB, 60 entries 512 / 504, 77 MB, 31 entries 604 / 610; k = 50, 63 MB, 60 entries 1103 / 1025
 //   2 groups: k = 32, 16 MB, 752 entries 610 / 374, 102 entries 78 / 82, 96 MB, 40 entries 236 / 228; dim 512, 48 MB, 26 entries 220 / 264;
@@ -1171,7 +1171,9 @@ bool pull_by_units(const maxk_graph* g, int dim, int k, int val_bytes)
     return pull_by_units(dim, k, val_bytes, g->N, g->nnz, 1.0 - hot_share(g, 4e6 / ((double)dim * val_bytes)));
 }
 
-// The two forms of the pull over CSC, in seconds (see auto_bwd_mode for where the figures come from).
+// The two forms of the pull over CSC, in seconds (see auto_bwd_mode for where the figures come from).  Whole rows are priced as the kernels by
+// units take them; by lane groups (pull_by_units) they take down to 0.4 of that where the rows sit in L2, so that another kernel may be taken where
+// they would be faster: 10 k nodes, degree 300, width 200, k = 24: sliced 139 us, whole rows by units 153, by lane groups 106.
 // Plain: a line costs 5 ps when its row sits in L2 (4 MB of the most frequent rows), 17 ps when it does not; below that
 // the gather's own instructions (12 + 0.55 k ps an entry).  One wavefront walks an item of at most `chunk` entries, 4 loads
 // at a time and 0.6 us a round: the tail of small graphs.
@@ -1201,8 +1203,8 @@ PullCost pull_cost(const maxk_graph* g, int dim, int k, int val_bytes, const voi
 
 // Backward kernel choice when the caller leaves it to the library: the lowest of five cost models, fitted on MI355X to
 // 153 shapes (R-MAT and uniform graphs of 4 thousand to 1 million nodes, average degree 12 to 400; widths 64 to 512;
-// k 8 to 128; fp32 and 16-bit dY) and the benchmark graphs.  Over those shapes the chosen kernel takes 5 % longer than
-// the best one on average (profiles/backward_choice_over_shapes.txt; the largest misses, 2 times, are 16-bit dY on
+// k 8 to 128; fp32 and 16-bit dY) and the benchmark graphs.  Over those shapes the chosen kernel took 5 % longer than
+// the best one on average with the kernels before pull by lane groups and tiles of 8 rows (profiles/backward_choice_over_shapes.txt; the largest misses, 2 times, are 16-bit dY on
 // 60 k nodes of degree 240, where hub visits end the launches of slab pull later than the model has it).  The lines of expand/reduce
 // and slab pull were fitted before product rows passed by L2 and long visits began a launch, and run high for both now: pull is
 // taken on 42 k nodes, 3.3 M entries, k = 32 (243 us, expand/reduce 191), 40 k, 1.6 M, k = 32 (136 / 100), 118 k, 1.7 M, k = 64

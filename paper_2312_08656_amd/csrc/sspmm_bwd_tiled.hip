@@ -4,7 +4,7 @@
 // columns fall into: about 1 KB of 128-byte lines per entry at hidden width 256 for 4k useful bytes, and the L2 -> L1
 // path (64 bytes per clock per CU) is what they wait for.  This kernel turns the traffic round: a workgroup OWNS a set
 // of D destination nodes, keeps their D x k accumulators in LDS for its whole life, and streams the source rows of dY
-// through LDS in tiles of 16 rows with full, coalesced 16-byte loads.  A tile is used by every entry (i -> j) with i in
+// through LDS in tiles of 16 rows (8 where the adjacency is dense: tiled_shape) with full, coalesced 16-byte loads.  A tile is used by every entry (i -> j) with i in
 // the tile and j in the set, so a row of dY is fetched once per destination set instead of once per entry:
 // (N / D) * N * dim * 4 bytes in all.  The sampled reads dY[i, sp_index[j, t]] and the read-add-write of the accumulators
 // are LDS traffic.  The workgroups of an XCD that sweep the same source range (a "pack") are kept within a few dozen
@@ -996,7 +996,8 @@ maxk_status launch_bwd_tiled(const TiledSet& T, const void* dY, int value_type, 
     }
     a.progress = T.d_progress;
     // Pacing window: 32 tiles (0.5 MB of dY at hidden width 256) measured best of 16..256 on the dense workload at
-    // k = 8, 16, 32: 3-5 % faster than without pacing, with a quarter of the L2 fills.  Calls that run at the same
+    // k = 8, 16, 32: 3-5 % faster than without pacing, with a quarter of the L2 fills.  Tiles of 8 rows, half as many bytes, 32 / 64 tiles: 12 k
+    // nodes, 24 M entries, k = 8 134 / 131 us, 20 k, 60 M, k = 16 518 / 513.  Calls that run at the same
     // time on one handle share the marks; that can only make them nap at the wrong moments.
     // Only when every workgroup has a CU from the start (256 CUs): otherwise the running ones are not one pack.
     // And only where a workgroup has more tiles than it may lead by.

@@ -1,7 +1,7 @@
 """The LDS-tiled backward kernel where visits have more than three entries: the rest is added bucket by bucket, eight under way together.
 
 Column j of the adjacency is filled to j / N, so that the buckets (one destination each here) hold every number of entries from none to
-about 100 (tiles of 8 rows), or to 0.15 j / N (tiles of 16).
+45 (tiles of 8 rows, at most nine of them in a range of the sources, five entries each beyond the third), or to 0.15 j / N (tiles of 16).
 """
 import numpy as np
 import pytest
