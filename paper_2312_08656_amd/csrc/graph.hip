@@ -1171,6 +1171,10 @@ bool pull_by_units(const maxk_graph* g, int dim, int k, int val_bytes)
     return pull_by_units(dim, k, val_bytes, g->N, g->nnz, 1.0 - hot_share(g, 4e6 / ((double)dim * val_bytes)));
 }
 
+// The same of the destinations that the register-tiled kernel leaves, with fewest in-entries: nothing that wavefronts could keep together over
+// (2.4 M nodes, k = 64, a whole pass: 12.24 ms by units, 11.96 by lane groups).
+bool pull_tail_by_units(const maxk_graph* g, int dim, int k, int val_bytes) { return k <= 32 && pull_by_units(dim, k, val_bytes, g->N, g->nnz, 0.0); }
+
 // The two forms of the pull over CSC, in seconds (see auto_bwd_mode for where the figures come from).  Whole rows are priced as the kernels by
 // units take them; by lane groups (pull_by_units) they take down to 0.4 of that where the rows sit in L2, so that another kernel may be taken where
 // they would be faster: 10 k nodes, degree 300, width 200, k = 24: sliced 139 us, whole rows by units 153, by lane groups 106.
@@ -1812,7 +1816,7 @@ MAXK_API maxk_status maxk_sspmm_bwd_narrow(maxk_graph* g, const void* d_dY, int3
         rest.d_items += rest.n_items - tail;
         rest.n_items = tail;
         rest.n_split = rest.n_slots = 0;
-        return launch_bwd_pull(rest, g->d_csc_src, g->d_csc_val, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, pull_by_units(g, dim, k, vb), d_dXs,
+        return launch_bwd_pull(rest, g->d_csc_src, g->d_csc_val, d_dY, value_type, d_sp_index, index_bytes, g->N, dim, k, pull_tail_by_units(g, dim, k, vb), d_dXs,
                                g->d_partials, s);
     }
     if (plan.mode == MAXK_BWD_TILED)
