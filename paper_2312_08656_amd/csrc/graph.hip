@@ -1149,11 +1149,12 @@ double lines_touched(int dim, int k, int val_bytes)
 // Whether the pull of whole rows works by units (bwd_pull_small_kernel, _wide_kernel), not by lane groups; `beyond`: share of the entries whose row is
 // not among the most frequent 4 MB of them.  By lane groups an entry takes a third of the instructions; but the faster a wavefront walks its entries,
 // the less the wavefronts keep together on their way over the sources, and rows that they shared in an L2 come from beyond it instead (8 k nodes, 0.8 M
-// entries, rows of 2 KB, k = 32: 219 / 463 MB fetched, 8.8 / 4.1 M hits, 80 / 130 us).  So units are taken where an entry's lines, most of them from
+// entries, rows of 2 KB, k = 32: 0.45 / 0.95 GB fetched, 8.8 / 4.1 M hits, 80 / 130 us).  So units are taken where an entry's lines, most of them from
 // beyond L2, weigh more than its instructions.  us, units / lane groups, rows of 4-byte elements but *: k = 16, 8 k nodes, degree 101, 1 KB 37 / 49; 20 k, 61, 1 KB
 // 73 / 82; 100 k, 61, 512 bytes* 289 / 319; 40 k, 31, 400 bytes (k = 13) 51 / 49; 300 k, 61, 256 bytes* (k = 12) 475 / 544; 300 k, 17, 256 bytes 167 / 132; k = 24, 8 k,
 // 501, 2 KB 301 / 516; 60 k, 201, 768 bytes* 663 / 793; k = 64, 14 k, 29, 1 KB 35 / 46; 150 k, 121, 1 KB 1704 / 2157; 20 k, 61, 1 KB 125 / 90; k = 100, 12 k, 101,
-// 2 KB 187 / 252; k = 128, 100 k, 61, 2 KB 1623 / 1437.  Over 966 such calls the kernel taken is 0.5 % above the better one on average, lane groups everywhere 4.2 %.
+// 2 KB 187 / 252; k = 128, 100 k, 61, 2 KB 1623 / 1437.  Over 966 such calls the kernel taken is 0.6 % above the better one on
+// average, 16 % at most, lane groups everywhere 4.3 and 74 % (profiles/pull_by_units_and_by_lane_groups.txt).
 // (16 < k <= 32 and a dY of several L2s together: 100 k nodes, degree 100 1043 / 1094, 169 k, 14 343 / 353, 1 M, 15 2361 / 2410.)
 bool pull_by_units(int dim, int k, int val_bytes, int64_t N, int64_t nnz, double beyond)
 {
