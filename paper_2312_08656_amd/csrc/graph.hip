@@ -1021,12 +1021,14 @@ bool fwd_uses_packed(const maxk_graph* g, int k, int index_bytes, int val_bytes)
 // several times an L2, the bins fill the chip (256 CUs x 16 wavefronts), and a bin has enough entries for its padding to whole
 // batches and its copies of the rows.  The lines are drawn by lane groups and row size where both sides were measured, over 11 graphs of
 // 30 k to 2 M nodes, average degree 15 to 500, k 8 to 128, widths 64 to 512 (profiles/forward_sweep_rule_over_graphs.txt: the kernel
-// taken is 0.2 % above the better one on average, 13 % at most, row by row 16 % on average); us, row by row / sweep (MB: of the CBSR; entries: of a lane group):
-//   8 groups: k = 8, 8.5 MB, 75 entries 678 / 641, 9.6 MB, 61 entries 709 / 652, 38 entries 337 / 372; k = 12 behind everywhere
-//   4 groups: k = 16, 13 MB, 150 entries 509 / 400, 32 MB, 60 entries 512 / 504, 77 MB, 31 entries 604 / 610; k = 50, 63 MB, 60 entries 1103 / 1025
-//   2 groups: k = 32, 16 MB, 752 entries 610 / 374, 102 entries 78 / 82, 96 MB, 40 entries 236 / 228; dim 512, 48 MB, 26 entries 220 / 264;
-//     bf16 values 77 MB, 152 entries 640 / 588, 32 MB, 301 entries 351 / 356; k = 96, 14 MB, 149 entries 60 / 58, 346 MB, 24 entries 674 / 733
-//   1 group: k = 64, 19 MB, 755 entries 310 / 264, 9.6 MB, 298 entries 53 / 79, 192 MB, 80 entries 569 / 512; k = 128, 23 MB, 298 entries 187 / 171
+// taken is 0.3 % above the better one on average, 15 % at most, row by row 12 %, the sweep 9 % on average); us, row by row / sweep (MB: of the CBSR; entries: of a lane group):
+//   8 groups: k = 8, 9.6 MB, 61 entries 715 / 649, 6.4 MB, 38 entries 275 / 290
+//   4 groups: k = 16, 13 MB, 150 entries 433 / 332, 32 MB, 60 entries 406 / 398, 128 MB, 26 entries 2389 / 2378 (bf16), 256 MB, 26 entries 2426 / 2527;
+//     k = 50, 62 MB, 60 entries 1603 / 1532, 25 MB, 20 entries 181 / 200
+//   2 groups: k = 32, 40 MB, 301 entries 734 / 593, 16 MB, 102 entries 84 / 87, 96 MB, 40 entries 308 / 296; dim 512, 115 MB, 20 entries 396 / 471;
+//     bf16 values 77 MB, 152 entries 707 / 669, 32 MB, 301 entries 418 / 432; k = 96, 14 MB, 149 entries 85 / 83, 346 MB, 27 entries 762 / 805
+//   1 group: k = 64, 19 MB, 755 entries 297 / 255, bf16 19 MB, 205 entries 104 / 115, 192 MB, 80 entries 456 / 403; k = 128, dim 512, 77 MB, 205 entries
+//     360 / 289, 23 MB, 298 entries 108 / 127
 int sweep_rows(const maxk_graph* g, int dim, int k, int index_bytes, int val_bytes)
 {
     if (!sweep_takes(k) || dim > 512 || g->N > (1 << kSweepRowShift) || g->nnz == 0 || g->fwd_sweep == 1) return 0;
