@@ -227,10 +227,12 @@ constexpr FwdGroups fwd_groups(int k)
 // Whether the row-by-row kernel works by units (spgemm_fwd_rmw_kernel).  k = 17 to 21 by lane groups has eight copies of a row to clear and to
 // add up, by units five: more than it gains where rows are wide and items short.  us, by units / lane groups, fp32: 60 k nodes, degree 16, width
 // 256 k = 17 48.4 / 44.6, 384 50.4 / 53.6, 512 60.8 / 71.2; 40 k, 31, width 1024 123 / 151; 1 M, 9, width 384 834 / 893; 300 k, 31, width 512
-// 484 / 513; 100 k, 61, width 512 226 / 200, 1024 401 / 433.  bf16: 60 k, 16, width 384 61.3 / 61.5, 512 71.9 / 79.4; 1 M, 9, width 384 916 / 867.
+// 484 / 513; 100 k, 61, width 512 226 / 200, 1024 401 / 433.  bf16: 60 k, 16, width 384 61.3 / 61.5, 512 71.9 / 79.4; 1 M, 9, width 384 916 / 867;
+// 300 k, 31, width 512 456 / 413; 40 k, 31, width 1024 136 / 145.
 constexpr bool fwd_by_units(int k, int dim, int val_bytes, int64_t items, int64_t entries)
 {
-    return !fwd_groups(k).lanes || (k >= 17 && k <= 21 && dim > (val_bytes == 4 ? 256 : 384) && entries * 9 < items * dim);
+    return !fwd_groups(k).lanes ||
+           (k >= 17 && k <= 21 && dim > (val_bytes == 4 ? 256 : 384) && entries * (val_bytes == 4 ? 9 : 18) < items * dim);
 }
 
 // Whether byte offsets into the CBSR need more than 32 bits (record: bytes of a packed one, 0: two arrays)

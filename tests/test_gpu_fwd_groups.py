@@ -19,12 +19,12 @@ _DTYPE = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
 _LENGTHS = (0, 1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 95, 96, 127, 128, 129, 191, 193, 300)
 
 
-def _graph(seed):
+def _graph(seed, shorter=1):
     rng = np.random.default_rng(seed)
     N = 331
     coo = []
     for i in range(N):
-        n = _LENGTHS[i % len(_LENGTHS)]
+        n = _LENGTHS[i % len(_LENGTHS)] // shorter
         coo += [(i, int(j), float(rng.normal())) for j in rng.choice(N, n, replace=False)]
     return N, *csr_from_coo(N, coo)
 
@@ -166,11 +166,12 @@ def test_widths_that_the_sweep_takes(monkeypatch, k, tables):
 
 
 # k = 17 to 21 on wide rows: by units where the work items are short, by lane groups where they are long
-@pytest.mark.parametrize("k,dim,ib,units", [(17, 256, 1, 0), (17, 257, 2, 0), (17, 1024, 2, 1), (19, 640, 4, 1), (21, 600, 2, 1), (20, 300, 2, 0)])
+@pytest.mark.parametrize("k,dim,ib,shorter,units", [(17, 256, 1, 1, 0), (17, 257, 2, 1, 0), (17, 1024, 2, 4, 1), (19, 640, 4, 4, 1), (21, 385, 2, 4, 1),
+                                                    (20, 300, 2, 1, 0)])
 @pytest.mark.parametrize("fmt", ["f32", "bf16", "f16"])
-def test_forward_of_wide_rows(monkeypatch, k, dim, ib, units, fmt):
+def test_forward_of_wide_rows(monkeypatch, k, dim, ib, shorter, units, fmt):
     monkeypatch.setenv("MAXK_FWD_SWEEP", "1")
-    N, rowptr, col, val = _graph(k)
+    N, rowptr, col, val = _graph(k, shorter)
     gr = maxk.maxk_graph_create(to_dev(rowptr), to_dev(col), to_dev(val))
     value_type = {"f32": maxk.VALUE_F32, "bf16": maxk.VALUE_BF16, "f16": maxk.VALUE_F16}[fmt]
     assert maxk.load_library().maxk_fwd_by_units(k, dim, value_type, gr.info()["n_fwd_items"], len(col)) == units
