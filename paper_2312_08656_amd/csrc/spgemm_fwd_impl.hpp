@@ -477,7 +477,7 @@ __device__ __forceinline__ uint32_t lds_address(const float* p)
 
 // Row by row: a wavefront per work item.  (k = 8, 10 .. 128 and 192; the others, and some calls at k = 17 .. 21, run spgemm_fwd_rmw_kernel.)
 // Wavefronts a SIMD that the registers leave room for: nothing of a pass may spill, and from two passes on 64 registers do not hold two
-// sets of loads.  us, by units / lane groups with spills for 8 wavefronts / with 6: 60 k nodes, degree 16, k = 50 with 4-byte columns
+// sets of loads (two passes of 8 lanes mostly fit).  us, by units / lane groups with spills for 8 wavefronts / with 6: 60 k nodes, degree 16, k = 50 with 4-byte columns
 // 82 / 102 / 80, width 512, k = 128 bf16 84 / 108 / 82; 100 k, 61, k = 50 bf16, 2-byte columns 359 / 284 / 231; 300 k, 31, k = 128 786 / 952 / 786.
 // Half as many loads under way leave room for more wavefronts, which is better where one group works on an entry (1 M nodes, degree 9,
 // k = 128 863 us by units, 1092 with spills, 928 / 854 with all loads / half) and in two passes of 16 lanes (717 k, 11, k = 24 462, 313, 345 / 309),
@@ -491,7 +491,9 @@ constexpr bool kRowHalf = (S::LANES == kWave && S::PASSES <= 2) || (S::LANES == 
 template <class S, int LAYOUT>
 using RowSplit = std::conditional_t<kRowHalf<S, LAYOUT>, HalfStep<S>, S>;
 template <class S, int LAYOUT, int VT>
-constexpr int kRowWaves = S::PASSES == 1 ? 8 : S::LANES == 16 && kRowHalf<S, LAYOUT> ? (VT == MAXK_VALUE_F32 ? 8 : 7) : 6;
+constexpr int kRowWaves = S::PASSES == 1 || (S::LANES == 8 && S::PASSES == 2 && (VT == MAXK_VALUE_F32 || LAYOUT != kFwdArrays)) ? 8
+                          : S::LANES == 16 && kRowHalf<S, LAYOUT>                                                             ? (VT == MAXK_VALUE_F32 ? 8 : 7)
+                                                                                                                              : 6;
 template <class S, int LAYOUT, int VT, typename IdxT>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(kRowWaves<S, LAYOUT, VT>))) void spgemm_fwd_row_kernel(
     const WorkItem* __restrict__ items, const int32_t* __restrict__ col, const float* __restrict__ val,
