@@ -491,11 +491,15 @@ constexpr bool kRowHalf = (S::LANES == kWave && S::PASSES <= 2) || (S::LANES == 
 template <class S, int LAYOUT>
 using RowSplit = std::conditional_t<kRowHalf<S, LAYOUT>, HalfStep<S>, S>;
 template <class S, int LAYOUT, int VT>
-constexpr int kRowWaves = S::PASSES == 1 || (S::LANES == 8 && S::PASSES == 2 && (VT == MAXK_VALUE_F32 || LAYOUT != kFwdArrays)) ? 8
-                          : S::LANES == 16 && kRowHalf<S, LAYOUT>                                                             ? (VT == MAXK_VALUE_F32 ? 8 : 7)
-                                                                                                                              : 6;
+constexpr int row_waves()
+{
+    constexpr bool F32 = VT == MAXK_VALUE_F32;
+    if (S::PASSES == 1 || (S::LANES == 8 && S::PASSES == 2 && (F32 || LAYOUT != kFwdArrays))) return 8;
+    if (S::LANES == 16 && kRowHalf<S, LAYOUT>) return F32 ? 8 : 7;
+    return S::LANES == 8 && S::PASSES == 3 && F32 ? 7 : 6;  // (100 k nodes, degree 17, width 64, k = 17: 55.7 us with 6, 51.8 with 7)
+}
 template <class S, int LAYOUT, int VT, typename IdxT>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(kRowWaves<S, LAYOUT, VT>))) void spgemm_fwd_row_kernel(
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(row_waves<S, LAYOUT, VT>()))) void spgemm_fwd_row_kernel(
     const WorkItem* __restrict__ items, const int32_t* __restrict__ col, const float* __restrict__ val,
     const value_store_t<VT>* __restrict__ sp_data, const IdxT* __restrict__ sp_index, const char* __restrict__ packed, int rec_bytes,
     int idx_off, int dim, int k, int wide, int vec_out, float* __restrict__ Y, float* __restrict__ partials)
